@@ -129,7 +129,8 @@ int ck_kmeans_assign(const ck_shape* sh, const void* K, int64_t tok_begin, int64
   CK_OPTIONAL_PTR(best_sim);
   return hip_result(ck::launch_assign(dm, (const ck::bf16*)K, tok_begin, tok_count,
                                       (const ck::bf16*)centroids_hat, c_begin, c_count, labels,
-                                      best_sim, nullptr, ck::KmCtl(), (hipStream_t)stream),
+                                      best_sim, ck::ChunkIndex(), ck::KmCtl(),
+                                      (hipStream_t)stream),
                     "assignment launch");
 }
 
@@ -175,7 +176,7 @@ int ck_build_metadata(const ck_shape* sh, const int32_t* labels, int64_t tok_beg
   if (workspace_bytes < ws.bytes)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws.bytes);
   return hip_result(ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes,
-                                        offsets, sorted_idx, ws.chunk_hist, false, nullptr,
+                                        offsets, sorted_idx, ws.chunks.seg, false, nullptr,
                                         (hipStream_t)stream),
                     "metadata launch");
 }
@@ -254,6 +255,9 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
     e = ck::launch_fill_i32(ws.changed, (int64_t)max_iter * dm.HP, 0, st);
     if (e != hipSuccess) return hip_result(e, "counter fill launch");
   }
+  // the iterations need the sums of the clusters, not the sorted index: the update reads the
+  // chunk index of the assignment, and the metadata is built once, after the last iteration
+  const bool chunked = ck::update_chunks_fits(dm, tok_count);
   for (int it = 0; it < max_iter; ++it) {
     ck::KmCtl ctl;
     ctl.bias = bias;
@@ -266,14 +270,27 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
       gate = it >= 1 ? ctl.changed : nullptr;
     }
     e = ck::launch_assign(dm, Kb, tok_begin, tok_count, ws.mu_hat, c_begin, c_count, labels,
-                          nullptr, ws.chunk_hist, ctl, st);
+                          nullptr, ws.chunks, ctl, st);
     if (e != hipSuccess) return hip_result(e, "assignment launch");
-    e = ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes, offsets,
-                            sorted_idx, ws.chunk_hist, true, gate, st);
-    if (e != hipSuccess) return hip_result(e, "metadata launch");
-    e = ck::launch_update(dm, Kb, offsets, sorted_idx, c_begin, c_count, (ck::bf16*)centroids,
-                          ws.mu_hat, nullptr, metric, bias, ws.bias_stride, gate, st);
+    if (chunked) {
+      e = ck::launch_update_chunks(dm, Kb, ws.chunks, tok_begin, tok_count, c_begin, c_count,
+                                   (ck::bf16*)centroids, ws.mu_hat, sizes, metric, bias,
+                                   ws.bias_stride, gate, st);
+    } else {
+      e = ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes, offsets,
+                              sorted_idx, ws.chunks.seg, true, gate, st);
+      if (e != hipSuccess) return hip_result(e, "metadata launch");
+      e = ck::launch_update(dm, Kb, offsets, sorted_idx, c_begin, c_count, (ck::bf16*)centroids,
+                            ws.mu_hat, nullptr, metric, bias, ws.bias_stride, gate, st);
+    }
     if (e != hipSuccess) return hip_result(e, "update launch");
+  }
+  if (chunked) {
+    // the metadata of the last labels; a head-problem that stopped early has left its chunk
+    // index as its last assignment wrote it
+    e = ck::launch_emit_index(dm, ws.chunks, tok_begin, tok_count, c_begin, c_count, sizes,
+                              offsets, sorted_idx, st);
+    if (e != hipSuccess) return hip_result(e, "metadata launch");
   }
   if (iters_done) {
     if (converge)

@@ -123,6 +123,20 @@ __device__ __forceinline__ int block_inclusive_scan(int (&v)[ITEMS], int* tmp) {
   return total;
 }
 
+// Makes the compiler fetch a kernel argument where this stands.  Kernel arguments are
+// read with scalar loads that the compiler otherwise issues piecemeal, each where it is
+// first needed and each a full (cold) memory round trip; a kernel that starts with a
+// chain of dependent steps pins one argument per 64-byte line of its argument block at
+// its top, so that the lines arrive together.
+#define CK_FETCH_ARG(x) asm volatile("" ::"s"(x))
+
+// LDS operations of ONE wavefront are served in order; this only keeps the compiler
+// from moving them across the point.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // ---- internal launchers (host side, defined next to their kernels) ----
 struct Dims {
   int S, Hq, Hkv, G, HP;   // HP = S * Hkv head-problems
@@ -136,9 +150,16 @@ constexpr int KM_SMALL_MAX_TOKENS = 384;    // token ranges up to this size (and
 constexpr int KM_SMALL_MAX_CLUSTERS = 8;    // this many clusters) are clustered by one kernel
 constexpr int KM_MAX_ITER_CONVERGE = 256;   // iteration cap of the run-until-convergence mode
 
+// What the assignment leaves behind for every chunk of consecutive tokens: the chunk's
+// tokens ordered by label (stable), and where each label's run stands in that list.
+struct ChunkIndex {
+  uint32_t* seg = nullptr;    // [HP, n_chunks, seg_stride(c_count)] first list position | count << 16
+  uint16_t* list = nullptr;   // [HP, n_chunks, chunk_tokens] token offsets inside the chunk
+};
+
 struct ClusterWorkspace {
   bf16* mu_hat;         // [HP, c_count, D] table the assignment reads (unit-length or raw means)
-  int32_t* chunk_hist;  // [HP, n_chunks, c_count] per-chunk histogram / base positions
+  ChunkIndex chunks;
   float* bias;          // [HP, bias_stride] -|mu_c|^2 / 2 of the table rows (l2 metric)
   int bias_stride;      // c_count rounded up to whole 32-row tiles
   int32_t* changed;     // [KM_MAX_ITER_CONVERGE + 1, HP] labels changed per iteration
@@ -171,26 +192,37 @@ hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin,
 hipError_t launch_iters_done(const int32_t* changed, int max_iter, int HP, int32_t* iters_done,
                              hipStream_t st);
 int assign_tile_tokens(const Dims& dm, int64_t tok_count);
-// chunk_hist (nullable): [HP, n_chunks, c_count] label histogram per workgroup tile
+// chunks (members nullable): index of every chunk of assign_tile_tokens() tokens by label
 hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,
                          const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
-                         float* best_sim, int32_t* chunk_hist, const KmCtl& ctl, hipStream_t st);
+                         float* best_sim, const ChunkIndex& chunks, const KmCtl& ctl,
+                         hipStream_t st);
 // streaming form for small tables (whole table in LDS); chunk size 512 tokens as above
 bool assign_stream_fits(int c_count);
 hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin,
                                 int64_t tok_count, const bf16* mu_hat, int c_begin, int c_count,
-                                int32_t* labels, float* best_sim, int32_t* chunk_hist,
+                                int32_t* labels, float* best_sim, const ChunkIndex& chunks,
                                 const KmCtl& ctl, int n_cu, hipStream_t st);
-// have_hist: chunk_hist already holds the histograms (written by launch_assign)
+// have_seg: seg already holds the counts (written by launch_assign); overwritten either way
 hipError_t launch_metadata(const Dims& dm, const int32_t* labels, int64_t tok_begin,
                            int64_t tok_count, int c_begin, int c_count, int32_t* sizes,
-                           int32_t* offsets, int32_t* sorted_idx, int32_t* chunk_hist,
-                           bool have_hist, const int32_t* gate, hipStream_t st);
+                           int32_t* offsets, int32_t* sorted_idx, uint32_t* seg,
+                           bool have_seg, const int32_t* gate, hipStream_t st);
 // gate (nullable, [HP]): head-problems whose entry is 0 are left untouched
 hipError_t launch_update(const Dims& dm, const bf16* K, const int32_t* offsets,
                          const int32_t* sorted_idx, int c_begin, int c_count, bf16* centroids,
                          bf16* mu_hat, float* centroids_f32, int metric, float* bias,
                          int bias_stride, const int32_t* gate, hipStream_t st);
+// the same update straight from the chunk index of the assignment, no sorted list needed
+bool update_chunks_fits(const Dims& dm, int64_t tok_count);
+hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
+                                int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
+                                bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
+                                float* bias, int bias_stride, const int32_t* gate, hipStream_t st);
+// offsets and sorted_idx of the labels the chunk index holds (sizes: as the update wrote them)
+hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
+                             int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
+                             int32_t* offsets, int32_t* sorted_idx, hipStream_t st);
 hipError_t launch_select(const Dims& dm, const void* q, const void* centroids,
                          const int32_t* sizes, int n_clusters, int budget, uint32_t flags,
                          int32_t* sel_clusters, int32_t* n_sel_clusters, int32_t* n_sel_tokens,

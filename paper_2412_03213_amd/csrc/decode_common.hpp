@@ -56,13 +56,6 @@ __device__ __forceinline__ float score_rows16(const uint4 (&t)[4], const bf16x8 
   return v;
 }
 
-// Makes the compiler fetch a kernel argument where this stands.  Kernel arguments are
-// read with scalar loads that the compiler otherwise issues piecemeal, each where it is
-// first needed and each a full (cold) memory round trip; a kernel that starts with a
-// chain of dependent steps pins one argument per 64-byte line of its argument block at
-// its top, so that the lines arrive together.
-#define CK_FETCH_ARG(x) asm volatile("" ::"s"(x))
-
 // Monotone map float -> uint32 (a < b  <=>  map(a) < map(b); -0 and +0 made equal).
 __device__ __forceinline__ uint32_t ordered_bits(float f) {
   if (f == 0.f) f = 0.f;                                    // -0 -> +0
@@ -312,13 +305,6 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
     L.full_rank = m > SELP_MAX_CAND;
   }
   __syncthreads();
-}
-
-// LDS operations of ONE wavefront are served in order; this only keeps the compiler
-// from moving them across the point.
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_wave_barrier();
-  asm volatile("" ::: "memory");
 }
 
 // The selection by ONE wavefront, without workgroup barriers, for tables of at most

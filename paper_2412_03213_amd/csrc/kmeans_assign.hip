@@ -14,7 +14,7 @@
 // LDS in double-buffered chunks of 64 rows shared by all wavefronts of the workgroup.
 #include <atomic>
 
-#include "ck_common.hpp"
+#include "chunk_sort.hpp"
 
 namespace ck {
 
@@ -31,7 +31,7 @@ constexpr int LDS_ROW = D + 8;             // bf16 elements per LDS row: 272 B, 
 template <int NKB, int WAVES, int WAVES_PER_SIMD, bool PHASED, bool HAS_BIAS>
 __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
-    float* __restrict__ best_sim, int32_t* __restrict__ chunk_hist, int n_hist_chunks,
+    float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks_hp, int label_bits,
     int64_t N_cap, int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
     const KmCtl ctl) {
   constexpr int THREADS = WAVES * 64;
@@ -204,13 +204,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
 
   // ---- lanes l and l+32 hold the two halves of each key's candidates ----
   // (the centroid buffers are free now: the loop ended with a barrier)
-  // One label histogram per 4 wavefronts = per chunk of the counting sort.
-  constexpr int HISTS = WAVES / 4;
-  int* hist = reinterpret_cast<int*>(&lds[0][0]) + (wave >> 2) * c_count;
-  if (chunk_hist) {
-    for (int c = tid; c < HISTS * c_count; c += THREADS) reinterpret_cast<int*>(&lds[0][0])[c] = 0;
-    __syncthreads();
-  }
+  constexpr int CHUNK = 4 * NKB * 32;                   // tokens of 4 wavefronts = one chunk
+  uint32_t* tok = reinterpret_cast<uint32_t*>(&lds[0][0]);   // pack_token words
+  int lane_label[(NKB + 1) / 2];                        // labels of tokens 64 i + lane of this wavefront
   int diff = 0;
 #pragma unroll
   for (int kb = 0; kb < NKB; ++kb) {
@@ -227,27 +223,47 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
       bidx = oi;
     }
     const int64_t t = wave_tok0 + kb * 32 + col;
+    if (half == (kb & 1) || NKB == 1) lane_label[kb / 2] = bidx;
     if (half == 0 && t < tok_count) {
       const int64_t o = (int64_t)hp * N_cap + tok_begin + t;
       if (ctl.changed) diff += (ctl.first || labels[o] != c_begin + bidx) ? 1 : 0;
       labels[o] = c_begin + bidx;
       if (best_sim) best_sim[o] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
-      if (chunk_hist) atomicAdd(&hist[bidx], 1);       // integer counts: order does not matter
     }
   }
   if (ctl.changed) {
     const int wsum = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
     if (lane == 0 && wsum) atomicAdd(&s_changed, wsum);
   }
-  if (chunk_hist || ctl.changed) __syncthreads();
+  if (chunks.seg) {
+    if constexpr (NKB == 1) {
+      // 32 tokens per wavefront: the even one of a pair ranks both halves of the group
+      uint32_t* raw = tok + WAVES * 32;
+      if (half == 0) raw[wave * 32 + col] = (uint32_t)lane_label[0];
+      __syncthreads();
+      if ((wave & 1) == 0)
+        tok[wave * 32 + lane] = pack_token((int)raw[wave * 32 + lane],
+                                           wave_tok0 + lane < tok_count, label_bits);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NKB / 2; ++i)
+        tok[(wave * (NKB / 2) + i) * WAVE + lane] =
+            pack_token(lane_label[i], wave_tok0 + i * WAVE + lane < tok_count, label_bits);
+    }
+  }
+  if (chunks.seg || ctl.changed) __syncthreads();
   if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
-  // label histograms of this workgroup's tokens = chunks of the counting sort
-  if (chunk_hist) {
-    for (int e = tid; e < HISTS * c_count; e += THREADS) {
-      const int hc = (int)blockIdx.x * HISTS + e / c_count;
-      if (hc < n_hist_chunks)
-        chunk_hist[((int64_t)hp * n_hist_chunks + hc) * c_count + e % c_count] =
-            reinterpret_cast<int*>(&lds[0][0])[e];
+  if (chunks.seg) {
+    // one wavefront per chunk
+    constexpr int CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * 4, SCRATCH = CNT + CHUNK * 2;
+    static_assert(WAVES / 4 * (CHUNK * 4 + SCRATCH) <= sizeof(lds), "chunk sort scratch");
+    const int64_t ch = (int64_t)blockIdx.x * (WAVES / 4) + wave;
+    if (wave < WAVES / 4 && ch < n_chunks_hp) {
+      char* scratch = reinterpret_cast<char*>(&lds[0][0]) + WAVES / 4 * CHUNK * 4 + wave * SCRATCH;
+      const int64_t o = (int64_t)hp * n_chunks_hp + ch;
+      chunk_sort<CHUNK / WAVE, CK_MAX_CLUSTERS>(tok + wave * CHUNK, c_count, reinterpret_cast<int*>(scratch),
+                               reinterpret_cast<uint16_t*>(scratch + CNT),
+                               chunks.seg + o * seg_stride(c_count), chunks.list + o * CHUNK);
     }
   }
 }
@@ -255,25 +271,27 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
 template <int NKB, int WAVES, int WPS, bool PHASED>
 static void launch_assign_variant(const Dims& dm, const bf16* K, int64_t tok_begin,
                                   int64_t tok_count, const bf16* mu_hat, int c_begin, int c_count,
-                                  int32_t* labels, float* best_sim, int32_t* chunk_hist,
+                                  int32_t* labels, float* best_sim, const ChunkIndex& chunks,
                                   const KmCtl& ctl, hipStream_t st) {
   constexpr int TOK = WAVES * NKB * 32;
   const int sort_chunk = 4 * NKB * 32;
-  const int n_hist_chunks = (int)((tok_count + sort_chunk - 1) / sort_chunk);
+  const int n_chunks = (int)((tok_count + sort_chunk - 1) / sort_chunk);
+  int label_bits = 0;
+  while ((1 << label_bits) < c_count) ++label_bits;
   dim3 grid((unsigned)((tok_count + TOK - 1) / TOK), dm.HP);
   if (ctl.bias)
     // the bias table takes 8 KB more LDS: at most three of the small workgroups fit a CU
     hipLaunchKernelGGL((k_assign<NKB, WAVES, (WPS > 3 ? 3 : WPS), PHASED, true>), grid, dim3(WAVES * 64), 0, st, K,
-                       mu_hat, labels, best_sim, chunk_hist, n_hist_chunks, dm.N_cap, tok_begin,
+                       mu_hat, labels, best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin,
                        tok_count, c_begin, c_count, ctl);
   else
     hipLaunchKernelGGL((k_assign<NKB, WAVES, WPS, PHASED, false>), grid, dim3(WAVES * 64), 0, st, K,
-                       mu_hat, labels, best_sim, chunk_hist, n_hist_chunks, dm.N_cap, tok_begin,
+                       mu_hat, labels, best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin,
                        tok_count, c_begin, c_count, ctl);
 }
 
 // Chunk size of the counting sort = the tokens of four assignment wavefronts (every
-// group of four emits the label histogram of exactly its own tokens).
+// group of four emits the label-ordered index of exactly its own tokens).
 // Large problems: 128 keys per wavefront (4 MFMAs per centroid fragment read), eight
 // wavefronts per workgroup.  Small ones (incremental clustering of a few hundred
 // tokens): 32 keys per wavefront, four per workgroup, so that more workgroups exist.
@@ -298,7 +316,8 @@ static int compute_units() {
 
 hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,
                          const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
-                         float* best_sim, int32_t* chunk_hist, const KmCtl& ctl, hipStream_t st) {
+                         float* best_sim, const ChunkIndex& chunks, const KmCtl& ctl,
+                         hipStream_t st) {
   if (assign_tile_tokens(dm, tok_count) == 512) {
     // Eight-wavefront workgroups (one per CU, each centroid chunk staged once for all
     // eight, the two wavefronts of a SIMD half a tile apart) win when the whole grid is
@@ -308,18 +327,18 @@ hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64
     const int n_cu = compute_units();
     if (assign_stream_fits(c_count))
       return launch_assign_stream(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count, labels,
-                                  best_sim, chunk_hist, ctl, n_cu, st);
+                                  best_sim, chunks, ctl, n_cu, st);
     const int64_t wg8 = (tok_count + 1023) / 1024 * dm.HP;
     if (wg8 > n_cu && c_count < 1024) {
       launch_assign_variant<4, 4, 2, false>(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count,
-                                            labels, best_sim, chunk_hist, ctl, st);
+                                            labels, best_sim, chunks, ctl, st);
       return hipGetLastError();
     }
     launch_assign_variant<4, 8, 2, true>(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count,
-                                         labels, best_sim, chunk_hist, ctl, st);
+                                         labels, best_sim, chunks, ctl, st);
   } else {
     launch_assign_variant<1, 4, 4, false>(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count,
-                                          labels, best_sim, chunk_hist, ctl, st);
+                                          labels, best_sim, chunks, ctl, st);
   }
   return hipGetLastError();
 }

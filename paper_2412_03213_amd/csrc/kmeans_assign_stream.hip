@@ -5,7 +5,7 @@
 // matrix cores touch in the accumulator half of the register file.
 #include <type_traits>
 
-#include "ck_common.hpp"
+#include "chunk_sort.hpp"
 
 namespace ck {
 
@@ -35,18 +35,17 @@ constexpr int ST_NKB = 2;                               // 64 keys per wavefront
 constexpr int ST_CHUNK = ST_WAVES * ST_NKB * 32;        // 512 tokens per block of a workgroup
 constexpr int ST_MAX_TILES = 16;                        // 512 centroids
 constexpr int ST_MAX_BLOCKS = 8;
-constexpr int ST_HIST_INTS = 5600;                      // LDS left for the label histograms
 
 template <bool HAS_BIAS>
 __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
-    float* __restrict__ best_sim, int32_t* __restrict__ chunk_hist, int n_hist_chunks,
+    float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks, int label_bits,
     int64_t N_cap, int64_t tok_begin, int64_t tok_count, int c_begin, int c_count, int blocks,
     const KmCtl ctl) {
   constexpr int NKB = ST_NKB, THREADS = ST_WAVES * 64;
   __shared__ __attribute__((aligned(16))) bf16 table[ST_MAX_TILES * 32 * LDS_ROW];
   __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? ST_MAX_TILES * 32 : 4];
-  __shared__ int hist[ST_HIST_INTS];
+  __shared__ uint32_t tok[ST_MAX_BLOCKS * ST_CHUNK];     // pack_token words of this workgroup's tokens
   __shared__ int s_changed, s_next_task;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -75,7 +74,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   };
   bf16x8 ka[NKB][8], kb2[NKB][8];
 
-  // ---- the table into LDS (rows beyond c_count are zero), bias, histograms ----
+  // ---- the table into LDS (rows beyond c_count are zero), bias, token words ----
   {
     const int n_seg = n_tiles * 32 * 16;                // 16-byte segments
     constexpr int PER = ST_MAX_TILES * 32 * 16 / THREADS;   // 16 per thread, all in flight at once
@@ -110,8 +109,8 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     for (int c = tid; c < n_tiles * 32; c += THREADS)
       lds_bias[c] = c < c_count ? ctl.bias[(int64_t)hp * ctl.bias_stride + c] : 0.f;
   }
-  if (chunk_hist)
-    for (int c = tid; c < blocks * c_count; c += THREADS) hist[c] = 0;
+  if (chunks.seg)
+    for (int t = tid; t < blocks * ST_CHUNK; t += THREADS) tok[t] = 0;
   if (tid == 0) {
     s_changed = 0;
     s_next_task = ST_WAVES;                             // tasks 0..7 are the wavefronts' first ones
@@ -199,6 +198,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     for (int r = 0; r < 8; ++r) readout(1, last, r, true);
 
     // lanes l and l+32 hold the two halves of each key's candidates
+    int lane_label = 0;                                 // label of token `lane` of the 64
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
       const int slot = 15 - (int)(__float_as_uint(bestp[kb]) & 15u);
@@ -212,16 +212,20 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
         best = ob;
         bidx = oi;
       }
+      if (half == kb) lane_label = bidx;
       const int64_t t = wave_tok0 + kb * 32 + col;
       if (half == 0 && t < tok_count) {
         const int64_t o = (int64_t)hp * N_cap + tok_begin + t;
         if (ctl.changed) diff += (ctl.first || labels[o] != c_begin + bidx) ? 1 : 0;
         labels[o] = c_begin + bidx;
         if (best_sim) best_sim[o] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
-        if (chunk_hist) atomicAdd(&hist[(b / ST_WAVES) * c_count + bidx], 1);   // integer counts: any order
       }
     }
+    // the ranking inside the group runs here, under the other wavefront's matrix work
+    if (chunks.seg)
+      tok[b * (NKB * 32) + lane] = pack_token(lane_label, wave_tok0 + lane < tok_count, label_bits);
   };
+  static_assert(NKB == 2, "a task is one group of 64 tokens");
 
   // A workgroup's range is cut into tasks of 64 tokens (8 per 512-token chunk).  Every
   // wavefront starts with the task of its own number and then takes the next free one
@@ -252,13 +256,18 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     const int wsum = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
     if (lane == 0 && wsum) atomicAdd(&s_changed, wsum);
   }
-  if (chunk_hist || ctl.changed) __syncthreads();
+  if (chunks.seg || ctl.changed) __syncthreads();
   if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
-  if (chunk_hist) {
-    for (int e = tid; e < blocks * c_count; e += THREADS) {
-      const int hc = (int)blockIdx.x * blocks + e / c_count;
-      if (hc < n_hist_chunks)
-        chunk_hist[((int64_t)hp * n_hist_chunks + hc) * c_count + e % c_count] = hist[e];
+  if (chunks.seg) {
+    // one wavefront per 512-token chunk; the centroid table's LDS is free by now
+    const int64_t ch = (int64_t)blockIdx.x * blocks + wave;
+    if (wave < blocks && ch < n_chunks) {
+      constexpr int CNT = chunk_sort_cnt_ints(ST_MAX_TILES * 32) * 4;
+      char* scratch = reinterpret_cast<char*>(table) + wave * (CNT + ST_CHUNK * 2);
+      const int64_t o = (int64_t)hp * n_chunks + ch;
+      chunk_sort<ST_CHUNK / WAVE, ST_MAX_TILES * 32>(tok + wave * ST_CHUNK, c_count, reinterpret_cast<int*>(scratch),
+                                  reinterpret_cast<uint16_t*>(scratch + CNT),
+                                  chunks.seg + o * seg_stride(c_count), chunks.list + o * ST_CHUNK);
     }
   }
 }
@@ -267,24 +276,25 @@ bool assign_stream_fits(int c_count) { return c_count <= ST_MAX_TILES * 32; }
 
 hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin,
                                 int64_t tok_count, const bf16* mu_hat, int c_begin, int c_count,
-                                int32_t* labels, float* best_sim, int32_t* chunk_hist,
+                                int32_t* labels, float* best_sim, const ChunkIndex& chunks,
                                 const KmCtl& ctl, int n_cu, hipStream_t st) {
-  // blocks of 512 tokens per workgroup: as many as keep every CU busy (at most 8, and
-  // what the label histograms leave room for)
+  // blocks of 512 tokens per workgroup: as many as keep every CU busy (at most 8: one
+  // wavefront each for the chunk index)
   const int64_t chunks_hp = (tok_count + ST_CHUNK - 1) / ST_CHUNK;
   int64_t blocks = chunks_hp * dm.HP / n_cu;
   if (blocks > ST_MAX_BLOCKS) blocks = ST_MAX_BLOCKS;
-  if (blocks > ST_HIST_INTS / c_count) blocks = ST_HIST_INTS / c_count;
   if (blocks > chunks_hp) blocks = chunks_hp;
   if (blocks < 1) blocks = 1;
   const dim3 grid((unsigned)((chunks_hp + blocks - 1) / blocks), dm.HP);
+  int label_bits = 0;
+  while ((1 << label_bits) < c_count) ++label_bits;
   if (ctl.bias)
     hipLaunchKernelGGL(k_assign_stream<true>, grid, dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels,
-                       best_sim, chunk_hist, (int)chunks_hp, dm.N_cap, tok_begin, tok_count,
+                       best_sim, chunks, (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count,
                        c_begin, c_count, (int)blocks, ctl);
   else
     hipLaunchKernelGGL(k_assign_stream<false>, grid, dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels,
-                       best_sim, chunk_hist, (int)chunks_hp, dm.N_cap, tok_begin, tok_count,
+                       best_sim, chunks, (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count,
                        c_begin, c_count, (int)blocks, ctl);
   return hipGetLastError();
 }

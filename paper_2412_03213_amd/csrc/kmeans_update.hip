@@ -3,13 +3,14 @@
 //
 // The paper's update kernel accumulates keys into shared-memory sums with
 // atomics, one thread block per head.  Here the update is a segmented
-// reduction instead: the labels are first counting-sorted into the
-// cluster-contiguous token index that the decode step needs anyway (sizes,
-// prefix sum, sorted indices), then one workgroup per cluster streams its member
-// rows and adds them in a fixed order.  No floating-point atomics, so the
-// centroids are bit-reproducible; the sort is stable (ascending token row inside
-// a cluster), so the metadata of the last iteration is the final metadata.
-#include "ck_common.hpp"
+// reduction instead: the assignment leaves every chunk of tokens sorted by label, and
+// one workgroup per cluster walks the chunks' runs, streams its member rows and adds
+// them in a fixed order (ascending token row).  No floating-point atomics, so the
+// centroids are bit-reproducible.  The cluster-contiguous index that the decode step
+// needs (sizes, prefix sum, sorted indices) is emitted once, from the chunk index of the
+// last assignment; the counting sort of given labels and the update from a sorted list
+// serve the calls that export the steps, and ranges of more chunks than the index holds.
+#include "chunk_sort.hpp"
 
 namespace ck {
 
@@ -78,18 +79,6 @@ hipError_t launch_init_centroids(const Dims& dm, const bf16* K, const int32_t* i
 }
 
 // ------------------------------------------------------------------ counting sort
-// Lanes of a wavefront that hold the same label, as a 64-bit mask (built from one
-// ballot per label bit), restricted to `valid` lanes.
-__device__ __forceinline__ uint64_t same_label_mask(int label, bool valid, int label_bits) {
-  uint64_t peers = __ballot(valid);
-  for (int b = 0; b < label_bits; ++b) {
-    const bool bit = (label >> b) & 1;
-    const uint64_t m = __ballot(bit);
-    peers &= bit ? m : ~m;
-  }
-  return peers;
-}
-
 constexpr int SORT_THREADS = 256;                       // 4 wavefronts, one chunk each
 
 // Pass 1 (only when the assignment kernel has not already produced it): label
@@ -97,7 +86,7 @@ constexpr int SORT_THREADS = 256;                       // 4 wavefronts, one chu
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(
     const int32_t* __restrict__ labels, int64_t N_cap, int64_t tok_begin, int64_t tok_count,
     int c_begin, int c_count, int label_bits, int n_chunks, int chunk_tokens,
-    int32_t* __restrict__ chunk_hist) {
+    uint32_t* __restrict__ seg) {
   extern __shared__ int lds_hist[];                     // [4][c_count]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hp = blockIdx.y;
   const int chunk = blockIdx.x * 4 + wave;
@@ -116,17 +105,17 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(
     if (valid && (peers & lt) == 0) hist[l] = hist[l] + __popcll(peers);
     __builtin_amdgcn_wave_barrier();
   }
-  int32_t* out = chunk_hist + ((int64_t)hp * n_chunks + chunk) * c_count;
-  for (int c = lane; c < c_count; c += WAVE) out[c] = hist[c];
+  uint32_t* out = seg + ((int64_t)hp * n_chunks + chunk) * seg_stride(c_count);
+  for (int c = lane; c < c_count; c += WAVE) out[c] = (uint32_t)hist[c] << 16;
 }
 
-// Pass 2: per cluster, exclusive scan of the chunk counts (in place) and the
-// cluster size.  Workgroup = 64 clusters x 16 groups of chunks.
+// Pass 2: per cluster, exclusive scan of the chunk counts (upper halves of seg; the
+// sums replace the words) and the cluster size.  Workgroup = 64 clusters x 16 groups of chunks.
 constexpr int SCAN_THREADS = 1024;
 constexpr int SCAN_GROUPS = SCAN_THREADS / 64;
 constexpr int SCAN_REG = 16;                            // chunk counts a thread keeps in registers
 __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(
-    int32_t* __restrict__ chunk_hist, int n_chunks, int C_cap, int c_begin, int c_count,
+    uint32_t* __restrict__ seg, int n_chunks, int C_cap, int c_begin, int c_count,
     int32_t* __restrict__ sizes, const int32_t* __restrict__ gate) {
   __shared__ int part[SCAN_GROUPS][64];
   const int cl = threadIdx.x & 63, grp = threadIdx.x >> 6, hp = blockIdx.y;
@@ -134,15 +123,16 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(
   const int c = blockIdx.x * 64 + cl;
   const int per = (n_chunks + SCAN_GROUPS - 1) / SCAN_GROUPS;
   const int k0 = grp * per, k1 = min(k0 + per, n_chunks);
-  int32_t* H = chunk_hist + (int64_t)hp * n_chunks * c_count + c;
+  const int stride = seg_stride(c_count);
+  uint32_t* H = seg + (int64_t)hp * n_chunks * stride + c;
   int v[SCAN_REG];
   int sum = 0;
   if (c < c_count) {
 #pragma unroll
-    for (int i = 0; i < SCAN_REG; ++i) v[i] = (k0 + i < k1) ? H[(int64_t)(k0 + i) * c_count] : 0;
+    for (int i = 0; i < SCAN_REG; ++i) v[i] = (k0 + i < k1) ? (int)(H[(int64_t)(k0 + i) * stride] >> 16) : 0;
 #pragma unroll
     for (int i = 0; i < SCAN_REG; ++i) sum += v[i];
-    for (int k = k0 + SCAN_REG; k < k1; ++k) sum += H[(int64_t)k * c_count];
+    for (int k = k0 + SCAN_REG; k < k1; ++k) sum += (int)(H[(int64_t)k * stride] >> 16);
   }
   part[grp][cl] = sum;
   __syncthreads();
@@ -157,12 +147,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_sort_scan(
 #pragma unroll
     for (int i = 0; i < SCAN_REG; ++i)
       if (k0 + i < k1) {
-        H[(int64_t)(k0 + i) * c_count] = run;
+        H[(int64_t)(k0 + i) * stride] = (uint32_t)run;
         run += v[i];
       }
     for (int k = k0 + SCAN_REG; k < k1; ++k) {
-      const int t = H[(int64_t)k * c_count];
-      H[(int64_t)k * c_count] = run;
+      const int t = (int)(H[(int64_t)k * stride] >> 16);
+      H[(int64_t)k * stride] = (uint32_t)run;
       run += t;
     }
     if (grp == 0) sizes[(int64_t)hp * C_cap + c_begin + c] = total;
@@ -178,7 +168,7 @@ constexpr int SCAT_ROUNDS = 2;                              // chunk_tokens <= 4
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
     const int32_t* __restrict__ labels, int64_t N_cap, int64_t tok_begin, int64_t tok_count,
     int C_cap, int c_begin, int c_count, int label_bits, int n_chunks, int chunk_tokens,
-    const int32_t* __restrict__ chunk_hist, const int32_t* __restrict__ sizes,
+    const uint32_t* __restrict__ seg, const int32_t* __restrict__ sizes,
     int32_t* __restrict__ offsets, int32_t* __restrict__ sorted_idx,
     const int32_t* __restrict__ gate) {
   extern __shared__ int lds_hist[];                     // [c_count] positions + [4][c_count] counts
@@ -201,7 +191,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
   int* cnt = lds_hist + c_count;
   int32_t* off_g = offsets + (int64_t)hp * (C_cap + 1);
   const int base0 = c_begin == 0 ? 0 : off_g[c_begin];
-  const int32_t* cbase = chunk_hist + ((int64_t)hp * n_chunks + chunk) * c_count;
+  const uint32_t* cbase = seg + ((int64_t)hp * n_chunks + chunk) * seg_stride(c_count);
   {
     const int32_t* sz = sizes + (int64_t)hp * C_cap + c_begin;
     int v[OFF_ITEMS], own[OFF_ITEMS], cb[OFF_ITEMS];
@@ -209,7 +199,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
     for (int i = 0; i < OFF_ITEMS; ++i) {
       const int c = tid * OFF_ITEMS + i;
       own[i] = v[i] = c < c_count ? sz[c] : 0;
-      cb[i] = c < c_count ? cbase[c] : 0;
+      cb[i] = c < c_count ? (int)cbase[c] : 0;
     }
     block_inclusive_scan<OFF_ITEMS>(v, tmp);
 #pragma unroll
@@ -259,27 +249,61 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
 
 hipError_t launch_metadata(const Dims& dm, const int32_t* labels, int64_t tok_begin,
                            int64_t tok_count, int c_begin, int c_count, int32_t* sizes,
-                           int32_t* offsets, int32_t* sorted_idx, int32_t* chunk_hist,
-                           bool have_hist, const int32_t* gate, hipStream_t st) {
+                           int32_t* offsets, int32_t* sorted_idx, uint32_t* seg,
+                           bool have_seg, const int32_t* gate, hipStream_t st) {
   const int chunk_tokens = assign_tile_tokens(dm, tok_count);
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
   const dim3 grid((n_chunks + 3) / 4, dm.HP);
-  if (!have_hist)
+  if (!have_seg)
     hipLaunchKernelGGL(k_sort_hist, grid, dim3(SORT_THREADS), (size_t)4 * c_count * sizeof(int),
                        st, labels, dm.N_cap, tok_begin, tok_count, c_begin, c_count, label_bits,
-                       n_chunks, chunk_tokens, chunk_hist);
+                       n_chunks, chunk_tokens, seg);
   hipLaunchKernelGGL(k_sort_scan, dim3((c_count + 63) / 64, dm.HP), dim3(SCAN_THREADS), 0, st,
-                     chunk_hist, n_chunks, dm.C_cap, c_begin, c_count, sizes, gate);
+                     seg, n_chunks, dm.C_cap, c_begin, c_count, sizes, gate);
   hipLaunchKernelGGL(k_sort_scatter, dim3(n_chunks, dm.HP), dim3(SORT_THREADS),
                      (size_t)5 * c_count * sizeof(int), st, labels, dm.N_cap, tok_begin, tok_count,
-                     dm.C_cap, c_begin, c_count, label_bits, n_chunks, chunk_tokens, chunk_hist,
+                     dm.C_cap, c_begin, c_count, label_bits, n_chunks, chunk_tokens, seg,
                      sizes, offsets, sorted_idx, gate);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ update
+// One wavefront turns the member sums of channels 2*lane, 2*lane+1 into the stored mean,
+// the table row of the next assignment and, for l2, its bias.
+__device__ __forceinline__ void store_mean(float m0, float m1, int n, int hp, int c, int C_cap,
+                                           int c_begin, int c_count, bf16* __restrict__ centroids,
+                                           bf16* __restrict__ mu_hat,
+                                           float* __restrict__ centroids_f32, int metric,
+                                           float* __restrict__ bias, int bias_stride) {
+  const int lane = threadIdx.x & 63;
+  const float inv_n = 1.0f / (float)n;
+  m0 *= inv_n;
+  m1 *= inv_n;
+  // written as one fused multiply-add: left to the compiler, its choice of the fused product
+  // (and with it the last bit of the norm) would depend on the kernel this is inlined into
+  const float n2 = wave_sum(fmaf(m1, m1, m0 * m0));
+  const float inv = n2 > 0.f ? 1.0f / sqrtf(n2) : 0.f;
+  const int64_t crow = (int64_t)hp * C_cap + c_begin + c;
+  const int64_t hrow = (int64_t)hp * c_count + c;
+  const uint32_t raw =
+      (uint32_t)float_to_bf16_bits(m0) | ((uint32_t)float_to_bf16_bits(m1) << 16);
+  reinterpret_cast<uint32_t*>(centroids + crow * D)[lane] = raw;
+  // table row of the next assignment: unit length (cosine) or the stored mean itself
+  reinterpret_cast<uint32_t*>(mu_hat + hrow * D)[lane] =
+      metric == CK_METRIC_COSINE
+          ? ((uint32_t)float_to_bf16_bits(m0 * inv) | ((uint32_t)float_to_bf16_bits(m1 * inv) << 16))
+          : raw;
+  if (metric == CK_METRIC_L2) {                         // wave-uniform
+    const float r0 = lo_bf16(raw), r1 = hi_bf16(raw);   // the rounded row is what gets compared
+    const float rn2 = wave_sum(fmaf(r1, r1, r0 * r0));
+    if (lane == 0) bias[(int64_t)hp * bias_stride + c] = -0.5f * rn2;
+  }
+  if (centroids_f32)
+    reinterpret_cast<float2*>(centroids_f32 + hrow * D)[lane] = make_float2(m0, m1);
+}
+
 // One workgroup per cluster.  A 16-lane group reads one member row per step
 // (16 B per lane), 4 rows per wavefront step, UPD_UNR steps in flight.  Partial
 // sums are combined in a fixed order: lane groups of a wavefront, then the
@@ -345,34 +369,14 @@ __global__ __launch_bounds__(UPD_WAVES * 64) void k_update(
   __syncthreads();
   if (tid < 64) {
     // lane handles channels 2*lane, 2*lane+1
-    const float inv_n = 1.0f / (float)n;
     float m0 = part[0][2 * lane], m1 = part[0][2 * lane + 1];
 #pragma unroll
     for (int wv = 1; wv < UPD_WAVES; ++wv) {
       m0 += part[wv][2 * lane];
       m1 += part[wv][2 * lane + 1];
     }
-    m0 *= inv_n;
-    m1 *= inv_n;
-    const float n2 = wave_sum(m0 * m0 + m1 * m1);
-    const float inv = n2 > 0.f ? 1.0f / sqrtf(n2) : 0.f;
-    const int64_t crow = (int64_t)hp * C_cap + c_begin + c;
-    const int64_t hrow = (int64_t)hp * c_count + c;
-    const uint32_t raw =
-        (uint32_t)float_to_bf16_bits(m0) | ((uint32_t)float_to_bf16_bits(m1) << 16);
-    reinterpret_cast<uint32_t*>(centroids + crow * D)[lane] = raw;
-    // table row of the next assignment: unit length (cosine) or the stored mean itself
-    reinterpret_cast<uint32_t*>(mu_hat + hrow * D)[lane] =
-        metric == CK_METRIC_COSINE
-            ? ((uint32_t)float_to_bf16_bits(m0 * inv) | ((uint32_t)float_to_bf16_bits(m1 * inv) << 16))
-            : raw;
-    if (metric == CK_METRIC_L2) {                       // wave-uniform
-      const float r0 = lo_bf16(raw), r1 = hi_bf16(raw); // the rounded row is what gets compared
-      const float rn2 = wave_sum(r0 * r0 + r1 * r1);
-      if (lane == 0) bias[(int64_t)hp * bias_stride + c] = -0.5f * rn2;
-    }
-    if (centroids_f32)
-      reinterpret_cast<float2*>(centroids_f32 + hrow * D)[lane] = make_float2(m0, m1);
+    store_mean(m0, m1, n, hp, c, C_cap, c_begin, c_count, centroids, mu_hat, centroids_f32, metric,
+               bias, bias_stride);
   }
 }
 
@@ -388,6 +392,243 @@ hipError_t launch_update(const Dims& dm, const bf16* K, const int32_t* offsets,
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ from the chunk index
+// The assignment leaves every chunk's tokens ordered by label (ChunkIndex), so the members of
+// a cluster in ascending token order are its runs of chunk 0, chunk 1, ...: no sorted list is
+// needed to sum them.  A wavefront scans the run lengths of its cluster over the chunks and
+// finds the run that holds the j-th member by binary search in LDS.
+constexpr int CHUNK_RUNS_MAX = 512;                     // chunks per head-problem (LDS: 2 words each)
+
+struct ChunkRuns {
+  const uint32_t* seg;
+  const uint16_t* list;
+  int n_chunks, chunk_tokens;
+  int64_t tok_count;
+
+  const uint32_t* runs;         // this cluster's words of seg, by chunk (LDS)
+  const int* upto;              // members up to and including a chunk (LDS)
+  const uint16_t* list_hp;
+  int n;                        // members
+
+  // All threads of the workgroup; ends with a barrier.  The words of clusters c0 .. c0 + CL,
+  // then cluster c0 + cl for this wavefront (the wavefronts of one cluster do the same scan).
+  template <int CL, int THREADS>
+  __device__ __forceinline__ void stage(uint32_t* lds, int hp, int c0, int cl, int c_count) {
+    constexpr int BATCH = 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int cpad = (n_chunks + 63) & ~63, stride = seg_stride(c_count);
+    const uint32_t* S = seg + (int64_t)hp * n_chunks * stride;
+    for (int e0 = tid; e0 < cpad * CL; e0 += BATCH * THREADS) {
+      uint32_t v[BATCH];
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {                 // unconditional: one round trip
+        const int k = (e0 + i * THREADS) / CL, w = e0 % CL;   // neighbouring clusters share a line
+        const bool ok = k < n_chunks && c0 + w < c_count;
+        v[i] = S[ok ? (int64_t)k * stride + c0 + w : 0];
+        v[i] = ok ? v[i] : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {
+        const int k = (e0 + i * THREADS) / CL, w = e0 % CL;
+        if (k < cpad) lds[(size_t)w * 2 * cpad + k] = v[i];
+      }
+    }
+    __syncthreads();
+    uint32_t* r = lds + (size_t)cl * 2 * cpad;
+    int* u = reinterpret_cast<int*>(r + cpad);
+    n = 0;
+    for (int k0 = 0; k0 < cpad; k0 += WAVE) {
+      const int v = wave_inclusive_scan((int)(r[k0 + lane] >> 16)) + n;
+      u[k0 + lane] = v;
+      n = __builtin_amdgcn_readlane(v, WAVE - 1);
+    }
+    runs = r;
+    upto = u;
+    list_hp = list + (int64_t)hp * n_chunks * chunk_tokens;
+    wave_lds_order();
+  }
+  // token (offset in the range) of member j, clamped to the last one; n > 0
+  __device__ __forceinline__ int member(int j) const {
+    j = j < n ? j : n - 1;
+    int lo = 0, hi = n_chunks - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (upto[mid] > j) hi = mid; else lo = mid + 1;
+    }
+    const uint32_t r = runs[lo];
+    int at = (int)(r & 0xFFFFu) + j - (upto[lo] - (int)(r >> 16));
+    at = at < 0 ? 0 : (at >= chunk_tokens ? chunk_tokens - 1 : at);
+    const int64_t t = (int64_t)lo * chunk_tokens + list_hp[(int64_t)lo * chunk_tokens + at];
+    return (int)(t < tok_count ? t : tok_count - 1);    // never outside the keys
+  }
+};
+
+// Update: one workgroup per cluster, wavefront w summing members 16 s + 4 w + (0..3) of every
+// step s, 128 rows in flight.  The additions run in k_update's order (16 member streams, the
+// four of a wavefront, then the wavefronts), so both give the same bits.
+// Bound: launch, two dependent look-ups (runs, list) and the rows at memory speed.  It takes
+// the place of a scan, a scatter and k_update, of which none has enough to do to hide its own
+// start; per iteration, assignment included: 8 head-problems x 32768 tokens x 400 clusters
+// 53.3 -> 47.0 us (reading those keys once: 10.4 us), 64 x 8163 x 102 58.5 -> 52.3,
+// 8 x 131072 x 1600 407 -> 399, 8 x 2985 x 37 15.8 -> 9.9.  One wavefront per cluster with
+// four accumulator sets (one to eight clusters per workgroup) is within 2 % on the large
+// shapes and 3 us slower on the small one; two wavefronts per cluster are slower everywhere.
+constexpr int UPC_WAVES = 4;
+constexpr int UPC_STEPS = 8;                            // 16-row steps whose loads are in flight together
+
+__global__ __launch_bounds__(UPC_WAVES * 64, 7) void k_update_chunks(
+    const bf16* __restrict__ K, const uint32_t* __restrict__ seg,
+    const uint16_t* __restrict__ list, int n_chunks, int chunk_tokens, int64_t N_cap,
+    int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin, int c_count,
+    bf16* __restrict__ centroids, bf16* __restrict__ mu_hat, int32_t* __restrict__ sizes,
+    int metric, float* __restrict__ bias, int bias_stride, const int32_t* __restrict__ gate) {
+  constexpr int SPAN = 256;                             // members whose ids a workgroup holds at once
+  extern __shared__ uint32_t lds_u[];
+  __shared__ __attribute__((aligned(16))) float part[UPC_WAVES][D];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  // neighbouring clusters, whose run words share cache lines, go to one XCD (workgroup i runs
+  // on XCD i % 8)
+  const int hp = blockIdx.y, c = (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8);
+  if (c >= c_count) return;
+  if (gate && gate[hp] == 0) return;
+  CK_FETCH_ARG(centroids);                              // used last, fetched with the others
+  CK_FETCH_ARG(metric);
+  ChunkRuns cr = {seg, list, n_chunks, chunk_tokens, tok_count};
+  cr.stage<1, UPC_WAVES * 64>(lds_u, hp, c, 0, c_count);
+  const int n = cr.n;
+  if (tid == 0) sizes[(int64_t)hp * C_cap + c_begin + c] = n;
+  if (n == 0) return;                                   // empty cluster keeps its centroid
+
+  const bf16* Khp = K + ((int64_t)hp * N_cap + tok_begin) * D + l16 * 8;
+  float acc[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+  const int jl = (lane >> 2) * 16 + wave * 4 + (lane & 3);   // the member whose id this lane holds
+  int id = cr.member(jl);
+  for (int j0 = 0; j0 < n; j0 += SPAN) {
+    const int now = id;
+#pragma unroll
+    for (int s0 = 0; s0 < SPAN / 16; s0 += UPC_STEPS) {
+      if (j0 + s0 * 16 >= n) break;                     // uniform
+      uint4 r[UPC_STEPS];
+#pragma unroll
+      for (int s = 0; s < UPC_STEPS; ++s) {
+        const int t = __shfl(now, (s0 + s) * 4 + g4, WAVE);
+        r[s] = *reinterpret_cast<const uint4*>(Khp + (int64_t)t * D);
+      }
+      // the members of the next pass are looked up while the first rows of this one travel
+      if (s0 == 0 && j0 + SPAN < n) id = cr.member(j0 + SPAN + jl);
+#pragma unroll
+      for (int s = 0; s < UPC_STEPS; ++s) {
+        const bool real = j0 + (s0 + s) * 16 + wave * 4 + g4 < n;
+        const uint32_t x = real ? r[s].x : 0u, y = real ? r[s].y : 0u;
+        const uint32_t z = real ? r[s].z : 0u, q = real ? r[s].w : 0u;
+        acc[0] += lo_bf16(x); acc[1] += hi_bf16(x);
+        acc[2] += lo_bf16(y); acc[3] += hi_bf16(y);
+        acc[4] += lo_bf16(z); acc[5] += hi_bf16(z);
+        acc[6] += lo_bf16(q); acc[7] += hi_bf16(q);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float v = xor32(xor16(acc[j], OpSum()), OpSum());
+    if (lane < 16) part[wave][l16 * 8 + j] = v;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  float m0 = part[0][2 * lane], m1 = part[0][2 * lane + 1];
+#pragma unroll
+  for (int w = 1; w < UPC_WAVES; ++w) {
+    m0 += part[w][2 * lane];
+    m1 += part[w][2 * lane + 1];
+  }
+  store_mean(m0, m1, n, hp, c, C_cap, c_begin, c_count, centroids, mu_hat, nullptr, metric, bias,
+             bias_stride);
+}
+
+// Metadata of the final labels: offsets (prefix sum of the sizes the last update wrote) and
+// the label-sorted index, one wavefront per cluster.  One launch where the counting sort needs
+// two, and the index leaves in coalesced stores.
+constexpr int EMIT_WAVES = 8;                           // clusters per workgroup
+
+__global__ __launch_bounds__(EMIT_WAVES * 64) void k_emit_index(
+    const uint32_t* __restrict__ seg, const uint16_t* __restrict__ list, int n_chunks,
+    int chunk_tokens, int64_t N_cap, int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin,
+    int c_count, const int32_t* __restrict__ sizes, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ sorted_idx) {
+  extern __shared__ uint32_t lds_u[];
+  __shared__ int below[EMIT_WAVES], own[EMIT_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int hp = blockIdx.y, c0 = blockIdx.x * EMIT_WAVES, c = c0 + wave;
+  int32_t* off_g = offsets + (int64_t)hp * (C_cap + 1);
+  const int32_t* sz = sizes + (int64_t)hp * C_cap + c_begin;
+  constexpr int PER = CK_MAX_CLUSTERS / (EMIT_WAVES * 64);
+  int sum = 0;                                          // sizes of the clusters before this workgroup's
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int b = tid + i * EMIT_WAVES * 64;
+    const int v = sz[b < c_count ? b : 0];
+    sum += b < c0 ? v : 0;
+  }
+  const int base0 = c_begin == 0 ? 0 : off_g[c_begin];
+  ChunkRuns cr = {seg, list, n_chunks, chunk_tokens, tok_count};
+  cr.stage<EMIT_WAVES, EMIT_WAVES * 64>(lds_u, hp, c0, wave, c_count);
+  sum = __builtin_amdgcn_readlane(wave_inclusive_scan(sum), WAVE - 1);
+  if (lane == 0) {
+    below[wave] = sum;
+    own[wave] = cr.n;
+  }
+  __syncthreads();
+  if (c >= c_count) return;
+  int base = base0;
+#pragma unroll
+  for (int w = 0; w < EMIT_WAVES; ++w) base += below[w] + (w < wave ? own[w] : 0);
+  if (lane == 0) {
+    off_g[c_begin + c + 1] = base + cr.n;
+    if (c == 0 && c_begin == 0) off_g[0] = 0;
+  }
+  int32_t* out = sorted_idx + (int64_t)hp * N_cap;
+  for (int j = lane; j < cr.n; j += WAVE) {
+    const int64_t pos = (int64_t)base + j;
+    if (pos >= 0 && pos < N_cap) out[pos] = (int32_t)(tok_begin + cr.member(j));
+  }
+}
+
+bool update_chunks_fits(const Dims& dm, int64_t tok_count) {
+  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+  return (tok_count + chunk_tokens - 1) / chunk_tokens <= CHUNK_RUNS_MAX;
+}
+
+static size_t chunk_runs_lds(int clusters, int n_chunks) {
+  return (size_t)clusters * 2 * ((n_chunks + 63) & ~63) * sizeof(uint32_t);
+}
+
+hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
+                                int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
+                                bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
+                                float* bias, int bias_stride, const int32_t* gate, hipStream_t st) {
+  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+  const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
+  hipLaunchKernelGGL(k_update_chunks, dim3((c_count + 7) / 8 * 8, dm.HP), dim3(UPC_WAVES * 64),
+                     chunk_runs_lds(1, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
+                     chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin, c_count,
+                     centroids, mu_hat, sizes, metric, bias, bias_stride, gate);
+  return hipGetLastError();
+}
+
+hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
+                             int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
+                             int32_t* offsets, int32_t* sorted_idx, hipStream_t st) {
+  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+  const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
+  hipLaunchKernelGGL(k_emit_index, dim3((c_count + EMIT_WAVES - 1) / EMIT_WAVES, dm.HP),
+                     dim3(EMIT_WAVES * 64), chunk_runs_lds(EMIT_WAVES, n_chunks), st, chunks.seg, chunks.list,
+                     n_chunks, chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin,
+                     c_count, sizes, offsets, sorted_idx);
+  return hipGetLastError();
+}
+
 ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count,
                                          void* base) {
   ClusterWorkspace w;
@@ -395,8 +636,10 @@ ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int 
   const int64_t n_chunks = (tok_count + chunk_tokens - 1) / chunk_tokens;
   size_t mu = (size_t)dm.HP * c_count * D * sizeof(bf16);
   mu = (mu + 255) & ~(size_t)255;
-  size_t hist = (size_t)dm.HP * n_chunks * c_count * sizeof(int32_t);
-  hist = (hist + 255) & ~(size_t)255;
+  size_t seg = (size_t)dm.HP * n_chunks * seg_stride(c_count) * sizeof(uint32_t);
+  seg = (seg + 255) & ~(size_t)255;
+  size_t list = (size_t)dm.HP * n_chunks * chunk_tokens * sizeof(uint16_t);
+  list = (list + 255) & ~(size_t)255;
   w.bias_stride = (c_count + 31) / 32 * 32;
   size_t bias = (size_t)dm.HP * w.bias_stride * sizeof(float);
   bias = (bias + 255) & ~(size_t)255;
@@ -404,10 +647,11 @@ ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int 
   chg = (chg + 255) & ~(size_t)255;
   char* b = reinterpret_cast<char*>(base);
   w.mu_hat = reinterpret_cast<bf16*>(b);
-  w.chunk_hist = reinterpret_cast<int32_t*>(b + mu);
-  w.bias = reinterpret_cast<float*>(b + mu + hist);
-  w.changed = reinterpret_cast<int32_t*>(b + mu + hist + bias);
-  w.bytes = mu + hist + bias + chg;
+  w.chunks.seg = reinterpret_cast<uint32_t*>(b + mu);
+  w.chunks.list = reinterpret_cast<uint16_t*>(b + mu + seg);
+  w.bias = reinterpret_cast<float*>(b + mu + seg + list);
+  w.changed = reinterpret_cast<int32_t*>(b + mu + seg + list + bias);
+  w.bytes = mu + seg + list + bias + chg;
   return w;
 }
 
