@@ -41,13 +41,40 @@ __device__ __forceinline__ void load_query_operand(const bf16* __restrict__ q_gr
   for (int sl = 0; sl < 4; ++sl)
     qb[sl] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p + sl * 32));
 }
-// t[sl]: this lane's 16 bytes of table row lane%16 (channels 32*sl + 8*(lane/16) ..).
-// Returns in lanes 0..15 the score of table row `lane` of the step.
-__device__ __forceinline__ float score_rows16(const uint4 (&t)[4], const bf16x8 (&qb)[4], int G) {
+// Sixteen rows of a table (or of K) as an MFMA operand.  The operand wants lane l to hold
+// channels 32*sl + 8*(l/16) .. +8 of row l%16, and loading it that way makes every lane of a
+// quarter wavefront touch another row: the address unit then spends about 64 cycles on a
+// 1 KB instruction instead of 16 (400 rows by one workgroup: 3.0 us against 1.0 us,
+// whether they come from L2 or from memory).  So 16 lanes load one whole 256-byte row --
+// lane l the 16 bytes l%16 of row 4*(l/16) + i of the step, i = 0..3 -- and the rows change
+// lanes through a wavefront-private piece of LDS (row stride 272 B: no bank conflicts).
+constexpr int STAGE_ROW = D + 8;                          // bf16 elements per staged row
+constexpr int STAGE_ELEMS = 16 * STAGE_ROW;               // of one wavefront
+struct Stage16 {
+  uint4* w;                                               // this lane's place in the rows it loaded
+  const uint4* r;                                         // and in the row it is the operand lane of
+  __device__ __forceinline__ Stage16(bf16* stage, int lane)
+      : w(reinterpret_cast<uint4*>(stage + 4 * (lane >> 4) * STAGE_ROW + (lane & 15) * 8)),
+        r(reinterpret_cast<const uint4*>(stage + (lane & 15) * STAGE_ROW + (lane >> 4) * 8)) {}
+  // LDS serves one wavefront in order: the reads see the writes, and the next writes wait
+  __device__ __forceinline__ void put(uint4 a, uint4 b, uint4 c, uint4 d) const {
+    wave_lds_order();
+    w[0] = a;
+    w[STAGE_ROW / 8] = b;
+    w[2 * (STAGE_ROW / 8)] = c;
+    w[3 * (STAGE_ROW / 8)] = d;
+    wave_lds_order();
+  }
+  __device__ __forceinline__ bf16x8 operand(int sl) const {
+    return __builtin_bit_cast(bf16x8, r[4 * sl]);
+  }
+};
+// Of the 16 staged table rows; returns in lanes 0..15 the score of row `lane`.
+__device__ __forceinline__ float score_rows16(const Stage16& st, const bf16x8 (&qb)[4], int G) {
   floatx4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int sl = 0; sl < 4; ++sl)
-    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qb[sl], __builtin_bit_cast(bf16x8, t[sl]), d, 0, 0, 0);
+    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qb[sl], st.operand(sl), d, 0, 0, 0);
   // accumulator i of lanes 0..15 is head i, of lanes 16..31 head 4 + i
   float v = d[0];
   if (G >= 2) v += d[1];
@@ -63,19 +90,18 @@ __device__ __forceinline__ uint32_t ordered_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-constexpr int SELP_THREADS = 256;          // every kernel that selects runs 256 threads
 constexpr int SELP_BINS = 256;
 constexpr int SELP_MAX_CAND = 512;         // more candidates than this: rank all clusters
 constexpr int SELP_SMALL = 512;            // cluster bound of the small instantiation
 
-// LDS of one selection, sized for at most CMAX clusters (512 or CK_MAX_CLUSTERS: the
-// launcher picks the smallest that holds the table, so that a few hundred clusters do
-// not reserve the LDS of two thousand and more workgroups fit a CU).  After
-// select_prefix(): ord[j], cbeg[j], cum[j] for j < n_sel describe the recalled clusters
-// in score order (cum = inclusive prefix sum of their sizes).
-template <int CMAX>
+// LDS of one selection by NT threads, sized for at most CMAX clusters (512 or
+// CK_MAX_CLUSTERS: the launcher picks the smallest that holds the table, so that a few
+// hundred clusters do not reserve the LDS of two thousand and more workgroups fit a CU).
+// After select_prefix_regs(): ord[j], cbeg[j], cum[j] for j < n_sel describe the recalled
+// clusters in score order (cum = inclusive prefix sum of their sizes).
+template <int CMAX, int NT>
 struct alignas(16) SelectLds {
-  static_assert(CMAX % SELP_THREADS == 0 && CMAX >= SELP_MAX_CAND, "cluster bound");
+  static_assert(CMAX % NT == 0 && CMAX >= SELP_MAX_CAND, "cluster bound");
   uint32_t key[CMAX];              // ~ordered(score): ascending key = descending score
   int ssz[CMAX];                   // size per cluster id
   int soff[CMAX];                  // offsets[cluster] per cluster id (when offsets are given)
@@ -86,9 +112,9 @@ struct alignas(16) SelectLds {
   uint32_t ckey[SELP_MAX_CAND];    // their keys, dense, so that the ranking loop streams
   int bin_size[SELP_BINS];
   int bin_cnt[SELP_BINS];
-  float red_f[2 * (SELP_THREADS / WAVE)];
-  int tmp[SELP_THREADS / WAVE + 1];
-  int n_cand, n_sel, n_tok, counter, full_rank, last_bin, n_app, fast_ok;
+  float red_f[2 * (NT / WAVE)];
+  int tmp[NT / WAVE + 1];
+  int n_cand, n_sel, n_tok, counter, full_rank, last_bin, n_app;
 };
 
 // Orders the clusters of one head-problem by descending score (ties: lower id
@@ -97,28 +123,28 @@ struct alignas(16) SelectLds {
 //   trim == 1: shortest prefix whose sizes sum to >= budget (all if the total is smaller).
 // A histogram of the scores (sizes accumulated per bin) bounds the prefix first, so
 // that only a few dozen candidates are ranked; degenerate score distributions fall
-// back to ranking every cluster.  Must be called by all SELP_THREADS threads.
-// This form takes the values a thread owns in registers (cluster tid + i * SELP_THREADS;
+// back to ranking every cluster.  Must be called by all NT threads.
+// This form takes the values a thread owns in registers (cluster tid + i * NT;
 // entries beyond C are ignored), so that a caller can have fetched them long before.
-template <int CMAX>
-__device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
-                                                   const float (&sc)[CMAX / SELP_THREADS],
-                                                   const int (&sz)[CMAX / SELP_THREADS],
-                                                   const int (&of)[CMAX / SELP_THREADS],
+template <int CMAX, int NT>
+__device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX, NT>& L,
+                                                   const float (&sc)[CMAX / NT],
+                                                   const int (&sz)[CMAX / NT],
+                                                   const int (&of)[CMAX / NT],
                                                    bool offsets, int C, int budget, int trim) {
-  constexpr int SELP_ITEMS = CMAX / SELP_THREADS;
+  constexpr int SELP_ITEMS = CMAX / NT;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float smax = -INFINITY, smin = INFINITY;
   if (offsets) {
 #pragma unroll
     for (int i = 0; i < SELP_ITEMS; ++i) {
-      const int c = tid + i * SELP_THREADS;
+      const int c = tid + i * NT;
       if (c < C) L.soff[c] = of[i];
     }
   }
 #pragma unroll
   for (int i = 0; i < SELP_ITEMS; ++i) {
-    const int c = tid + i * SELP_THREADS;
+    const int c = tid + i * NT;
     if (c < C) {
       L.key[c] = ~ordered_bits(sc[i]);
       L.ssz[c] = sz[i];
@@ -126,11 +152,11 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
       smin = fminf(smin, sc[i]);
     }
   }
-  for (int b = tid; b < SELP_BINS; b += SELP_THREADS) {
+  for (int b = tid; b < SELP_BINS; b += NT) {
     L.bin_size[b] = 0;
     L.bin_cnt[b] = 0;
   }
-  for (int i = tid; i < SELP_MAX_CAND; i += SELP_THREADS) {
+  for (int i = tid; i < SELP_MAX_CAND; i += NT) {
     L.ckey[i] = 0xFFFFFFFFu;                     // padding that never ranks before anything
     L.cand[i] = 0x7FFFFFFF;
   }
@@ -142,20 +168,20 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
   smin = wave_min(smin);
   if (lane == 0) {
     L.red_f[wave] = smax;
-    L.red_f[SELP_THREADS / WAVE + wave] = smin;
+    L.red_f[NT / WAVE + wave] = smin;
   }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < SELP_THREADS / WAVE; ++w) {
+  for (int w = 0; w < NT / WAVE; ++w) {
     smax = fmaxf(smax, L.red_f[w]);
-    smin = fminf(smin, L.red_f[SELP_THREADS / WAVE + w]);
+    smin = fminf(smin, L.red_f[NT / WAVE + w]);
   }
   const float span = smax - smin;
   const float inv = span > 0.f ? (float)(SELP_BINS - 1) / span : 0.f;
   int bin[SELP_ITEMS];
 #pragma unroll
   for (int i = 0; i < SELP_ITEMS; ++i) {
-    const int c = tid + i * SELP_THREADS;
+    const int c = tid + i * NT;
     // monotone: a larger score never lands in a later bin
     int b = (int)((smax - sc[i]) * inv);
     b = b < 0 ? 0 : (b > SELP_BINS - 1 ? SELP_BINS - 1 : b);
@@ -209,7 +235,7 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
     // themselves ----
 #pragma unroll
     for (int i = 0; i < SELP_ITEMS; ++i) {
-      const int c = tid + i * SELP_THREADS;
+      const int c = tid + i * NT;
       if (c < C && bin[i] <= last_bin) {
         const int pos = atomicAdd(&L.n_app, 1);
         L.cand[pos] = c;
@@ -218,7 +244,7 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
     }
     __syncthreads();
     const int m_pad = (m + 3) & ~3;
-    for (int i = tid; i < m; i += SELP_THREADS) {
+    for (int i = tid; i < m; i += NT) {
       const int c = L.cand[i];
       const uint32_t kc = L.ckey[i];
       const int ob = offsets ? L.soff[c] : 0;
@@ -238,9 +264,9 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
   } else {
     // ---- rank every cluster (all scores equal, budget beyond the total, ...) ----
     const int n_pad = (C + 3) & ~3;
-    for (int j = C + tid; j < n_pad; j += SELP_THREADS) L.key[j] = 0xFFFFFFFFu;
+    for (int j = C + tid; j < n_pad; j += NT) L.key[j] = 0xFFFFFFFFu;
     __syncthreads();
-    for (int c = tid; c < C; c += SELP_THREADS) {
+    for (int c = tid; c < C; c += NT) {
       const uint32_t kc = L.key[c];
       int rank = 0;
       for (int j = 0; j < n_pad; j += 4) {
@@ -307,163 +333,163 @@ __device__ __forceinline__ void select_prefix_regs(SelectLds<CMAX>& L,
   __syncthreads();
 }
 
-// The selection by ONE wavefront, without workgroup barriers, for tables of at most
-// SELP_SMALL clusters whose recalled prefix is bounded by at most 64 candidates (the usual
-// case: a few dozen).  Same result as select_prefix_regs.  Before the call: sc[c] (LDS),
-// L.ssz[c] and L.soff[c] hold score, size and offset of every cluster c < C, and a
-// workgroup barrier has been passed.  All threads call it; it ends with a barrier and
-// returns false (for every thread) when the candidate bound does not hold, in which case
-// nothing has been selected and the general form has to run.
-__device__ __forceinline__ bool select_prefix_wave(SelectLds<SELP_SMALL>& L, const float* sc,
-                                                   int C, int budget, int trim) {
-  constexpr int PER_LANE = SELP_SMALL / WAVE;           // 8 clusters per lane: 8*lane + i
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (tid < WAVE) {
-    float s[PER_LANE];
-    int z[PER_LANE];
-    {
-      const floatx4* sp = reinterpret_cast<const floatx4*>(sc + lane * PER_LANE);
-      const int4* zp = reinterpret_cast<const int4*>(&L.ssz[lane * PER_LANE]);
+// ---- the usual selection: a recalled prefix bounded by at most 64 candidates ----
+// Every phase is spread over the workgroup and the three barriers are all there is: binning
+// of the scores (all threads), the bin where the budget is crossed (every wavefront for
+// itself), compaction of the candidates (all threads), their ranks (64 / NW candidates
+// per wavefront, NW lanes each), and the prefix sum over the ranked sizes (every wavefront for
+// itself, in registers, where the resolution of positions to token rows reads it).
+// One wavefront doing all of it, without barriers, took 2.6 us at 400 clusters: a long chain
+// of dependent instructions with nothing to issue in between.
+template <int NT>
+struct alignas(16) QuickLds {
+  unsigned long long bin[SELP_BINS];       // sizes of the clusters of a bin | their number << 32
+  unsigned long long ckey[WAVE];           // candidates: key << 32 | cluster id, any order
+  int csz[WAVE], coff[WAVE];               // their sizes and offsets
+  int ord[WAVE], osz[WAVE], ooff[WAVE];    // cluster id, size and offset by rank
+  float mx[NT / WAVE], mn[NT / WAVE];      // score range seen by every wavefront
+  int n_app;
+};
+// What a wavefront knows afterwards: lane j holds the cluster of rank j (j < m).
+struct Quick {
+  int m;                                   // candidates; > 64: nothing selected, use the general form
+  int n_sel, n_tok;                        // recalled clusters and tokens
+  int id, size, off, cum;                  // of rank `lane`; cum = inclusive prefix sum of sizes
+};
+
+// Before the score range and the first barrier.
+template <int NT>
+__device__ __forceinline__ void quick_clear(QuickLds<NT>& Q) {
+  for (int b = threadIdx.x; b < SELP_BINS; b += NT) Q.bin[b] = 0ull;
+  if (threadIdx.x < WAVE) Q.ckey[threadIdx.x] = ~0ull;   // padding that never ranks before anything
+  if (threadIdx.x == 0) Q.n_app = 0;
+}
+// Score range of this wavefront's clusters, into Q; a workgroup barrier has to follow.
+template <int NT>
+__device__ __forceinline__ void quick_range(QuickLds<NT>& Q, float mx, float mn) {
+  mx = wave_max(mx);
+  mn = wave_min(mn);
+  if ((threadIdx.x & 63) == 0) {
+    Q.mx[threadIdx.x >> 6] = mx;
+    Q.mn[threadIdx.x >> 6] = mn;
+  }
+}
+// sc, sz, of: score, size, offset of cluster tid + i * NT.  Ends without a barrier.
+template <int NT, int ITEMS>
+__device__ __forceinline__ Quick quick_select(QuickLds<NT>& Q, const float (&sc)[ITEMS],
+                                              const int (&sz)[ITEMS], const int (&of)[ITEMS], int C,
+                                              int budget, int trim) {
+  constexpr int NW = NT / WAVE;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float smax = Q.mx[0], smin = Q.mn[0];
 #pragma unroll
-      for (int h = 0; h < PER_LANE / 4; ++h) {
-        const floatx4 a = sp[h];
-        const int4 b = zp[h];
-        s[4 * h] = a[0]; s[4 * h + 1] = a[1]; s[4 * h + 2] = a[2]; s[4 * h + 3] = a[3];
-        z[4 * h] = b.x; z[4 * h + 1] = b.y; z[4 * h + 2] = b.z; z[4 * h + 3] = b.w;
+  for (int w = 1; w < NW; ++w) {
+    smax = fmaxf(smax, Q.mx[w]);
+    smin = fminf(smin, Q.mn[w]);
+  }
+  const float span = smax - smin;
+  // (any positive factor gives a valid binning; the clamp below takes care of its rounding)
+  const float inv = span > 0.f ? (float)(SELP_BINS - 1) * __builtin_amdgcn_rcpf(span) : 0.f;
+  int bin[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    int b = (int)((smax - sc[i]) * inv);               // monotone: a larger score, no later bin
+    b = b < 0 ? 0 : (b > SELP_BINS - 1 ? SELP_BINS - 1 : b);
+    const bool ok = tid + i * NT < C;
+    bin[i] = ok ? b : SELP_BINS;                        // never a candidate
+    if (ok) atomicAdd(&Q.bin[b], (1ull << 32) | (uint32_t)sz[i]);
+  }
+  __syncthreads();
+  // first bin at which the running size crosses the budget; everything up to and including
+  // it is a candidate
+  constexpr int PER = SELP_BINS / WAVE;
+  int ss[PER], nn[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const unsigned long long v = Q.bin[lane * PER + i];
+    ss[i] = (int)(uint32_t)v + (i ? ss[i - 1] : 0);
+    nn[i] = (int)(v >> 32) + (i ? nn[i - 1] : 0);
+  }
+  const int sbase = wave_inclusive_scan(ss[PER - 1]) - ss[PER - 1];
+  const int nbase = wave_inclusive_scan(nn[PER - 1]) - nn[PER - 1];
+  int first = SELP_BINS, ncand = 0;
+#pragma unroll
+  for (int i = PER - 1; i >= 0; --i) {
+    const int cs = sbase + ss[i];
+    if (trim ? cs >= budget : cs > budget) {
+      first = lane * PER + i;
+      ncand = nbase + nn[i];
+    }
+  }
+  Quick r;
+  const uint64_t crossing = __ballot(first < SELP_BINS);
+  int last_bin = SELP_BINS - 1;
+  r.m = C;                                              // no crossing: every cluster is recalled
+  if (crossing) {
+    const int src = __builtin_ctzll(crossing);          // lowest lane = lowest bin
+    last_bin = __builtin_amdgcn_readlane(first, src);
+    r.m = __builtin_amdgcn_readlane(ncand, src);
+  }
+  r.n_sel = r.n_tok = 0;
+  r.id = r.size = r.off = r.cum = 0;
+  if (r.m > WAVE) return r;                             // the same in every wavefront
+  const uint64_t lt = ((uint64_t)1 << lane) - 1;
+  uint64_t mask[ITEMS];
+  int total = 0;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    mask[i] = __ballot(bin[i] <= last_bin);
+    total += __popcll(mask[i]);
+  }
+  if (total) {                                          // wave-uniform
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&Q.n_app, total);
+    base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      if (bin[i] <= last_bin) {
+        const int pos = base + __popcll(mask[i] & lt);
+        Q.ckey[pos] = ((unsigned long long)~ordered_bits(sc[i]) << 32) | (uint32_t)(tid + i * NT);
+        Q.csz[pos] = sz[i];
+        Q.coff[pos] = of[i];
       }
+      base += __popcll(mask[i]);
     }
-    float smax = -INFINITY, smin = INFINITY;
-#pragma unroll
-    for (int i = 0; i < PER_LANE; ++i) {
-      const bool ok = lane * PER_LANE + i < C;
-      smax = fmaxf(smax, ok ? s[i] : -INFINITY);
-      smin = fminf(smin, ok ? s[i] : INFINITY);
-    }
-    smax = wave_max(smax);
-    smin = wave_min(smin);
-    const float span = smax - smin;
-    const float inv = span > 0.f ? (float)(SELP_BINS - 1) / span : 0.f;
-    // histogram of the scores, sizes accumulated per bin
-    {
-      int4* bs = reinterpret_cast<int4*>(&L.bin_size[lane * 4]);
-      int4* bc = reinterpret_cast<int4*>(&L.bin_cnt[lane * 4]);
-      *bs = make_int4(0, 0, 0, 0);
-      *bc = make_int4(0, 0, 0, 0);
-    }
-    wave_lds_order();
-    int bin[PER_LANE];
-#pragma unroll
-    for (int i = 0; i < PER_LANE; ++i) {
-      int b = (int)((smax - s[i]) * inv);               // monotone: a larger score, no later bin
-      b = b < 0 ? 0 : (b > SELP_BINS - 1 ? SELP_BINS - 1 : b);
-      const bool ok = lane * PER_LANE + i < C;
-      bin[i] = ok ? b : SELP_BINS;                      // never a candidate
-      if (ok) {
-        atomicAdd(&L.bin_size[b], z[i]);
-        atomicAdd(&L.bin_cnt[b], 1);
-      }
-    }
-    wave_lds_order();
-    // first bin at which the running size crosses the budget
-    constexpr int PER = SELP_BINS / WAVE;
-    int ss[PER], nn[PER];
-    int ssum = 0, nsum = 0;
-    {
-      const int4 a = *reinterpret_cast<const int4*>(&L.bin_size[lane * PER]);
-      const int4 b = *reinterpret_cast<const int4*>(&L.bin_cnt[lane * PER]);
-      ss[0] = a.x; ss[1] = ss[0] + a.y; ss[2] = ss[1] + a.z; ss[3] = ss[2] + a.w;
-      nn[0] = b.x; nn[1] = nn[0] + b.y; nn[2] = nn[1] + b.z; nn[3] = nn[2] + b.w;
-      ssum = ss[3];
-      nsum = nn[3];
-    }
-    const int sbase = wave_inclusive_scan(ssum) - ssum, nbase = wave_inclusive_scan(nsum) - nsum;
-    int first = SELP_BINS, ncand = 0;
-#pragma unroll
-    for (int i = PER - 1; i >= 0; --i) {
-      const int cs = sbase + ss[i];
-      if (trim ? cs >= budget : cs > budget) {
-        first = lane * PER + i;
-        ncand = nbase + nn[i];
-      }
-    }
-    const uint64_t crossing = __ballot(first < SELP_BINS);
-    int last_bin = SELP_BINS - 1, m = C;                // no crossing: every cluster is recalled
-    if (crossing) {
-      const int src = __builtin_ctzll(crossing);        // lowest lane = lowest bin
-      last_bin = __builtin_amdgcn_readlane(first, src);
-      m = __builtin_amdgcn_readlane(ncand, src);
-    }
-    if (m > WAVE) {                                     // wave-uniform
-      if (lane == 0) L.fast_ok = 0;
-    } else {
-      // compact the candidates (any order), one per lane afterwards
-      const uint64_t lt = ((uint64_t)1 << lane) - 1;
-      int base = 0;
-#pragma unroll
-      for (int i = 0; i < PER_LANE; ++i) {
-        const bool is_c = bin[i] <= last_bin;
-        const uint64_t mask = __ballot(is_c);
-        if (is_c) {
-          const int pos = base + __popcll(mask & lt);
-          L.cand[pos] = lane * PER_LANE + i;
-          L.ckey[pos] = ~ordered_bits(s[i]);
-        }
-        base += __popcll(mask);
-      }
-      wave_lds_order();
-      const int c = lane < m ? L.cand[lane] : 0x7FFFFFFF;
-      const uint32_t kc = lane < m ? L.ckey[lane] : 0xFFFFFFFFu;
-      // rank among the candidates: ascending key = descending score, ties to the lower id
+  }
+  __syncthreads();
+  // rank among the candidates: ascending key = descending score, ties to the lower id
+  {
+    constexpr int PW = WAVE / NW;                       // candidates of this wavefront, NW lanes each
+    const int c = wave * PW + lane / NW, part = lane % NW;
+    if (wave * PW < r.m) {                              // wave-uniform
+      const unsigned long long kc = Q.ckey[c];
+      const int size = Q.csz[c], off = Q.coff[c];
       int rank = 0;
-      for (int j = 0; j < m; ++j) {
-        const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)kc, j);
-        const int cj = __builtin_amdgcn_readlane(c, j);
-        rank += (kj < kc || (kj == kc && cj < c)) ? 1 : 0;
-      }
-      if (lane < m) {
-        L.ord[rank] = c;
-        L.cum[rank] = L.ssz[c];
-        L.cbeg[rank] = L.soff[c];
-      }
-      wave_lds_order();
-      const int own = lane < m ? L.cum[lane] : 0;
-      const int v = wave_inclusive_scan(own);
-      if (lane < m) L.cum[lane] = v;
-      const bool in = lane < m && (trim ? (v < budget) : (v <= budget));
-      int n_sel = __popcll(__ballot(in));
-      if (trim) n_sel = n_sel + 1 < m ? n_sel + 1 : m;
-      int n_tok = n_sel > 0 ? __shfl(v, n_sel - 1, WAVE) : 0;
-      if (trim && n_tok > budget) n_tok = budget;
-      if (lane == 0) {
-        L.n_sel = n_sel;
-        L.n_tok = n_tok;
-        L.full_rank = 0;
-        L.fast_ok = 1;
+#pragma unroll
+      for (int i = 0; i < PW; ++i) rank += Q.ckey[part * PW + i] < kc ? 1 : 0;
+      // over the NW lanes of a candidate (4 or 8, inside one row of 16)
+      rank += __builtin_amdgcn_update_dpp(0, rank, DPP_XOR1, 0xf, 0xf, false);
+      rank += __builtin_amdgcn_update_dpp(0, rank, DPP_XOR2, 0xf, 0xf, false);
+      if (NW == 8) rank += __builtin_amdgcn_update_dpp(0, rank, DPP_HALF_MIRROR, 0xf, 0xf, false);
+      if (part == 0 && c < r.m) {
+        Q.ord[rank] = (int)(uint32_t)kc;
+        Q.osz[rank] = size;
+        Q.ooff[rank] = off;
       }
     }
   }
   __syncthreads();
-  return L.fast_ok != 0;
-}
-
-// The same, loading scores (global memory or LDS), sizes and offsets (nullable) here.
-template <int CMAX>
-__device__ __forceinline__ void select_prefix(SelectLds<CMAX>& L, const float* scores,
-                                              const int32_t* __restrict__ sizes,
-                                              const int32_t* __restrict__ offsets, int C,
-                                              int budget, int trim) {
-  constexpr int SELP_ITEMS = CMAX / SELP_THREADS;
-  const int tid = threadIdx.x;
-  float sc[SELP_ITEMS];
-  int sz[SELP_ITEMS], of[SELP_ITEMS];
-#pragma unroll
-  for (int i = 0; i < SELP_ITEMS; ++i) {
-    const int c = tid + i * SELP_THREADS;
-    sc[i] = c < C ? scores[c] : 0.f;
-    sz[i] = c < C ? sizes[c] : 0;
-    of[i] = (offsets && c < C) ? offsets[c] : 0;      // same round trip as the scores
-  }
-  select_prefix_regs<CMAX>(L, sc, sz, of, offsets != nullptr, C, budget, trim);
+  const bool in_m = lane < r.m;
+  r.id = in_m ? Q.ord[lane] : 0;
+  r.size = in_m ? Q.osz[lane] : 0;
+  r.off = in_m ? Q.ooff[lane] : 0;
+  r.cum = wave_inclusive_scan(r.size);
+  const bool in = in_m && (trim ? (r.cum < budget) : (r.cum <= budget));
+  r.n_sel = __popcll(__ballot(in));
+  if (trim) r.n_sel = r.n_sel + 1 < r.m ? r.n_sel + 1 : r.m;
+  r.n_tok = r.n_sel > 0 ? __builtin_amdgcn_readlane(r.cum, r.n_sel - 1) : 0;
+  if (trim && r.n_tok > budget) r.n_tok = budget;
+  return r;
 }
 
 }  // namespace ck

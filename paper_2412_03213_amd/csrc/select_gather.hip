@@ -28,19 +28,22 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_score(
     const int lane = tid & 63, wave = tid >> 6, col = lane & 15, kg = lane >> 4;
     bf16x8 qb[4];
     load_query_operand(q + ((int64_t)s * Hq + h * G) * D, G, lane, qb);
-    const bf16* Thp = table + ((int64_t)hp * table_stride + row_begin) * D + kg * 8;
+    __shared__ __attribute__((aligned(16))) bf16 stage[SCORE_THREADS / WAVE * STAGE_ELEMS];
+    const bf16* Thp = table + ((int64_t)hp * table_stride + row_begin) * D + col * 8;
+    const Stage16 st(stage + wave * STAGE_ELEMS, lane);
     uint4 a[U][4];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int r = c0 + (u * 4 + wave) * 16 + col;
-      if (r >= n_rows) r = n_rows - 1;                      // clamp: result is discarded
-#pragma unroll
-      for (int sl = 0; sl < 4; ++sl)
-        a[u][sl] = *reinterpret_cast<const uint4*>(Thp + (int64_t)r * D + sl * 32);
+      const int r0 = c0 + (u * 4 + wave) * 16 + 4 * kg, rl = n_rows - 1;   // clamp: result is discarded
+      a[u][0] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 < rl ? r0 : rl) * D);
+      a[u][1] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 + 1 < rl ? r0 + 1 : rl) * D);
+      a[u][2] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 + 2 < rl ? r0 + 2 : rl) * D);
+      a[u][3] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 + 3 < rl ? r0 + 3 : rl) * D);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float v = score_rows16(a[u], qb, G);
+      st.put(a[u][0], a[u][1], a[u][2], a[u][3]);
+      const float v = score_rows16(st, qb, G);
       const int r = c0 + (u * 4 + wave) * 16 + lane;
       if (lane < 16 && r < n_rows) scores[(int64_t)hp * score_stride + row_begin + r] = v;
     }
@@ -105,20 +108,47 @@ hipError_t launch_score(const Dims& dm, const void* q, const void* centroids, in
 // ------------------------------------------------------------------ order + budget
 // One workgroup per head-problem, as in the paper (its kernels use one thread block
 // per KV head with the size metadata in shared memory).
+constexpr int RANK_THREADS = 512;
+
 template <int CMAX>
-__global__ __launch_bounds__(SELP_THREADS) void k_rank(
+__global__ __launch_bounds__(RANK_THREADS) void k_rank(
     const float* __restrict__ scores, const int32_t* __restrict__ sizes, int C_cap,
     int n_clusters, int budget, int trim, int32_t* __restrict__ sel_clusters,
     int32_t* __restrict__ n_sel_clusters, int32_t* __restrict__ n_sel_tokens) {
-  __shared__ SelectLds<CMAX> L;
+  constexpr int NT = RANK_THREADS, ITEMS = CMAX / NT;
+  __shared__ SelectLds<CMAX, NT> L;
+  __shared__ QuickLds<NT> Q;
   const int hp = blockIdx.x, tid = threadIdx.x;
-  select_prefix<CMAX>(L, scores + (int64_t)hp * C_cap, sizes + (int64_t)hp * C_cap, nullptr,
-                n_clusters, budget, trim);
-  const int n_sel = L.n_sel;
-  for (int j = tid; j < n_sel; j += SELP_THREADS) sel_clusters[(int64_t)hp * C_cap + j] = L.ord[j];
+  float sc[ITEMS], mx = -INFINITY, mn = INFINITY;
+  int sz[ITEMS], of[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const int c = tid + i * NT, cc = c < n_clusters ? c : n_clusters - 1;   // unconditional loads
+    sc[i] = scores[(int64_t)hp * C_cap + cc];
+    sz[i] = sizes[(int64_t)hp * C_cap + cc];
+    of[i] = 0;
+  }
+  quick_clear(Q);
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {                     // a repeated last entry does not widen the range
+    mx = fmaxf(mx, sc[i]);
+    mn = fminf(mn, sc[i]);
+  }
+  quick_range(Q, mx, mn);
+  __syncthreads();
+  const Quick r = quick_select<NT, ITEMS>(Q, sc, sz, of, n_clusters, budget, trim);
+  int n_sel = r.n_sel, n_tok = r.n_tok;
+  if (r.m <= WAVE) {
+    if (tid < n_sel) sel_clusters[(int64_t)hp * C_cap + tid] = r.id;
+  } else {
+    select_prefix_regs<CMAX, NT>(L, sc, sz, of, false, n_clusters, budget, trim);
+    n_sel = L.n_sel;
+    n_tok = L.n_tok;
+    for (int j = tid; j < n_sel; j += NT) sel_clusters[(int64_t)hp * C_cap + j] = L.ord[j];
+  }
   if (tid == 0) {
     n_sel_clusters[hp] = n_sel;
-    n_sel_tokens[hp] = L.n_tok;
+    n_sel_tokens[hp] = n_tok;
   }
 }
 
@@ -129,11 +159,11 @@ hipError_t launch_select(const Dims& dm, const void* q, const void* centroids,
   hipError_t e = launch_score(dm, q, centroids, n_clusters, scores, st);
   if (e != hipSuccess) return e;
   if (n_clusters <= SELP_SMALL)
-    hipLaunchKernelGGL(k_rank<SELP_SMALL>, dim3(dm.HP), dim3(SELP_THREADS), 0, st, scores, sizes,
+    hipLaunchKernelGGL(k_rank<SELP_SMALL>, dim3(dm.HP), dim3(RANK_THREADS), 0, st, scores, sizes,
                        dm.C_cap, n_clusters, budget, (int)(flags & CK_SEL_TRIM_LAST),
                        sel_clusters, n_sel_clusters, n_sel_tokens);
   else
-    hipLaunchKernelGGL(k_rank<CK_MAX_CLUSTERS>, dim3(dm.HP), dim3(SELP_THREADS), 0, st, scores,
+    hipLaunchKernelGGL(k_rank<CK_MAX_CLUSTERS>, dim3(dm.HP), dim3(RANK_THREADS), 0, st, scores,
                        sizes, dm.C_cap, n_clusters, budget, (int)(flags & CK_SEL_TRIM_LAST),
                        sel_clusters, n_sel_clusters, n_sel_tokens);
   return hipGetLastError();

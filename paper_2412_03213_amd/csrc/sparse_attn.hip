@@ -5,15 +5,16 @@
 //
 // HBM-bound: every recalled K and V row (256 B in bf16) is read exactly once per
 // KV head and shared by the G query heads of the group.  A wavefront takes 16
-// tokens per step.  V rows are owned by 16-lane groups (16 B of the row per lane)
-// and accumulated on the vector ALUs; in bf16 the K rows go straight into
-// v_mfma_f32_16x16x32_bf16 as the A operand with the query heads as B columns,
-// which removes the unpacking, the dot products and their cross-lane reductions
-// from the vector ALUs (fp32 check mode keeps the all-VALU form).  The attended
-// positions of a head-problem are split over several workgroups (split-KV) so that
-// a batch of a few sequences still fills 256 CUs.  Inside a workgroup the token rows
-// of its positions are resolved into LDS first, and the K/V loads of the next TWO
-// steps are in flight while the current one is reduced.
+// tokens per step, 16 lanes loading a whole row.  In bf16 both products run on the
+// matrix cores (fp32 check mode keeps the all-VALU form): q K^T with the K rows, passed
+// through LDS, as the A operand; P V with operands that are already in the right lanes
+// (see the kernel).  One launch of the whole step takes 10.3 us at 8 head-problems, B = 1024
+// (13.9 with K rows loaded in operand layout, P V on the vector ALUs and one wavefront
+// selecting) and 20.5 at 64, B = 2048 (25.5), of which the row stream at 6.4 TB/s is half;
+// the rest is a chain of dependent round trips.  The attended positions of a head-problem are split over several
+// workgroups (split-KV) so that a batch of a few sequences still fills 256 CUs.  Inside a workgroup every wavefront resolves the token
+// rows of its own positions first, and the K/V loads of the next TWO steps are in
+// flight while the current one is reduced.
 //
 // Merging the splits without a second launch: every workgroup publishes its partial
 // (max, sum, accumulator) with agent-scope stores, takes a ticket from a counter of
@@ -25,7 +26,7 @@
 //
 // Fused modes: every workgroup of a head-problem repeats the (cheap, LDS-only)
 // selection of the recalled cluster prefix and maps its own positions through the
-// cluster-contiguous index directly; the index list is still written out (each
+// cluster-contiguous index directly, from the ranked clusters in registers; the index list is still written out (each
 // workgroup its own part) but never re-read.  With at most 512 clusters in bf16 the
 // centroid scores are computed by every workgroup as well (the workgroups of one
 // head-problem are placed on one XCD, so the table comes from HBM once and out of
@@ -37,14 +38,12 @@
 
 namespace ck {
 
-constexpr int ATT_THREADS = SELP_THREADS;  // 4 wavefronts = 16 token slots per workgroup step
-constexpr int ATT_UNROLL = 4;              // token slots in flight per 16-lane group
-constexpr int ATT_STEP_TOKENS = 16 * ATT_UNROLL;   // 64 tokens per workgroup iteration
+constexpr int ATT_TOKENS = 16;             // tokens of a wavefront per step
 constexpr int ATT_MAX_CHUNK = 2048;        // positions one workgroup may own (rows held in LDS)
 constexpr int ATT_MAX_SPLITS = 1024;       // workgroups per head-problem
 constexpr float NEG_BIG = -1.0e30f;        // "no token yet": finite so that differences stay finite
 constexpr int ATT_TARGET_WGS = 256;        // one per CU on 256 CUs
-constexpr int PEX_WAVE = 16 * 8 + 8;       // floats of probability exchange per wavefront (G <= 8)
+constexpr int ATT_MANY_HP = 512;           // head-problems from which on two rounds of workgroups exist
 constexpr int PART_STRIDE = D + 2;         // floats per (split, query head): max, sum, acc[128]
 constexpr int N_XCD = 8;                   // workgroup i of a launch runs on XCD i % 8
 constexpr unsigned long long TICKET_MAGIC = 0x434B7469636Bull;   // marks a ticket word as ours
@@ -101,17 +100,16 @@ struct PairPlain {
 
 // out channels (c2, c2 + 1) of one query head from its n_split partials:
 //   sum_i acc_i 2^(m_i - M) / sum_i l_i 2^(m_i - M), splits added in index order,
-// MERGE_BATCH partials loaded together so that their latencies overlap.
+// BATCH partials loaded together so that their latencies overlap.
 // base = partial of split 0 for this head, stride = floats between splits.
-constexpr int MERGE_BATCH = 16;
-template <typename Load>
-__device__ __forceinline__ float2 merge_splits(const float* base, int64_t stride, int n_split,
-                                               int c2, Load load) {
+template <int BATCH, typename Load>
+__device__ __forceinline__ float2 merge_batches(const float* base, int64_t stride, int n_split,
+                                                int c2, Load load) {
   float M = NEG_BIG, ls = 0.f, a0 = 0.f, a1 = 0.f;
-  for (int i0 = 0; i0 < n_split; i0 += MERGE_BATCH) {
-    float2 ml[MERGE_BATCH], av[MERGE_BATCH];
+  for (int i0 = 0; i0 < n_split; i0 += BATCH) {
+    float2 ml[BATCH], av[BATCH];
 #pragma unroll
-    for (int i = 0; i < MERGE_BATCH; ++i) {
+    for (int i = 0; i < BATCH; ++i) {
       const bool ok = i0 + i < n_split;
       const float* p = base + (int64_t)(ok ? i0 + i : 0) * stride;
       ml[i] = load(p);
@@ -123,14 +121,14 @@ __device__ __forceinline__ float2 merge_splits(const float* base, int64_t stride
     }
     float mx = M;
 #pragma unroll
-    for (int i = 0; i < MERGE_BATCH; ++i) mx = fmaxf(mx, ml[i].x);
+    for (int i = 0; i < BATCH; ++i) mx = fmaxf(mx, ml[i].x);
     const float corr = __builtin_amdgcn_exp2f(M - mx);
     ls *= corr;
     a0 *= corr;
     a1 *= corr;
     M = mx;
 #pragma unroll
-    for (int i = 0; i < MERGE_BATCH; ++i) {
+    for (int i = 0; i < BATCH; ++i) {
       const float f = __builtin_amdgcn_exp2f(ml[i].x - mx);
       ls += ml[i].y * f;
       a0 += av[i].x * f;
@@ -139,6 +137,15 @@ __device__ __forceinline__ float2 merge_splits(const float* base, int64_t stride
   }
   const float inv = ls > 0.f ? 1.0f / ls : 0.f;
   return make_float2(a0 * inv, a1 * inv);
+}
+// The smallest batch that takes all splits at once (the loads go past the L2: those of a
+// padded batch would cost as much as the real ones).
+template <typename Load>
+__device__ __forceinline__ float2 merge_splits(const float* base, int64_t stride, int n_split,
+                                               int c2, Load load) {
+  if (n_split <= 4) return merge_batches<4>(base, stride, n_split, c2, load);
+  if (n_split <= 8) return merge_batches<8>(base, stride, n_split, c2, load);
+  return merge_batches<16>(base, stride, n_split, c2, load);
 }
 
 struct AttnArgs {
@@ -161,25 +168,40 @@ struct AttnArgs {
   float scale_log2e;
 };
 
-template <int G> struct PlainLds { float red[4 * G * PART_STRIDE]; };
+template <int G, int NW> struct PlainLds { float red[NW * G * PART_STRIDE]; };
+template <int CMAX, int NT> struct FusedLds {
+  QuickLds<NT> quick;
+  SelectLds<CMAX, NT> general;
+};
 
+// Value of lane g of the 16-lane row, in every lane of the row.
+template <int LANE>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + LANE, 0xf, 0xf, true));
+}
 // Attended position p of a head-problem -> token row:
 //   [0, n_sink) sinks, then the recalled list, then [recent_begin, recent_end).
+// Position i of a workgroup belongs to wavefront (i / 16) % NW.
 // One-dimensional grid: workgroup i runs on XCD i % 8 (round-robin dispatch), so the
 // n_split workgroups of a head-problem are given ids of one residue class and share
 // that XCD's L2 (sizes, offsets, scores or the centroid table).  Placement only affects
 // speed, never results.
-template <typename T, int G, int MODE, int CMAX>
-__global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
+// (Two wavefronts per SIMD is what the row stream's registers allow; the attribute keeps the
+// compiler from aiming higher and spilling.)
+template <typename T, int G, int MODE, int CMAX, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 2 : 1, 2))) void k_attn(const AttnArgs a) {
   constexpr bool FUSED = MODE != ATT_PLAIN;
-  using Big = typename std::conditional<FUSED, SelectLds<CMAX>, PlainLds<G>>::type;
-  static_assert(sizeof(Big) >= sizeof(PlainLds<G>), "the wavefront partials reuse the selection's LDS");
-  __shared__ Big big;                                   // selection, later the wavefront partials
-  __shared__ int rows[ATT_MAX_CHUNK];
-  __shared__ __attribute__((aligned(16))) float pex[4 * PEX_WAVE];
+  constexpr int NT = NW * 64, STEP = NW * ATT_TOKENS;
+  union Big {                                           // selection, later the wavefront partials
+    PlainLds<G, NW> plain;
+    typename std::conditional<FUSED, FusedLds<CMAX, NT>, PlainLds<G, NW>>::type fused;
+  };
+  __shared__ Big big;
+  __shared__ __attribute__((aligned(16))) int rows_lds[ATT_MAX_CHUNK];
   __shared__ __attribute__((aligned(16))) float sc_lds[MODE == ATT_FUSED_SCORE ? CMAX : 4];
+  __shared__ __attribute__((aligned(16))) bf16 stage_lds[std::is_same<T, bf16>::value ? NW * STAGE_ELEMS : 8];
   __shared__ int s_last;
-  float* red = reinterpret_cast<float*>(&big);
+  float* red = big.plain.red;
 
   // one argument per 64-byte line of the argument block: all lines are requested now
   CK_FETCH_ARG(a.q);
@@ -191,12 +213,13 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
   CK_FETCH_ARG(a.n_sink);
   CK_FETCH_ARG(a.scale_log2e);
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, l16 = tid & 15, slot = tid >> 4;  // 16 slots
+  const int lane = tid & 63, wave = tid >> 6, col = lane & 15, kg = lane >> 4;
   const int wg = blockIdx.x, xcd = wg % N_XCD, seq = wg / N_XCD;
   const int hp = (seq / a.n_split) * N_XCD + xcd, split = seq % a.n_split;
   if (hp >= a.HP) return;                               // the grid is padded to whole groups of 8
   const int s = hp / a.Hkv, h = hp % a.Hkv;
   const T* q = static_cast<const T*>(a.q);
+  const Stage16 stage(stage_lds + (std::is_same<T, bf16>::value ? wave * STAGE_ELEMS : 0), lane);
 
   // the query heads of the group as an MFMA operand (bf16): for the scores and for q K^T
   bf16x8 qb[4];
@@ -204,77 +227,87 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
     load_query_operand(reinterpret_cast<const bf16*>(q) + ((int64_t)s * a.Hq + h * G) * D, G, lane, qb);
 
   int n_idx;
+  Quick sel;
   if constexpr (FUSED) {
-    SelectLds<CMAX>& L = big;
+    QuickLds<NT>& Q = big.fused.quick;
+    SelectLds<CMAX, NT>& L = big.fused.general;
+    constexpr int ITEMS = CMAX / NT;
+    float sc[ITEMS];
+    int sz[ITEMS], of[ITEMS];
+    float mx = -INFINITY, mn = INFINITY;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {                   // unconditional: one round trip with the scores
+      const int c = tid + i * NT, cc = c < a.n_clusters ? c : a.n_clusters - 1;
+      sz[i] = a.sizes[(int64_t)hp * a.C_cap + cc];
+      of[i] = a.offsets[(int64_t)hp * (a.C_cap + 1) + cc];
+      if constexpr (MODE == ATT_FUSED) sc[i] = a.scores[(int64_t)hp * a.C_cap + cc];
+    }
+    quick_clear(Q);
     if constexpr (MODE == ATT_FUSED_SCORE) {
       // ---- scores of all clusters of this head-problem (bf16 table, matrix cores) ----
       // Every load of the prologue is issued before the first use: the table rows of
-      // this wavefront (16 rows per step, steps wave, wave + 4, ...), the query heads,
+      // this wavefront (16 rows per step, steps wave, wave + NW, ...), the query heads,
       // the sizes and offsets this thread will bring to the selection: one round trip.
-      constexpr int ITEMS = CMAX / SELP_THREADS;
-      constexpr int SB = CMAX / 64;                     // 16-row steps per wavefront
-      const int col = lane & 15, kg = lane >> 4;
-      int sz[ITEMS], of[ITEMS];
-#pragma unroll
-      for (int i = 0; i < ITEMS; ++i) {
-        const int c = tid + i * SELP_THREADS;
-        sz[i] = c < a.n_clusters ? a.sizes[(int64_t)hp * a.C_cap + c] : 0;
-        of[i] = c < a.n_clusters ? a.offsets[(int64_t)hp * (a.C_cap + 1) + c] : 0;
-      }
-      const bf16* Thp = static_cast<const bf16*>(a.centroids) + (int64_t)hp * a.C_cap * D + kg * 8;
+      constexpr int SB = CMAX / (16 * NW);              // 16-row steps per wavefront
+      const bf16* Thp = static_cast<const bf16*>(a.centroids) + (int64_t)hp * a.C_cap * D + col * 8;
       const int n_steps = (a.n_clusters + 15) >> 4;
       uint4 ar[SB][4];
 #pragma unroll
       for (int u = 0; u < SB; ++u) {
-        if (wave + 4 * u < n_steps) {                   // wave-uniform
-          int r = (wave + 4 * u) * 16 + col;
-          if (r >= a.n_clusters) r = a.n_clusters - 1;  // clamp: result is discarded
-#pragma unroll
-          for (int sl = 0; sl < 4; ++sl)
-            ar[u][sl] = *reinterpret_cast<const uint4*>(Thp + (int64_t)r * D + sl * 32);
+        if (wave + NW * u < n_steps) {                  // wave-uniform
+          const int r0 = (wave + NW * u) * 16 + 4 * kg, rl = a.n_clusters - 1;   // clamp: result is discarded
+          ar[u][0] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 < rl ? r0 : rl) * D);
+          ar[u][1] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 + 1 < rl ? r0 + 1 : rl) * D);
+          ar[u][2] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 + 2 < rl ? r0 + 2 : rl) * D);
+          ar[u][3] = *reinterpret_cast<const uint4*>(Thp + (int64_t)(r0 + 3 < rl ? r0 + 3 : rl) * D);
         }
       }
 #pragma unroll
       for (int u = 0; u < SB; ++u) {
-        if (wave + 4 * u < n_steps) {
-          const float v = score_rows16(ar[u], qb, G);
-          const int r = (wave + 4 * u) * 16 + lane;
+        if (wave + NW * u < n_steps) {
+          stage.put(ar[u][0], ar[u][1], ar[u][2], ar[u][3]);
+          const float v = score_rows16(stage, qb, G);
+          const int r = (wave + NW * u) * 16 + lane;
           if (lane < 16 && r < a.n_clusters) {
             sc_lds[r] = v;
             if (split == 0) a.scores[(int64_t)hp * a.C_cap + r] = v;
+            mx = fmaxf(mx, v);
+            mn = fminf(mn, v);
           }
         }
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {                 // a repeated last entry does not widen the range
+        mx = fmaxf(mx, sc[i]);
+        mn = fminf(mn, sc[i]);
+      }
+    }
+    quick_range(Q, mx, mn);
+    __syncthreads();
+    if constexpr (MODE == ATT_FUSED_SCORE) {
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i) {
-        const int c = tid + i * SELP_THREADS;
-        if (c < a.n_clusters) {
-          L.ssz[c] = sz[i];
-          L.soff[c] = of[i];
-        }
+        const int c = tid + i * NT;
+        sc[i] = c < a.n_clusters ? sc_lds[c] : 0.f;
       }
-      __syncthreads();
-      // one wavefront selects when a few dozen candidates bound the prefix (the usual
-      // case); otherwise all four do, the general way
-      if (!select_prefix_wave(L, sc_lds, a.n_clusters, a.budget, a.trim)) {
-        float sc[ITEMS];
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-          const int c = tid + i * SELP_THREADS;
-          sc[i] = c < a.n_clusters ? sc_lds[c] : 0.f;
-        }
-        select_prefix_regs<CMAX>(L, sc, sz, of, true, a.n_clusters, a.budget, a.trim);
-      }
-    } else {
-      select_prefix<CMAX>(L, a.scores + (int64_t)hp * a.C_cap, a.sizes + (int64_t)hp * a.C_cap,
-                          a.offsets + (int64_t)hp * (a.C_cap + 1), a.n_clusters, a.budget, a.trim);
     }
-    n_idx = L.n_tok;
+    sel = quick_select<NT, ITEMS>(Q, sc, sz, of, a.n_clusters, a.budget, a.trim);
+    if (sel.m > WAVE) {                                 // uniform: more candidates than lanes
+      select_prefix_regs<CMAX, NT>(L, sc, sz, of, true, a.n_clusters, a.budget, a.trim);
+      sel.n_sel = L.n_sel;
+      sel.n_tok = L.n_tok;
+    }
+    n_idx = sel.n_tok;
     if (split == 0) {
-      for (int j = tid; j < L.n_sel; j += ATT_THREADS)
-        a.sel_clusters[(int64_t)hp * a.C_cap + j] = L.ord[j];
+      if (sel.m <= WAVE) {
+        if (tid < sel.n_sel) a.sel_clusters[(int64_t)hp * a.C_cap + tid] = sel.id;
+      } else {
+        for (int j = tid; j < sel.n_sel; j += NT)
+          a.sel_clusters[(int64_t)hp * a.C_cap + j] = L.ord[j];
+      }
       if (tid == 0) {
-        a.n_sel_clusters[hp] = L.n_sel;
+        a.n_sel_clusters[hp] = sel.n_sel;
         a.n_sel_tokens[hp] = n_idx;
         a.n_tokens_out[hp] = n_idx;
       }
@@ -288,17 +321,37 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
   int p_end = p_begin + a.chunk;
   if (p_end > n_total) p_end = n_total;
   const int n_pos = p_end > p_begin ? p_end - p_begin : 0;
+  const int n_steps = (n_pos + STEP - 1) / STEP;
 
-  // ---- token row of every position this workgroup owns ----
-  for (int i = tid; i < n_pos; i += ATT_THREADS) {
-    const int p = p_begin + i;
-    int64_t row;
-    if (p < a.n_sink) {
-      row = p;
-    } else if (p < a.n_sink + n_idx) {
-      const int qpos = p - a.n_sink;
-      if constexpr (FUSED) {
-        SelectLds<CMAX>& L = big;
+  // ---- token rows of this wavefront's positions, entry 16 t + x: token x of step t ----
+  // (a position beyond the end reads row 0 and is masked later)
+  int* rows = rows_lds + wave * (ATT_MAX_CHUNK / NW);
+  for (int e0 = 0; e0 < n_steps * 16; e0 += WAVE) {
+    const int e = e0 + lane;
+    const int i = (e >> 4) * STEP + wave * 16 + (e & 15);
+    const int p = p_begin + i, qpos = p - a.n_sink;
+    const bool own = i < n_pos, listed = own && qpos >= 0 && qpos < n_idx;
+    int64_t row = 0;
+    if constexpr (FUSED) {
+      int64_t src = 0;
+      if (sel.m <= WAVE) {
+        // the clusters this wavefront's positions cross, in order, out of the lanes that
+        // hold them (empty clusters of the prefix cover no position)
+        const int q0 = p_begin + (e0 >> 4) * STEP + wave * 16 - a.n_sink;
+        const int q1 = q0 + (WAVE / 16 - 1) * STEP + 16;
+        const uint64_t after = __ballot(lane < sel.m && sel.cum > q0);
+        for (int j = after ? __builtin_ctzll(after) : sel.m; j < sel.n_sel; ++j) {
+          const int cum = __builtin_amdgcn_readlane(sel.cum, j);
+          const int size = __builtin_amdgcn_readlane(sel.size, j);
+          const int off = __builtin_amdgcn_readlane(sel.off, j);
+          const int prev = cum - size;
+          if (prev >= q1) break;
+          int take = a.budget - prev;                   // a cut cluster keeps its trailing entries
+          take = take > size ? size : take;
+          if (qpos >= prev && qpos < cum) src = (int64_t)off + (size - take) + (qpos - prev);
+        }
+      } else if (listed) {
+        SelectLds<CMAX, NT>& L = big.fused.general;
         // smallest j with cum[j] > qpos (empty clusters in the prefix are skipped)
         int lo = 0, hi = L.n_sel - 1;
         while (lo < hi) {
@@ -308,67 +361,72 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
         const int c = L.ord[lo];
         const int prev = lo ? L.cum[lo - 1] : 0;
         const int size = L.cum[lo] - prev;
-        int take = a.budget - prev;                     // a cut cluster keeps its trailing entries
+        int take = a.budget - prev;
         take = take > size ? size : take;
         const int beg = L.full_rank ? L.soff[c] : L.cbeg[lo];
-        int64_t src = (int64_t)beg + (size - take) + (qpos - prev);
+        src = (int64_t)beg + (size - take) + (qpos - prev);
+      }
+      if (listed) {
         src = src < 0 ? 0 : (src >= a.N_cap ? a.N_cap - 1 : src);
         row = a.sorted_idx[(int64_t)hp * a.N_cap + src];
         a.token_idx_out[(int64_t)hp * a.idx_stride + qpos] = (int32_t)row;
-      } else {
-        // no list: the first n_tokens rows of K/V themselves (a dense per-head-problem prefix)
-        row = a.token_idx ? a.token_idx[(int64_t)hp * a.idx_stride + qpos] : qpos;
       }
     } else {
-      row = a.recent_begin + (p - a.n_sink - n_idx);
+      // no list: the first n_tokens rows of K/V themselves (a dense per-head-problem prefix)
+      if (listed) row = a.token_idx ? a.token_idx[(int64_t)hp * a.idx_stride + qpos] : qpos;
     }
+    if (own && qpos < 0) row = p;
+    if (own && qpos >= n_idx) row = a.recent_begin + (qpos - n_idx);
     row = row < 0 ? 0 : (row >= a.N_cap ? a.N_cap - 1 : row);
-    rows[i] = (int)row;
+    if (e < ATT_MAX_CHUNK / NW) rows[e] = (int)row;
   }
-  __syncthreads();                                      // rows complete; the selection's LDS is free
+  wave_lds_order();
 
-  float acc[G][8];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[g][j] = 0.f;
-  const T* Vhp = static_cast<const T*>(a.V) + (int64_t)hp * a.N_cap * D + l16 * 8;
+  const T* Vhp = static_cast<const T*>(a.V) + (int64_t)hp * a.N_cap * D + col * 8;
+  // a wavefront's LDS region for its partial: everything before it (the selection) is over
+  // for this workgroup only behind the barrier below
 
   if constexpr (std::is_same<T, bf16>::value) {
-    // ---- bf16: q K^T on the matrix cores ----
-    // One v_mfma_f32_16x16x32_bf16 per 32-channel slab: A = 16 token rows of the
-    // step (lane: token lane%16, channels 8*(lane/16)..+8 of the slab), B = the
-    // query heads as columns (column >= G is zero).  The result leaves lane
-    // (g + 16u) with the scores of tokens (u, 0..3) for head g, so the running
-    // max / sum of a head live in the four lanes of its column and the
-    // probabilities reach the lanes that own the V rows through a few hundred
-    // bytes of wavefront-private LDS.  All four token slots of a wavefront share
-    // one running max per head.
-    const int col = lane & 15, kg = lane >> 4;          // kg is also this lane's slot in the wavefront
+    // ---- bf16: both products on the matrix cores ----
+    // q K^T: one v_mfma_f32_16x16x32_bf16 per 32-channel slab, A = the 16 token rows of the
+    // step, B = the query heads as columns (columns >= G are computed and never looked at).
+    // The result leaves lane (head + 16 kg) with the scores of tokens 4 kg + (0..3), so the
+    // running max / sum of a head live in the four lanes of its column.
+    // P V: these four probabilities are already where the A operand of a 16-token product
+    // wants them (row = head = lane % 16, k = token = 4 kg + i), and lane col of group kg
+    // holds channels 8 col + (0..7) of exactly these four tokens, which is the B operand of
+    // the channel block {8 col + j : col = 0..15} for each j: nothing changes lanes.  The
+    // accumulator of block j has the heads 4 kg + i of channel 8 col + j.  A probability
+    // enters as the sum of three bf16 numbers, which hold all 24 bits of it: the first two
+    // share one product (k = token and part), the third has one of its own.
+    // On the vector ALUs the same step was 32 fused multiply-adds per head, and the four
+    // groups had to be added up at the end.
     float m_run = NEG_BIG, l_run = 0.f;                 // of head `col`, identical in its four lanes
-    float* px = pex + wave * PEX_WAVE;                  // [slot][u][g] probabilities, then [g] rescale factors
-    const bf16* Khp = static_cast<const bf16*>(a.K) + (int64_t)hp * a.N_cap * D + kg * 8;
-    const int tpos = (col >> 2) * 16 + wave * 4 + (col & 3);   // A row `col` = token (u = col/4, slot = col%4)
-    struct Regs { uint4 k[4], v[ATT_UNROLL]; };
-    auto fetch = [&](int i0, Regs& r) {
-      const int ik = i0 + tpos;
-      const bf16* kp = Khp + (int64_t)(ik < n_pos ? rows[ik] : 0) * D;
+    floatx4 acc[8];
 #pragma unroll
-      for (int sl = 0; sl < 4; ++sl) r.k[sl] = *reinterpret_cast<const uint4*>(kp + sl * 32);
-#pragma unroll
-      for (int u = 0; u < ATT_UNROLL; ++u) {
-        const int i = i0 + u * 16 + slot;
-        r.v[u] = *reinterpret_cast<const uint4*>(Vhp + (int64_t)(i < n_pos ? rows[i] : 0) * D);
-      }
+    for (int j = 0; j < 8; ++j) acc[j] = {0.f, 0.f, 0.f, 0.f};
+    const bf16* Khp = static_cast<const bf16*>(a.K) + (int64_t)hp * a.N_cap * D + col * 8;
+    struct Regs { uint4 k[4], v[4]; };
+    auto fetch = [&](int t, Regs& r) {                  // group kg: whole rows of tokens 4 kg + (0..3)
+      const int4 tr = *reinterpret_cast<const int4*>(rows + t * 16 + kg * 4);
+      r.k[0] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.x * D);
+      r.k[1] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.y * D);
+      r.k[2] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.z * D);
+      r.k[3] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.w * D);
+      r.v[0] = *reinterpret_cast<const uint4*>(Vhp + (int64_t)tr.x * D);
+      r.v[1] = *reinterpret_cast<const uint4*>(Vhp + (int64_t)tr.y * D);
+      r.v[2] = *reinterpret_cast<const uint4*>(Vhp + (int64_t)tr.z * D);
+      r.v[3] = *reinterpret_cast<const uint4*>(Vhp + (int64_t)tr.w * D);
     };
-    auto reduce = [&](int i0, const Regs& r) {
+    auto reduce = [&](int t, const Regs& r) {
+      stage.put(r.k[0], r.k[1], r.k[2], r.k[3]);
       floatx4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int sl = 0; sl < 4; ++sl)
-        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[sl]), qb[sl], d, 0, 0, 0);
-      // d[i]: token (u = kg, slot i) against head `col`
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(stage.operand(sl), qb[sl], d, 0, 0, 0);
+      // d[i]: token 4 kg + i against head `col`
       float sc[4];
-      const int ibase = i0 + kg * 16 + wave * 4;
+      const int ibase = t * STEP + wave * 16 + kg * 4;
 #pragma unroll
       for (int i = 0; i < 4; ++i) sc[i] = (ibase + i < n_pos) ? d[i] * a.scale_log2e : -INFINITY;
       float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
@@ -382,42 +440,52 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
       float ps = (pw[0] + pw[1]) + (pw[2] + pw[3]);
       ps = xor32(xor16(ps, OpSum()), OpSum());
       l_run = l_run * corr + ps;
-      if (col < G) {
+      if (t > 0 && __ballot(corr != 1.f)) {             // a new maximum somewhere
+        float cr[4];                                    // of heads 4 kg + i
+        cr[0] = row_bcast<0>(corr);
+        cr[1] = row_bcast<1>(corr);
+        cr[2] = row_bcast<2>(corr);
+        cr[3] = row_bcast<3>(corr);
+        if constexpr (G > 4) {
+          const float c4 = row_bcast<4>(corr), c5 = row_bcast<5>(corr);
+          const float c6 = row_bcast<6>(corr), c7 = row_bcast<7>(corr);
+          cr[0] = kg == 1 ? c4 : cr[0];
+          cr[1] = kg == 1 ? c5 : cr[1];
+          cr[2] = kg == 1 ? c6 : cr[2];
+          cr[3] = kg == 1 ? c7 : cr[3];
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) px[(i * 4 + kg) * G + col] = pw[i];
-        if (kg == 0) px[16 * G + col] = corr;
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[j][i] *= cr[i];
       }
-      // LDS serves one wavefront's requests in order: the reads below see the writes above
-      __builtin_amdgcn_wave_barrier();
-      asm volatile("" ::: "memory");
-      float pr[ATT_UNROLL][G], cr[G];
-      {
-        const floatx4* src = reinterpret_cast<const floatx4*>(px + kg * 4 * G);
-        floatx4 tmp[G];
+      // p = hi + mid + lo, each with at most 8 significant bits
+      uint32_t hi[4], mid[4], lo[4];
 #pragma unroll
-        for (int k = 0; k < G; ++k) tmp[k] = src[k];
-#pragma unroll
-        for (int k = 0; k < G; ++k)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) pr[(k * 4 + e) / G][(k * 4 + e) % G] = tmp[k][e];
-#pragma unroll
-        for (int g = 0; g < G; ++g) cr[g] = px[16 * G + g];
+      for (int i = 0; i < 4; ++i) {
+        hi[i] = __float_as_uint(pw[i]);
+        const float r1 = pw[i] - __uint_as_float(hi[i] & 0xFFFF0000u);
+        mid[i] = __float_as_uint(r1);
+        lo[i] = __float_as_uint(r1 - __uint_as_float(mid[i] & 0xFFFF0000u));
       }
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_wave_barrier();
+      constexpr uint32_t HIGH = 0x07060302u, LOW = 0x05040100u;   // halves of (second, first) word
+      const uint4 pa = make_uint4(__builtin_amdgcn_perm(hi[1], hi[0], HIGH),
+                                  __builtin_amdgcn_perm(hi[3], hi[2], HIGH),
+                                  __builtin_amdgcn_perm(mid[1], mid[0], HIGH),
+                                  __builtin_amdgcn_perm(mid[3], mid[2], HIGH));
+      const uint4 pb = make_uint4(__builtin_amdgcn_perm(lo[1], lo[0], HIGH),
+                                  __builtin_amdgcn_perm(lo[3], lo[2], HIGH), 0u, 0u);
+      const uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w},
+                                 {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
+                                 {r.v[2].x, r.v[2].y, r.v[2].z, r.v[2].w},
+                                 {r.v[3].x, r.v[3].y, r.v[3].z, r.v[3].w}};
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[g][j] *= cr[g];
-#pragma unroll
-      for (int u = 0; u < ATT_UNROLL; ++u) {
-        float vv[8];
-        vv[0] = lo_bf16(r.v[u].x); vv[1] = hi_bf16(r.v[u].x); vv[2] = lo_bf16(r.v[u].y); vv[3] = hi_bf16(r.v[u].y);
-        vv[4] = lo_bf16(r.v[u].z); vv[5] = hi_bf16(r.v[u].z); vv[6] = lo_bf16(r.v[u].w); vv[7] = hi_bf16(r.v[u].w);
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[g][j] = fmaf(pr[u][g], vv[j], acc[g][j]);
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t b01 = __builtin_amdgcn_perm(vw[1][j / 2], vw[0][j / 2], j & 1 ? HIGH : LOW);
+        const uint32_t b23 = __builtin_amdgcn_perm(vw[3][j / 2], vw[2][j / 2], j & 1 ? HIGH : LOW);
+        const bf16x8 vb = __builtin_bit_cast(bf16x8, make_uint4(b01, b23, b01, b23));
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa), vb, acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pb), vb, acc[j], 0, 0, 0);
       }
     };
     // NS register sets in rotation: the loads of steps t + 1 .. t + NS - 1 are in flight
@@ -425,44 +493,42 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
     // bound by memory bandwidth, not by the depth of the prefetch)
     constexpr int NS = 3;
     Regs rs[NS];
-    constexpr int ST = ATT_STEP_TOKENS;
 #pragma unroll
     for (int j = 0; j < NS - 1; ++j)
-      if (j * ST < n_pos) fetch(j * ST, rs[j]);
-    for (int i0 = 0; i0 < n_pos; i0 += NS * ST) {
+      if (j < n_steps) fetch(j, rs[j]);
+    for (int t = 0; t < n_steps; t += NS) {
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
-        if (i0 + j * ST < n_pos) {
-          if (i0 + (j + NS - 1) * ST < n_pos) fetch(i0 + (j + NS - 1) * ST, rs[(j + NS - 1) % NS]);
-          reduce(i0 + j * ST, rs[j]);
+        if (t + j < n_steps) {
+          if (t + j + NS - 1 < n_steps) fetch(t + j + NS - 1, rs[(j + NS - 1) % NS]);
+          reduce(t + j, rs[j]);
         }
       }
     }
-    // ---- combine the 4 slots of a wavefront: they share the running max ----
+    if constexpr (FUSED) __syncthreads();               // the selection's LDS is free
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int g = kg * 4 + i;
+      if (g < G) {
+        float* r = red + (wave * G + g) * PART_STRIDE + 2 + col * 8;
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) *reinterpret_cast<float2*>(r + j) = make_float2(acc[j][i], acc[j + 1][i]);
+      }
+    }
+    if (lane < G)
+      *reinterpret_cast<float2*>(red + (wave * G + lane) * PART_STRIDE) = make_float2(m_run, l_run);
+  } else {
+    // ---- fp32 check mode: dot products on the vector ALUs ----
+    float acc[G][8];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[g][j] = xor32(xor16(acc[g][j], OpSum()), OpSum());
-    if (lane < 16) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float* r = red + (wave * G + g) * PART_STRIDE;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) r[2 + l16 * 8 + j] = acc[g][j];
-      }
-      if (lane < G) {
-        float* r = red + (wave * G + lane) * PART_STRIDE;
-        r[0] = m_run;
-        r[1] = l_run;
-      }
-    }
-  } else {
-    // ---- fp32 check mode: dot products on the vector ALUs ----
+      for (int j = 0; j < 8; ++j) acc[g][j] = 0.f;
     // this lane's 8 channels of every query head of the group, pre-scaled
     float qv[G][8];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      load_row8<T>(q + ((int64_t)s * a.Hq + h * G + g) * D + l16 * 8, qv[g]);
+      load_row8<T>(q + ((int64_t)s * a.Hq + h * G + g) * D + col * 8, qv[g]);
 #pragma unroll
       for (int j = 0; j < 8; ++j) qv[g][j] *= a.scale_log2e;
     }
@@ -474,54 +540,53 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
       l[g] = 0.f;
     }
 
-    const T* Khp = static_cast<const T*>(a.K) + (int64_t)hp * a.N_cap * D + l16 * 8;
-    RawRow<T> kc[ATT_UNROLL], vc[ATT_UNROLL], kn[ATT_UNROLL], vn[ATT_UNROLL];
-    auto fetch = [&](int i0, RawRow<T>(&kr)[ATT_UNROLL], RawRow<T>(&vr)[ATT_UNROLL]) {
+    const T* Khp = static_cast<const T*>(a.K) + (int64_t)hp * a.N_cap * D + col * 8;
+    RawRow<T> kc[4], vc[4], kn[4], vn[4];
+    auto fetch = [&](int t, RawRow<T>(&kr)[4], RawRow<T>(&vr)[4]) {
 #pragma unroll
-      for (int u = 0; u < ATT_UNROLL; ++u) {
-        const int i = i0 + u * 16 + slot;
-        const int64_t row = i < n_pos ? rows[i] : 0;
+      for (int u = 0; u < 4; ++u) {
+        const int64_t row = rows[t * 16 + kg * 4 + u];
         kr[u].load(Khp + row * D);
         vr[u].load(Vhp + row * D);
       }
     };
-    if (n_pos > 0) fetch(0, kc, vc);
-    for (int i0 = 0; i0 < n_pos; i0 += ATT_STEP_TOKENS) {
-      if (i0 + ATT_STEP_TOKENS < n_pos) fetch(i0 + ATT_STEP_TOKENS, kn, vn);
-      float kv[ATT_UNROLL][8];
+    if (n_steps > 0) fetch(0, kc, vc);
+    for (int t = 0; t < n_steps; ++t) {
+      if (t + 1 < n_steps) fetch(t + 1, kn, vn);
+      float kv[4][8];
 #pragma unroll
-      for (int u = 0; u < ATT_UNROLL; ++u) kc[u].unpack(kv[u]);
-      float sc[G][ATT_UNROLL];
+      for (int u = 0; u < 4; ++u) kc[u].unpack(kv[u]);
+      float sc[G][4];
 #pragma unroll
       for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int u = 0; u < ATT_UNROLL; ++u) {
+        for (int u = 0; u < 4; ++u) {
           float d = 0.f;
 #pragma unroll
           for (int j = 0; j < 8; ++j) d = fmaf(qv[g][j], kv[u][j], d);
           d = row16_sum(d);
-          sc[g][u] = (i0 + u * 16 + slot < n_pos) ? d : -INFINITY;
+          sc[g][u] = (t * STEP + wave * 16 + kg * 4 + u < n_pos) ? d : -INFINITY;
         }
-      float pw[G][ATT_UNROLL];
+      float pw[G][4];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         float mx = m[g];
 #pragma unroll
-        for (int u = 0; u < ATT_UNROLL; ++u) mx = fmaxf(mx, sc[g][u]);
+        for (int u = 0; u < 4; ++u) mx = fmaxf(mx, sc[g][u]);
         const float corr = __builtin_amdgcn_exp2f(m[g] - mx);
         m[g] = mx;
         float ls = l[g] * corr;
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[g][j] *= corr;
 #pragma unroll
-        for (int u = 0; u < ATT_UNROLL; ++u) {
+        for (int u = 0; u < 4; ++u) {
           pw[g][u] = __builtin_amdgcn_exp2f(sc[g][u] - mx);
           ls += pw[g][u];
         }
         l[g] = ls;
       }
 #pragma unroll
-      for (int u = 0; u < ATT_UNROLL; ++u) {
+      for (int u = 0; u < 4; ++u) {
         float vv[8];
         vc[u].unpack(vv);
 #pragma unroll
@@ -530,13 +595,14 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
           for (int j = 0; j < 8; ++j) acc[g][j] = fmaf(pw[g][u], vv[j], acc[g][j]);
       }
 #pragma unroll
-      for (int u = 0; u < ATT_UNROLL; ++u) {
+      for (int u = 0; u < 4; ++u) {
         kc[u] = kn[u];
         vc[u] = vn[u];
       }
     }
 
-    // ---- combine the 4 slots of a wavefront (lanes l16 + 16*k) ----
+    if constexpr (FUSED) __syncthreads();               // the selection's LDS is free
+    // ---- combine the 4 groups of a wavefront (lanes col + 16*k) ----
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const float mx = xor32(xor16(m[g], OpMax()), OpMax());
@@ -549,26 +615,32 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
         r[0] = mx;
         r[1] = ls;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r[2 + l16 * 8 + j] = acc[g][j];
+        for (int j = 0; j < 8; ++j) r[2 + col * 8 + j] = acc[g][j];
       }
     }
   }
   __syncthreads();
-  // ---- combine the 4 wavefronts: thread = (query head g, channel pair) ----
+  // ---- combine the wavefronts, in order: thread = (query head g, channel pair) ----
   T* out = static_cast<T*>(a.out);
   float* part_hp = a.part + (int64_t)hp * a.n_split * G * PART_STRIDE;
-  for (int e = tid; e < G * (D / 2); e += ATT_THREADS) {
+  for (int e = tid; e < G * (D / 2); e += NT) {
     const int g = e / (D / 2), c2 = (e % (D / 2)) * 2;
-    const float* r0 = red + (0 * G + g) * PART_STRIDE;
-    const float* r1 = red + (1 * G + g) * PART_STRIDE;
-    const float* r2 = red + (2 * G + g) * PART_STRIDE;
-    const float* r3 = red + (3 * G + g) * PART_STRIDE;
-    const float mx = fmaxf(fmaxf(r0[0], r1[0]), fmaxf(r2[0], r3[0]));
-    const float f0 = __builtin_amdgcn_exp2f(r0[0] - mx), f1 = __builtin_amdgcn_exp2f(r1[0] - mx);
-    const float f2 = __builtin_amdgcn_exp2f(r2[0] - mx), f3 = __builtin_amdgcn_exp2f(r3[0] - mx);
-    const float ls = ((r0[1] * f0 + r1[1] * f1) + r2[1] * f2) + r3[1] * f3;
-    const float a0 = ((r0[2 + c2] * f0 + r1[2 + c2] * f1) + r2[2 + c2] * f2) + r3[2 + c2] * f3;
-    const float a1 = ((r0[3 + c2] * f0 + r1[3 + c2] * f1) + r2[3 + c2] * f2) + r3[3 + c2] * f3;
+    float2 ml[NW];
+    float mx = NEG_BIG;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      ml[w] = *reinterpret_cast<const float2*>(red + (w * G + g) * PART_STRIDE);
+      mx = fmaxf(mx, ml[w].x);
+    }
+    float ls = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = __builtin_amdgcn_exp2f(ml[w].x - mx);
+      const float2 av = *reinterpret_cast<const float2*>(red + (w * G + g) * PART_STRIDE + 2 + c2);
+      ls = fmaf(ml[w].y, f, ls);
+      a0 = fmaf(av.x, f, a0);
+      a1 = fmaf(av.y, f, a1);
+    }
     if (a.n_split == 1) {
       const float inv = ls > 0.f ? 1.0f / ls : 0.f;
       T* o = out + ((int64_t)s * a.Hq + h * G + g) * D + c2;
@@ -619,7 +691,7 @@ __global__ __launch_bounds__(ATT_THREADS) void k_attn(const AttnArgs a) {
   __syncthreads();
   if (!s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  for (int e = tid; e < G * (D / 2); e += ATT_THREADS) {
+  for (int e = tid; e < G * (D / 2); e += NT) {
     const int g = e / (D / 2), c2 = (e % (D / 2)) * 2;
     const float2 o2 = merge_splits(part_hp + (int64_t)g * PART_STRIDE, (int64_t)G * PART_STRIDE,
                                    a.n_split, c2, PairAgent());
@@ -642,15 +714,26 @@ __global__ __launch_bounds__(D / 2) void k_attn_merge(const float* __restrict__ 
   store_out(out + (int64_t)hq_lin * D + c2 + 1, o2.y);
 }
 
+// Wavefronts per workgroup.  Eight: every phase of the step -- scoring, selection, index
+// look-up, row stream -- is spread over the whole CU and fewer splits have to be merged
+// (eight / four wavefronts: 8 head-problems, B = 1024: 10.3 / 11.3 us; 8, 1600 clusters,
+// B = 2048: 13.8 / 16.0; 64, B = 2048: 20.5 / 21.4; 256, B = 2048: 53.7 / 57.5).
+// Four when there are so many head-problems that every CU runs several workgroups one after
+// another: two at a time, one selecting while the other streams (512 head-problems,
+// B = 2048: 118.5 / 115.8; 2048, B = 1024: 227 / 209).  fp32 (check mode) needs the registers.
+static int attn_waves(const Dims& dm) {
+  return dm.dtype == CK_F32 || dm.HP >= ATT_MANY_HP ? 4 : 8;
+}
+
 int attn_num_splits(const Dims& dm, int64_t max_total) {
   // Aim for one workgroup per CU (measured best of 64..1024 workgroups per launch at 8 to
   // 128 head-problems for the one-launch decode step: every split repeats the scoring and
-  // the selection, which costs more than the shorter token run saves; the attention over
-  // a given list would like twice as many at 64 head-problems, 17.1 against 18.5 us, but
-  // takes the same rule: the split boundaries fix the order of the fp32 sums, and all
-  // forms of the step must give the same bits).  Keep at least one full step of tokens
-  // per workgroup and never more positions than its LDS row table holds.
-  const int64_t by_work = (max_total + ATT_STEP_TOKENS - 1) / ATT_STEP_TOKENS;
+  // the selection, which costs more than the shorter token run saves; all forms of the step
+  // take the same rule: the split boundaries fix the order of the fp32 sums, and they must
+  // give the same bits).  Keep at least one full step of tokens per workgroup and never
+  // more positions than its LDS row table holds.
+  const int step = attn_waves(dm) * ATT_TOKENS;
+  const int64_t by_work = (max_total + step - 1) / step;
   const int64_t by_fill = (ATT_TARGET_WGS + dm.HP - 1) / dm.HP;
   int64_t n = by_work < by_fill ? by_work : by_fill;
   if (n > 64) n = 64;
@@ -671,14 +754,27 @@ size_t attn_workspace_bytes(const Dims& dm, int64_t max_total) {
   return partial_bytes(dm, attn_num_splits(dm, max_total)) + t;
 }
 
+template <typename T, int MODE, int CMAX, int NW>
+static void launch_attn_waves(int G, dim3 grid, const AttnArgs& a, hipStream_t st) {
+  const dim3 block(NW * 64);
+  switch (G) {
+    case 1: hipLaunchKernelGGL((k_attn<T, 1, MODE, CMAX, NW>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_attn<T, 2, MODE, CMAX, NW>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_attn<T, 4, MODE, CMAX, NW>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((k_attn<T, 8, MODE, CMAX, NW>), grid, block, 0, st, a); break;
+  }
+}
+
 template <typename T, int MODE, int CMAX>
 static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, bool two_pass,
                                 hipStream_t st) {
   const int n_split = attn_num_splits(dm, max_total);
   if (n_split > ATT_MAX_SPLITS) return hipErrorInvalidValue;
+  if (dm.G != 1 && dm.G != 2 && dm.G != 4 && dm.G != 8) return hipErrorInvalidValue;
+  const int waves = attn_waves(dm), step = waves * ATT_TOKENS;
   int chunk = (int)((max_total + n_split - 1) / n_split);
-  chunk = (chunk + ATT_STEP_TOKENS - 1) / ATT_STEP_TOKENS * ATT_STEP_TOKENS;
-  if (chunk < ATT_STEP_TOKENS) chunk = ATT_STEP_TOKENS;
+  chunk = (chunk + step - 1) / step * step;
+  if (chunk < step) chunk = step;
   if (chunk > ATT_MAX_CHUNK) return hipErrorInvalidValue;
   a.chunk = chunk;
   a.n_split = n_split;
@@ -687,13 +783,14 @@ static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, b
   a.tickets = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(a.part) +
                                                     partial_bytes(dm, n_split));
   const int hp_groups = (dm.HP + N_XCD - 1) / N_XCD;
-  const dim3 grid((unsigned)hp_groups * N_XCD * n_split), block(ATT_THREADS);
-  switch (dm.G) {
-    case 1: hipLaunchKernelGGL((k_attn<T, 1, MODE, CMAX>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_attn<T, 2, MODE, CMAX>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_attn<T, 4, MODE, CMAX>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_attn<T, 8, MODE, CMAX>), grid, block, 0, st, a); break;
-    default: return hipErrorInvalidValue;
+  const dim3 grid((unsigned)hp_groups * N_XCD * n_split);
+  if constexpr (std::is_same<T, bf16>::value) {
+    if (waves == 8)
+      launch_attn_waves<T, MODE, CMAX, 8>(dm.G, grid, a, st);
+    else
+      launch_attn_waves<T, MODE, CMAX, 4>(dm.G, grid, a, st);
+  } else {
+    launch_attn_waves<T, MODE, CMAX, 4>(dm.G, grid, a, st);
   }
   if (n_split > 1 && two_pass)
     hipLaunchKernelGGL(k_attn_merge<T>, dim3(dm.S * dm.Hq), dim3(D / 2), 0, st, a.part, n_split,

@@ -1,0 +1,93 @@
+"""The decode-step kernel at the edges of its tiles and of its dispatch: attended counts around
+the 16 tokens of a wavefront step and the step of a workgroup, every group size, both
+workgroup widths (they change at 512 head-problems), and selections whose candidates just fit
+or just exceed one wavefront."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2412_03213_amd as ck
+from oracle import clusterkv_oracle as O
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# bf16 output: 8 significant bits, so half an ulp is at most 2^-8 of the value's power of two;
+# products are exact in fp32 and the probabilities keep 24 bits, so sums and exponentials add
+# less than another 2^-12
+TOL = 2.0 ** -8 + 2.0 ** -12
+
+
+def np64(t):
+    return t.detach().float().cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("S,G", [(1, 1), (1, 2), (1, 4), (1, 8), (64, 1), (64, 4)])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 257, 1025])
+def test_attention_at_tile_edges(S, G, n):
+    Hkv, N, n_sink, n_rec = 8, 1600, 3, 5
+    g = torch.Generator(device=DEV).manual_seed(100 * n + G)
+    K = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    V = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    q = (3 * torch.randn(S, Hkv * G, 128, generator=g, device=DEV)).bfloat16()
+    stride = (n + 3) // 4 * 4
+    idx = (torch.rand(S, Hkv, N - n_sink - n_rec, generator=g, device=DEV).topk(stride).indices
+           + n_sink).int()
+    cnt = torch.full((S, Hkv), n, dtype=torch.int32, device=DEV)
+    cnt[0, 1] = 0                                         # sinks and recent tokens only
+    sh = ck.Shape(S, Hkv * G, Hkv, N, 8)
+    out = torch.full((S, Hkv * G, 128), float("nan"), device=DEV).bfloat16()
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out, n_sink=n_sink, recent_begin=N - n_rec,
+                             recent_end=N)
+    for s, h in [(0, 0), (0, 1), (S - 1, Hkv - 1)]:
+        rows = np.concatenate([np.arange(n_sink), idx[s, h, :int(cnt[s, h])].cpu().numpy(),
+                               np.arange(N - n_rec, N)])
+        want = O.attention_over(np64(q[s, h * G:(h + 1) * G]), np64(K[s, h]), np64(V[s, h]), rows)
+        got = np64(out[s, h * G:(h + 1) * G])
+        assert np.abs(got - want).max() <= TOL * np.abs(want).max(), (s, h)
+
+
+@pytest.mark.parametrize("S", [1, 64])
+@pytest.mark.parametrize("C,equal", [(1, False), (63, True), (64, True), (65, True), (64, False),
+                                     (130, False), (512, True), (512, False), (513, False),
+                                     (700, True)])
+@pytest.mark.parametrize("budget,flags", [(1, 0), (77, 0), (77, 1), (600, 0), (600, 1), (5000, 1)])
+def test_selection_at_the_candidate_limit(S, C, equal, budget, flags):
+    Hkv, G, N = 8, 2, 1400
+    rng = np.random.default_rng(C * 7 + budget)
+    g = torch.Generator(device=DEV).manual_seed(C + budget)
+    sh = ck.Shape(S, Hkv * G, Hkv, N, C)
+    st = ck.ClusterState(sh, DEV, budget=budget)
+    st.n_clusters = C
+    mu = torch.randn(S, Hkv, C, 128, generator=g, device=DEV).bfloat16()
+    if equal:                                             # every cluster scores the same: ties by id
+        mu[:] = mu[:, :, :1]
+    st.centroids.copy_(mu)
+    sizes = rng.multinomial(N, rng.dirichlet(np.full(C, 0.3)), size=(S, Hkv)).astype(np.int32)
+    offs = np.zeros((S, Hkv, C + 1), np.int32)
+    offs[:, :, 1:] = sizes.cumsum(-1)
+    sidx = np.stack([rng.permutation(N) for _ in range(S * Hkv)]).reshape(S, Hkv, N).astype(np.int32)
+    st.sizes.copy_(torch.from_numpy(sizes))
+    st.offsets.copy_(torch.from_numpy(offs))
+    st.sorted_idx.copy_(torch.from_numpy(sidx))
+    K = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    V = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    q = torch.randn(S, Hkv * G, 128, generator=g, device=DEV).bfloat16()
+    out = ck.decode_step(st, q, K, V, flags=flags).clone()
+    three = ck.ClusterState(sh, DEV, budget=budget)
+    for name in ("centroids", "sizes", "offsets", "sorted_idx"):
+        getattr(three, name).copy_(getattr(st, name))
+    three.n_clusters = C
+    assert torch.equal(out, ck.decode_step(three, q, K, V, flags=flags, fused=False))
+    mode = O.TRIM_LAST if flags else O.WHOLE
+    for s, h in [(0, 0), (S - 1, Hkv - 1)]:
+        scores = st.scores[s, h].double().cpu().numpy()
+        # from the step's own scores, so that nothing is a near-tie
+        order, n_sel, n_tok = O.select_clusters(scores, sizes[s, h], budget, mode)
+        assert int(st.n_sel_clusters[s, h]) == n_sel
+        assert int(st.n_sel_tokens[s, h]) == int(st.n_tokens[s, h]) == n_tok
+        assert np.array_equal(st.sel_clusters[s, h, :n_sel].cpu().numpy(), order[:n_sel])
+        rows = O.gather_indices(order, n_sel, offs[s, h], sidx[s, h], budget, mode)
+        assert np.array_equal(st.token_idx[s, h, :n_tok].cpu().numpy(), rows)
+        want = O.attention_over(np64(q[s, h * G:(h + 1) * G]), np64(K[s, h]), np64(V[s, h]), rows)
+        got = np64(out[s, h * G:(h + 1) * G])
+        assert np.abs(got - want).max() <= TOL * max(np.abs(want).max(), 1e-30)
