@@ -459,14 +459,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
 #pragma unroll
           for (int i = 0; i < 4; ++i) acc[j][i] *= cr[i];
       }
-      // p = hi + mid + lo, each with at most 8 significant bits
+      // p = hi + mid + lo, each with at most 8 significant bits.  A part that is zero (or unused) is
+      // replaced by the smallest normal number: zero times an infinite value would be a NaN
+      // where the sum has to be infinite (and 2^-126 of a finite one is below its last bit).
       uint32_t hi[4], mid[4], lo[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         hi[i] = __float_as_uint(pw[i]);
         const float r1 = pw[i] - __uint_as_float(hi[i] & 0xFFFF0000u);
-        mid[i] = __float_as_uint(r1);
-        lo[i] = __float_as_uint(r1 - __uint_as_float(mid[i] & 0xFFFF0000u));
+        mid[i] = max(__float_as_uint(r1), 0x00800000u);
+        const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xFFFF0000u);
+        lo[i] = max(__float_as_uint(r2), 0x00800000u);
       }
       constexpr uint32_t HIGH = 0x07060302u, LOW = 0x05040100u;   // halves of (second, first) word
       const uint4 pa = make_uint4(__builtin_amdgcn_perm(hi[1], hi[0], HIGH),
@@ -474,11 +477,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
                                   __builtin_amdgcn_perm(mid[1], mid[0], HIGH),
                                   __builtin_amdgcn_perm(mid[3], mid[2], HIGH));
       const uint4 pb = make_uint4(__builtin_amdgcn_perm(lo[1], lo[0], HIGH),
-                                  __builtin_amdgcn_perm(lo[3], lo[2], HIGH), 0u, 0u);
-      const uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w},
-                                 {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
-                                 {r.v[2].x, r.v[2].y, r.v[2].z, r.v[2].w},
-                                 {r.v[3].x, r.v[3].y, r.v[3].z, r.v[3].w}};
+                                  __builtin_amdgcn_perm(lo[3], lo[2], HIGH), 0x00800080u, 0x00800080u);
+      uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w},
+                           {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
+                           {r.v[2].x, r.v[2].y, r.v[2].z, r.v[2].w},
+                           {r.v[3].x, r.v[3].y, r.v[3].z, r.v[3].w}};
+      if (t * STEP + wave * 16 + 16 > n_pos) {          // wave-uniform: the row that stands in for a
+#pragma unroll                                          // position beyond the end is not looked at
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) vw[i][w] = ibase + i < n_pos ? vw[i][w] : 0u;
+      }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const uint32_t b01 = __builtin_amdgcn_perm(vw[1][j / 2], vw[0][j / 2], j & 1 ? HIGH : LOW);

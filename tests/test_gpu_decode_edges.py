@@ -91,3 +91,32 @@ def test_selection_at_the_candidate_limit(S, C, equal, budget, flags):
         want = O.attention_over(np64(q[s, h * G:(h + 1) * G]), np64(K[s, h]), np64(V[s, h]), rows)
         got = np64(out[s, h * G:(h + 1) * G])
         assert np.abs(got - want).max() <= TOL * max(np.abs(want).max(), 1e-30)
+
+
+@pytest.mark.parametrize("S", [1, 64])
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_infinite_values_and_unattended_rows(S, G):
+    """An infinite value makes its channel infinite (not NaN: parts of a probability are zero),
+    and row 0, which stands in for positions beyond the end, is not looked at."""
+    Hkv, N, n = 8, 300, 37
+    g = torch.Generator(device=DEV).manual_seed(G)
+    K = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    V = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    q = torch.zeros(S, Hkv * G, 128, device=DEV).bfloat16()   # all probabilities exactly 2^0
+    idx = (torch.rand(S, Hkv, N - 1, generator=g, device=DEV).topk(40).indices + 1).int()
+    cnt = torch.full((S, Hkv), n, dtype=torch.int32, device=DEV)
+    sh = ck.Shape(S, Hkv * G, Hkv, N, 8)
+    out = torch.zeros(S, Hkv * G, 128, device=DEV).bfloat16()
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out)
+    clean = out.clone()
+    V[:, :, 0] = float("inf")
+    K[:, :, 0] = float("nan")
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out)
+    assert torch.equal(out, clean)
+    b, h = torch.meshgrid(torch.arange(S, device=DEV), torch.arange(Hkv, device=DEV), indexing="ij")
+    V[b, h, idx[:, :, 7].long(), 5] = float("inf")
+    V[b, h, idx[:, :, 36].long(), 77] = float("-inf")
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out)
+    clean[:, :, 5] = float("inf")
+    clean[:, :, 77] = float("-inf")
+    assert torch.equal(out, clean)
