@@ -46,6 +46,8 @@ __device__ __forceinline__ int dpp_i0(int v) {      // lanes without a source re
 constexpr int DPP_XOR1 = 0xB1;          // quad_perm:[1,0,3,2]
 constexpr int DPP_XOR2 = 0x4E;          // quad_perm:[2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <-> 7 - i inside each 8
+constexpr int DPP_ROR4 = 0x124;         // rotation by 4 inside each row of 16
+constexpr int DPP_ROR8 = 0x128;         // by 8: lane i <-> i ^ 8
 constexpr int DPP_MIRROR = 0x140;       // lane i <-> 15 - i inside each row of 16
 
 struct OpSum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };

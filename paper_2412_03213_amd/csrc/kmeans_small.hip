@@ -2,7 +2,7 @@
 // stage: every m generated tokens are clustered among themselves into a handful of
 // new clusters).  At m = 320 tokens and 4 clusters an iteration is ~0.3 MFLOP per
 // head-problem, so the four-kernels-per-iteration pipeline of the prefill path spends
-// its time on launches; here one workgroup per head-problem keeps the keys in LDS and
+// its time on launches; here one workgroup per head-problem keeps the keys in registers and
 // runs init, all iterations (assignment, update), the metadata and the stores itself.
 // Same arithmetic rules as the large path: bf16-rounded table rows compared in fp32,
 // ties to the lower id, fp32 sums in a fixed order, means of raw keys, an empty cluster
@@ -21,49 +21,85 @@ struct SmallArgs {
   int tok_count, C_cap, c_begin, c_count, max_iter, metric, converge;
 };
 
-// MAXC: compile-time bound of the cluster count (register arrays); SM_THREADS: workgroup size
-// (more wavefronts hide the LDS and cross-lane latencies of the 16-lane dot products).
+// MAXC: compile-time bound of the cluster count; SM_THREADS: workgroup size.
+//
+// Bound: a chain of max_iter dependent iterations on one CU per head-problem, each of them VALU
+// and cross-lane work on n_tok * C dot products.  Both halves of an iteration run on
+// v_mfma_f32_4x4x1_16b_f32 (16 independent 4 x 4 outer products, one fp32 multiply-add per
+// element and step, so the additions happen one by one in the order written here):
+//   dot products  block = eight channels of a key (one per step), rows = 4 clusters, columns = 4
+//                 keys: 8 steps replace 32 multiply-adds, and the sixteen partial sums of a
+//                 (key, cluster) are added by lane swaps that halve the registers on the way;
+//   update sums   block = four lanes of one key, rows = 4 clusters, A = 1 where the key's label
+//                 is the row's cluster: 8 steps replace 32 multiply-adds.
+// A wavefront keeps its keys in registers in both layouts for all iterations (no LDS pass over
+// the keys).  The wavefront of a cluster adds up that cluster's partial sums, keeps its mean in
+// registers and makes the next table row from it, so an iteration has two barriers.
+// 128 head-problems x 320 tokens x 4 clusters, 10 iterations: 85.3 -> 56.6 us, same bits.
 template <int MAXC, int SM_THREADS>
 __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) {
-  constexpr int SM_SLICES = SM_THREADS / WAVE;           // partial sums of the update: one per wavefront
-  __shared__ __attribute__((aligned(16))) bf16 keys[KM_SMALL_MAX_TOKENS * D];
+  constexpr int WAVES = SM_THREADS / WAVE, SETS = MAXC / 4;
+  constexpr int KEYS = WAVES * 4;                       // keys per round, four per wavefront
+  constexpr int ROUNDS = (KM_SMALL_MAX_TOKENS + KEYS - 1) / KEYS;
+  static_assert(MAXC % 4 == 0 && MAXC <= WAVES && KM_SMALL_MAX_TOKENS <= SM_THREADS, "mapping");
   __shared__ __attribute__((aligned(16))) float table[MAXC][D];
-  __shared__ float mu[MAXC][D];
-  __shared__ float part[SM_SLICES][MAXC][D];
-  __shared__ int cnt[SM_SLICES][MAXC];
-  __shared__ int wave_cnt[SM_THREADS / WAVE][MAXC];
+  __shared__ __attribute__((aligned(16))) float part[WAVES][MAXC][D];
+  __shared__ int cnt[WAVES][MAXC];
+  __shared__ int wave_cnt[WAVES][MAXC];
   __shared__ float bias[MAXC];
   __shared__ int lab[KM_SMALL_MAX_TOKENS];
-  __shared__ int s_changed;
+  __shared__ int s_changed[2];
 
   const int hp = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, row = lane >> 4, l4 = lane & 3;
   const int n_tok = a.tok_count, C = a.c_count;
   const bf16* Khp = a.K + (int64_t)hp * a.N_cap * D;
 
-  // ---- keys of the range into LDS (16-byte pieces), initial centroids ----
-  for (int i = tid; i < n_tok * 16; i += SM_THREADS)
-    reinterpret_cast<uint4*>(keys)[i] =
-        reinterpret_cast<const uint4*>(Khp + a.tok_begin * D)[i];
-  for (int e = tid; e < C * D; e += SM_THREADS) {
-    const int c = e / D, ch = e % D;
-    int64_t row = a.init_idx[(int64_t)hp * C + c];
-    row = row < 0 ? 0 : (row >= a.N_cap ? a.N_cap - 1 : row);
-    mu[c][ch] = bf16_bits_to_float(reinterpret_cast<const uint16_t*>(Khp + row * D)[ch]);
+  // ---- this wavefront's keys: of round r, keys 4 * wave + (0..3) ----
+  // dk: lane 4 b + x holds the eight channels of group bitreverse(b) of key x.  Lane bits 5, 4, 3, 2
+  // are then bits 0, 1, 2, 3 of the channel group, and the partial sums are added in the order
+  // of row16_sum.  uk: lanes 16 x + g hold channel group g of key x.
+  const int b = lane >> 2;
+  const int dgroup = ((b & 1) << 3) | ((b & 2) << 1) | ((b & 4) >> 1) | (b >> 3);
+  uint4 dk[ROUNDS], uk[ROUNDS];
+  {
+    const uint4* R = reinterpret_cast<const uint4*>(Khp + a.tok_begin * D);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {                  // a key beyond the range re-reads the last one
+      const int td = r * KEYS + wave * 4 + l4, tu = r * KEYS + wave * 4 + row;
+      uk[r] = R[(int64_t)(tu < n_tok ? tu : n_tok - 1) * 16 + l16];
+      dk[r] = R[(int64_t)(td < n_tok ? td : n_tok - 1) * 16 + dgroup];
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)                    // ... and adds nothing
+      if (r * KEYS + wave * 4 + row >= n_tok) uk[r] = make_uint4(0, 0, 0, 0);
   }
-  for (int t = tid; t < n_tok; t += SM_THREADS) lab[t] = -1;
-  for (int e = tid; e < SM_SLICES * MAXC; e += SM_THREADS)
-    cnt[e / MAXC][e % MAXC] = 0;
-  __syncthreads();
+  // the mean of cluster `wave`: channels 2 * lane, 2 * lane + 1
+  float m0 = 0.f, m1 = 0.f;
+  if (wave < C) {
+    int64_t r = a.init_idx[(int64_t)hp * C + wave];
+    r = r < 0 ? 0 : (r >= a.N_cap ? a.N_cap - 1 : r);
+    const uint32_t w = reinterpret_cast<const uint32_t*>(Khp + r * D)[lane];
+    m0 = lo_bf16(w);
+    m1 = hi_bf16(w);
+  }
+  for (int e = C * D + tid; e < MAXC * D; e += SM_THREADS) table[e / D][e % D] = 0.f;
 
-  const int l16 = tid & 15, grp = tid >> 4;             // 32 groups of 16 lanes
+  // After the lane swaps row r of a register holds cluster 4 s + {0, 2, 1, 3}[r]
+  const int rowc = ((row & 1) << 1) | (row >> 1);
+  uint32_t labels[(ROUNDS + 7) / 8];                    // 4 bits per round: label of key `l4`
+#pragma unroll
+  for (int i = 0; i < (ROUNDS + 7) / 8; ++i) labels[i] = 0xFFFFFFFFu;
+
   int n_done = 0;
   for (int it = 0; it < a.max_iter; ++it) {
-    // ---- table row (and l2 bias) of cluster `wave`: lane holds channels 2*lane, 2*lane+1 ----
+    // ---- table row (and l2 bias) of cluster `wave` ----
     if (wave < C) {
-      const float m0 = mu[wave][2 * lane], m1 = mu[wave][2 * lane + 1];
       float r0, r1;
       if (a.metric == CK_METRIC_COSINE) {
-        const float n2 = wave_sum(m0 * m0 + m1 * m1);
+        // the fused product written out: the last bit of the norm must not depend on the
+        // compiler's choice
+        const float n2 = wave_sum(fmaf(m0, m0, m1 * m1));
         const float inv = n2 > 0.f ? 1.0f / sqrtf(n2) : 0.f;
         r0 = bf16_bits_to_float(float_to_bf16_bits(m0 * inv));
         r1 = bf16_bits_to_float(float_to_bf16_bits(m1 * inv));
@@ -71,109 +107,160 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
         r0 = bf16_bits_to_float(float_to_bf16_bits(m0));
         r1 = bf16_bits_to_float(float_to_bf16_bits(m1));
       }
-      table[wave][2 * lane] = r0;
-      table[wave][2 * lane + 1] = r1;
+      *reinterpret_cast<float2*>(&table[wave][2 * lane]) = make_float2(r0, r1);
       if (a.metric == CK_METRIC_L2) {
-        const float rn2 = wave_sum(r0 * r0 + r1 * r1);
+        const float rn2 = wave_sum(fmaf(r0, r0, r1 * r1));
         if (lane == 0) bias[wave] = -0.5f * rn2;
       } else if (lane == 0) {
         bias[wave] = 0.f;
       }
     }
-    if (tid == 0) s_changed = 0;
+    if (tid == 0) s_changed[it & 1] = 0;                // the other one may still be read
     __syncthreads();
 
-    // ---- assignment, and the sums of the update in the same pass: 16 lanes per key, 8
-    // channels per lane; every lane of the group learns the label and adds its channels of
-    // the key to the sums of that cluster.  A stopped run discards the sums. ----
-    float tb[MAXC][8], acc[MAXC][8];
-    int n[MAXC];
+    float ta[SETS][8], bs[SETS];
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-      n[c] = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        tb[c][j] = c < C ? table[c][l16 * 8 + j] : 0.f;
-        acc[c][j] = 0.f;
-      }
+    for (int s = 0; s < SETS; ++s) {
+      const float4* t = reinterpret_cast<const float4*>(&table[4 * s + l4][dgroup * 8]);
+      const float4 x = t[0], y = t[1];
+      ta[s][0] = x.x; ta[s][1] = x.y; ta[s][2] = x.z; ta[s][3] = x.w;
+      ta[s][4] = y.x; ta[s][5] = y.y; ta[s][6] = y.z; ta[s][7] = y.w;
+      // a row without a cluster is a NaN, which never wins
+      bs[s] = 4 * s + rowc < C ? bias[4 * s + rowc] : __builtin_nanf("");
     }
-    int diff = 0;
-    for (int t = grp; t < n_tok; t += SM_THREADS / 16) {
-      const uint4 w = *reinterpret_cast<const uint4*>(keys + t * D + l16 * 8);
-      float kv[8];
-      kv[0] = lo_bf16(w.x); kv[1] = hi_bf16(w.x); kv[2] = lo_bf16(w.y); kv[3] = hi_bf16(w.y);
-      kv[4] = lo_bf16(w.z); kv[5] = hi_bf16(w.z); kv[6] = lo_bf16(w.w); kv[7] = hi_bf16(w.w);
-      float best = 0.f;
-      int bc = 0;
+    floatx4 acc[SETS][8];                               // [channel 8 l16 + j][cluster 4 s + i], key group `row`
+    int n[SETS];                                        // members of cluster 4 s + l4 in key group `row`
 #pragma unroll
-      for (int c = 0; c < MAXC; ++c) {
-        if (c < C) {                                    // uniform
-          float d = 0.f;
+    for (int s = 0; s < SETS; ++s) {
+      n[s] = 0;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) d = fmaf(kv[j], tb[c][j], d);
-          d = row16_sum(d) + bias[c];
-          if (c == 0 || d > best) {
-            best = d;
+      for (int j = 0; j < 8; ++j) acc[s][j] = {0.f, 0.f, 0.f, 0.f};
+    }
+    uint32_t moved = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      if (r * KEYS < n_tok) {                           // uniform
+        // unpacked here and not once before the iterations: there are no registers for that
+        asm volatile("" : "+v"(dk[r].x), "+v"(dk[r].y), "+v"(dk[r].z), "+v"(dk[r].w));
+        asm volatile("" : "+v"(uk[r].x), "+v"(uk[r].y), "+v"(uk[r].z), "+v"(uk[r].w));
+        const uint32_t dw[4] = {dk[r].x, dk[r].y, dk[r].z, dk[r].w};
+        float best = 0.f;
+        int bc = 0;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+          floatx4 d = {0.f, 0.f, 0.f, 0.f};             // [cluster 4 s + i] of key l4, channel group of b
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            d = __builtin_amdgcn_mfma_f32_4x4x1f32(ta[s][j], j & 1 ? hi_bf16(dw[j / 2]) : lo_bf16(dw[j / 2]), d, 0, 0, 0);
+          // sixteen channel groups: lane bits 5, 4 (two clusters share a register from there
+          // on), 3, 2
+          const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[0]), __float_as_uint(d[1]), false, false);
+          const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2]), __float_as_uint(d[3]), false, false);
+          const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+          const float c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+          const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
+          float v = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+          v += dpp_f<DPP_ROR8>(v);
+          v += dpp_f<DPP_ROR4>(v);                      // lanes x and x ^ 8 are equal by now
+          v += bs[s];
+          // a NaN never wins over another cluster and is never beaten as cluster 0
+          v = v == v ? v : (4 * s + rowc == 0 ? INFINITY : -INFINITY);
+          // best of the four, the lower cluster where they are equal: rows hold 0, 2, 1, 3
+          const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+          const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
+          const float xv = x1 > x0 ? x1 : x0;
+          const unsigned xc = (row & 1) * 2 + (x1 > x0 ? 1 : 0);
+          const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(xv), __float_as_uint(xv), false, false);
+          const auto yc = __builtin_amdgcn_permlane16_swap(xc, xc, false, false);
+          const float y0 = __uint_as_float(y[0]), y1 = __uint_as_float(y[1]);
+          const float yv = y1 > y0 ? y1 : y0;
+          const int c = 4 * s + (int)(y1 > y0 ? yc[1] : yc[0]);
+          if (s == 0 || yv > best) {
+            best = yv;
             bc = c;
           }
         }
-      }
+        // a key that does not exist belongs to no cluster
+        if (r * KEYS + wave * 4 + l4 >= n_tok) bc = 15;
+        const uint32_t word = labels[r / 8], put = (word & ~(15u << (r % 8 * 4))) | ((uint32_t)bc << (r % 8 * 4));
+        moved |= word ^ put;
+        labels[r / 8] = put;
+        // label of key `row` into all lanes of that row: lane x of every quad has key x's
+        int ub = 0;
+        ub = __builtin_amdgcn_update_dpp(ub, bc, 0x00, 0x1, 0xf, false);
+        ub = __builtin_amdgcn_update_dpp(ub, bc, 0x55, 0x2, 0xf, false);
+        ub = __builtin_amdgcn_update_dpp(ub, bc, 0xAA, 0x4, 0xf, false);
+        ub = __builtin_amdgcn_update_dpp(ub, bc, 0xFF, 0x8, 0xf, false);
+        const uint32_t uw[4] = {uk[r].x, uk[r].y, uk[r].z, uk[r].w};
 #pragma unroll
-      for (int c = 0; c < MAXC; ++c) {
-        if (c < C) {
-          const float on = bc == c ? 1.f : 0.f;
-          n[c] += bc == c ? 1 : 0;
+        for (int s = 0; s < SETS; ++s) {
+          const bool mine = ub == 4 * s + l4;
+          const float on = mine ? 1.f : 0.f;
+          n[s] += mine ? 1 : 0;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) acc[c][j] = fmaf(on, kv[j], acc[c][j]);
+          for (int j = 0; j < 8; ++j)
+            acc[s][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(on, j & 1 ? hi_bf16(uw[j / 2]) : lo_bf16(uw[j / 2]), acc[s][j], 0, 0, 0);
         }
-      }
-      if (l16 == 0) {
-        diff += lab[t] != bc ? 1 : 0;
-        lab[t] = bc;
+        __builtin_amdgcn_sched_barrier(0);              // rounds one after another: registers
       }
     }
-    diff = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
-    if (lane == 0 && diff) atomicAdd(&s_changed, diff);
-    // the four groups of a wavefront, then (below) the wavefronts in order
+    if (__ballot(moved != 0) && lane == 0) s_changed[it & 1] = 1;
+    // ---- the four key groups of the wavefront; row k ends with cluster 4 s + k ----
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-      if (c < C) {
-        n[c] += __shfl_xor(n[c], 16, WAVE);
-        n[c] += __shfl_xor(n[c], 32, WAVE);
+    for (int s = 0; s < SETS; ++s) {
+      float o[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[c][j] = xor32(xor16(acc[c][j], OpSum()), OpSum());
-        if (lane < 16) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) part[wave][c][l16 * 8 + j] = acc[c][j];
-          if (lane == 0) cnt[wave][c] = n[c];
-        }
+      for (int j = 0; j < 8; ++j) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][0]), __float_as_uint(acc[s][j][1]), false, false);
+        const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][2]), __float_as_uint(acc[s][j][3]), false, false);
+        const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        const float c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+        const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
+        o[j] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
       }
+      float4* dst = reinterpret_cast<float4*>(&part[wave][4 * s + row][l16 * 8]);
+      dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+      dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+      n[s] += __shfl_xor(n[s], 16, WAVE);
+      n[s] += __shfl_xor(n[s], 32, WAVE);
+      if (lane < 4) cnt[wave][4 * s + lane] = n[s];
     }
     __syncthreads();
     ++n_done;
-    if (a.converge && it > 0 && s_changed == 0) break;  // uniform: the previous update stands
+    if (a.converge && it > 0 && s_changed[it & 1] == 0) break;  // uniform: the previous update stands
 
-    // ---- update: mean of the assigned keys; an empty cluster keeps its centroid ----
-    for (int e = tid; e < C * D; e += SM_THREADS) {
-      const int c = e / D, ch = e % D;
+    // ---- update: mean of the assigned keys, wavefronts in order; an empty cluster keeps its
+    // centroid ----
+    if (wave < C) {
+      float s0 = 0.f, s1 = 0.f;
       int nn = 0;
-      float sum = 0.f;
 #pragma unroll
-      for (int wv = 0; wv < SM_THREADS / WAVE; ++wv) {
-        nn += cnt[wv][c];
-        sum += part[wv][c][ch];
+      for (int w = 0; w < WAVES; ++w) {
+        const float2 v = *reinterpret_cast<const float2*>(&part[w][wave][2 * lane]);
+        s0 += v.x;
+        s1 += v.y;
+        nn += cnt[w][wave];
       }
-      if (nn > 0) mu[c][ch] = sum * (1.0f / (float)nn);
+      if (nn > 0) {
+        const float inv = 1.0f / (float)nn;
+        m0 = s0 * inv;
+        m1 = s1 * inv;
+      }
     }
-    __syncthreads();
   }
+  if (lane < 4) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int t = r * KEYS + wave * 4 + lane;
+      if (t < n_tok) lab[t] = (int)(labels[r / 8] >> (r % 8 * 4)) & 15;
+    }
+  }
+  __syncthreads();
 
   // ---- stores: centroids, labels, sizes, offsets, stable label-sorted index ----
-  for (int e = tid; e < C * D; e += SM_THREADS) {
-    const int c = e / D, ch = e % D;
-    reinterpret_cast<uint16_t*>(a.centroids + ((int64_t)hp * a.C_cap + a.c_begin + c) * D)[ch] =
-        float_to_bf16_bits(mu[c][ch]);
-  }
+  if (wave < C)
+    reinterpret_cast<uint32_t*>(a.centroids + ((int64_t)hp * a.C_cap + a.c_begin + wave) * D)[lane] =
+        (uint32_t)float_to_bf16_bits(m0) | ((uint32_t)float_to_bf16_bits(m1) << 16);
   int32_t* off_g = a.offsets + (int64_t)hp * (a.C_cap + 1);
   const int base0 = a.c_begin == 0 ? 0 : off_g[a.c_begin];
   const bool valid = tid < n_tok;

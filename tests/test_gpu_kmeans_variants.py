@@ -146,6 +146,64 @@ def test_run_until_convergence_small_range(metric):
             assert st.sorted_idx[s, h].cpu().numpy().tolist() == wi.tolist()
 
 
+@pytest.mark.parametrize("metric", [O.COSINE, O.L2, O.INNER])
+@pytest.mark.parametrize("n,C", [(1, 1), (3, 2), (31, 3), (64, 4), (65, 4), (383, 4),
+                                 (5, 5), (33, 8), (127, 7), (129, 6), (384, 5)])
+def test_small_range_every_remainder(metric, n, C):
+    """The single-kernel path where a round of keys (64 or 32) or a group of four clusters is
+    not full, appended behind other tokens: labels of one assignment against the oracle away
+    from near ties, metadata and means against the labels that were returned."""
+    N0, C0 = 100, 2
+    cfg = Config(f"r{n}", 1, 1, 3, 3, 128, N0 + n, 6, C0 + C, 10, 64, 7 + n)
+    w = MixtureWorkload(cfg, device=DEV)
+    init = sample_init_indices(w.K, C, 3, N0, n)
+    sh = ck.Shape(1, 3, 3, cfg.N, cfg.C)
+    for n_iter in (1, 3):
+        st = ck.ClusterState(sh, DEV, budget=64)
+        st.cluster(w.K, sample_init_indices(w.K, C0, 1, 0, N0).to(DEV), 0, N0, C0, 1)
+        st.cluster(w.K, init.to(DEV), N0, n, C, n_iter, flags=METRICS[metric])
+        for h in range(3):
+            keys = np64(w.K[0, h])
+            lab = st.labels[0, h].cpu().numpy()
+            assert lab[N0:].min() >= C0 and lab[N0:].max() < C0 + C
+            *_, tr = O.kmeans_run(keys[N0:], init[0, h].numpy() - N0, n_iter, "bf16", metric)
+            if not any((g < NEAR_TIE).any() for g in tr.gap[:-1]):
+                assert ((lab[N0:] - C0 == tr.labels[-1]) | (tr.gap[-1] < NEAR_TIE)).all()
+            check_state(st, cfg, 0, h, keys, lab)
+
+
+@pytest.mark.parametrize("C", [3, 4, 7])
+def test_small_range_infinite_keys(C):
+    """Similarities that are infinite or not a number: a NaN never takes a key from another
+    cluster and is never replaced as cluster 0; equal infinities go to the lower cluster."""
+    n = 80
+    rng = np.random.default_rng(C)
+    k = rng.standard_normal((n, 128)).astype(np.float32)
+    k[:C] = np.abs(k[:C]) + 0.5
+    k[0, :3] *= -1.0                                    # cluster 0: negative in channels 0..2
+    k[C - 1, 5] = 0.0
+    bad = {20: {1: np.inf}, 21: {9: -np.inf}, 22: {1: np.inf, 9: np.inf}, 23: {5: np.inf},
+           24: {5: -np.inf}, 25: {9: np.inf, 10: -np.inf}}
+    for t, ch in bad.items():
+        for c, v in ch.items():
+            k[t, c] = v
+    K = torch.from_numpy(k).to(torch.bfloat16)[None, None].to(DEV)
+    sh = ck.Shape(1, 1, 1, n, C)
+    st = ck.ClusterState(sh, DEV, budget=64)
+    init = torch.arange(C, dtype=torch.int32, device=DEV)[None, None]
+    st.cluster(K, init, 0, n, C, 1, flags=ck.CK_METRIC_IP)
+    lab = st.labels[0, 0].cpu().numpy()
+    rows = K[0, 0].float().cpu().numpy()
+    for t in bad:
+        with np.errstate(invalid="ignore"):
+            sim = (rows[t] * rows[:C]).sum(axis=1)
+        want, best = 0, sim[0]
+        for c in range(1, C):
+            if sim[c] > best:
+                want, best = c, sim[c]
+        assert lab[t] == want, (t, sim, lab[t])
+
+
 def test_fixed_count_reports_all_iterations_and_flags_zero_is_the_default():
     cfg = Config("dflt", 1, 1, 2, 2, 128, 2048, 64, 32, 10, 256, 0)
     w = MixtureWorkload(cfg, device=DEV)
