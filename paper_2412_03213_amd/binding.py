@@ -1,4 +1,5 @@
-"""ctypes binding of libclusterkv.so: argument marshalling only.
+"""Binding of libclusterkv.so: argument marshalling only, through ctypes and, for the call
+that is made once per layer and generated token, through the native _ckhost module.
 
 Functions carry the names of the C entry points (include/clusterkv.h) and take
 torch tensors in the layouts documented there.  Work is enqueued on torch's
@@ -20,6 +21,7 @@ CK_WS_CLUSTER_KEYS, CK_WS_SPARSE_ATTN, CK_WS_OBJECTIVE = 0, 1, 2
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libclusterkv.so")
+HOST_PATH = os.path.join(_PKG, "_ckhost.so")
 
 EXPORTS = ("ck_version", "ck_strerror", "ck_last_error_detail", "ck_workspace_bytes",
            "ck_cluster_keys", "ck_cluster_keys_opt", "ck_kmeans_assign", "ck_kmeans_objective", "ck_build_metadata", "ck_kmeans_update",
@@ -74,9 +76,10 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(HOST_PATH)):
         if not build_if_missing:
-            raise RuntimeError(f"{LIB_PATH} is missing: run python -m paper_2412_03213_amd.build")
+            missing = HOST_PATH if os.path.exists(LIB_PATH) else LIB_PATH
+            raise RuntimeError(f"{missing} is missing: run python -m paper_2412_03213_amd.build")
         from .build import build
         build(verbose=False)
     lib = ctypes.CDLL(LIB_PATH)
@@ -140,6 +143,9 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
                                           P, P, P, P, SZ, P]
     lib.ck_probe_mfma_bf16.restype = ctypes.c_int
     lib.ck_probe_mfma_bf16.argtypes = [I32, I32, P, P, P, ctypes.POINTER(ctypes.c_double), P]
+    from . import _ckhost
+    lib.host_decode_step = _ckhost.decode_step
+    lib.decode_step_entry = ctypes.cast(lib.ck_decode_step, P).value
     _lib = lib
     return lib
 
@@ -163,7 +169,7 @@ def _ptr(t):
 
 def _stream(t) -> int:
     if isinstance(t, torch.Tensor) and t.is_cuda:
-        return torch.cuda.current_stream(t.device).cuda_stream
+        return torch._C._cuda_getCurrentRawStream(t.get_device())
     return 0
 
 
@@ -520,16 +526,24 @@ def ck_decode_step(sh: Shape, q, K, V, centroids, sizes, offsets, sorted_idx, n_
     if workspace is None:
         workspace = _workspace(
             ck_workspace_bytes(sh, CK_WS_SPARSE_ATTN, budget + n_sink + n_recent), q)
-    stride = token_idx.shape[-1] if isinstance(token_idx, torch.Tensor) else budget
-    s = sh.c()
-    _check(lib.ck_decode_step(ctypes.byref(s), _ptr(q), _ptr(K), _ptr(V), _ptr(centroids),
-                              _ptr(sizes), _ptr(offsets), _ptr(sorted_idx), n_clusters, budget,
-                              flags, n_sink, recent_begin, recent_end, softmax_scale,
-                              _ptr(scores), _ptr(sel_clusters), _ptr(n_sel_clusters),
-                              _ptr(n_sel_tokens), _ptr(token_idx), stride, _ptr(n_tokens),
-                              _ptr(out), _ptr(workspace),
-                              workspace.numel() if isinstance(workspace, torch.Tensor) else 0,
-                              _stream(q)))
+    stride = token_idx.size(-1) if isinstance(token_idx, torch.Tensor) else budget
+    stream = _stream(q)
+    rc = lib.host_decode_step(lib.decode_step_entry, sh, q, K, V, centroids, sizes, offsets,
+                              sorted_idx, scores, sel_clusters, n_sel_clusters, n_sel_tokens,
+                              token_idx, n_tokens, out, workspace, n_clusters, budget, flags,
+                              n_sink, recent_begin, recent_end, softmax_scale, stride, stream)
+    if rc is None:                  # raw addresses, null pointers, numbers of other types
+        s = sh.c()
+        rc = lib.ck_decode_step(ctypes.byref(s), _ptr(q), _ptr(K), _ptr(V), _ptr(centroids),
+                                _ptr(sizes), _ptr(offsets), _ptr(sorted_idx), n_clusters, budget,
+                                flags, n_sink, recent_begin, recent_end, softmax_scale,
+                                _ptr(scores), _ptr(sel_clusters), _ptr(n_sel_clusters),
+                                _ptr(n_sel_tokens), _ptr(token_idx), stride, _ptr(n_tokens),
+                                _ptr(out), _ptr(workspace),
+                                workspace.numel() if isinstance(workspace, torch.Tensor) else 0,
+                                stream)
+    if rc != 0:
+        _check(rc)
     return workspace
 
 

@@ -1,14 +1,16 @@
-"""Build libclusterkv.so (gfx950) in-tree with hipcc.
+"""Build libclusterkv.so (gfx950) in-tree with hipcc, and _ckhost.so (the native form of the
+binding's hot call) with the host compiler.
 
     python -m paper_2412_03213_amd.build [--force]
 
-Objects go to _build/ at the repository root, the library next to this file.
+Objects go to _build/ at the repository root, the libraries next to this file.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -17,11 +19,14 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJ_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libclusterkv.so")
+HOST_SRC = os.path.join(CSRC, "host_call.cpp")
+HOST_LIB = os.path.join(PKG, "_ckhost.so")
 
 SOURCES = ["api.hip", "kmeans_assign.hip", "kmeans_assign_stream.hip", "kmeans_update.hip", "kmeans_small.hip", "select_gather.hip",
            "sparse_attn.hip", "evaluate.hip", "cluster_cache.hip",
            "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed-FP32 instruction selection is kept off for every device function
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -65,6 +70,10 @@ def build(force: bool = False, verbose: bool = True) -> str:
         list(ex.map(run, jobs))
     if force or jobs or not os.path.exists(LIB):
         run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    header = os.path.join(INCLUDE, "clusterkv.h")
+    if force or _newer(HOST_SRC, HOST_LIB) or _newer(header, HOST_LIB):
+        run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE,
+             "-I", sysconfig.get_paths()["include"], HOST_SRC, "-o", HOST_LIB])
     return LIB
 
 

@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2412_03213_amd as ck
 from paper_2412_03213_amd import binding
@@ -238,3 +239,39 @@ def test_missing_library_is_an_error(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(RuntimeError):
         binding.load_library(build_if_missing=False)
+
+
+@pytest.mark.parametrize("change, error", [
+    ({}, ck.ClusterKVError),                                      # S = 0: refused by the library
+    ({"K": "strided"}, ValueError),                               # marshalling refuses it
+    ({"budget": 2.0}, ctypes.ArgumentError),
+    ({"flags": None}, ctypes.ArgumentError),
+    ({"scores": None}, ck.ClusterKVError),
+    ({"V": 4096}, ck.ClusterKVError),                             # raw address
+    ({"n_sink": 1 << 40}, ck.ClusterKVError),
+    ({"budget": (1 << 32) + 5}, ck.ClusterKVError),               # cut to 32 bits as before
+])
+def test_decode_step_refuses_the_same_calls_on_either_way(change, error):
+    """The native marshalling hands every argument that is not plain to the ctypes call."""
+    bf, i32 = dict(dtype=torch.bfloat16), dict(dtype=torch.int32)
+    kv = torch.zeros(1, 2, 16, 128, **bf)
+    a = dict(q=torch.zeros(1, 2, 128, **bf), K=kv, V=kv, centroids=torch.zeros(1, 2, 4, 128, **bf),
+             sizes=torch.zeros(1, 2, 4, **i32), offsets=torch.zeros(1, 2, 5, **i32),
+             sorted_idx=torch.zeros(1, 2, 16, **i32), n_clusters=4, budget=8, flags=0,
+             scores=torch.zeros(1, 2, 4), sel_clusters=torch.zeros(1, 2, 4, **i32),
+             n_sel_clusters=torch.zeros(1, 2, **i32), n_sel_tokens=torch.zeros(1, 2, **i32),
+             token_idx=torch.zeros(1, 2, 8, **i32), n_tokens=torch.zeros(1, 2, **i32),
+             out=torch.zeros(1, 2, 128, **bf), workspace=torch.zeros(65536, dtype=torch.uint8))
+    for k, v in change.items():
+        a[k] = kv.transpose(2, 3) if isinstance(v, str) else v
+    sh = ck.Shape(0, 2, 2, 16, 4)
+    with pytest.raises(error) as native:
+        ck.ck_decode_step(sh, **a)
+    lib = ck.load_library()
+    real, lib.host_decode_step = lib.host_decode_step, lambda *args: None
+    try:
+        with pytest.raises(error) as general:
+            ck.ck_decode_step(sh, **a)
+    finally:
+        lib.host_decode_step = real
+    assert str(native.value) == str(general.value)
