@@ -39,23 +39,27 @@ class LayerStack:
     def compressed(self, layer: int) -> bool:
         return layer >= self.full_kv_layers
 
-    def _on_side(self, layer: int, fn):
-        """Run fn on the side stream after everything enqueued so far on the current one."""
-        cur = torch.cuda.current_stream(self.device)
-        self.side.wait_stream(cur)
+    def _cluster_on_side(self, layer: int, K, init_idx, tok_begin, tok_count, c_count):
+        """Cluster on the side stream, after everything enqueued so far on the current one."""
+        st = self.states[layer]
+        self.side.wait_stream(torch.cuda.current_stream(self.device))
         with torch.cuda.stream(self.side):
-            fn()
+            st.cluster(K, init_idx, tok_begin, tok_count, c_count, self.n_iter)
             self.ready[layer].record(self.side)
+        # The caller may drop its last reference to any of these as soon as this returns, with
+        # the clustering still queued behind other layers': their memory must not go to the
+        # next allocation of the current stream before the side stream is through with it.
+        for t in (K, init_idx, st.centroids, st.labels, st.sizes, st.offsets, st.sorted_idx):
+            if isinstance(t, torch.Tensor) and t.is_cuda:
+                t.record_stream(self.side)
         self.pending[layer] = True
 
     def cluster_prefill(self, layer: int, K, init_idx):
         """Cluster tokens [n_sink, n_prefill) of a layer into C0 clusters, asynchronously."""
         if not self.compressed(layer):
             return
-        st = self.states[layer]
-        st.n_clusters = 0
-        n = self.n_prefill - self.n_sink
-        self._on_side(layer, lambda: st.cluster(K, init_idx, self.n_sink, n, self.C0, self.n_iter))
+        self.states[layer].n_clusters = 0
+        self._cluster_on_side(layer, K, init_idx, self.n_sink, self.n_prefill - self.n_sink, self.C0)
         self.clustered_to[layer] = self.n_prefill
 
     def cluster_generated(self, layer: int, K, n_ctx: int, init_idx) -> bool:
@@ -63,9 +67,8 @@ class LayerStack:
         new clusters on the side stream.  init_idx: [S, Hkv, c_plus] rows among those tokens."""
         if not self.compressed(layer) or n_ctx - self.clustered_to[layer] < self.m:
             return False
-        st = self.states[layer]
         t0 = self.clustered_to[layer]
-        self._on_side(layer, lambda: st.cluster(K, init_idx, t0, self.m, self.c_plus, self.n_iter))
+        self._cluster_on_side(layer, K, init_idx, t0, self.m, self.c_plus)
         self.clustered_to[layer] = t0 + self.m
         return True
 

@@ -89,3 +89,31 @@ def test_layer_stack_matches_sequential_calls_and_oracle():
         torch.cuda.synchronize()
         assert torch.equal(stack.states[l].sorted_idx, ref[l].sorted_idx)
         assert torch.equal(stack.states[l].centroids, ref[l].centroids)
+
+
+def test_clustering_in_flight_keeps_its_inputs():
+    """Keys and initial rows that the caller drops right after the call, with the clustering
+    still queued on the side stream: later allocations must not take their memory over."""
+    L, S, Hkv, N0, C0, m, cp, sink = 3, 1, 8, 8192, 100, 64, 2, 16
+    stack = ck.LayerStack(L, S, Hkv, Hkv, N0, m, C0, 256, DEV, n_sink=sink, full_kv_layers=0, m=m,
+                          c_plus=cp, n_iter=8)
+    ref = [ck.ClusterState(stack.sh, DEV, 256) for _ in range(L)]
+    g = torch.Generator(device=DEV).manual_seed(5)
+    Ks = [torch.randn(S, Hkv, N0 + m, 128, generator=g, device=DEV).bfloat16() for _ in range(L)]
+    first = [sample_init_indices(K, C0, 1, sink, N0 - sink).to(DEV) for K in Ks]
+    more = [sample_init_indices(K, cp, 2, N0, m).to(DEV) for K in Ks]
+    for l in range(L):
+        ref[l].cluster(Ks[l], first[l], sink, N0 - sink, C0, 8)
+        ref[l].cluster(Ks[l], more[l], N0, m, cp, 8)
+    torch.cuda.synchronize()
+    junk = []
+    for l in range(L):
+        stack.cluster_prefill(l, Ks[l].clone(), first[l].clone())
+        junk += [torch.zeros_like(Ks[l]), torch.zeros_like(first[l])]
+    for l in range(L):
+        assert stack.cluster_generated(l, Ks[l].clone(), N0 + m, more[l].clone())
+        junk += [torch.zeros_like(Ks[l]), torch.zeros_like(more[l])]
+    torch.cuda.synchronize()
+    for l in range(L):
+        for name in ("labels", "sizes", "offsets", "sorted_idx", "centroids"):
+            assert torch.equal(getattr(stack.states[l], name), getattr(ref[l], name)), (l, name)
