@@ -36,7 +36,7 @@ constexpr int seg_stride(int c_count) { return (c_count + 3) & ~3; }   // words 
 constexpr int chunk_sort_cnt_ints(int c_max) { return (c_max + 255) & ~255; }
 
 // Stable counting sort of a chunk of ROUNDS * 64 tokens by label, by one wavefront.  tok
-// (LDS): the pack_token words of the chunk; cnt (LDS, chunk_sort_cnt_ints(CMAX) ints) and
+// (LDS): the pack_token words of the chunk, every label below c_count; cnt (LDS, chunk_sort_cnt_ints(CMAX) ints) and
 // order (LDS, ROUNDS * 64 entries) are 16-byte aligned scratch of this wavefront.
 // The groups of 64 add their label counts to the chunk's in order, the first lane of every
 // label with one LDS atomic that returns the count of the groups before; all rounds are

@@ -222,6 +222,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
       best = ob;
       bidx = oi;
     }
+    // a key with a NaN or infinite channel may have no similarity that is a number: a padded
+    // row has won then, and the key goes to the last cluster
+    bidx = bidx < c_count ? bidx : c_count - 1;
     const int64_t t = wave_tok0 + kb * 32 + col;
     if (half == (kb & 1) || NKB == 1) lane_label[kb / 2] = bidx;
     if (half == 0 && t < tok_count) {

@@ -212,6 +212,9 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
         best = ob;
         bidx = oi;
       }
+      // a key with a NaN or infinite channel may have no similarity that is a number: a padded
+      // row has won then, and the key goes to the last cluster
+      bidx = bidx < c_count ? bidx : c_count - 1;
       if (half == kb) lane_label = bidx;
       const int64_t t = wave_tok0 + kb * 32 + col;
       if (half == 0 && t < tok_count) {

@@ -188,3 +188,35 @@ def test_mfma_probe_runs():
     torch.cuda.synchronize()
     assert flops == 64 * 4 * 16 * 10 * 32768
     assert float(sink.abs().sum()) == 0.0
+
+
+@pytest.mark.parametrize("flags", [ck.CK_METRIC_COSINE, ck.CK_METRIC_L2,
+                                   ck.CK_METRIC_COSINE | ck.CK_KM_UNTIL_CONVERGED])
+@pytest.mark.parametrize("N,Hkv,C", [(500, 1, 16), (500, 2, 37), (8200, 8, 37), (8200, 8, 520),
+                                     (33000, 8, 520)])
+def test_non_finite_keys_stay_in_the_index(N, Hkv, C, flags):
+    """A key with NaN or infinite channels has no similarity that is a number.  On every
+    assignment kernel, at cluster counts that do not fill the last tile of 32, it still gets a
+    label of the range, and sizes, offsets and sorted_idx hold every token exactly once."""
+    c0, begin = 3, 5
+    g = torch.Generator(device=DEV).manual_seed(C)
+    K = torch.randn(1, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    init = torch.stack([torch.randperm(N - begin - 60, generator=g, device=DEV)[:C]
+                        for _ in range(Hkv)])[None].int() + begin
+    K[0, :, N - 1] = float("nan")                         # never an initial row
+    K[0, :, N - 2, 7] = float("inf")
+    K[0, :, N - 40, 9] = float("-inf")
+    K[0, :, N - 41] = float("inf")
+    sh = ck.Shape(1, Hkv, Hkv, N, c0 + C)
+    st = ck.ClusterState(sh, DEV, budget=64)
+    st.n_clusters = c0
+    st.sorted_idx.fill_(-1)
+    st.cluster(K, init, begin, N - begin, C, 3, flags=flags)
+    torch.cuda.synchronize()
+    assert int(st.labels[:, :, begin:].min()) >= c0 and int(st.labels.max()) < c0 + C
+    for h in range(Hkv):
+        lab = st.labels[0, h, begin:].cpu().numpy() - c0
+        sizes, offs, sidx = O.build_metadata(lab, C)
+        assert st.sizes[0, h, c0:].cpu().numpy().tolist() == sizes.tolist()
+        assert st.offsets[0, h, c0:].cpu().numpy().tolist() == offs.tolist()
+        assert st.sorted_idx[0, h, :N - begin].cpu().numpy().tolist() == (sidx + begin).tolist()
