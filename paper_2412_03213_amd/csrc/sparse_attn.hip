@@ -398,7 +398,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     // the channel block {8 col + j : col = 0..15} for each j: nothing changes lanes.  The
     // accumulator of block j has the heads 4 kg + i of channel 8 col + j.  A probability
     // enters as the sum of three bf16 numbers, which hold all 24 bits of it: the first two
-    // share one product (k = token and part), the third has one of its own.
+    // share one product (k = token and part), the third fills both places of another.
     // On the vector ALUs the same step was 32 fused multiply-adds per head, and the four
     // groups had to be added up at the end.
     float m_run = NEG_BIG, l_run = 0.f;                 // of head `col`, identical in its four lanes
@@ -459,25 +459,32 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
 #pragma unroll
           for (int i = 0; i < 4; ++i) acc[j][i] *= cr[i];
       }
-      // p = hi + mid + lo, each with at most 8 significant bits.  A part that is zero (or unused) is
-      // replaced by the smallest normal number: zero times an infinite value would be a NaN
-      // where the sum has to be infinite (and 2^-126 of a finite one is below its last bit).
+      // p = hi + mid + 2 lo exactly, each with at most 8 significant bits and none of them zero
+      // unless p is: zero times an infinite value would be a NaN where the sum has to be
+      // infinite.  So hi and mid are what a truncation leaves of the next smaller number, and lo
+      // fills both places of the second product.  Below 2^-94 the rest has bits under the
+      // smallest bf16 number, 2^-133, which then stands in for it: a token is off by at most
+      // 2^-131 times its value, and a probability that underflowed adds nothing.
+      // (Constants 2^-126 in place of zero parts would be 0.05 us faster per step, and wrong by
+      // up to 12 where a token of probability zero has a value near the largest bf16 number.)
       uint32_t hi[4], mid[4], lo[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        hi[i] = __float_as_uint(pw[i]);
+        const uint32_t bits = __float_as_uint(pw[i]), least = min(bits, 0x00010000u);
+        hi[i] = __builtin_elementwise_sub_sat(bits, 1u);
         const float r1 = pw[i] - __uint_as_float(hi[i] & 0xFFFF0000u);
-        mid[i] = max(__float_as_uint(r1), 0x00800000u);
-        const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xFFFF0000u);
-        lo[i] = max(__float_as_uint(r2), 0x00800000u);
+        mid[i] = max(__builtin_elementwise_sub_sat(__float_as_uint(r1), 1u), least);
+        const float r2 = r1 - __uint_as_float(mid[i] & 0xFFFF0000u);
+        lo[i] = max(__float_as_int(0.5f * r2), (int)least);   // r2 < 0 where mid stood in for less
       }
       constexpr uint32_t HIGH = 0x07060302u, LOW = 0x05040100u;   // halves of (second, first) word
+      const uint32_t lo01 = __builtin_amdgcn_perm(lo[1], lo[0], HIGH);
+      const uint32_t lo23 = __builtin_amdgcn_perm(lo[3], lo[2], HIGH);
       const uint4 pa = make_uint4(__builtin_amdgcn_perm(hi[1], hi[0], HIGH),
                                   __builtin_amdgcn_perm(hi[3], hi[2], HIGH),
                                   __builtin_amdgcn_perm(mid[1], mid[0], HIGH),
                                   __builtin_amdgcn_perm(mid[3], mid[2], HIGH));
-      const uint4 pb = make_uint4(__builtin_amdgcn_perm(lo[1], lo[0], HIGH),
-                                  __builtin_amdgcn_perm(lo[3], lo[2], HIGH), 0x00800080u, 0x00800080u);
+      const uint4 pb = make_uint4(lo01, lo23, lo01, lo23);
       uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w},
                            {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
                            {r.v[2].x, r.v[2].y, r.v[2].z, r.v[2].w},

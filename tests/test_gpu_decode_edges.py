@@ -120,3 +120,46 @@ def test_infinite_values_and_unattended_rows(S, G):
     clean[:, :, 5] = float("inf")
     clean[:, :, 77] = float("-inf")
     assert torch.equal(out, clean)
+
+
+@pytest.mark.parametrize("S", [1, 64])
+@pytest.mark.parametrize("G", [1, 4, 8])
+@pytest.mark.parametrize("drop", [60.0, 100.0, 115.0, 140.0])
+def test_unlikely_tokens_with_large_values(S, G, drop):
+    """A token whose probability is about 2^-drop beside ordinary ones: a large finite value adds
+    its product and nothing else (exactly nothing once the probability is zero), and an infinite
+    one makes its channel infinite as long as there is a probability."""
+    Hkv, N, n = 8, 300, 37
+    g = torch.Generator(device=DEV).manual_seed(G)
+    K = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    V = torch.randn(S, Hkv, N, 128, generator=g, device=DEV).bfloat16()
+    q = torch.zeros(S, Hkv * G, 128, device=DEV).bfloat16()
+    q[..., 0] = 8.0
+    K[..., 0] = 0.0
+    idx = (torch.rand(S, Hkv, N, generator=g, device=DEV).topk(40).indices).int()
+    cnt = torch.full((S, Hkv), n, dtype=torch.int32, device=DEV)
+    b, h = torch.meshgrid(torch.arange(S, device=DEV), torch.arange(Hkv, device=DEV), indexing="ij")
+    at = idx[:, :, 7].long()
+    K[b, h, at, 0] = -drop / (8.0 * 128 ** -0.5 * 1.4426950408889634)
+    V[b, h, at, :] = 0.0
+    sh = ck.Shape(S, Hkv * G, Hkv, N, 8)
+    out = torch.zeros(S, Hkv * G, 128, device=DEV).bfloat16()
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out)
+    clean = out.clone()
+    V[b, h, at, 5] = 3.3e38 if drop > 126 else 2.0 ** drop
+    V[b, h, at, 6] = -3.3e38 if drop > 126 else 3.0 * 2.0 ** drop
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out)
+    if drop > 126:
+        assert torch.equal(out, clean)
+        return
+    for s, kv in [(0, 0), (S - 1, Hkv - 1)]:
+        want = O.attention_over(np64(q[s, kv * G:(kv + 1) * G]), np64(K[s, kv]), np64(V[s, kv]),
+                                idx[s, kv, :n].cpu().numpy())
+        got = np64(out[s, kv * G:(kv + 1) * G])
+        assert np.abs(got - want).max() <= TOL * np.abs(want).max(), (s, kv)
+    V[b, h, at, 5] = float("inf")
+    V[b, h, at, 6] = float("-inf")
+    ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, out)
+    clean[:, :, 5] = float("inf")
+    clean[:, :, 6] = float("-inf")
+    assert torch.equal(out, clean)
