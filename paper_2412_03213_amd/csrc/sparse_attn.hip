@@ -42,8 +42,7 @@ constexpr int ATT_TOKENS = 16;             // tokens of a wavefront per step
 constexpr int ATT_MAX_CHUNK = 2048;        // positions one workgroup may own (rows held in LDS)
 constexpr int ATT_MAX_SPLITS = 1024;       // workgroups per head-problem
 constexpr float NEG_BIG = -1.0e30f;        // "no token yet": finite so that differences stay finite
-constexpr int ATT_TARGET_WGS = 256;        // one per CU on 256 CUs
-constexpr int ATT_MANY_HP = 512;           // head-problems from which on two rounds of workgroups exist
+constexpr int ATT_XCD_CUS = 32;            // compute units of one XCD
 constexpr int PART_STRIDE = D + 2;         // floats per (split, query head): max, sum, acc[128]
 constexpr int N_XCD = 8;                   // workgroup i of a launch runs on XCD i % 8
 constexpr unsigned long long TICKET_MAGIC = 0x434B7469636Bull;   // marks a ticket word as ours
@@ -730,44 +729,92 @@ __global__ __launch_bounds__(D / 2) void k_attn_merge(const float* __restrict__ 
   store_out(out + (int64_t)hq_lin * D + c2 + 1, o2.y);
 }
 
-// Wavefronts per workgroup.  Eight: every phase of the step -- scoring, selection, index
-// look-up, row stream -- is spread over the whole CU and fewer splits have to be merged
-// (eight / four wavefronts: 8 head-problems, B = 1024: 10.3 / 11.3 us; 8, 1600 clusters,
-// B = 2048: 13.8 / 16.0; 64, B = 2048: 20.5 / 21.4; 256, B = 2048: 53.7 / 57.5).
-// Four when there are so many head-problems that every CU runs several workgroups one after
-// another: two at a time, one selecting while the other streams (512 head-problems,
-// B = 2048: 118.5 / 115.8; 2048, B = 1024: 227 / 209).  fp32 (check mode) needs the registers.
-static int attn_waves(const Dims& dm) {
-  return dm.dtype == CK_F32 || dm.HP >= ATT_MANY_HP ? 4 : 8;
-}
-
-int attn_num_splits(const Dims& dm, int64_t max_total) {
-  // Aim for one workgroup per CU (measured best of 64..1024 workgroups per launch at 8 to
-  // 128 head-problems for the one-launch decode step: every split repeats the scoring and
-  // the selection, which costs more than the shorter token run saves; all forms of the step
-  // take the same rule: the split boundaries fix the order of the fp32 sums, and they must
-  // give the same bits).  Keep at least one full step of tokens per workgroup and never
-  // more positions than its LDS row table holds.
-  const int step = attn_waves(dm) * ATT_TOKENS;
-  const int64_t by_work = (max_total + step - 1) / step;
-  const int64_t by_fill = (ATT_TARGET_WGS + dm.HP - 1) / dm.HP;
-  int64_t n = by_work < by_fill ? by_work : by_fill;
-  if (n > 64) n = 64;
-  const int64_t need = (max_total + ATT_MAX_CHUNK - 1) / ATT_MAX_CHUNK;
+// How a call is spread over the chip.  All forms of the step take the same rule: the split
+// boundaries fix the order of the fp32 sums, and they must give the same bits.
+//
+// All splits of a head-problem run on one XCD, ceil(HP / 8) head-problems share it, and the
+// registers allow two wavefronts per SIMD: 32 workgroups of eight wavefronts or 64 of four are
+// resident on an XCD together.  One more and it runs its whole chain -- scoring, selection, rows
+// -- after the others are through, so a call takes as many splits as fit in ONE round:
+//  - eight wavefronts if they do: every phase is spread over the whole CU and fewer splits
+//    have to be merged;
+//  - four, two workgroups per CU, where the row table (2048 positions a workgroup) asks for
+//    more splits than eight allow;
+//  - eight again where that is not enough either: the contexts are long and the row stream is
+//    all that counts;
+//  - above 256 head-problems workgroups follow each other anyway: four wavefronts, one
+//    workgroup selecting while the other streams, and three splits up to 320, where whole
+//    head-problems would leave half of the places empty.
+// Microseconds of the fused step, eight / four wavefronts, each at its best number of splits of
+// one round, and [eight wavefronts with ceil(256 / HP) splits, which is a second round for a few]:
+//   HP            8           24           40           56           88           120
+//   B = 1024  10.5 / 10.7  11.0 / 11.6  12.7 / 13.4  14.1 / 14.7  18.5 / 19.1  20.4 / 20.9
+//                [10.5]       [11.1]       [13.3]       [18.4]       [23.1]       [29.2]
+//   B = 2048  11.7 / 12.0  13.4 / 14.0  16.6 / 17.6  19.1 / 19.7  26.5 / 27.2  31.2 / 31.6
+//                [11.7]       [14.3]       [19.7]       [22.0]       [32.0]       [42.1]
+//   HP           160          256          320          512         1024         2048
+//   B = 1024  23.7 / 24.4  30.5 / 31.9  49.4 / 43.8  62.6 / 57.4  122  / 109   231  / 205
+//   B = 2048  39.0 / 37.2  55.2 / 56.3  88.4 / 81.9  115  / 110   215  / 205
+//                [32.7, 49.2]     (two rounds and more of eight wavefronts from HP = 257 on)
+// Four wavefronts, one / two / three splits: HP = 264: 38.3 / 40.1 / 37.3 and 71.8 / 69.2 / 61.8,
+// 320: 41.5 / 42.6 / 41.7 and 77.5 / 76.0 / 73.5, 352: 43.4 / 45.9 / 46.1 and 82.3 / 82.5 / 87.5;
+// full attention over 2048 tokens at HP = 264: 57.9 / 54.8 / 48.8, 352: 65.2 / 68.1 / 69.4.
+// Full attention over 32864 tokens, eight / four: HP = 1: 21.8 / 24.9 (64 splits of eight, two rounds:
+// 28.1), 8: 27.0 / 27.0, 12: 42.4 / 39.7, 24: 80.7 / 78.7; 32: 104.5 / 113.2 and 40: 129.9 / 134.1 are
+// more than one round either way.
+struct AttnPlan {
+  int waves;        // wavefronts per workgroup
+  int max_splits;   // grows with the attended total: a workspace sized for more holds less
+  int chunk;        // positions of a split, whole steps of the workgroup
+  int n_split;      // splits that have positions (not monotone in the attended total)
+};
+static AttnPlan attn_plan(const Dims& dm, int64_t max_total) {
+  const int64_t per_xcd = (dm.HP + N_XCD - 1) / N_XCD;  // head-problems of the fullest XCD
+  int64_t need = (max_total + ATT_MAX_CHUNK - 1) / ATT_MAX_CHUNK;
+  if (need < 1) need = 1;
+  AttnPlan p;
+  int64_t n;
+  if (dm.dtype == CK_F32) {                             // check mode: one workgroup per CU
+    p.waves = 4;
+    n = (N_XCD * ATT_XCD_CUS + dm.HP - 1) / dm.HP;
+    if (n > 64) n = 64;
+  } else if (per_xcd * need <= ATT_XCD_CUS) {
+    p.waves = 8;
+    n = ATT_XCD_CUS / per_xcd;
+  } else if (per_xcd > ATT_XCD_CUS) {
+    p.waves = 4;
+    n = per_xcd <= ATT_XCD_CUS + 8 ? 3 : 1;
+  } else if (per_xcd * need <= 2 * ATT_XCD_CUS) {
+    p.waves = 4;
+    n = 2 * ATT_XCD_CUS / per_xcd;
+  } else {
+    p.waves = 8;
+    n = need;
+  }
+  // at least one full step of tokens per workgroup, no more positions than its row table holds
+  const int64_t step = p.waves * ATT_TOKENS, by_work = (max_total + step - 1) / step;
+  if (n > by_work) n = by_work;
   if (n < need) n = need;
-  if (n < 1) n = 1;
-  return (int)n;
+  p.max_splits = (int)n;
+  // whole steps, and no split without a position: it would score and select for nothing
+  int64_t chunk = ((max_total + n - 1) / n + step - 1) / step * step;
+  if (chunk < step) chunk = step;
+  n = (max_total + chunk - 1) / chunk;
+  p.chunk = (int)chunk;
+  p.n_split = n < 1 ? 1 : (int)n;
+  return p;
 }
 
-static size_t partial_bytes(const Dims& dm, int n_split) {
-  const size_t b = (size_t)dm.HP * n_split * dm.G * PART_STRIDE * sizeof(float);
-  return (b + 255) & ~(size_t)255;
+// The workspace: one 64-bit ticket word per head-problem, whose place must not depend on the
+// number of splits, then the split partials.
+static size_t ticket_bytes(const Dims& dm) {
+  return ((size_t)dm.HP * sizeof(unsigned long long) + 255) & ~(size_t)255;
 }
 
 size_t attn_workspace_bytes(const Dims& dm, int64_t max_total) {
-  // split partials, then one 64-bit ticket word per head-problem
-  const size_t t = ((size_t)dm.HP * sizeof(unsigned long long) + 255) & ~(size_t)255;
-  return partial_bytes(dm, attn_num_splits(dm, max_total)) + t;
+  const size_t b =
+      (size_t)dm.HP * attn_plan(dm, max_total).max_splits * dm.G * PART_STRIDE * sizeof(float);
+  return ticket_bytes(dm) + ((b + 255) & ~(size_t)255);
 }
 
 template <typename T, int MODE, int CMAX, int NW>
@@ -782,26 +829,22 @@ static void launch_attn_waves(int G, dim3 grid, const AttnArgs& a, hipStream_t s
 }
 
 template <typename T, int MODE, int CMAX>
-static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, bool two_pass,
-                                hipStream_t st) {
-  const int n_split = attn_num_splits(dm, max_total);
-  if (n_split > ATT_MAX_SPLITS) return hipErrorInvalidValue;
+static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, void* workspace,
+                                bool two_pass, hipStream_t st) {
+  const AttnPlan plan = attn_plan(dm, max_total);
+  const int n_split = plan.n_split;
+  if (n_split > ATT_MAX_SPLITS || plan.chunk > ATT_MAX_CHUNK) return hipErrorInvalidValue;
   if (dm.G != 1 && dm.G != 2 && dm.G != 4 && dm.G != 8) return hipErrorInvalidValue;
-  const int waves = attn_waves(dm), step = waves * ATT_TOKENS;
-  int chunk = (int)((max_total + n_split - 1) / n_split);
-  chunk = (chunk + step - 1) / step * step;
-  if (chunk < step) chunk = step;
-  if (chunk > ATT_MAX_CHUNK) return hipErrorInvalidValue;
-  a.chunk = chunk;
+  a.chunk = plan.chunk;
   a.n_split = n_split;
   a.two_pass = two_pass ? 1 : 0;
   a.HP = dm.HP;
-  a.tickets = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(a.part) +
-                                                    partial_bytes(dm, n_split));
+  a.tickets = reinterpret_cast<unsigned long long*>(workspace);
+  a.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + ticket_bytes(dm));
   const int hp_groups = (dm.HP + N_XCD - 1) / N_XCD;
   const dim3 grid((unsigned)hp_groups * N_XCD * n_split);
   if constexpr (std::is_same<T, bf16>::value) {
-    if (waves == 8)
+    if (plan.waves == 8)
       launch_attn_waves<T, MODE, CMAX, 8>(dm.G, grid, a, st);
     else
       launch_attn_waves<T, MODE, CMAX, 4>(dm.G, grid, a, st);
@@ -816,13 +859,12 @@ static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, b
 
 static AttnArgs common_args(const Dims& dm, const void* q, const void* K, const void* V,
                             int idx_stride, int max_tokens, int64_t n_sink, int64_t recent_begin,
-                            int64_t recent_end, float softmax_scale, void* out, void* workspace) {
+                            int64_t recent_end, float softmax_scale, void* out) {
   AttnArgs a = {};
   a.q = q;
   a.K = K;
   a.V = V;
   a.out = out;
-  a.part = reinterpret_cast<float*>(workspace);
   a.idx_stride = idx_stride;
   a.max_tokens = max_tokens;
   a.Hq = dm.Hq;
@@ -843,12 +885,12 @@ hipError_t launch_sparse_attn(const Dims& dm, const void* q, const void* K, cons
                               bool two_pass, hipStream_t st) {
   const int n_recent = (int)(recent_end > recent_begin ? recent_end - recent_begin : 0);
   AttnArgs a = common_args(dm, q, K, V, idx_stride, (int)(max_total - n_sink - n_recent), n_sink,
-                           recent_begin, recent_end, softmax_scale, out, workspace);
+                           recent_begin, recent_end, softmax_scale, out);
   a.token_idx = token_idx;
   a.n_tokens = n_tokens;
   if (dm.dtype == CK_BF16)
-    return launch_attn_t<bf16, ATT_PLAIN, SELP_SMALL>(dm, a, max_total, two_pass, st);
-  return launch_attn_t<float, ATT_PLAIN, SELP_SMALL>(dm, a, max_total, two_pass, st);
+    return launch_attn_t<bf16, ATT_PLAIN, SELP_SMALL>(dm, a, max_total, workspace, two_pass, st);
+  return launch_attn_t<float, ATT_PLAIN, SELP_SMALL>(dm, a, max_total, workspace, two_pass, st);
 }
 
 hipError_t launch_decode_fused(const Dims& dm, const void* q, const void* K, const void* V,
@@ -860,7 +902,7 @@ hipError_t launch_decode_fused(const Dims& dm, const void* q, const void* K, con
                                int32_t* n_sel_tokens, int32_t* token_idx, int idx_stride,
                                int32_t* n_tokens, void* out, void* workspace, hipStream_t st) {
   AttnArgs a = common_args(dm, q, K, V, idx_stride, budget, n_sink, recent_begin, recent_end,
-                           softmax_scale, out, workspace);
+                           softmax_scale, out);
   a.centroids = centroids;
   a.scores = scores;
   a.sizes = sizes;
@@ -876,14 +918,14 @@ hipError_t launch_decode_fused(const Dims& dm, const void* q, const void* K, con
   a.trim = (int)(flags & CK_SEL_TRIM_LAST);
   const int64_t max_total = (int64_t)budget + n_sink + a.n_recent;
   if (dm.dtype == CK_BF16 && n_clusters <= SELP_SMALL)  // one launch for the whole step
-    return launch_attn_t<bf16, ATT_FUSED_SCORE, SELP_SMALL>(dm, a, max_total, false, st);
+    return launch_attn_t<bf16, ATT_FUSED_SCORE, SELP_SMALL>(dm, a, max_total, workspace, false, st);
   const hipError_t e = launch_score(dm, q, centroids, n_clusters, scores, st);
   if (e != hipSuccess) return e;
   if (dm.dtype == CK_BF16)
-    return launch_attn_t<bf16, ATT_FUSED, CK_MAX_CLUSTERS>(dm, a, max_total, false, st);
+    return launch_attn_t<bf16, ATT_FUSED, CK_MAX_CLUSTERS>(dm, a, max_total, workspace, false, st);
   if (n_clusters <= SELP_SMALL)
-    return launch_attn_t<float, ATT_FUSED, SELP_SMALL>(dm, a, max_total, false, st);
-  return launch_attn_t<float, ATT_FUSED, CK_MAX_CLUSTERS>(dm, a, max_total, false, st);
+    return launch_attn_t<float, ATT_FUSED, SELP_SMALL>(dm, a, max_total, workspace, false, st);
+  return launch_attn_t<float, ATT_FUSED, CK_MAX_CLUSTERS>(dm, a, max_total, workspace, false, st);
 }
 
 // ---- library-owned scratch for callers that cannot allocate ----

@@ -56,6 +56,31 @@ def test_strerror_and_workspace_sizes():
     assert ck.ck_workspace_bytes(ck.Shape(1, 32, 8, 32768, 400, d=64), 0, 100, 4) == 0
 
 
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_attention_workspace_is_one_round_of_workgroups(G):
+    """The workspace shows the number of splits: every XCD (32 compute units, one workgroup of
+    eight wavefronts or two of four each) runs its share of the head-problems in one round where
+    the 2048 positions of a workgroup allow it (up to 256 head-problems), and a workspace for a larger attended total
+    holds every smaller one (its splits may be more)."""
+    for HP in [*range(1, 140), 160, 200, 256, 257, 320, 512, 600, 2048]:
+        sh = ck.Shape(1, HP * G, HP, 1 << 22, 8)
+        per_xcd, last = -(-HP // 8), 0
+        for total in [1, 64, 65, 127, 128, 129, 500, 1000, 1024, 1025, 2047, 2048, 2049, 2300, 4096,
+                      8192, 32864, 131072, 1 << 20]:
+            b = ck.ck_workspace_bytes(sh, binding.CK_WS_SPARSE_ATTN, total)
+            splits = (b - (HP * 8 + 255) // 256 * 256) // (HP * G * 130 * 4)
+            need = -(-total // 2048)
+            room = 32 if per_xcd * need <= 32 else 64
+            if 32 < per_xcd <= 40:                       # taken in turns, in smaller pieces
+                room = 3 * per_xcd
+            assert need <= splits <= max(need, room // per_xcd), (HP, total)
+            assert splits <= max(1, -(-total // 64))
+            assert b >= last, (HP, total)
+            last = b
+            if per_xcd * need <= 64:                     # fits the library's own scratch buffer
+                assert b <= 4 << 20
+
+
 A = 0x1000  # a 16-byte aligned fake device address: validation never dereferences it
 
 

@@ -1,6 +1,6 @@
 """The decode-step kernel at the edges of its tiles and of its dispatch: attended counts around
 the 16 tokens of a wavefront step and the step of a workgroup, every group size, both
-workgroup widths (they change at 512 head-problems), and selections whose candidates just fit
+workgroup widths (8 head-problems: eight wavefronts, 512: four), and selections whose candidates just fit
 or just exceed one wavefront."""
 import numpy as np
 import pytest

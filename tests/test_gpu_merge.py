@@ -66,6 +66,36 @@ def test_single_launch_merge_equals_two_pass(S, Hq, Hkv, N, n_max, dtype):
         assert np.abs(got - want).max() <= tol * max(np.abs(want).max(), 1e-30)
 
 
+@pytest.mark.parametrize("S,Hkv", [(3, 1), (3, 8), (5, 8), (11, 8), (20, 8), (33, 8), (40, 8),
+                                   (65, 8)])
+def test_splits_between_the_powers_of_two(S, Hkv):
+    """Head-problem counts that do not divide the chip, attended totals around the steps of a
+    workgroup and the 2048 positions it may own, one workspace for all of them (a larger total
+    can have fewer splits): against the two-pass form and the oracle."""
+    G, N, n_sink, n_rec = 2, 2400, 16, 200
+    g, K, V, idx = make(S, Hkv * G, Hkv, N, 2100, seed=S)
+    sh = ck.Shape(S, Hkv * G, Hkv, N, 8)
+    ws = torch.empty(ck.ck_workspace_bytes(sh, 1, 2100 + n_sink + n_rec), dtype=torch.uint8,
+                     device=DEV).random_(0, 256)
+    ws2 = torch.empty_like(ws)
+    a = torch.zeros(S, Hkv * G, 128, dtype=torch.bfloat16, device=DEV)
+    b = torch.zeros_like(a)
+    for n in [700, 2100, 1, 384, 808, 809, 1300, 1832, 1833, 2100, 1024, 640, 128]:
+        q = (2 * torch.randn(S, Hkv * G, 128, generator=g, device=DEV)).bfloat16()
+        cnt = torch.full((S, Hkv), n, dtype=torch.int32, device=DEV)
+        cnt[-1, 0] = n // 3
+        kw = dict(n_sink=n_sink, recent_begin=N - n_rec, recent_end=N)
+        ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, a.fill_(float("nan")), workspace=ws, **kw)
+        ck.ck_sparse_decode_attn(sh, q, K, V, idx, cnt, n, b, workspace=ws2, two_pass=True, **kw)
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), n
+        for s, h in [(0, 0), (S - 1, 0), (S - 1, Hkv - 1)]:
+            rows = np.concatenate([np.arange(n_sink), idx[s, h, :int(cnt[s, h])].cpu().numpy(),
+                                   np.arange(N - n_rec, N)])
+            want = O.attention_over(np64(q[s, h * G:(h + 1) * G]), np64(K[s, h]), np64(V[s, h]), rows)
+            got = np64(a[s, h * G:(h + 1) * G])
+            assert np.abs(got - want).max() <= 2.0 ** -7 * np.abs(want).max(), (n, s, h)
+
+
 def test_decode_step_graph_replays_match_eager():
     """ck_decode_step captured in a HIP graph: the launch keeps its ticket epoch across
     replays, so the last workgroup must leave the tickets ready for the next replay.
