@@ -258,6 +258,9 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
   // the iterations need the sums of the clusters, not the sorted index: the update reads the
   // chunk index of the assignment, and the metadata is built once, after the last iteration
   const bool chunked = ck::update_chunks_fits(dm, tok_count);
+  // ... or, in ranges of more chunks than it can walk, only the counts for the counting sort
+  ck::ChunkIndex chunks = ws.chunks;
+  if (!chunked) chunks.list = nullptr;
   for (int it = 0; it < max_iter; ++it) {
     ck::KmCtl ctl;
     ctl.bias = bias;
@@ -270,7 +273,7 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
       gate = it >= 1 ? ctl.changed : nullptr;
     }
     e = ck::launch_assign(dm, Kb, tok_begin, tok_count, ws.mu_hat, c_begin, c_count, labels,
-                          nullptr, ws.chunks, ctl, st);
+                          nullptr, chunks, ctl, st);
     if (e != hipSuccess) return hip_result(e, "assignment launch");
     if (chunked) {
       e = ck::launch_update_chunks(dm, Kb, ws.chunks, tok_begin, tok_count, c_begin, c_count,

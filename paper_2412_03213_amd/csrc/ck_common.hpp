@@ -194,7 +194,8 @@ hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin,
 hipError_t launch_iters_done(const int32_t* changed, int max_iter, int HP, int32_t* iters_done,
                              hipStream_t st);
 int assign_tile_tokens(const Dims& dm, int64_t tok_count);
-// chunks (members nullable): index of every chunk of assign_tile_tokens() tokens by label
+// chunks (members nullable): index of every chunk of assign_tile_tokens() tokens by label;
+// without list only the counts of seg
 hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,
                          const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
                          float* best_sim, const ChunkIndex& chunks, const KmCtl& ctl,

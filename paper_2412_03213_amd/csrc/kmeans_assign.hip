@@ -207,6 +207,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
   constexpr int CHUNK = 4 * NKB * 32;                   // tokens of 4 wavefronts = one chunk
   uint32_t* tok = reinterpret_cast<uint32_t*>(&lds[0][0]);   // pack_token words
   int lane_label[(NKB + 1) / 2];                        // labels of tokens 64 i + lane of this wavefront
+  const bool count_only = chunks.seg && !chunks.list;   // [chunk][cluster] counts in place of the words
+  if (count_only) {
+    static_assert(WAVES / 4 * CK_MAX_CLUSTERS * 4 <= sizeof(lds), "counts");
+    for (int c = tid; c < WAVES / 4 * c_count; c += THREADS) tok[c] = 0;
+    __syncthreads();
+  }
   int diff = 0;
 #pragma unroll
   for (int kb = 0; kb < NKB; ++kb) {
@@ -232,13 +238,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
       if (ctl.changed) diff += (ctl.first || labels[o] != c_begin + bidx) ? 1 : 0;
       labels[o] = c_begin + bidx;
       if (best_sim) best_sim[o] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
+      if (count_only) atomicAdd(&tok[(wave >> 2) * c_count + bidx], 1u);
     }
   }
   if (ctl.changed) {
     const int wsum = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
     if (lane == 0 && wsum) atomicAdd(&s_changed, wsum);
   }
-  if (chunks.seg) {
+  if (chunks.list) {
     if constexpr (NKB == 1) {
       // 32 tokens per wavefront: the even one of a pair ranks both halves of the group
       uint32_t* raw = tok + WAVES * 32;
@@ -256,7 +263,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES_PER_SIMD) void k_assign(
   }
   if (chunks.seg || ctl.changed) __syncthreads();
   if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
-  if (chunks.seg) {
+  if (count_only) {
+    for (int e = tid; e < WAVES / 4 * c_count; e += THREADS) {
+      const int64_t ch = (int64_t)blockIdx.x * (WAVES / 4) + e / c_count;
+      if (ch < n_chunks_hp)
+        chunks.seg[((int64_t)hp * n_chunks_hp + ch) * seg_stride(c_count) + e % c_count] = tok[e] << 16;
+    }
+  } else if (chunks.seg) {
     // one wavefront per chunk
     constexpr int CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * 4, SCRATCH = CNT + CHUNK * 2;
     static_assert(WAVES / 4 * (CHUNK * 4 + SCRATCH) <= sizeof(lds), "chunk sort scratch");

@@ -45,7 +45,8 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   constexpr int NKB = ST_NKB, THREADS = ST_WAVES * 64;
   __shared__ __attribute__((aligned(16))) bf16 table[ST_MAX_TILES * 32 * LDS_ROW];
   __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? ST_MAX_TILES * 32 : 4];
-  __shared__ uint32_t tok[ST_MAX_BLOCKS * ST_CHUNK];     // pack_token words of this workgroup's tokens
+  __shared__ uint32_t tok[ST_MAX_BLOCKS * ST_CHUNK];     // pack_token words of this workgroup's tokens, or
+                                                         // [chunk][cluster] counts (clusters <= ST_CHUNK)
   __shared__ int s_changed, s_next_task;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -225,10 +226,13 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
       }
     }
     // the ranking inside the group runs here, under the other wavefront's matrix work
-    if (chunks.seg)
+    if (chunks.list)
       tok[b * (NKB * 32) + lane] = pack_token(lane_label, wave_tok0 + lane < tok_count, label_bits);
+    else if (chunks.seg && wave_tok0 + lane < tok_count)   // counts only
+      atomicAdd(&tok[(b / ST_WAVES) * c_count + lane_label], 1u);
   };
   static_assert(NKB == 2, "a task is one group of 64 tokens");
+  static_assert(ST_MAX_TILES * 32 <= ST_CHUNK, "counts take the place of the token words");
 
   // A workgroup's range is cut into tasks of 64 tokens (8 per 512-token chunk).  Every
   // wavefront starts with the task of its own number and then takes the next free one
@@ -261,7 +265,13 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   }
   if (chunks.seg || ctl.changed) __syncthreads();
   if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
-  if (chunks.seg) {
+  if (chunks.seg && !chunks.list) {
+    for (int e = tid; e < blocks * c_count; e += THREADS) {
+      const int64_t ch = (int64_t)blockIdx.x * blocks + e / c_count;
+      if (ch < n_chunks)
+        chunks.seg[((int64_t)hp * n_chunks + ch) * seg_stride(c_count) + e % c_count] = tok[e] << 16;
+    }
+  } else if (chunks.seg) {
     // one wavefront per 512-token chunk; the centroid table's LDS is free by now
     const int64_t ch = (int64_t)blockIdx.x * blocks + wave;
     if (wave < blocks && ch < n_chunks) {

@@ -19,7 +19,9 @@ DEV = "cuda:0"
     (1, 8, 8200, 512, 0, 0),         # largest LDS-resident table
     (1, 1, 65535, 60, 0, 0),         # chunks of 128: exactly as many as the index holds
     (1, 1, 262144, 64, 0, 0),        # chunks of 512: exactly as many
-    (1, 1, 262145, 64, 0, 0),        # one chunk more: the sorted-list form
+    (1, 1, 262145, 64, 0, 0),        # one chunk more: counts only, and the sorted-list form
+    (1, 2, 262700, 512, 7, 3),       # the same with the largest LDS-resident table
+    (1, 1, 263681, 1100, 0, 0),      # and with the table streamed in chunks
     (1, 2, 2300, 2048, 0, 0),        # most clusters, many of them of one member or empty
 ])
 def test_cluster_keys_equals_the_exported_steps(S, Hkv, N, C, begin, c_begin):
