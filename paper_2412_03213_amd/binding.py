@@ -1,5 +1,6 @@
 """Binding of libclusterkv.so: argument marshalling only, through ctypes and, for the call
-that is made once per layer and generated token, through the native _ckhost module.
+that is made once per layer and generated token, through the native _ckhost module where it
+has been built for this interpreter.
 
 Functions carry the names of the C entry points (include/clusterkv.h) and take
 torch tensors in the layouts documented there.  Work is enqueued on torch's
@@ -21,7 +22,6 @@ CK_WS_CLUSTER_KEYS, CK_WS_SPARSE_ATTN, CK_WS_OBJECTIVE = 0, 1, 2
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libclusterkv.so")
-HOST_PATH = os.path.join(_PKG, "_ckhost.so")
 
 EXPORTS = ("ck_version", "ck_strerror", "ck_last_error_detail", "ck_workspace_bytes",
            "ck_cluster_keys", "ck_cluster_keys_opt", "ck_kmeans_assign", "ck_kmeans_objective", "ck_build_metadata", "ck_kmeans_update",
@@ -71,15 +71,25 @@ class Shape:
 _lib = None
 
 
+def _host_decode_step():
+    """Marshals plain arguments of ck_decode_step natively and returns the status code, or None
+    for any others.  Without a module for this interpreter every call is of the latter kind:
+    the library is the same, the call takes 4 us longer on the host."""
+    try:
+        from . import _ckhost
+    except ImportError:
+        return lambda *args: None
+    return _ckhost.decode_step
+
+
 def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     """Load the in-tree library; build it first only when no built library exists."""
     global _lib
     if _lib is not None:
         return _lib
-    if not (os.path.exists(LIB_PATH) and os.path.exists(HOST_PATH)):
+    if not os.path.exists(LIB_PATH):
         if not build_if_missing:
-            missing = HOST_PATH if os.path.exists(LIB_PATH) else LIB_PATH
-            raise RuntimeError(f"{missing} is missing: run python -m paper_2412_03213_amd.build")
+            raise RuntimeError(f"{LIB_PATH} is missing: run python -m paper_2412_03213_amd.build")
         from .build import build
         build(verbose=False)
     lib = ctypes.CDLL(LIB_PATH)
@@ -143,8 +153,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
                                           P, P, P, P, SZ, P]
     lib.ck_probe_mfma_bf16.restype = ctypes.c_int
     lib.ck_probe_mfma_bf16.argtypes = [I32, I32, P, P, P, ctypes.POINTER(ctypes.c_double), P]
-    from . import _ckhost
-    lib.host_decode_step = _ckhost.decode_step
+    lib.host_decode_step = _host_decode_step()
     lib.decode_step_entry = ctypes.cast(lib.ck_decode_step, P).value
     _lib = lib
     return lib
@@ -167,9 +176,15 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# torch's own accelerator interfaces ask for the stream this way, without making an object of it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(t) -> int:
     if isinstance(t, torch.Tensor) and t.is_cuda:
-        return torch._C._cuda_getCurrentRawStream(t.get_device())
+        if _raw_stream is None:
+            return torch.cuda.current_stream(t.device).cuda_stream
+        return _raw_stream(t.get_device())
     return 0
 
 

@@ -1,5 +1,5 @@
-"""Build libclusterkv.so (gfx950) in-tree with hipcc, and _ckhost.so (the native form of the
-binding's hot call) with the host compiler.
+"""Build libclusterkv.so (gfx950) in-tree with hipcc, and the _ckhost module (the native form of
+the binding's hot call, for the interpreter that runs this) with the host compiler.
 
     python -m paper_2412_03213_amd.build [--force]
 
@@ -20,7 +20,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJ_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libclusterkv.so")
 HOST_SRC = os.path.join(CSRC, "host_call.cpp")
-HOST_LIB = os.path.join(PKG, "_ckhost.so")
+HOST_LIB = os.path.join(PKG, "_ckhost" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["api.hip", "kmeans_assign.hip", "kmeans_assign_stream.hip", "kmeans_update.hip", "kmeans_small.hip", "select_gather.hip",
            "sparse_attn.hip", "evaluate.hip", "cluster_cache.hip",
@@ -60,7 +60,7 @@ def build(force: bool = False, verbose: bool = True) -> str:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed:\n{r.stdout}\n{r.stderr}")
+            raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n{r.stdout}\n{r.stderr}")
         noise = "is not a recognized feature"
         err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
         if verbose and err.strip():
@@ -72,8 +72,15 @@ def build(force: bool = False, verbose: bool = True) -> str:
         run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     header = os.path.join(INCLUDE, "clusterkv.h")
     if force or _newer(HOST_SRC, HOST_LIB) or _newer(header, HOST_LIB):
-        run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE,
-             "-I", sysconfig.get_paths()["include"], HOST_SRC, "-o", HOST_LIB])
+        # the binding does without it: a machine without a host compiler or Python's headers
+        # still gets the library
+        if os.path.exists(HOST_LIB):
+            os.remove(HOST_LIB)
+        try:
+            run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE,
+                 "-I", sysconfig.get_paths()["include"], HOST_SRC, "-o", HOST_LIB])
+        except (RuntimeError, OSError) as e:
+            print(f"_ckhost is not built, decode_step is called through ctypes: {e}", flush=True)
     return LIB
 
 

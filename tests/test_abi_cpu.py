@@ -4,6 +4,7 @@ anything (so these calls are safe without a device)."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 import torch
@@ -264,6 +265,37 @@ def test_missing_library_is_an_error(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(RuntimeError):
         binding.load_library(build_if_missing=False)
+
+
+def _without_host_module(monkeypatch):
+    monkeypatch.setitem(sys.modules, "paper_2412_03213_amd._ckhost", None)
+    monkeypatch.delattr(ck, "_ckhost", raising=False)
+    monkeypatch.setattr(binding, "_lib", None)
+
+
+def test_library_is_enough_without_the_host_module(monkeypatch):
+    """No module for this interpreter: the library loads, and calls go through ctypes."""
+    _without_host_module(monkeypatch)
+    lib = ck.load_library(build_if_missing=False)
+    assert lib.host_decode_step(1, 2, 3) is None
+    z = torch.zeros(16)
+    with pytest.raises(ck.ClusterKVError):                        # S = 0
+        ck.ck_decode_step(ck.Shape(0, 2, 2, 16, 4), z, z, z, z, z, z, z, 4, 8, 0, z, z, z, z, z, z,
+                          z, workspace=z)
+
+
+def test_build_goes_on_without_a_host_compiler(monkeypatch, tmp_path, capsys):
+    from paper_2412_03213_amd import build as b
+    monkeypatch.setattr(b, "SOURCES", [])                         # the library stands
+    monkeypatch.setattr(b, "HOST_LIB", str(tmp_path / "_ckhost.so"))
+    monkeypatch.setattr(b, "CXX", "no-such-compiler")
+    assert b.build(verbose=False) == b.LIB
+    assert "ctypes" in capsys.readouterr().out and not os.path.exists(b.HOST_LIB)
+
+
+def test_stream_without_the_raw_form(monkeypatch):
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream(torch.zeros(1)) == 0
 
 
 @pytest.mark.parametrize("change, error", [
