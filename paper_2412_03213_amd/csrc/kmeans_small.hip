@@ -247,6 +247,13 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
         m1 = s1 * inv;
       }
     }
+    // one cluster: further iterations would find the same labels, sums and mean, and the matrix
+    // form does the work of four clusters for it (16 head-problems x 320 tokens x 10 iterations:
+    // 39.7 us on the vector ALUs, 55 with all iterations, 10.5)
+    if (C == 1 && a.max_iter > 1) {
+      n_done = a.converge ? 2 : a.max_iter;
+      break;
+    }
   }
   if (lane < 4) {
 #pragma unroll

@@ -225,3 +225,23 @@ def test_cap_reached_without_convergence_reports_the_cap():
     st_fix, _ = run_gpu(w, cfg, init, 2, 0)
     assert iters.cpu().numpy().tolist() == [[2, 2]]
     assert torch.equal(st.labels, st_fix.labels) and torch.equal(st.centroids, st_fix.centroids)
+
+
+@pytest.mark.parametrize("n", [1, 3, 100, 384])
+@pytest.mark.parametrize("max_iter,converge,ran", [(1, 0, 1), (10, 0, 10), (1, 1, 1), (2, 1, 2), (9, 1, 2)])
+def test_one_cluster(n, max_iter, converge, ran):
+    """A single cluster is its range's mean after any number of iterations."""
+    N, c0 = n + 5, 2
+    g = torch.Generator(device=DEV).manual_seed(n)
+    K = torch.randn(2, 2, N, 128, generator=g, device=DEV).bfloat16()
+    st = ck.ClusterState(ck.Shape(2, 2, 2, N, c0 + 1), DEV, budget=64)
+    st.n_clusters = c0
+    iters = torch.zeros(2, 2, dtype=torch.int32, device=DEV)
+    st.cluster(K, torch.full((2, 2, 1), 5, dtype=torch.int32, device=DEV), 5, n, 1, max_iter,
+               ck.CK_KM_UNTIL_CONVERGED if converge else 0, iters)
+    assert (iters == ran).all() and (st.labels[:, :, 5:] == c0).all()
+    assert (st.sizes[:, :, c0] == n).all() and (st.offsets[:, :, c0 + 1] == n).all()
+    assert torch.equal(st.sorted_idx[:, :, :n], torch.arange(5, N, device=DEV).int().expand(2, 2, n))
+    want = K[:, :, 5:].double().mean(2)
+    got = st.centroids[:, :, c0].double()
+    assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all()
