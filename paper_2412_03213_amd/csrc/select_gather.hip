@@ -141,7 +141,7 @@ __global__ __launch_bounds__(RANK_THREADS) void k_rank(
   if (r.m <= WAVE) {
     if (tid < n_sel) sel_clusters[(int64_t)hp * C_cap + tid] = r.id;
   } else {
-    select_prefix_regs<CMAX, NT>(L, sc, sz, of, false, n_clusters, budget, trim);
+    select_many<CMAX, NT>(L, Q, sc, sz, of, r.m, r.last_bin, n_clusters, budget, trim);
     n_sel = L.n_sel;
     n_tok = L.n_tok;
     for (int j = tid; j < n_sel; j += NT) sel_clusters[(int64_t)hp * C_cap + j] = L.ord[j];

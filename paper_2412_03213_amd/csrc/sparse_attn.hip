@@ -293,7 +293,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     }
     sel = quick_select<NT, ITEMS>(Q, sc, sz, of, a.n_clusters, a.budget, a.trim);
     if (sel.m > WAVE) {                                 // uniform: more candidates than lanes
-      select_prefix_regs<CMAX, NT>(L, sc, sz, of, true, a.n_clusters, a.budget, a.trim);
+      select_many<CMAX, NT>(L, Q, sc, sz, of, sel.m, sel.last_bin, a.n_clusters, a.budget, a.trim);
       sel.n_sel = L.n_sel;
       sel.n_tok = L.n_tok;
     }
