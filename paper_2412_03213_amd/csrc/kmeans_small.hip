@@ -1,8 +1,8 @@
 // Whole K-means of a small token range in ONE kernel (paper Section III-B, decode
 // stage: every m generated tokens are clustered among themselves into a handful of
 // new clusters).  At m = 320 tokens and 4 clusters an iteration is ~0.3 MFLOP per
-// head-problem, so the four-kernels-per-iteration pipeline of the prefill path spends
-// its time on launches; here one workgroup per head-problem keeps the keys in registers and
+// head-problem, so the prefill path with its two launches per iteration would spend
+// its time on them; here one workgroup per head-problem keeps the keys in registers and
 // runs init, all iterations (assignment, update), the metadata and the stores itself.
 // Same arithmetic rules as the large path: bf16-rounded table rows compared in fp32,
 // ties to the lower id, fp32 sums in a fixed order, means of raw keys, an empty cluster
@@ -36,17 +36,20 @@ struct SmallArgs {
 // the keys).  The wavefront of a cluster adds up that cluster's partial sums, keeps its mean in
 // registers and makes the next table row from it, so an iteration has two barriers.
 // 128 head-problems x 320 tokens x 4 clusters, 10 iterations: 85.3 -> 56.6 us, same bits.
+// MAXC = 2 is a form of its own: rows 2 and 3 of the products are idle there, and with the lane
+// exchanges of four clusters it was slower than the vector ALUs (352 tokens x 2 clusters: 55.6 us on
+// the vector ALUs, 62.8 as four clusters, 52.9 now; 100 tokens: 38.6, 33.1, 28.3).
 template <int MAXC, int SM_THREADS>
 __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) {
-  constexpr int WAVES = SM_THREADS / WAVE, SETS = MAXC / 4;
+  constexpr int WAVES = SM_THREADS / WAVE, SETS = (MAXC + 3) / 4, ROWS = 4 * SETS;
   constexpr int KEYS = WAVES * 4;                       // keys per round, four per wavefront
   constexpr int ROUNDS = (KM_SMALL_MAX_TOKENS + KEYS - 1) / KEYS;
-  static_assert(MAXC % 4 == 0 && MAXC <= WAVES && KM_SMALL_MAX_TOKENS <= SM_THREADS, "mapping");
-  __shared__ __attribute__((aligned(16))) float table[MAXC][D];
+  static_assert((MAXC == 2 || MAXC % 4 == 0) && MAXC <= WAVES && KM_SMALL_MAX_TOKENS <= SM_THREADS, "mapping");
+  __shared__ __attribute__((aligned(16))) float table[ROWS][D];
   __shared__ __attribute__((aligned(16))) float part[WAVES][MAXC][D];
   __shared__ int cnt[WAVES][MAXC];
   __shared__ int wave_cnt[WAVES][MAXC];
-  __shared__ float bias[MAXC];
+  __shared__ float bias[ROWS];
   __shared__ int lab[KM_SMALL_MAX_TOKENS];
   __shared__ int s_changed[2];
 
@@ -83,10 +86,11 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
     m0 = lo_bf16(w);
     m1 = hi_bf16(w);
   }
-  for (int e = C * D + tid; e < MAXC * D; e += SM_THREADS) table[e / D][e % D] = 0.f;
+  for (int e = C * D + tid; e < ROWS * D; e += SM_THREADS) table[e / D][e % D] = 0.f;
 
-  // After the lane swaps row r of a register holds cluster 4 s + {0, 2, 1, 3}[r]
-  const int rowc = ((row & 1) << 1) | (row >> 1);
+  // After the lane swaps row r of a register holds cluster 4 s + {0, 2, 1, 3}[r], or of two
+  // clusters {0, 0, 1, 1}[r]
+  const int rowc = MAXC == 2 ? row >> 1 : ((row & 1) << 1) | (row >> 1);
   uint32_t labels[(ROUNDS + 7) / 8];                    // 4 bits per round: label of key `l4`
 #pragma unroll
   for (int i = 0; i < (ROUNDS + 7) / 8; ++i) labels[i] = 0xFFFFFFFFu;
@@ -139,7 +143,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
     uint32_t moved = 0;
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
-      if (r * KEYS < n_tok) {                           // uniform
+      // two clusters: wavefronts without keys in a round sit it out (321 tokens 55.3 -> 51.4 us, but
+      // 320 tokens 49.0 -> 50.7, and 56.0 -> 57.6 with four clusters, where a round in full is the rule)
+      if (r * KEYS + (MAXC == 2 ? wave * 4 : 0) < n_tok) {   // wave-uniform
         // unpacked here and not once before the iterations: there are no registers for that
         asm volatile("" : "+v"(dk[r].x), "+v"(dk[r].y), "+v"(dk[r].z), "+v"(dk[r].w));
         asm volatile("" : "+v"(uk[r].x), "+v"(uk[r].y), "+v"(uk[r].z), "+v"(uk[r].w));
@@ -155,9 +161,12 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
           // sixteen channel groups: lane bits 5, 4 (two clusters share a register from there
           // on), 3, 2
           const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[0]), __float_as_uint(d[1]), false, false);
-          const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2]), __float_as_uint(d[3]), false, false);
           const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-          const float c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+          float c23 = c01;
+          if constexpr (MAXC > 2) {
+            const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2]), __float_as_uint(d[3]), false, false);
+            c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+          }
           const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
           float v = __uint_as_float(w[0]) + __uint_as_float(w[1]);
           v += dpp_f<DPP_ROR8>(v);
@@ -168,16 +177,20 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
           // best of the four, the lower cluster where they are equal: rows hold 0, 2, 1, 3
           const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
           const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
-          const float xv = x1 > x0 ? x1 : x0;
-          const unsigned xc = (row & 1) * 2 + (x1 > x0 ? 1 : 0);
-          const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(xv), __float_as_uint(xv), false, false);
-          const auto yc = __builtin_amdgcn_permlane16_swap(xc, xc, false, false);
-          const float y0 = __uint_as_float(y[0]), y1 = __uint_as_float(y[1]);
-          const float yv = y1 > y0 ? y1 : y0;
-          const int c = 4 * s + (int)(y1 > y0 ? yc[1] : yc[0]);
-          if (s == 0 || yv > best) {
-            best = yv;
-            bc = c;
+          if constexpr (MAXC == 2) {
+            bc = x1 > x0 ? 1 : 0;
+          } else {
+            const float xv = x1 > x0 ? x1 : x0;
+            const unsigned xc = (row & 1) * 2 + (x1 > x0 ? 1 : 0);
+            const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(xv), __float_as_uint(xv), false, false);
+            const auto yc = __builtin_amdgcn_permlane16_swap(xc, xc, false, false);
+            const float y0 = __uint_as_float(y[0]), y1 = __uint_as_float(y[1]);
+            const float yv = y1 > y0 ? y1 : y0;
+            const int c = 4 * s + (int)(y1 > y0 ? yc[1] : yc[0]);
+            if (s == 0 || yv > best) {
+              best = yv;
+              bc = c;
+            }
           }
         }
         // a key that does not exist belongs to no cluster
@@ -205,25 +218,30 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
       }
     }
     if (__ballot(moved != 0) && lane == 0) s_changed[it & 1] = 1;
-    // ---- the four key groups of the wavefront; row k ends with cluster 4 s + k ----
+    // ---- the four key groups of the wavefront; row k ends with cluster 4 s + k (of two: k & 1) ----
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
       float o[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][0]), __float_as_uint(acc[s][j][1]), false, false);
-        const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][2]), __float_as_uint(acc[s][j][3]), false, false);
         const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-        const float c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+        float c23 = c01;
+        if constexpr (MAXC > 2) {
+          const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][2]), __float_as_uint(acc[s][j][3]), false, false);
+          c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+        }
         const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
         o[j] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
       }
-      float4* dst = reinterpret_cast<float4*>(&part[wave][4 * s + row][l16 * 8]);
-      dst[0] = make_float4(o[0], o[1], o[2], o[3]);
-      dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+      if (4 * s + row < MAXC) {
+        float4* dst = reinterpret_cast<float4*>(&part[wave][4 * s + row][l16 * 8]);
+        dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+        dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+      }
       n[s] += __shfl_xor(n[s], 16, WAVE);
       n[s] += __shfl_xor(n[s], 32, WAVE);
-      if (lane < 4) cnt[wave][4 * s + lane] = n[s];
+      if (lane < 4 && 4 * s + lane < MAXC) cnt[wave][4 * s + lane] = n[s];
     }
     __syncthreads();
     ++n_done;
@@ -329,7 +347,9 @@ hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin,
   a.max_iter = max_iter;
   a.metric = metric;
   a.converge = converge ? 1 : 0;
-  if (c_count <= 4)
+  if (c_count <= 2)
+    hipLaunchKernelGGL((k_kmeans_small<2, 1024>), dim3(dm.HP), dim3(1024), 0, st, a);
+  else if (c_count <= 4)
     hipLaunchKernelGGL((k_kmeans_small<4, 1024>), dim3(dm.HP), dim3(1024), 0, st, a);
   else
     hipLaunchKernelGGL((k_kmeans_small<KM_SMALL_MAX_CLUSTERS, 512>), dim3(dm.HP), dim3(512), 0, st, a);

@@ -245,3 +245,22 @@ def test_one_cluster(n, max_iter, converge, ran):
     want = K[:, :, 5:].double().mean(2)
     got = st.centroids[:, :, c0].double()
     assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all()
+
+
+@pytest.mark.parametrize("C", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("n", [9, 64, 65, 127, 320, 321, 384])
+@pytest.mark.parametrize("metric", [O.COSINE, O.L2])
+def test_small_range_at_round_edges(C, n, metric):
+    """The one-kernel form around its rounds of 32 and 64 keys, in each of its cluster bounds, one
+    iteration against the oracle: labels off near-ties, metadata, and means."""
+    cfg = Config(f"e{n}", 1, 2, 2, 2, 128, n, max(2, C), C, 1, 64, 50 + n)
+    w = MixtureWorkload(cfg, device=DEV)
+    init = sample_init_indices(w.K, C, cfg.seed)
+    st, _ = run_gpu(w, cfg, init, 1, METRICS[metric])
+    for s in range(cfg.S):
+        for h in range(cfg.Hkv):
+            keys = np64(w.K[s, h])
+            _, labels, _, _, tr = O.kmeans_run(keys, init[s, h].numpy(), 1, "bf16", metric)
+            bad = (st.labels[s, h].cpu().numpy() != labels) & ~(tr.gap[-1] < NEAR_TIE)
+            assert not bad.any()
+            check_state(st, cfg, s, h, keys, labels)
