@@ -22,8 +22,8 @@ __device__ __forceinline__ void load_row8<float>(const float* p, float (&v)[8]) 
 
 // ---- cluster / row scores of a bf16 table on the matrix cores ----
 // s_r = sum_g <q_g, row_r> for 16 consecutive table rows per wavefront step:
-// v_mfma_f32_16x16x32_bf16 with the query heads of the group as the rows of A (row >= G
-// is zero) and the 16 table rows as the columns of B.  Lane l < 16 then holds, for table
+// v_mfma_f32_16x16x32_bf16 with the query heads of the group as the rows of A (rows >= G
+// repeat head 0, see below) and the 16 table rows as the columns of B.  Lane l < 16 then holds, for table
 // row l of the step, the four heads 0..3 in its four accumulators (lanes 16..31: heads
 // 4..7), so the sum over the heads is three in-lane additions (one lane exchange more for
 // G = 8) and the 16 scores leave the wavefront as one 64-byte store.  Every caller that

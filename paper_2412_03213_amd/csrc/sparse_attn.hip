@@ -8,13 +8,14 @@
 // tokens per step, 16 lanes loading a whole row.  In bf16 both products run on the
 // matrix cores (fp32 check mode keeps the all-VALU form): q K^T with the K rows, passed
 // through LDS, as the A operand; P V with operands that are already in the right lanes
-// (see the kernel).  One launch of the whole step takes 10.3 us at 8 head-problems, B = 1024
+// (see the kernel).  One launch of the whole step takes 10.4 us at 8 head-problems, B = 1024
 // (13.9 with K rows loaded in operand layout, P V on the vector ALUs and one wavefront
 // selecting) and 20.5 at 64, B = 2048 (25.5), of which the row stream at 6.4 TB/s is half;
-// the rest is a chain of dependent round trips.  The attended positions of a head-problem are split over several
-// workgroups (split-KV) so that a batch of a few sequences still fills 256 CUs.  Inside a workgroup every wavefront resolves the token
-// rows of its own positions first, and the K/V loads of the next TWO steps are in
-// flight while the current one is reduced.
+// the rest is a chain of dependent round trips.  The attended positions of a head-problem are
+// split over several workgroups (split-KV) so that a batch of a few sequences still fills 256
+// CUs, and never over more than are resident together (attn_plan).  Inside a workgroup every
+// wavefront resolves the token rows of its own positions first, and the K/V loads of the next
+// TWO steps are in flight while the current one is reduced.
 //
 // Merging the splits without a second launch: every workgroup publishes its partial
 // (max, sum, accumulator) with agent-scope stores, takes a ticket from a counter of
@@ -26,8 +27,8 @@
 //
 // Fused modes: every workgroup of a head-problem repeats the (cheap, LDS-only)
 // selection of the recalled cluster prefix and maps its own positions through the
-// cluster-contiguous index directly, from the ranked clusters in registers; the index list is still written out (each
-// workgroup its own part) but never re-read.  With at most 512 clusters in bf16 the
+// cluster-contiguous index directly, from the ranked clusters in registers; the index list is
+// still written out (each workgroup its own part) but never re-read.  With at most 512 clusters in bf16 the
 // centroid scores are computed by every workgroup as well (the workgroups of one
 // head-problem are placed on one XCD, so the table comes from HBM once and out of
 // that XCD's L2 otherwise); larger or fp32 tables are scored by a launch of their own.
