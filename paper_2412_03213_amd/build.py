@@ -22,7 +22,8 @@ LIB = os.path.join(PKG, "libclusterkv.so")
 HOST_SRC = os.path.join(CSRC, "host_call.cpp")
 HOST_LIB = os.path.join(PKG, "_ckhost" + sysconfig.get_config_var("EXT_SUFFIX"))
 
-SOURCES = ["api.hip", "kmeans_assign.hip", "kmeans_assign_stream.hip", "kmeans_update.hip", "kmeans_small.hip", "select_gather.hip",
+SOURCES = ["api.hip", "kmeans_assign.hip", "kmeans_assign_stream.hip", "kmeans_assign_wide.hip",
+           "kmeans_update.hip", "kmeans_small.hip", "select_gather.hip",
            "sparse_attn.hip", "evaluate.hip", "cluster_cache.hip",
            "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -35,7 +36,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 
 # per-file additions: keep MFMA accumulators in vector registers where the kernel reads
 # them with vector instructions and has other data (MFMA-only operands) for the AGPRs
-EXTRA_FLAGS = {"kmeans_assign_stream.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+               for f in ("kmeans_assign_stream.hip", "kmeans_assign_wide.hip")}
 
 
 def _newer(a: str, b: str) -> bool:

@@ -206,6 +206,11 @@ hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin
                                 int64_t tok_count, const bf16* mu_hat, int c_begin, int c_count,
                                 int32_t* labels, float* best_sim, const ChunkIndex& chunks,
                                 const KmCtl& ctl, int n_cu, hipStream_t st);
+// larger tables: centroid tiles through LDS, 128 keys per wavefront; the same chunk size
+hipError_t launch_assign_wide(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,
+                              const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
+                              float* best_sim, const ChunkIndex& chunks, const KmCtl& ctl,
+                              hipStream_t st);
 // have_seg: seg already holds the counts (written by launch_assign); overwritten either way
 hipError_t launch_metadata(const Dims& dm, const int32_t* labels, int64_t tok_begin,
                            int64_t tok_count, int c_begin, int c_count, int32_t* sizes,

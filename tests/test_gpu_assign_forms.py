@@ -1,0 +1,61 @@
+"""The assignment kernels at the edges of their tiles, rings and blocks: every key's label and the
+label-ordered chunks behind the metadata, against the same contraction in 64 bits."""
+import pytest
+import torch
+
+import paper_2412_03213_amd as ck
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+NEAR_TIE = 1e-4                      # cosine gap below which either of two labels may stand
+
+# (head-problems, tokens, clusters)
+WIDE = [(1, 65537, 513),             # one row in the last tile, one token in the last workgroup
+        (2, 32800, 544),             # whole tiles, ragged last workgroup
+        (1, 66000, 575),             # 18 tiles: the ring of six three times round
+        (3, 21900, 609),             # 20 tiles, one row in the last
+        (1, 65536, 2048)]            # most clusters
+STREAM = [(1, 65537, 512),           # one token in the last block, largest table
+          (2, 40960, 129),           # keys requested behind the staging of the table
+          (8, 8193, 128),            # with it
+          (8, 50000, 40),            # 98 blocks a head-problem: four to a workgroup
+          (40, 10000, 33),           # 20 blocks, four to a workgroup of five
+          (64, 20000, 31),           # 40 blocks, ten rounds' worth in two
+          (300, 600, 7)]             # more head-problems than compute units
+
+
+@pytest.mark.parametrize("hp,n,C", WIDE + STREAM)
+def test_labels_against_64_bits(hp, n, C):
+    g = torch.Generator(device=DEV).manual_seed(n + C)
+    K = torch.randn(1, hp, n + 3, 128, generator=g, device=DEV).to(torch.bfloat16)
+    hat = torch.randn(1, hp, C, 128, generator=g, device=DEV)
+    hat = (hat / hat.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    labels = torch.full((1, hp, n + 3), -1, dtype=torch.int32, device=DEV)
+    ck.ck_kmeans_assign(ck.Shape(1, hp, hp, n + 3, C), K, 2, n, hat, 0, C, labels)
+    torch.cuda.synchronize()
+    assert (labels[:, :, :2] == -1).all() and (labels[:, :, n + 2:] == -1).all()
+    ties = 0
+    for h in range(hp):
+        keys = K[0, h, 2:n + 2].double()
+        sim = keys @ hat[0, h].double().T
+        two = sim.topk(min(2, C), dim=-1).values
+        gap = (two[:, 0] - two[:, -1]) / keys.norm(dim=-1)
+        wrong = labels[0, h, 2:n + 2] != sim.argmax(-1)
+        assert not (wrong & (gap >= NEAR_TIE)).any(), h
+        ties += int((gap < NEAR_TIE).sum())
+    assert ties < 0.01 * hp * n
+
+
+@pytest.mark.parametrize("hp,n,C", WIDE + STREAM)
+def test_iterations_leave_consistent_metadata(hp, n, C):
+    g = torch.Generator(device=DEV).manual_seed(n - C)
+    K = torch.randn(1, hp, n, 128, generator=g, device=DEV).to(torch.bfloat16)
+    init = torch.rand(1, hp, n, generator=g, device=DEV).topk(C, dim=-1).indices.int()
+    st = ck.ClusterState(ck.Shape(1, hp, hp, n, C), DEV, budget=64)
+    st.cluster(K, init, 0, n, C, 2)
+    torch.cuda.synchronize()
+    lab = st.labels[0].long()
+    sizes = torch.zeros(hp, C, dtype=torch.int64, device=DEV).scatter_add_(1, lab, torch.ones_like(lab))
+    assert torch.equal(st.sizes[0].long(), sizes)
+    assert torch.equal(st.offsets[0, :, 1:].long(), sizes.cumsum(1))
+    assert torch.equal(st.sorted_idx[0].long(), lab.sort(dim=1, stable=True).indices)
