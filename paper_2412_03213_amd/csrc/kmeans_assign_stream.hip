@@ -35,8 +35,9 @@ constexpr int ST_NKB = 2;                               // 64 keys per wavefront
 constexpr int ST_CHUNK = ST_WAVES * ST_NKB * 32;        // 512 tokens per block of a workgroup
 constexpr int ST_MAX_TILES = 16;                        // 512 centroids
 constexpr int ST_MAX_BLOCKS = 8;
+constexpr int ST_EARLY_TILES = 4;                       // up to this size the keys are requested with the table
 
-template <bool HAS_BIAS>
+template <bool HAS_BIAS, bool EARLY>
 __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks, int label_bits,
@@ -49,6 +50,11 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
                                                          // [chunk][cluster] counts (clusters <= ST_CHUNK)
   __shared__ int s_changed, s_next_task;
 
+  // one argument per 64-byte line of the argument block: a line that is fetched where it is first
+  // used queues behind the key loads
+  CK_FETCH_ARG(labels);
+  CK_FETCH_ARG(tok_count);
+  CK_FETCH_ARG(ctl.first);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   const int hp = blockIdx.y;
@@ -100,12 +106,12 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
         *reinterpret_cast<uint4*>(&table[(seg >> 4) * LDS_ROW + (seg & 15) * 8]) = v;
     }
   }
-  // the first keys are requested after the table has arrived: loads come back in the
-  // order they were issued and share the memory system's bandwidth, and every earlier
-  // placement of this request that was tried (before the table, between its loads and
-  // its LDS writes, for half of the wavefronts only) delayed the table by more than it
-  // advanced the keys
-  load_keys(wave, ka);
+  // EARLY: a small table is staged before the key requests pile up.  Otherwise they come behind
+  // the barrier: a compute unit has about 32 KB of loads in flight, and a wavefront whose request
+  // does not fit stands still, in front of the barrier with all others (8 x 32768 x 400: barrier
+  // passed after 6.0 us, now 3.1).  Ten iterations, early / behind: 128 x 2048 x 25 320 / 333 us,
+  // 64 x 8179 x 102 530 / 536, 8 x 16384 x 200 238 / 225, 8 x 32768 x 400 475 / 455.
+  if constexpr (EARLY) load_keys(wave, ka);
   if constexpr (HAS_BIAS) {
     for (int c = tid; c < n_tiles * 32; c += THREADS)
       lds_bias[c] = c < c_count ? ctl.bias[(int64_t)hp * ctl.bias_stride + c] : 0.f;
@@ -117,12 +123,14 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     s_next_task = ST_WAVES;                             // tasks 0..7 are the wavefronts' first ones
   }
   __syncthreads();
+  if constexpr (!EARLY) load_keys(wave, ka);
 
+  const int n_tasks = blocks * ST_WAVES;
   int diff = 0;
   const bf16* arow0 = table + col * LDS_ROW + half * 8; // this lane's A fragments of tile 0
 
   // One block of 128 keys against every centroid tile, then its labels.
-  auto process = [&](int b, const bf16x8 (&bk)[NKB][8]) {
+  auto process = [&](int b, const bf16x8 (&bk)[NKB][8], int nxt, bf16x8 (&nk)[NKB][8]) {
     const int64_t wave_tok0 = wg_tok0 + (int64_t)b * (NKB * 32);
     if (wave_tok0 >= tok_count) return;                 // wave-uniform: nothing of this block exists
     float bestp[NKB];
@@ -190,6 +198,8 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     using No = std::false_type;
     const int last = n_tiles - 1;
     step(T0(), No(), 0, false, nullptr);                // tile 0, key block 0: nothing to read out yet
+    // not before the matrix work has begun: the wavefront stands still until its requests fit
+    if (nxt < n_tasks) load_keys(nxt, nk);
     for (int tile = 0; tile < last; ++tile) {
       step(T1(), Yes(), tile, false, arow0 + (tile + 1) * 32 * LDS_ROW);   // reads out block 0 of `tile`
       step(T0(), Yes(), tile, false, nullptr);          // block 0 of tile + 1; reads out block 1 of `tile`
@@ -240,7 +250,6 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   // whole task early.  Two wavefronts share a SIMD and the hardware does not split it
   // evenly between them; with a fixed share the slower one would finish alone, at the
   // speed of one wavefront.
-  const int n_tasks = blocks * ST_WAVES;
   auto grab = [&]() {
     int t = 0;
     if (lane == 0) t = atomicAdd(&s_next_task, 1);
@@ -249,13 +258,11 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   int cur = wave;
   while (cur < n_tasks) {
     int nxt = grab();
-    if (nxt < n_tasks) load_keys(nxt, kb2);
-    process(cur, ka);
+    process(cur, ka, nxt, kb2);
     cur = nxt;
     if (cur >= n_tasks) break;
     nxt = grab();
-    if (nxt < n_tasks) load_keys(nxt, ka);
-    process(cur, kb2);
+    process(cur, kb2, nxt, ka);
     cur = nxt;
   }
 
@@ -291,24 +298,29 @@ hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin
                                 int64_t tok_count, const bf16* mu_hat, int c_begin, int c_count,
                                 int32_t* labels, float* best_sim, const ChunkIndex& chunks,
                                 const KmCtl& ctl, int n_cu, hipStream_t st) {
-  // blocks of 512 tokens per workgroup: as many as keep every CU busy (at most 8: one
-  // wavefront each for the chunk index)
+  // Blocks of 512 tokens per workgroup (at most 8: one wavefront each for the chunk index): the
+  // number with the least rounds of workgroups (one per CU) times blocks and start-up of a round,
+  // which takes about as long as a block (C = 102: 6 us and 5.2, C = 400: 8 and 9.4).  Filling the
+  // CUs once with floor(chunks / CUs) blocks instead, a few workgroups more than CUs are a second
+  // round: 8 x 40000 x 416 764 us for ten iterations, now 545; 64 x 20000 x 250 1851, now 1632.
   const int64_t chunks_hp = (tok_count + ST_CHUNK - 1) / ST_CHUNK;
-  int64_t blocks = chunks_hp * dm.HP / n_cu;
-  if (blocks > ST_MAX_BLOCKS) blocks = ST_MAX_BLOCKS;
-  if (blocks > chunks_hp) blocks = chunks_hp;
-  if (blocks < 1) blocks = 1;
+  int64_t blocks = 1, least = INT64_MAX;
+  for (int64_t b = 1; b <= ST_MAX_BLOCKS && b <= chunks_hp; ++b) {
+    const int64_t wgs = (chunks_hp + b - 1) / b * dm.HP, cost = (wgs + n_cu - 1) / n_cu * (b + 1);
+    if (cost < least) {
+      least = cost;
+      blocks = b;
+    }
+  }
   const dim3 grid((unsigned)((chunks_hp + blocks - 1) / blocks), dm.HP);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
-  if (ctl.bias)
-    hipLaunchKernelGGL(k_assign_stream<true>, grid, dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels,
-                       best_sim, chunks, (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count,
-                       c_begin, c_count, (int)blocks, ctl);
-  else
-    hipLaunchKernelGGL(k_assign_stream<false>, grid, dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels,
-                       best_sim, chunks, (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count,
-                       c_begin, c_count, (int)blocks, ctl);
+  const auto kernel = c_count <= ST_EARLY_TILES * 32
+                          ? (ctl.bias ? k_assign_stream<true, true> : k_assign_stream<false, true>)
+                          : (ctl.bias ? k_assign_stream<true, false> : k_assign_stream<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels, best_sim, chunks,
+                     (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count, c_begin, c_count,
+                     (int)blocks, ctl);
   return hipGetLastError();
 }
 
