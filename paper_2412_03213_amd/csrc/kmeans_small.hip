@@ -35,7 +35,9 @@ struct SmallArgs {
 // A wavefront keeps its keys in registers in both layouts for all iterations (no LDS pass over
 // the keys).  The wavefront of a cluster adds up that cluster's partial sums, keeps its mean in
 // registers and makes the next table row from it, so an iteration has two barriers.
-// 128 head-problems x 320 tokens x 4 clusters, 10 iterations: 85.3 -> 56.6 us, same bits.
+// 128 head-problems x 320 tokens x 4 clusters, 10 iterations: 85.3 -> 56.6 us, same bits; 53.0 since
+// a wavefront whose keys have all kept their labels leaves its sums of the iteration before standing
+// (a mixture of 128 centers: labels settle after 5 to 20 iterations, 9.7 on average).
 // MAXC = 2 is a form of its own: rows 2 and 3 of the products are idle there, and with the lane
 // exchanges of four clusters it was slower than the vector ALUs (352 tokens x 2 clusters: 55.6 us on
 // the vector ALUs, 62.8 as four clusters, 52.9 now; 100 tokens: 38.6, 33.1, 28.3).
@@ -132,14 +134,6 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
       // a row without a cluster is a NaN, which never wins
       bs[s] = 4 * s + rowc < C ? bias[4 * s + rowc] : __builtin_nanf("");
     }
-    floatx4 acc[SETS][8];                               // [channel 8 l16 + j][cluster 4 s + i], key group `row`
-    int n[SETS];                                        // members of cluster 4 s + l4 in key group `row`
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) {
-      n[s] = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[s][j] = {0.f, 0.f, 0.f, 0.f};
-    }
     uint32_t moved = 0;
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
@@ -148,7 +142,6 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
       if (r * KEYS + (MAXC == 2 ? wave * 4 : 0) < n_tok) {   // wave-uniform
         // unpacked here and not once before the iterations: there are no registers for that
         asm volatile("" : "+v"(dk[r].x), "+v"(dk[r].y), "+v"(dk[r].z), "+v"(dk[r].w));
-        asm volatile("" : "+v"(uk[r].x), "+v"(uk[r].y), "+v"(uk[r].z), "+v"(uk[r].w));
         const uint32_t dw[4] = {dk[r].x, dk[r].y, dk[r].z, dk[r].w};
         float best = 0.f;
         int bc = 0;
@@ -198,54 +191,77 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
         const uint32_t word = labels[r / 8], put = (word & ~(15u << (r % 8 * 4))) | ((uint32_t)bc << (r % 8 * 4));
         moved |= word ^ put;
         labels[r / 8] = put;
-        // label of key `row` into all lanes of that row: lane x of every quad has key x's
-        int ub = 0;
-        ub = __builtin_amdgcn_update_dpp(ub, bc, 0x00, 0x1, 0xf, false);
-        ub = __builtin_amdgcn_update_dpp(ub, bc, 0x55, 0x2, 0xf, false);
-        ub = __builtin_amdgcn_update_dpp(ub, bc, 0xAA, 0x4, 0xf, false);
-        ub = __builtin_amdgcn_update_dpp(ub, bc, 0xFF, 0x8, 0xf, false);
-        const uint32_t uw[4] = {uk[r].x, uk[r].y, uk[r].z, uk[r].w};
-#pragma unroll
-        for (int s = 0; s < SETS; ++s) {
-          const bool mine = ub == 4 * s + l4;
-          const float on = mine ? 1.f : 0.f;
-          n[s] += mine ? 1 : 0;
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            acc[s][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(on, j & 1 ? hi_bf16(uw[j / 2]) : lo_bf16(uw[j / 2]), acc[s][j], 0, 0, 0);
-        }
         __builtin_amdgcn_sched_barrier(0);              // rounds one after another: registers
       }
     }
-    if (__ballot(moved != 0) && lane == 0) s_changed[it & 1] = 1;
-    // ---- the four key groups of the wavefront; row k ends with cluster 4 s + k (of two: k & 1) ----
+    // ---- the sums over this wavefront's keys: where none of its labels has changed, those of the
+    // iteration before stand in part and cnt ----
+    const bool any_moved = __ballot(moved != 0) != 0;
+    if (any_moved && lane == 0) s_changed[it & 1] = 1;
+    if (any_moved || it == 0) {
+      floatx4 acc[SETS][8];                               // [channel 8 l16 + j][cluster 4 s + i], key group `row`
+      int n[SETS];                                        // members of cluster 4 s + l4 in key group `row`
 #pragma unroll
-    for (int s = 0; s < SETS; ++s) {
-      float o[8];
+      for (int s = 0; s < SETS; ++s) {
+        n[s] = 0;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][0]), __float_as_uint(acc[s][j][1]), false, false);
-        const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-        float c23 = c01;
-        if constexpr (MAXC > 2) {
-          const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][2]), __float_as_uint(acc[s][j][3]), false, false);
-          c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+        for (int j = 0; j < 8; ++j) acc[s][j] = {0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r) {
+        if (r * KEYS + (MAXC == 2 ? wave * 4 : 0) < n_tok) {   // wave-uniform
+          asm volatile("" : "+v"(uk[r].x), "+v"(uk[r].y), "+v"(uk[r].z), "+v"(uk[r].w));
+          const int bc = (int)(labels[r / 8] >> (r % 8 * 4)) & 15;
+          // label of key `row` into all lanes of that row: lane x of every quad has key x's
+          int ub = 0;
+          ub = __builtin_amdgcn_update_dpp(ub, bc, 0x00, 0x1, 0xf, false);
+          ub = __builtin_amdgcn_update_dpp(ub, bc, 0x55, 0x2, 0xf, false);
+          ub = __builtin_amdgcn_update_dpp(ub, bc, 0xAA, 0x4, 0xf, false);
+          ub = __builtin_amdgcn_update_dpp(ub, bc, 0xFF, 0x8, 0xf, false);
+          const uint32_t uw[4] = {uk[r].x, uk[r].y, uk[r].z, uk[r].w};
+#pragma unroll
+          for (int s = 0; s < SETS; ++s) {
+            const bool mine = ub == 4 * s + l4;
+            const float on = mine ? 1.f : 0.f;
+            n[s] += mine ? 1 : 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              acc[s][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(on, j & 1 ? hi_bf16(uw[j / 2]) : lo_bf16(uw[j / 2]), acc[s][j], 0, 0, 0);
+          }
         }
-        const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
-        o[j] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
       }
-      if (4 * s + row < MAXC) {
-        float4* dst = reinterpret_cast<float4*>(&part[wave][4 * s + row][l16 * 8]);
-        dst[0] = make_float4(o[0], o[1], o[2], o[3]);
-        dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+      // ---- the four key groups of the wavefront; row k ends with cluster 4 s + k (of two: k & 1) ----
+#pragma unroll
+      for (int s = 0; s < SETS; ++s) {
+        float o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][0]), __float_as_uint(acc[s][j][1]), false, false);
+          const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+          float c23 = c01;
+          if constexpr (MAXC > 2) {
+            const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][j][2]), __float_as_uint(acc[s][j][3]), false, false);
+            c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+          }
+          const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
+          o[j] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+        }
+        if (4 * s + row < MAXC) {
+          float4* dst = reinterpret_cast<float4*>(&part[wave][4 * s + row][l16 * 8]);
+          dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+          dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+        }
+        n[s] += __shfl_xor(n[s], 16, WAVE);
+        n[s] += __shfl_xor(n[s], 32, WAVE);
+        if (lane < 4 && 4 * s + lane < MAXC) cnt[wave][4 * s + lane] = n[s];
       }
-      n[s] += __shfl_xor(n[s], 16, WAVE);
-      n[s] += __shfl_xor(n[s], 32, WAVE);
-      if (lane < 4 && 4 * s + lane < MAXC) cnt[wave][4 * s + lane] = n[s];
     }
     __syncthreads();
     ++n_done;
-    if (a.converge && it > 0 && s_changed[it & 1] == 0) break;  // uniform: the previous update stands
+    if (it > 0 && s_changed[it & 1] == 0) {             // uniform: the previous update stands, and
+      if (!a.converge) n_done = a.max_iter;             // further iterations would find it again
+      break;
+    }
 
     // ---- update: mean of the assigned keys, wavefronts in order; an empty cluster keeps its
     // centroid ----
