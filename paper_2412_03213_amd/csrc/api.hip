@@ -732,9 +732,6 @@ int ck_cached_decode_step(const ck_shape* sh, const void* q, const void* K_home,
   if (workspace_bytes < need)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = ck::launch_select(dm, q, centroids, sizes, n_clusters, budget, CK_SEL_WHOLE,
-                                   sel_clusters, n_sel_clusters, n_sel_tokens, scores, st);
-  if (e != hipSuccess) return hip_result(e, "selection launch");
   const int g = step_parity, o = step_parity ^ 1;
   ck::CacheArgs a;
   a.K_home = K_home;
@@ -759,6 +756,14 @@ int ck_cached_decode_step(const ck_shape* sh, const void* q, const void* K_home,
   a.C_cap = dm.C_cap;
   a.cap = cache->cap_tokens;
   a.row_bytes = dm.dtype == CK_BF16 ? 256 : 512;
+  if (dm.dtype == CK_BF16)
+    return hip_result(ck::launch_cached_step(dm, q, centroids, n_clusters, budget, softmax_scale, scores,
+                                             sel_clusters, n_sel_clusters, n_sel_tokens, a, out,
+                                             workspace, st),
+                      "cached step launch");
+  hipError_t e = ck::launch_select(dm, q, centroids, sizes, n_clusters, budget, CK_SEL_WHOLE,
+                                   sel_clusters, n_sel_clusters, n_sel_tokens, scores, st);
+  if (e != hipSuccess) return hip_result(e, "selection launch");
   e = ck::launch_cache_fill(dm, a, budget, st);
   if (e != hipSuccess) return hip_result(e, "cache fill launch");
   // attention over the first n_sel_tokens rows of the new generation

@@ -265,6 +265,12 @@ struct CacheArgs {
   int C_cap, cap, row_bytes;
 };
 hipError_t launch_cache_fill(const Dims& dm, const CacheArgs& a, int budget, hipStream_t st);
+// a whole cached step of bf16 rows
+hipError_t launch_cached_step(const Dims& dm, const void* q, const void* centroids,
+                              int n_clusters, int budget, float softmax_scale, float* scores,
+                              int32_t* sel_clusters, int32_t* n_sel_clusters,
+                              int32_t* n_sel_tokens, const CacheArgs& cache, void* out,
+                              void* workspace, hipStream_t st);
 // evaluation helpers
 hipError_t launch_row_scores(const Dims& dm, const void* q, const void* table,
                              int64_t table_stride, int64_t row_begin, int n_rows, float* scores,

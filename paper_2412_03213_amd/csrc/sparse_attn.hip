@@ -166,6 +166,7 @@ struct AttnArgs {
   int HP, idx_stride, max_tokens, Hq, Hkv, n_sink, n_recent, chunk, n_split, two_pass;
   int64_t N_cap, recent_begin;
   float scale_log2e;
+  CacheArgs cache;              // CACHED: K and V above are the home copy
 };
 
 template <int G, int NW> struct PlainLds { float red[NW * G * PART_STRIDE]; };
@@ -188,7 +189,13 @@ __device__ __forceinline__ float row_bcast(float v) {
 // speed, never results.
 // (Two wavefronts per SIMD is what the row stream's registers allow; the attribute keeps the
 // compiler from aiming higher and spilling.)
-template <typename T, int G, int MODE, int CMAX, int NW>
+// CACHED: the step over a home copy in host memory and the cluster cache (see cluster_cache.hip).  A
+// row comes from the previous generation where its cluster is held there and from the home copy
+// otherwise, and is stored into the new generation on its way into the products, so that selection,
+// fetch and attention are one launch and only the host link counts: four steps at 8 head-problems,
+// B = 1024 took 337 us as scoring, selection, fill and attention, 299 now (14.7 MB over the link, whose
+// 55 GB/s are 267 us of it).
+template <typename T, int G, int MODE, int CMAX, int NW, bool CACHED>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 2 : 1, 2))) void k_attn(const AttnArgs a) {
   constexpr bool FUSED = MODE != ATT_PLAIN;
   constexpr int NT = NW * 64, STEP = NW * ATT_TOKENS;
@@ -201,6 +208,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
   __shared__ __attribute__((aligned(16))) float sc_lds[MODE == ATT_FUSED_SCORE ? CMAX : 4];
   __shared__ __attribute__((aligned(16))) bf16 stage_lds[std::is_same<T, bf16>::value ? NW * STAGE_ELEMS : 8];
   __shared__ int s_last;
+  static_assert(!CACHED || (FUSED && std::is_same<T, bf16>::value), "cached steps select and are bf16");
+  int* held = nullptr;                                  // cluster id -> first row in the previous generation, -1
   float* red = big.plain.red;
 
   // one argument per 64-byte line of the argument block: all lines are requested now
@@ -212,6 +221,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
   CK_FETCH_ARG(a.C_cap);
   CK_FETCH_ARG(a.n_sink);
   CK_FETCH_ARG(a.scale_log2e);
+  if constexpr (CACHED) {
+    CK_FETCH_ARG(a.cache.old_clusters);
+    CK_FETCH_ARG(a.cache.cap);
+  }
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6, col = lane & 15, kg = lane >> 4;
   const int wg = blockIdx.x, xcd = wg % N_XCD, seq = wg / N_XCD;
@@ -241,6 +254,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
       sz[i] = a.sizes[(int64_t)hp * a.C_cap + cc];
       of[i] = a.offsets[(int64_t)hp * (a.C_cap + 1) + cc];
       if constexpr (MODE == ATT_FUSED) sc[i] = a.scores[(int64_t)hp * a.C_cap + cc];
+    }
+    int old_id[ITEMS], old_row[ITEMS], n_old = 0;
+    if constexpr (CACHED) {
+      n_old = a.cache.old_n[hp];
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        const int c = tid + i * NT, cc = c < a.C_cap ? c : a.C_cap - 1;
+        old_id[i] = a.cache.old_clusters[(int64_t)hp * a.C_cap + cc];
+        old_row[i] = a.cache.old_starts[(int64_t)hp * (a.C_cap + 1) + cc];
+      }
     }
     quick_clear(Q);
     if constexpr (MODE == ATT_FUSED_SCORE) {
@@ -299,6 +322,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
       sel.n_tok = L.n_tok;
     }
     n_idx = sel.n_tok;
+    if constexpr (CACHED) {
+      held = reinterpret_cast<int*>(L.key);             // the selection is through with it
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) held[tid + i * NT] = -1;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i)
+        if (tid + i * NT < n_old && tid + i * NT < a.C_cap && (unsigned)old_id[i] < (unsigned)CMAX)
+          held[old_id[i]] = old_row[i];
+      // more clusters held than this form selects from: the table was larger at the step before
+      for (int j = tid + ITEMS * NT; j < n_old && j < a.C_cap; j += NT) {
+        const int id = a.cache.old_clusters[(int64_t)hp * a.C_cap + j];
+        if ((unsigned)id < (unsigned)CMAX) held[id] = a.cache.old_starts[(int64_t)hp * (a.C_cap + 1) + j];
+      }
+      __syncthreads();
+    }
     if (split == 0) {
       if (sel.m <= WAVE) {
         if (tid < sel.n_sel) a.sel_clusters[(int64_t)hp * a.C_cap + tid] = sel.id;
@@ -309,7 +348,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
       if (tid == 0) {
         a.n_sel_clusters[hp] = sel.n_sel;
         a.n_sel_tokens[hp] = n_idx;
-        a.n_tokens_out[hp] = n_idx;
+        if constexpr (!CACHED) a.n_tokens_out[hp] = n_idx;
+      }
+      if constexpr (CACHED) {                           // the new generation's directory
+        int miss = 0;
+        if (wave == 0) {
+          for (int j = lane; j < sel.n_sel; j += WAVE) {
+            const bool few = sel.m <= WAVE;
+            const int id = few ? sel.id : L.ord[j], end = few ? sel.cum : L.cum[j];
+            const int begin = few ? sel.cum - sel.size : (j ? L.cum[j - 1] : 0);
+            a.cache.new_clusters[(int64_t)hp * a.C_cap + j] = id;
+            a.cache.new_starts[(int64_t)hp * (a.C_cap + 1) + j] = begin;
+            if (held[id] < 0) miss += end - begin;
+          }
+          miss = __builtin_amdgcn_readlane(wave_inclusive_scan(miss), WAVE - 1);
+          if (lane == 0) {
+            a.cache.new_starts[(int64_t)hp * (a.C_cap + 1) + sel.n_sel] = n_idx;
+            a.cache.new_n[hp] = sel.n_sel;
+            a.cache.miss_tokens[hp] = miss;
+          }
+        }
       }
     }
   } else {
@@ -325,7 +383,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
 
   // ---- token rows of this wavefront's positions, entry 16 t + x: token x of step t ----
   // (a position beyond the end reads row 0 and is masked later)
+  // CACHED: ~row of the previous generation, or a row of the home copy; what stands in for a
+  // position beyond the end does not come over the host link
   int* rows = rows_lds + wave * (ATT_MAX_CHUNK / NW);
+  int sel_held = -1;                                    // of the cluster of rank `lane`
+  if constexpr (CACHED)
+    if (sel.m <= WAVE && lane < sel.n_sel) sel_held = held[sel.id];
   for (int e0 = 0; e0 < n_steps * 16; e0 += WAVE) {
     const int e = e0 + lane;
     const int i = (e >> 4) * STEP + wave * 16 + (e & 15);
@@ -334,6 +397,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     int64_t row = 0;
     if constexpr (FUSED) {
       int64_t src = 0;
+      int from_old = -1;
       if (sel.m <= WAVE) {
         // the clusters this wavefront's positions cross, in order, out of the lanes that
         // hold them (empty clusters of the prefix cover no position)
@@ -348,7 +412,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
           if (prev >= q1) break;
           int take = a.budget - prev;                   // a cut cluster keeps its trailing entries
           take = take > size ? size : take;
-          if (qpos >= prev && qpos < cum) src = (int64_t)off + (size - take) + (qpos - prev);
+          const int old = CACHED ? __builtin_amdgcn_readlane(sel_held, j) : -1;
+          if (qpos >= prev && qpos < cum) {
+            src = (int64_t)off + (size - take) + (qpos - prev);
+            if (CACHED && old >= 0) from_old = old + (qpos - prev);
+          }
         }
       } else if (listed) {
         SelectLds<CMAX, NT>& L = big.fused.general;
@@ -365,6 +433,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
         take = take > size ? size : take;
         const int beg = L.full_rank ? L.soff[c] : L.cbeg[lo];
         src = (int64_t)beg + (size - take) + (qpos - prev);
+        if constexpr (CACHED)
+          if (held[c] >= 0) from_old = held[c] + (qpos - prev);
+      }
+      if constexpr (CACHED) {
+        if (listed && from_old < 0) {
+          src = src < 0 ? 0 : (src >= a.N_cap ? a.N_cap - 1 : src);
+          row = a.sorted_idx[(int64_t)hp * a.N_cap + src];
+          row = row < 0 ? 0 : (row >= a.N_cap ? a.N_cap - 1 : row);
+        } else {
+          from_old = listed ? from_old : 0;
+          row = ~(int64_t)(from_old < a.cache.cap ? from_old : a.cache.cap - 1);
+        }
+        if (e < ATT_MAX_CHUNK / NW) rows[e] = (int)row;
+        continue;
       }
       if (listed) {
         src = src < 0 ? 0 : (src >= a.N_cap ? a.N_cap - 1 : src);
@@ -409,6 +491,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     struct Regs { uint4 k[4], v[4]; };
     auto fetch = [&](int t, Regs& r) {                  // group kg: whole rows of tokens 4 kg + (0..3)
       const int4 tr = *reinterpret_cast<const int4*>(rows + t * 16 + kg * 4);
+      if constexpr (CACHED) {
+        const int64_t base = (int64_t)hp * a.cache.cap * D + col * 8;
+        const bf16* Ko = static_cast<const bf16*>(a.cache.K_old) + base;
+        const bf16* Vo = static_cast<const bf16*>(a.cache.V_old) + base;
+        const int w[4] = {tr.x, tr.y, tr.z, tr.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t at = (int64_t)(w[i] < 0 ? ~w[i] : w[i]) * D;
+          r.k[i] = *reinterpret_cast<const uint4*>((w[i] < 0 ? Ko : Khp) + at);
+          r.v[i] = *reinterpret_cast<const uint4*>((w[i] < 0 ? Vo : Vhp) + at);
+        }
+        return;
+      }
       r.k[0] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.x * D);
       r.k[1] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.y * D);
       r.k[2] = *reinterpret_cast<const uint4*>(Khp + (int64_t)tr.z * D);
@@ -419,6 +514,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
       r.v[3] = *reinterpret_cast<const uint4*>(Vhp + (int64_t)tr.w * D);
     };
     auto reduce = [&](int t, const Regs& r) {
+      if constexpr (CACHED) {
+        const int i0 = t * STEP + wave * 16 + kg * 4;
+        const int64_t at = ((int64_t)hp * a.cache.cap + p_begin + i0) * D + col * 8;
+        bf16* Kn = static_cast<bf16*>(a.cache.K_new) + at;
+        bf16* Vn = static_cast<bf16*>(a.cache.V_new) + at;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i0 + i < n_pos) {
+            *reinterpret_cast<uint4*>(Kn + i * D) = r.k[i];
+            *reinterpret_cast<uint4*>(Vn + i * D) = r.v[i];
+          }
+      }
       stage.put(r.k[0], r.k[1], r.k[2], r.k[3]);
       floatx4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -818,18 +925,18 @@ size_t attn_workspace_bytes(const Dims& dm, int64_t max_total) {
   return ticket_bytes(dm) + ((b + 255) & ~(size_t)255);
 }
 
-template <typename T, int MODE, int CMAX, int NW>
+template <typename T, int MODE, int CMAX, int NW, bool CACHED>
 static void launch_attn_waves(int G, dim3 grid, const AttnArgs& a, hipStream_t st) {
   const dim3 block(NW * 64);
   switch (G) {
-    case 1: hipLaunchKernelGGL((k_attn<T, 1, MODE, CMAX, NW>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_attn<T, 2, MODE, CMAX, NW>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_attn<T, 4, MODE, CMAX, NW>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_attn<T, 8, MODE, CMAX, NW>), grid, block, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((k_attn<T, 1, MODE, CMAX, NW, CACHED>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_attn<T, 2, MODE, CMAX, NW, CACHED>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_attn<T, 4, MODE, CMAX, NW, CACHED>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((k_attn<T, 8, MODE, CMAX, NW, CACHED>), grid, block, 0, st, a); break;
   }
 }
 
-template <typename T, int MODE, int CMAX>
+template <typename T, int MODE, int CMAX, bool CACHED = false>
 static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, void* workspace,
                                 bool two_pass, hipStream_t st) {
   const AttnPlan plan = attn_plan(dm, max_total);
@@ -846,11 +953,11 @@ static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, v
   const dim3 grid((unsigned)hp_groups * N_XCD * n_split);
   if constexpr (std::is_same<T, bf16>::value) {
     if (plan.waves == 8)
-      launch_attn_waves<T, MODE, CMAX, 8>(dm.G, grid, a, st);
+      launch_attn_waves<T, MODE, CMAX, 8, CACHED>(dm.G, grid, a, st);
     else
-      launch_attn_waves<T, MODE, CMAX, 4>(dm.G, grid, a, st);
+      launch_attn_waves<T, MODE, CMAX, 4, CACHED>(dm.G, grid, a, st);
   } else {
-    launch_attn_waves<T, MODE, CMAX, 4>(dm.G, grid, a, st);
+    launch_attn_waves<T, MODE, CMAX, 4, CACHED>(dm.G, grid, a, st);
   }
   if (n_split > 1 && two_pass)
     hipLaunchKernelGGL(k_attn_merge<T>, dim3(dm.S * dm.Hq), dim3(D / 2), 0, st, a.part, n_split,
@@ -927,6 +1034,30 @@ hipError_t launch_decode_fused(const Dims& dm, const void* q, const void* K, con
   if (n_clusters <= SELP_SMALL)
     return launch_attn_t<float, ATT_FUSED, SELP_SMALL>(dm, a, max_total, workspace, false, st);
   return launch_attn_t<float, ATT_FUSED, CK_MAX_CLUSTERS>(dm, a, max_total, workspace, false, st);
+}
+
+hipError_t launch_cached_step(const Dims& dm, const void* q, const void* centroids,
+                              int n_clusters, int budget, float softmax_scale, float* scores,
+                              int32_t* sel_clusters, int32_t* n_sel_clusters,
+                              int32_t* n_sel_tokens, const CacheArgs& cache, void* out,
+                              void* workspace, hipStream_t st) {
+  AttnArgs a = common_args(dm, q, cache.K_home, cache.V_home, 0, budget, 0, 0, 0, softmax_scale, out);
+  a.centroids = centroids;
+  a.scores = scores;
+  a.sizes = cache.sizes;
+  a.offsets = cache.offsets;
+  a.sorted_idx = cache.sorted_idx;
+  a.sel_clusters = sel_clusters;
+  a.n_sel_clusters = n_sel_clusters;
+  a.n_sel_tokens = n_sel_tokens;
+  a.n_clusters = n_clusters;
+  a.budget = budget;
+  a.cache = cache;
+  if (n_clusters <= SELP_SMALL)
+    return launch_attn_t<bf16, ATT_FUSED_SCORE, SELP_SMALL, true>(dm, a, budget, workspace, false, st);
+  const hipError_t e = launch_score(dm, q, centroids, n_clusters, scores, st);
+  if (e != hipSuccess) return e;
+  return launch_attn_t<bf16, ATT_FUSED, CK_MAX_CLUSTERS, true>(dm, a, budget, workspace, false, st);
 }
 
 // ---- library-owned scratch for callers that cannot allocate ----

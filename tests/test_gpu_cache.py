@@ -79,6 +79,30 @@ def test_cached_steps_equal_uncached_and_count_misses(home, S, Hkv, G, N, C, B):
     assert total > 0
 
 
+@pytest.mark.parametrize("S,Hkv,G,N,C,B", [(1, 2, 2, 600, 400, 300),     # more recalled clusters than lanes
+                                           (1, 2, 4, 900, 600, 500),     # the same in the large form
+                                           (40, 8, 1, 200, 20, 100),     # more head-problems than CUs
+                                           (3, 1, 2, 9000, 90, 6000)])   # several steps of rows, many splits
+def test_cached_steps_in_other_forms(S, Hkv, G, N, C, B):
+    test_cached_steps_equal_uncached_and_count_misses("device", S, Hkv, G, N, C, B)
+
+
+def test_a_smaller_table_than_at_the_step_before():
+    """Clusters held at list places beyond what the small form's threads look at are still found."""
+    cfg = Config("cache3", 1, 1, 1, 2, 128, 1200, 32, 1000, 10, 1200, 3)
+    w, sh, st = clustered(cfg)
+    cache = ck.ClusterCache(sh, DEV, cap_tokens=1200)
+    ck.ck_cache_reset(sh, cache)
+    q = w.query()
+    ck.cached_decode_step(st, cache, q, w.K, w.V)       # every cluster fits
+    torch.cuda.synchronize()
+    assert int(cache.n_held[0]) == 1000
+    st.n_clusters = 300
+    ck.cached_decode_step(st, cache, q, w.K, w.V)
+    torch.cuda.synchronize()
+    assert int(st.n_sel_clusters) == 300 and int(cache.miss_tokens) == 0
+
+
 def test_same_query_twice_is_all_hits_and_reset_empties():
     cfg = Config("cache2", 1, 1, 2, 8, 128, 4096, 64, 51, 10, 1024, 4)
     w, sh, st = clustered(cfg)
