@@ -220,14 +220,13 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
   const int64_t o = (int64_t)hp * n_chunks_hp + blockIdx.x;
   if (count_only) {
     for (int c = tid; c < c_count; c += THREADS) chunks.seg[o * seg_stride(c_count) + c] = tok[c] << 16;
-  } else if (chunks.seg && wave == 0) {
-    constexpr int CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * 4;
-    static_assert(CHUNK * 4 + CNT + CHUNK * 2 <= sizeof(lds), "chunk sort scratch");
-    char* scratch = reinterpret_cast<char*>(&lds[0][0]) + CHUNK * 4;
-    chunk_sort<CHUNK / WAVE, CK_MAX_CLUSTERS>(tok, c_count, reinterpret_cast<int*>(scratch),
-                                              reinterpret_cast<uint16_t*>(scratch + CNT),
-                                              chunks.seg + o * seg_stride(c_count),
-                                              chunks.list + o * CHUNK);
+  } else if (chunks.seg) {
+    constexpr int W = CHUNK / WAVE, CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * W;
+    static_assert((CHUNK + CNT + 4) * 4 + CHUNK * 2 <= sizeof(lds), "chunk sort scratch");
+    int* cnt = reinterpret_cast<int*>(tok) + CHUNK;
+    chunk_sort<CHUNK / WAVE, CK_MAX_CLUSTERS, W>(
+        tok, c_count, wave, wave < W, cnt, cnt + CNT, reinterpret_cast<uint16_t*>(cnt + CNT + 4),
+        chunks.seg + o * seg_stride(c_count), chunks.list + o * CHUNK);
   }
 }
 

@@ -279,16 +279,23 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
         chunks.seg[((int64_t)hp * n_chunks + ch) * seg_stride(c_count) + e % c_count] = tok[e] << 16;
     }
   } else if (chunks.seg) {
-    // one wavefront per 512-token chunk; the centroid table's LDS is free by now
-    const int64_t ch = (int64_t)blockIdx.x * blocks + wave;
-    if (wave < blocks && ch < n_chunks) {
-      constexpr int CNT = chunk_sort_cnt_ints(ST_MAX_TILES * 32) * 4;
-      char* scratch = reinterpret_cast<char*>(table) + wave * (CNT + ST_CHUNK * 2);
-      const int64_t o = (int64_t)hp * n_chunks + ch;
-      chunk_sort<ST_CHUNK / WAVE, ST_MAX_TILES * 32>(tok + wave * ST_CHUNK, c_count, reinterpret_cast<int*>(scratch),
-                                  reinterpret_cast<uint16_t*>(scratch + CNT),
-                                  chunks.seg + o * seg_stride(c_count), chunks.list + o * ST_CHUNK);
-    }
+    // as many wavefronts per 512-token chunk as there are; the centroid table's LDS is free by now
+    auto sort = [&](auto WT) {
+      constexpr int W = decltype(WT)::value, CNT = chunk_sort_cnt_ints(ST_MAX_TILES * 32) * W;
+      constexpr int SCRATCH = (CNT + 8) * 4 + ST_CHUNK * 2;
+      static_assert(ST_WAVES / W * SCRATCH <= sizeof(table), "chunk sort scratch");
+      const int k = wave / W;
+      const int64_t ch = (int64_t)blockIdx.x * blocks + k, o = (int64_t)hp * n_chunks + ch;
+      int* cnt = reinterpret_cast<int*>(reinterpret_cast<char*>(table) + k * SCRATCH);
+      chunk_sort<ST_CHUNK / WAVE, ST_MAX_TILES * 32, W>(
+          tok + k * ST_CHUNK, c_count, wave % W, k < blocks && ch < n_chunks, cnt, cnt + CNT,
+          reinterpret_cast<uint16_t*>(cnt + CNT + 8), chunks.seg + o * seg_stride(c_count),
+          chunks.list + o * ST_CHUNK);
+    };
+    if (blocks == 1) sort(std::integral_constant<int, 8>());
+    else if (blocks == 2) sort(std::integral_constant<int, 4>());
+    else if (blocks <= 4) sort(std::integral_constant<int, 2>());
+    else sort(std::integral_constant<int, 1>());
   }
 }
 

@@ -241,14 +241,13 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
   const int64_t o = (int64_t)hp * n_chunks + blockIdx.x;
   if (count_only) {
     for (int c = tid; c < c_count; c += THREADS) chunks.seg[o * seg_stride(c_count) + c] = tok[c] << 16;
-  } else if (chunks.seg && wave == 0) {
-    constexpr int CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * 4;
-    static_assert(WD_CHUNK * 4 + CNT + WD_CHUNK * 2 <= sizeof(ring), "chunk sort scratch");
-    char* scratch = reinterpret_cast<char*>(ring) + WD_CHUNK * 4;
-    chunk_sort<WD_CHUNK / WAVE, CK_MAX_CLUSTERS>(tok, c_count, reinterpret_cast<int*>(scratch),
-                                                 reinterpret_cast<uint16_t*>(scratch + CNT),
-                                                 chunks.seg + o * seg_stride(c_count),
-                                                 chunks.list + o * WD_CHUNK);
+  } else if (chunks.seg) {
+    constexpr int CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * WD_WAVES;
+    static_assert((WD_CHUNK + CNT + WD_WAVES) * 4 + WD_CHUNK * 2 <= sizeof(ring), "chunk sort scratch");
+    int* cnt = reinterpret_cast<int*>(ring) + WD_CHUNK;
+    chunk_sort<WD_CHUNK / WAVE, CK_MAX_CLUSTERS, WD_WAVES>(
+        tok, c_count, wave, true, cnt, cnt + CNT, reinterpret_cast<uint16_t*>(cnt + CNT + WD_WAVES),
+        chunks.seg + o * seg_stride(c_count), chunks.list + o * WD_CHUNK);
   }
 }
 
