@@ -418,8 +418,13 @@ struct ChunkRuns {
   // then cluster c0 + cl for this wavefront (the wavefronts of one cluster do the same scan).
   template <int CL, int THREADS>
   __device__ __forceinline__ void stage(uint32_t* lds, int hp, int c0, int cl, int c_count) {
+    load<CL, THREADS>(lds, hp, c0, c_count);
+    scan(lds, hp, cl);
+  }
+  template <int CL, int THREADS>
+  __device__ __forceinline__ void load(uint32_t* lds, int hp, int c0, int c_count) const {
     constexpr int BATCH = 4;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int cpad = (n_chunks + 63) & ~63, stride = seg_stride(c_count);
     const uint32_t* S = seg + (int64_t)hp * n_chunks * stride;
     for (int e0 = tid; e0 < cpad * CL; e0 += BATCH * THREADS) {
@@ -438,6 +443,9 @@ struct ChunkRuns {
       }
     }
     __syncthreads();
+  }
+  __device__ __forceinline__ void scan(uint32_t* lds, int hp, int cl) {
+    const int lane = threadIdx.x & 63, cpad = (n_chunks + 63) & ~63;
     uint32_t* r = lds + (size_t)cl * 2 * cpad;
     int* u = reinterpret_cast<int*>(r + cpad);
     n = 0;
@@ -467,7 +475,7 @@ struct ChunkRuns {
   }
 };
 
-// Update: one workgroup per cluster, wavefront w summing members 16 s + 4 w + (0..3) of every
+// Update: one workgroup per CL neighbouring clusters, wavefront w summing members 16 s + 4 w + (0..3) of every
 // step s, 128 rows in flight.  The additions run in k_update's order (16 member streams, the
 // four of a wavefront, then the wavefronts), so both give the same bits.
 // Bound: launch, two dependent look-ups (runs, list) and the rows at memory speed.  It takes
@@ -477,10 +485,14 @@ struct ChunkRuns {
 // 8 x 131072 x 1600 407 -> 399, 8 x 2985 x 37 15.8 -> 9.9.  One wavefront per cluster with
 // four accumulator sets (one to eight clusters per workgroup) is within 2 % on the large
 // shapes and 3 us slower on the small one; two wavefronts per cluster are slower everywhere.
+// Four clusters share the lines of the run table (a cluster uses 4 bytes of each: 420 MB through the
+// L2s for 13 MB of words at 8 x 131072 x 1600) and one's rows travel while the next one's members
+// are looked up; see launch_update_chunks for where that pays.
 constexpr int UPC_WAVES = 4;
 constexpr int UPC_STEPS = 8;                            // 16-row steps whose loads are in flight together
 
-__global__ __launch_bounds__(UPC_WAVES * 64, 7) void k_update_chunks(
+template <int CL>
+__global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chunks(
     const bf16* __restrict__ K, const uint32_t* __restrict__ seg,
     const uint16_t* __restrict__ list, int n_chunks, int chunk_tokens, int64_t N_cap,
     int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin, int c_count,
@@ -488,67 +500,88 @@ __global__ __launch_bounds__(UPC_WAVES * 64, 7) void k_update_chunks(
     int metric, float* __restrict__ bias, int bias_stride, const int32_t* __restrict__ gate) {
   constexpr int SPAN = 256;                             // members whose ids a workgroup holds at once
   extern __shared__ uint32_t lds_u[];
-  __shared__ __attribute__((aligned(16))) float part[UPC_WAVES][D];
+  __shared__ __attribute__((aligned(16))) float part[CL][UPC_WAVES][D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
   // neighbouring clusters, whose run words share cache lines, go to one XCD (workgroup i runs
   // on XCD i % 8)
-  const int hp = blockIdx.y, c = (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8);
-  if (c >= c_count) return;
+  const int hp = blockIdx.y, c0 = (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8) * CL;
+  if (c0 >= c_count) return;
   if (gate && gate[hp] == 0) return;
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
-  ChunkRuns cr = {seg, list, n_chunks, chunk_tokens, tok_count};
-  cr.stage<1, UPC_WAVES * 64>(lds_u, hp, c, 0, c_count);
-  const int n = cr.n;
-  if (tid == 0) sizes[(int64_t)hp * C_cap + c_begin + c] = n;
-  if (n == 0) return;                                   // empty cluster keeps its centroid
+  ChunkRuns cr[CL];
+#pragma unroll
+  for (int cl = 0; cl < CL; ++cl) cr[cl] = {seg, list, n_chunks, chunk_tokens, tok_count};
+  cr[0].template load<CL, UPC_WAVES * 64>(lds_u, hp, c0, c_count);
+#pragma unroll
+  for (int cl = 0; cl < CL; ++cl) {
+    cr[cl].scan(lds_u, hp, cl);
+    if (tid == 0 && c0 + cl < c_count) sizes[(int64_t)hp * C_cap + c_begin + c0 + cl] = cr[cl].n;
+  }
+  if (CL == 1 && cr[0].n == 0) return;                  // empty cluster keeps its centroid
 
   const bf16* Khp = K + ((int64_t)hp * N_cap + tok_begin) * D + l16 * 8;
-  float acc[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
   const int jl = (lane >> 2) * 16 + wave * 4 + (lane & 3);   // the member whose id this lane holds
-  int id = cr.member(jl);
-  for (int j0 = 0; j0 < n; j0 += SPAN) {
-    const int now = id;
+  int id = CL == 1 || cr[0].n > 0 ? cr[0].member(jl) : 0;
 #pragma unroll
-    for (int s0 = 0; s0 < SPAN / 16; s0 += UPC_STEPS) {
-      if (j0 + s0 * 16 >= n) break;                     // uniform
-      uint4 r[UPC_STEPS];
+  for (int cl = 0; cl < CL; ++cl) {
+    const int n = cr[cl].n;
+    float acc[8];
 #pragma unroll
-      for (int s = 0; s < UPC_STEPS; ++s) {
-        const int t = __shfl(now, (s0 + s) * 4 + g4, WAVE);
-        r[s] = *reinterpret_cast<const uint4*>(Khp + (int64_t)t * D);
-      }
-      // the members of the next pass are looked up while the first rows of this one travel
-      if (s0 == 0 && j0 + SPAN < n) id = cr.member(j0 + SPAN + jl);
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    for (int j0 = 0; j0 < n; j0 += SPAN) {
+      const int now = id;
 #pragma unroll
-      for (int s = 0; s < UPC_STEPS; ++s) {
-        const bool real = j0 + (s0 + s) * 16 + wave * 4 + g4 < n;
-        const uint32_t x = real ? r[s].x : 0u, y = real ? r[s].y : 0u;
-        const uint32_t z = real ? r[s].z : 0u, q = real ? r[s].w : 0u;
-        acc[0] += lo_bf16(x); acc[1] += hi_bf16(x);
-        acc[2] += lo_bf16(y); acc[3] += hi_bf16(y);
-        acc[4] += lo_bf16(z); acc[5] += hi_bf16(z);
-        acc[6] += lo_bf16(q); acc[7] += hi_bf16(q);
+      for (int s0 = 0; s0 < SPAN / 16; s0 += UPC_STEPS) {
+        if (j0 + s0 * 16 >= n) break;                   // uniform
+        uint4 r[UPC_STEPS];
+#pragma unroll
+        for (int s = 0; s < UPC_STEPS; ++s) {
+          const int t = __shfl(now, (s0 + s) * 4 + g4, WAVE);
+          r[s] = *reinterpret_cast<const uint4*>(Khp + (int64_t)t * D);
+        }
+        // the members of the next pass, or of the next cluster, are looked up while the first rows
+        // of this one travel
+        if (s0 == 0) {
+          if (j0 + SPAN < n) id = cr[cl].member(j0 + SPAN + jl);
+          else if (cl + 1 < CL && cr[cl + 1 < CL ? cl + 1 : cl].n > 0) id = cr[cl + 1 < CL ? cl + 1 : cl].member(jl);
+        }
+#pragma unroll
+        for (int s = 0; s < UPC_STEPS; ++s) {
+          const bool real = j0 + (s0 + s) * 16 + wave * 4 + g4 < n;
+          const uint32_t x = real ? r[s].x : 0u, y = real ? r[s].y : 0u;
+          const uint32_t z = real ? r[s].z : 0u, q = real ? r[s].w : 0u;
+          acc[0] += lo_bf16(x); acc[1] += hi_bf16(x);
+          acc[2] += lo_bf16(y); acc[3] += hi_bf16(y);
+          acc[4] += lo_bf16(z); acc[5] += hi_bf16(z);
+          acc[6] += lo_bf16(q); acc[7] += hi_bf16(q);
+        }
       }
     }
-  }
+    if (cl + 1 < CL && n == 0 && cr[cl + 1 < CL ? cl + 1 : cl].n > 0) id = cr[cl + 1 < CL ? cl + 1 : cl].member(jl);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float v = xor32(xor16(acc[j], OpSum()), OpSum());
-    if (lane < 16) part[wave][l16 * 8 + j] = v;
+    for (int j = 0; j < 8; ++j) {
+      const float v = xor32(xor16(acc[j], OpSum()), OpSum());
+      if (lane < 16) part[cl][wave][l16 * 8 + j] = v;
+    }
   }
   __syncthreads();
-  if (wave != 0) return;
-  float m0 = part[0][2 * lane], m1 = part[0][2 * lane + 1];
+  // wavefront w finishes cluster w
+  if (wave >= CL) return;
 #pragma unroll
-  for (int w = 1; w < UPC_WAVES; ++w) {
-    m0 += part[w][2 * lane];
-    m1 += part[w][2 * lane + 1];
+  for (int cl = 0; cl < CL; ++cl) {
+    const int c = c0 + cl, n = cr[cl].n;
+    if (wave != cl || c >= c_count) continue;
+    if (n == 0) continue;
+    float m0 = part[cl][0][2 * lane], m1 = part[cl][0][2 * lane + 1];
+#pragma unroll
+    for (int w = 1; w < UPC_WAVES; ++w) {
+      m0 += part[cl][w][2 * lane];
+      m1 += part[cl][w][2 * lane + 1];
+    }
+    store_mean(m0, m1, n, hp, c, C_cap, c_begin, c_count, centroids, mu_hat, nullptr, metric, bias,
+               bias_stride);
   }
-  store_mean(m0, m1, n, hp, c, C_cap, c_begin, c_count, centroids, mu_hat, nullptr, metric, bias,
-             bias_stride);
 }
 
 // Metadata of the final labels: offsets (prefix sum of the sizes the last update wrote) and
@@ -614,8 +647,14 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
                                 float* bias, int bias_stride, const int32_t* gate, hipStream_t st) {
   const int chunk_tokens = assign_tile_tokens(dm, tok_count);
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
-  hipLaunchKernelGGL(k_update_chunks, dim3((c_count + 7) / 8 * 8, dm.HP), dim3(UPC_WAVES * 64),
-                     chunk_runs_lds(1, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
+  // Four clusters per workgroup where a cluster's runs are many and there are workgroups enough for
+  // several rounds all the same.  Ten iterations, one / four: 8 x 131072 x 1600 (256 chunks) 3671 /
+  // 3608 us, 16 x 65536 x 800 (128 chunks) 2166 / 2154, but 4 x 100000 x 1250 (5000 clusters) 1421 /
+  // 1430, 64 x 16384 x 200 (32 chunks) 1079 / 1095, 8 x 32768 x 400 457 / 478.
+  const bool four = n_chunks >= 128 && (int64_t)c_count * dm.HP >= 10240;
+  const int cl = four ? 4 : 1, groups = ((c_count + cl - 1) / cl + 7) / 8 * 8;
+  hipLaunchKernelGGL(four ? k_update_chunks<4> : k_update_chunks<1>, dim3(groups, dm.HP), dim3(UPC_WAVES * 64),
+                     chunk_runs_lds(cl, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
                      chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin, c_count,
                      centroids, mu_hat, sizes, metric, bias, bias_stride, gate);
   return hipGetLastError();

@@ -23,6 +23,7 @@ SHAPES = [
     (1, 2, 262700, 512, 7, 3),       # the same with the largest LDS-resident table
     (1, 1, 263681, 1100, 0, 0),      # and with the table streamed in chunks
     (1, 2, 2300, 2048, 0, 0),        # most clusters, many of them of one member or empty
+    (5, 1, 65530, 2047, 0, 0),       # four clusters to a workgroup of the update, three in the last
 ]
 
 
