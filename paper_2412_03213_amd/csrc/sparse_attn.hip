@@ -169,7 +169,7 @@ struct AttnArgs {
   CacheArgs cache;              // CACHED: K and V above are the home copy
 };
 
-template <int G, int NW> struct PlainLds { float red[NW * G * PART_STRIDE]; };
+template <int G, int NW> struct PlainLds { float red[G ? NW * G * PART_STRIDE : 1]; };
 template <int CMAX, int NT> struct FusedLds {
   QuickLds<NT> quick;
   SelectLds<CMAX, NT> general;
@@ -199,18 +199,23 @@ template <typename T, int G, int MODE, int CMAX, int NW, bool CACHED>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 2 : 1, 2))) void k_attn(const AttnArgs a) {
   constexpr bool FUSED = MODE != ATT_PLAIN;
   constexpr int NT = NW * 64, STEP = NW * ATT_TOKENS;
-  union Big {                                           // selection, later the wavefront partials
-    PlainLds<G, NW> plain;
-    typename std::conditional<FUSED, FusedLds<CMAX, NT>, PlainLds<G, NW>>::type fused;
+  constexpr bool BF16 = std::is_same<T, bf16>::value;
+  union Big {                                           // selection, later the wavefront partials (fp32)
+    PlainLds<BF16 ? 0 : G, NW> plain;
+    typename std::conditional<FUSED, FusedLds<CMAX, NT>, PlainLds<BF16 ? 0 : G, NW>>::type fused;
   };
   __shared__ Big big;
   __shared__ __attribute__((aligned(16))) int rows_lds[ATT_MAX_CHUNK];
   __shared__ __attribute__((aligned(16))) float sc_lds[MODE == ATT_FUSED_SCORE ? CMAX : 4];
-  __shared__ __attribute__((aligned(16))) bf16 stage_lds[std::is_same<T, bf16>::value ? NW * STAGE_ELEMS : 8];
+  __shared__ __attribute__((aligned(16))) bf16 stage_lds[BF16 ? NW * STAGE_ELEMS : 8];
   __shared__ int s_last;
   static_assert(!CACHED || (FUSED && std::is_same<T, bf16>::value), "cached steps select and are bf16");
   int* held = nullptr;                                  // cluster id -> first row in the previous generation, -1
-  float* red = big.plain.red;
+  // Partial of a wavefront: in bf16 where its rows changed lanes, which is its own, so that it need
+  // not wait for the others to be through with the selection.
+  constexpr int RED_STRIDE = BF16 ? STAGE_ELEMS / 2 : G * PART_STRIDE;
+  static_assert(RED_STRIDE >= G * PART_STRIDE, "partial in the staging area");
+  float* red = BF16 ? reinterpret_cast<float*>(stage_lds) : big.plain.red;
 
   // one argument per 64-byte line of the argument block: all lines are requested now
   CK_FETCH_ARG(a.q);
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
   if (hp >= a.HP) return;                               // the grid is padded to whole groups of 8
   const int s = hp / a.Hkv, h = hp % a.Hkv;
   const T* q = static_cast<const T*>(a.q);
-  const Stage16 stage(stage_lds + (std::is_same<T, bf16>::value ? wave * STAGE_ELEMS : 0), lane);
+  const Stage16 stage(stage_lds + (BF16 ? wave * STAGE_ELEMS : 0), lane);
 
   // the query heads of the group as an MFMA operand (bf16): for the scores and for q K^T
   bf16x8 qb[4];
@@ -465,8 +470,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
   wave_lds_order();
 
   const T* Vhp = static_cast<const T*>(a.V) + (int64_t)hp * a.N_cap * D + col * 8;
-  // a wavefront's LDS region for its partial: everything before it (the selection) is over
-  // for this workgroup only behind the barrier below
 
   if constexpr (std::is_same<T, bf16>::value) {
     // ---- bf16: both products on the matrix cores ----
@@ -628,18 +631,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
         }
       }
     }
-    if constexpr (FUSED) __syncthreads();               // the selection's LDS is free
+    wave_lds_order();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int g = kg * 4 + i;
       if (g < G) {
-        float* r = red + (wave * G + g) * PART_STRIDE + 2 + col * 8;
+        float* r = red + wave * RED_STRIDE + g * PART_STRIDE + 2 + col * 8;
 #pragma unroll
         for (int j = 0; j < 8; j += 2) *reinterpret_cast<float2*>(r + j) = make_float2(acc[j][i], acc[j + 1][i]);
       }
     }
     if (lane < G)
-      *reinterpret_cast<float2*>(red + (wave * G + lane) * PART_STRIDE) = make_float2(m_run, l_run);
+      *reinterpret_cast<float2*>(red + wave * RED_STRIDE + lane * PART_STRIDE) = make_float2(m_run, l_run);
   } else {
     // ---- fp32 check mode: dot products on the vector ALUs ----
     float acc[G][8];
@@ -734,7 +737,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[g][j] = xor32(xor16(acc[g][j] * w, OpSum()), OpSum());
       if (lane < 16) {
-        float* r = red + (wave * G + g) * PART_STRIDE;
+        float* r = red + wave * RED_STRIDE + g * PART_STRIDE;
         r[0] = mx;
         r[1] = ls;
 #pragma unroll
@@ -752,14 +755,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     float mx = NEG_BIG;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      ml[w] = *reinterpret_cast<const float2*>(red + (w * G + g) * PART_STRIDE);
+      ml[w] = *reinterpret_cast<const float2*>(red + w * RED_STRIDE + g * PART_STRIDE);
       mx = fmaxf(mx, ml[w].x);
     }
     float ls = 0.f, a0 = 0.f, a1 = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float f = __builtin_amdgcn_exp2f(ml[w].x - mx);
-      const float2 av = *reinterpret_cast<const float2*>(red + (w * G + g) * PART_STRIDE + 2 + c2);
+      const float2 av = *reinterpret_cast<const float2*>(red + w * RED_STRIDE + g * PART_STRIDE + 2 + c2);
       ls = fmaf(ml[w].y, f, ls);
       a0 = fmaf(av.x, f, a0);
       a1 = fmaf(av.y, f, a1);
