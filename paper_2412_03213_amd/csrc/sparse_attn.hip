@@ -163,7 +163,7 @@ struct AttnArgs {
   int32_t *sel_clusters, *n_sel_clusters, *n_sel_tokens, *token_idx_out, *n_tokens_out;
   int n_clusters, budget, trim, C_cap;
   // common
-  int HP, idx_stride, max_tokens, Hq, Hkv, n_sink, n_recent, chunk, n_split, two_pass;
+  int HP, idx_stride, max_tokens, Hq, Hkv, n_sink, n_recent, chunk, n_split, two_pass, spread;
   int64_t N_cap, recent_begin;
   float scale_log2e;
   CacheArgs cache;              // CACHED: K and V above are the home copy
@@ -233,7 +233,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6, col = lane & 15, kg = lane >> 4;
   const int wg = blockIdx.x, xcd = wg % N_XCD, seq = wg / N_XCD;
-  const int hp = (seq / a.n_split) * N_XCD + xcd, split = seq % a.n_split;
+  const bool spread = MODE == ATT_PLAIN && a.spread;    // see launch_attn_t
+  const int hp = spread ? wg % a.HP : (seq / a.n_split) * N_XCD + xcd;
+  const int split = spread ? wg / a.HP : seq % a.n_split;
   if (hp >= a.HP) return;                               // the grid is padded to whole groups of 8
   const int s = hp / a.Hkv, h = hp % a.Hkv;
   const T* q = static_cast<const T*>(a.q);
@@ -953,7 +955,12 @@ static hipError_t launch_attn_t(const Dims& dm, AttnArgs a, int64_t max_total, v
   a.tickets = reinterpret_cast<unsigned long long*>(workspace);
   a.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + ticket_bytes(dm));
   const int hp_groups = (dm.HP + N_XCD - 1) / N_XCD;
-  const dim3 grid((unsigned)hp_groups * N_XCD * n_split);
+  // Fewer head-problems than XCDs, no table to share and long rows: the splits of a head-problem go
+  // over all XCDs, whose share of the memory's rate is the limit otherwise.  Full attention, one XCD
+  // each / spread: 1 x 32864 tokens 21.6 / 16.7 us, 4 x 131072 79.2 / 55.6, 4 x 8192 14.4 / 12.8,
+  // but 2 x 2048 5.2 / 5.4 (the merge reads what another XCD wrote), a list of 256 rows 5.8 / 6.1.
+  a.spread = MODE == ATT_PLAIN && dm.HP < N_XCD && max_total > 2 * ATT_MAX_CHUNK;
+  const dim3 grid((unsigned)(a.spread ? dm.HP : hp_groups * N_XCD) * n_split);
   if constexpr (std::is_same<T, bf16>::value) {
     if (plan.waves == 8)
       launch_attn_waves<T, MODE, CMAX, 8, CACHED>(dm.G, grid, a, st);

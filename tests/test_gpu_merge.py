@@ -34,6 +34,9 @@ def make(S, Hq, Hkv, N, n_max, seed, dtype=torch.bfloat16):
     (8, 32, 8, 4096, 2048, ck.CK_BF16),      # 8 splits, 64 head-problems
     (3, 16, 2, 4096, 700, ck.CK_BF16),       # G = 8, head-problem count not a multiple of 8
     (2, 4, 4, 2048, 500, ck.CK_F32),         # fp32 check mode, G = 1
+    (1, 4, 1, 16384, 9000, ck.CK_BF16),      # few head-problems, long rows: splits over all XCDs
+    (1, 6, 3, 8192, 4097, ck.CK_BF16),       # the shortest such rows, three head-problems
+    (1, 7, 7, 8192, 5000, ck.CK_F32),        # in fp32
 ])
 def test_single_launch_merge_equals_two_pass(S, Hq, Hkv, N, n_max, dtype):
     tdt = torch.bfloat16 if dtype == ck.CK_BF16 else torch.float32
