@@ -9,8 +9,8 @@
 // space, and the fetch is issued by the GPU itself (16 lanes read one 256-byte row
 // over the host link), so that no miss list ever travels to the host and nothing
 // synchronises: selection, cache look-up, fetch and attention stay enqueued on one
-// stream.  In bf16 they are one launch (k_attn in its cached form); this kernel fills the
-// cache for the fp32 check mode, whose attention then runs over the dense rows of the step.
+// stream.  Steps of few rows in bf16 are one launch (k_attn in its cached form); this kernel
+// fills the cache for the others, whose attention then runs over the dense rows of the step.
 #include "decode_common.hpp"
 
 namespace ck {

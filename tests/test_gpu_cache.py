@@ -81,8 +81,10 @@ def test_cached_steps_equal_uncached_and_count_misses(home, S, Hkv, G, N, C, B):
 
 @pytest.mark.parametrize("S,Hkv,G,N,C,B", [(1, 2, 2, 600, 400, 300),     # more recalled clusters than lanes
                                            (1, 2, 4, 900, 600, 500),     # the same in the large form
-                                           (40, 8, 1, 200, 20, 100),     # more head-problems than CUs
-                                           (3, 1, 2, 9000, 90, 6000)])   # several steps of rows, many splits
+                                           (40, 8, 1, 100, 10, 40),      # more head-problems than CUs
+                                           (40, 8, 1, 200, 20, 100),     # the same by four launches
+                                           (1, 1, 2, 9000, 90, 6000),    # several steps of rows, many splits
+                                           (3, 1, 2, 9000, 90, 6000)])   # by four launches
 def test_cached_steps_in_other_forms(S, Hkv, G, N, C, B):
     test_cached_steps_equal_uncached_and_count_misses("device", S, Hkv, G, N, C, B)
 
