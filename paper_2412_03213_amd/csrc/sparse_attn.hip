@@ -8,9 +8,9 @@
 // tokens per step, 16 lanes loading a whole row.  In bf16 both products run on the
 // matrix cores (fp32 check mode keeps the all-VALU form): q K^T with the K rows, passed
 // through LDS, as the A operand; P V with operands that are already in the right lanes
-// (see the kernel).  One launch of the whole step takes 10.4 us at 8 head-problems, B = 1024
+// (see the kernel).  One launch of the whole step takes 10.1 us at 8 head-problems, B = 1024
 // (13.9 with K rows loaded in operand layout, P V on the vector ALUs and one wavefront
-// selecting) and 20.5 at 64, B = 2048 (25.5), of which the row stream at 6.4 TB/s is half;
+// selecting) and 20.3 at 64, B = 2048 (25.5), of which the row stream at 6.4 TB/s is half;
 // the rest is a chain of dependent round trips.  The attended positions of a head-problem are
 // split over several workgroups (split-KV) so that a batch of a few sequences still fills 256
 // CUs, and never over more than are resident together (attn_plan).  Inside a workgroup every
@@ -858,6 +858,7 @@ __global__ __launch_bounds__(D / 2) void k_attn_merge(const float* __restrict__ 
 //  - above 256 head-problems workgroups follow each other anyway: four wavefronts, one
 //    workgroup selecting while the other streams, and three splits up to 320, where whole
 //    head-problems would leave half of the places empty.
+// (The figures are from before the partials lost a barrier, 0.1 to 0.3 us on either side.)
 // Microseconds of the fused step, eight / four wavefronts, each at its best number of splits of
 // one round, and [eight wavefronts with ceil(256 / HP) splits, which is a second round for a few]:
 //   HP            8           24           40           56           88           120
