@@ -330,6 +330,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     }
     n_idx = sel.n_tok;
     if constexpr (CACHED) {
+      // A prefix of whole clusters fits the budget; where sizes that are no sizes make its sum wrap, no
+      // row behind it is stored all the same.
+      n_idx = n_idx < a.budget ? n_idx : a.budget;
       held = reinterpret_cast<int*>(L.key);             // the selection is through with it
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i) held[tid + i * NT] = -1;

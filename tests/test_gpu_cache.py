@@ -105,6 +105,38 @@ def test_a_smaller_table_than_at_the_step_before():
     assert int(st.n_sel_clusters) == 300 and int(cache.miss_tokens) == 0
 
 
+def test_no_row_is_stored_behind_the_budget():
+    """Sizes whose sums wrap make the selection's prefix seem longer than the budget (2000 rows of
+    the first cluster, a sum below zero with the second, 1998 with the third): the cached rows end
+    at the budget all the same.  The guarded tail holds every row a workgroup could reach."""
+    N, B, HP, tail = 2048, 1000, 2, 256
+    sh = ck.Shape(1, HP, HP, N, 8)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    K, V = (torch.randn(1, HP, N, 128, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.zeros(1, HP, 128, dtype=torch.bfloat16, device=DEV)
+    q[..., 0] = 1
+    st = ck.ClusterState(sh, DEV, budget=B)
+    st.n_clusters = 8
+    st.centroids[:, :, :3, 0] = torch.tensor([10., 10., 5.], device=DEV).to(torch.bfloat16)
+    st.sizes[:, :, :3] = torch.tensor([2000, 2 ** 31 - 1, 2 ** 31 - 1], device=DEV).int()
+    st.sorted_idx[:] = torch.arange(N, device=DEV).int()
+
+    cache = ck.ClusterCache(sh, DEV, cap_tokens=B)
+    guards = []
+    for rows in (cache.K, cache.V):
+        for i in range(2):
+            buf = torch.full((HP * B + tail, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+            rows[i] = buf[:HP * B].view(1, HP, B, 128)
+            guards.append(buf[HP * B:])
+    ck.cached_decode_step(st, cache, q, K, V)
+    torch.cuda.synchronize()
+    assert (st.n_sel_tokens == B).all()
+    for guard in guards:
+        assert (guard == 7).all()
+    # its trailing rows, as a cut cluster keeps them
+    assert torch.equal(cache.K[0], K[:, :, 1000:2000]) and torch.equal(cache.V[0], V[:, :, 1000:2000])
+
+
 def test_same_query_twice_is_all_hits_and_reset_empties():
     cfg = Config("cache2", 1, 1, 2, 8, 128, 4096, 64, 51, 10, 1024, 4)
     w, sh, st = clustered(cfg)
