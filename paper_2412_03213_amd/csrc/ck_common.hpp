@@ -223,6 +223,7 @@ hipError_t launch_update(const Dims& dm, const bf16* K, const int32_t* offsets,
                          int bias_stride, const int32_t* gate, hipStream_t st);
 // the same update straight from the chunk index of the assignment, no sorted list needed
 bool update_chunks_fits(const Dims& dm, int64_t tok_count);
+int update_clusters_per_workgroup(int n_chunks, int c_count, int hp);
 hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,

@@ -487,7 +487,7 @@ struct ChunkRuns {
 // shapes and 3 us slower on the small one; two wavefronts per cluster are slower everywhere.
 // Four clusters share the lines of the run table (a cluster uses 4 bytes of each: 420 MB through the
 // L2s for 13 MB of words at 8 x 131072 x 1600) and one's rows travel while the next one's members
-// are looked up; see launch_update_chunks for where that pays.
+// are looked up; see update_clusters_per_workgroup for where that pays.
 constexpr int UPC_WAVES = 4;
 constexpr int UPC_STEPS = 8;                            // 16-row steps whose loads are in flight together
 
@@ -641,19 +641,29 @@ static size_t chunk_runs_lds(int clusters, int n_chunks) {
   return (size_t)clusters * 2 * ((n_chunks + 63) & ~63) * sizeof(uint32_t);
 }
 
+// Four clusters to a workgroup where the run table weighs as much as the keys.  A cluster on its own
+// fetches a line of 128 bytes per chunk of 512 tokens and 256 bytes per member, so the table's share
+// grows with the clusters: it is three quarters of the rows at 768.  Below 2M words (lines of 256 MB in
+// all, the Infinity Cache) the lines come fast and the longer workgroups cost more than they spare, and
+// up to 128 chunks a table is scanned in two steps.  One / four, us per launch: 8 x 131072 x 1600
+// 56.8 / 50.9, 16 x 131072 x 819 118.3 / 113.2, 12 x 98304 x 1200 68.5 / 63.9, 6 x 196608 x 1012
+// 63.1 / 59.8, 5 x 262144 x 1016 77.0 / 69.3, but with few clusters 16 x 131072 x 400 103.9 / 107.9,
+// 9 x 262144 x 510 121.0 / 124.8, with few words 4 x 131072 x 1600 26.7 / 28.5, 8 x 131072 x 819
+// 48.9 / 49.8, 4 x 262144 x 1014 50.3 / 51.7, and with 128 chunks 24 x 65536 x 800 89.9 / 90.5 and ten
+// iterations of 16 x 65536 x 800 2202 / 2221.  With 144 and 160 chunks either is up to 3 % faster.
+int update_clusters_per_workgroup(int n_chunks, int c_count, int hp) {
+  return n_chunks > 128 && c_count >= 768 && (int64_t)n_chunks * c_count * hp >= 1 << 21 ? 4 : 1;
+}
+
 hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
                                 float* bias, int bias_stride, const int32_t* gate, hipStream_t st) {
   const int chunk_tokens = assign_tile_tokens(dm, tok_count);
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
-  // Four clusters per workgroup where a cluster's runs are many and there are workgroups enough for
-  // several rounds all the same.  Ten iterations, one / four: 8 x 131072 x 1600 (256 chunks) 3671 /
-  // 3608 us, 16 x 65536 x 800 (128 chunks) 2166 / 2154, but 4 x 100000 x 1250 (5000 clusters) 1421 /
-  // 1430, 64 x 16384 x 200 (32 chunks) 1079 / 1095, 8 x 32768 x 400 457 / 478.
-  const bool four = n_chunks >= 128 && (int64_t)c_count * dm.HP >= 10240;
-  const int cl = four ? 4 : 1, groups = ((c_count + cl - 1) / cl + 7) / 8 * 8;
-  hipLaunchKernelGGL(four ? k_update_chunks<4> : k_update_chunks<1>, dim3(groups, dm.HP), dim3(UPC_WAVES * 64),
+  const int cl = update_clusters_per_workgroup(n_chunks, c_count, dm.HP);
+  const int groups = ((c_count + cl - 1) / cl + 7) / 8 * 8;
+  hipLaunchKernelGGL(cl == 4 ? k_update_chunks<4> : k_update_chunks<1>, dim3(groups, dm.HP), dim3(UPC_WAVES * 64),
                      chunk_runs_lds(cl, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
                      chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin, c_count,
                      centroids, mu_hat, sizes, metric, bias, bias_stride, gate);

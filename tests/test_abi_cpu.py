@@ -332,3 +332,19 @@ def test_decode_step_refuses_the_same_calls_on_either_way(change, error):
     finally:
         lib.host_decode_step = real
     assert str(native.value) == str(general.value)
+
+
+def test_form_of_the_chunk_update():
+    """The launcher's choice between one cluster and four per workgroup, on both sides of each of
+    its lines, and that the GPU tests of the second form are in it."""
+    rule = ck.load_library()._ZN2ck29update_clusters_per_workgroupEiii
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 3
+    assert rule(256, 1600, 8) == 4 and rule(129, 2048, 8) == 4
+    assert rule(128, 2048, 64) == 1                     # few chunks
+    assert rule(512, 767, 64) == 1 and rule(512, 768, 64) == 4
+    assert rule(512, 2048, 1) == 1 and rule(512, 2048, 2) == 4
+    assert rule(512, 2048, 65535) == 4                  # the product of all three is beyond 32 bits
+    from tests.test_gpu_chunk_update import FOUR
+    for S, Hkv, N, C, begin, _ in FOUR:
+        assert (N - begin) * S * Hkv >= 65536           # chunks of 512 tokens
+        assert rule((N - begin + 511) // 512, C, S * Hkv) == 4 and C % 4

@@ -23,8 +23,11 @@ SHAPES = [
     (1, 2, 262700, 512, 7, 3),       # the same with the largest LDS-resident table
     (1, 1, 263681, 1100, 0, 0),      # and with the table streamed in chunks
     (1, 2, 2300, 2048, 0, 0),        # most clusters, many of them of one member or empty
-    (5, 1, 65530, 2047, 0, 0),       # four clusters to a workgroup of the update, three in the last
+    (5, 1, 65530, 2047, 0, 0),       # 128 chunks, the most that are scanned in two steps
+    (8, 1, 66053, 2047, 3, 1),       # four clusters to a workgroup of the update, three in the last
+    (4, 2, 66049, 2045, 0, 0),       # the same with one in the last
 ]
+FOUR = SHAPES[-2:]                   # see test_abi_cpu.py: they are in the form that they are here for
 
 
 @pytest.mark.parametrize("S,Hkv,N,C,begin,c_begin", SHAPES)
