@@ -59,3 +59,28 @@ def test_iterations_leave_consistent_metadata(hp, n, C):
     assert torch.equal(st.sizes[0].long(), sizes)
     assert torch.equal(st.offsets[0, :, 1:].long(), sizes.cumsum(1))
     assert torch.equal(st.sorted_idx[0].long(), lab.sort(dim=1, stable=True).indices)
+
+
+@pytest.mark.parametrize("hp,n,C", [(1, 65537, 513), (2, 32801, 2047),      # k_assign_wide with its bias table
+                                    (1, 65537, 511), (8, 8193, 100),        # k_assign_stream
+                                    (1, 2500, 2047), (2, 385, 9)])          # k_assign
+def test_l2_labels_against_64_bits(hp, n, C):
+    """One iteration by l2 assigns every key to the nearest of the given rows.  A similarity
+    x mu - |mu|^2 / 2 is off by at most 128 * 2^-24 of |x| |mu| + |mu|^2 / 2 (fp32 sums of exact
+    products) and 2^-19 of itself (packed maximum): 1e-5, and two are compared."""
+    g = torch.Generator(device=DEV).manual_seed(n * C)
+    K = torch.randn(1, hp, n + 2, 128, generator=g, device=DEV).to(torch.bfloat16)
+    init = (torch.rand(1, hp, n, generator=g, device=DEV).topk(C, dim=-1).indices + 2).int()
+    st = ck.ClusterState(ck.Shape(1, hp, hp, n + 2, C), DEV, budget=64)
+    st.cluster(K, init, 2, n, C, 1, ck.CK_METRIC_L2)
+    torch.cuda.synchronize()
+    ties = 0
+    for h in range(hp):
+        keys, mu = K[0, h, 2:].double(), K[0, h][init[0, h].long()].double()
+        two = (keys @ mu.T - mu.square().sum(-1) / 2).topk(2, dim=-1)
+        longest = mu.norm(dim=-1).max()
+        near = two.values[:, 0] - two.values[:, 1] < 2 ** -15 * (keys.norm(dim=-1) + longest / 2) * longest
+        wrong = st.labels[0, h, 2:] != two.indices[:, 0]
+        assert not (wrong & ~near).any(), h
+        ties += int(near.sum())
+    assert ties < 0.01 * hp * n

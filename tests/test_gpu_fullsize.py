@@ -237,10 +237,10 @@ def test_assignment_chunk_streaming_kernel_all_keys_teacher_forced(C):
 @pytest.mark.parametrize("S,Hkv,C", [(1, 2, 200), (2, 8, 200), (1, 2, 600), (2, 8, 600)])
 def test_l2_assignment_large_tiles_all_keys(S, Hkv, C):
     """The l2 metric (bias -|mu|^2/2 added in the assignment read-out) at 32768 tokens per
-    head-problem: C = 200 takes the streaming kernel (table in LDS), C = 600 the
-    chunk-streaming one, with 2 head-problems in its eight-wavefront form and with 16 in
-    its four-wavefront form.  One iteration from the given initial rows is a teacher-forced
-    assignment: the labels must be the oracle's nearest stored centroid off near-ties."""
+    head-problem: C = 200 takes the streaming kernel (table in LDS), C = 600 the wide one
+    (tiles through a ring in LDS), with 128 workgroups and with 1024.  One iteration from the
+    given initial rows is a teacher-forced assignment: the labels must be the oracle's nearest
+    stored centroid off near-ties."""
     N = 32768
     cfg = Config("l2_big", 1, S, Hkv, Hkv, 128, N, 256, C, 1, 256, seed=31 + S)
     w = MixtureWorkload(cfg, device=DEV)
