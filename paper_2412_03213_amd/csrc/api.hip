@@ -756,10 +756,15 @@ int ck_cached_decode_step(const ck_shape* sh, const void* q, const void* K_home,
   a.C_cap = dm.C_cap;
   a.cap = cache->cap_tokens;
   a.row_bytes = dm.dtype == CK_BF16 ? 256 : 512;
-  // One launch for the whole step where its rows are few: from about 10 MB on, a grid that has all of
-  // its rows under way at once gets less out of the host link than the fill kernel.  Four launches /
-  // one, us per step: 8 x 1024 rows 86 / 77, 8 x 2048 154 / 150, 16 x 1024 146 / 141, 32 x 512
-  // 131 / 126, but 32 x 1024 252 / 261, 16 x 2048 269 / 286, 32 x 1918 479 / 488, 128 x 700 635 / 645.
+  // One launch for the whole step where its rows are few.  It spares 10 to 13 us of launches, but a grid
+  // that has all of its rows under way at once gets up to 12 % less out of the host link than the fill
+  // kernel.  Four launches / one, us per step with nothing held and with everything held:
+  //   8 x 1024 rows 105 / 92, 27 / 14     2 x 4096 110 / 112, 31 / 19    16 x 1024 176 / 174, 29 / 16
+  //   4 x 2048      108 / 103, 28 / 15    4 x 4096 183 / 192, 31 / 19    64 x 256  158 / 163, 26 / 14
+  //   8 x 2048      177 / 181, 29 / 16    1 x 16384 201 / 203, 47 / 38   256 x 64  120 / 127, 23 / 15
+  // So close to the line one launch loses a few us on an empty cache and is even from a quarter of the rows
+  // held on (at 4 x 4096 from half).  Beyond it the link is all: 32 x 1024 252 / 261, 16 x 2048 269 / 286,
+  // 32 x 1918 479 / 488, 128 x 700 635 / 645.
   if (dm.dtype == CK_BF16 && (int64_t)dm.HP * budget <= 16384)
     return hip_result(ck::launch_cached_step(dm, q, centroids, n_clusters, budget, softmax_scale, scores,
                                              sel_clusters, n_sel_clusters, n_sel_tokens, a, out,

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   int diff = 0;
   const bf16* arow0 = table + col * LDS_ROW + half * 8; // this lane's A fragments of tile 0
 
-  // One block of 128 keys against every centroid tile, then its labels.
+  // One task, 64 keys against every centroid tile, then its labels.
   auto process = [&](int b, const bf16x8 (&bk)[NKB][8], int nxt, bf16x8 (&nk)[NKB][8]) {
     const int64_t wave_tok0 = wg_tok0 + (int64_t)b * (NKB * 32);
     if (wave_tok0 >= tok_count) return;                 // wave-uniform: nothing of this block exists
@@ -305,11 +305,14 @@ hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin
                                 int64_t tok_count, const bf16* mu_hat, int c_begin, int c_count,
                                 int32_t* labels, float* best_sim, const ChunkIndex& chunks,
                                 const KmCtl& ctl, int n_cu, hipStream_t st) {
-  // Blocks of 512 tokens per workgroup (at most 8: one wavefront each for the chunk index): the
-  // number with the least rounds of workgroups (one per CU) times blocks and start-up of a round,
-  // which takes about as long as a block (C = 102: 6 us and 5.2, C = 400: 8 and 9.4).  Filling the
-  // CUs once with floor(chunks / CUs) blocks instead, a few workgroups more than CUs are a second
-  // round: 8 x 40000 x 416 764 us for ten iterations, now 545; 64 x 20000 x 250 1851, now 1632.
+  // Blocks of 512 tokens per workgroup (at most 8: the chunk index is sorted by one wavefront a block
+  // at least): the number with the least rounds of workgroups (one per CU) times blocks and start-up
+  // of a round, which takes about as long as a block (C = 102: 6 us and 5.2, C = 400: 8 and 9.4).
+  // Filling the CUs once with floor(chunks / CUs) blocks instead, a few workgroups more than CUs are a
+  // second round: 8 x 40000 x 416 764 us for ten iterations, now 545; 64 x 20000 x 250 1851, now 1632;
+  // 20 x 65536 x 100 1446 / 1352, 24 x 65536 x 400 2415 / 2373.  Where the keys are more than the
+  // Infinity Cache and the products few, the rounds overlap better than that: 24 x 65536 x 100 is 1.3 %
+  // slower than with floor (1660 / 1681), x 129 2.3 % (1707 / 1747).
   const int64_t chunks_hp = (tok_count + ST_CHUNK - 1) / ST_CHUNK;
   int64_t blocks = 1, least = INT64_MAX;
   for (int64_t b = 1; b <= ST_MAX_BLOCKS && b <= chunks_hp; ++b) {

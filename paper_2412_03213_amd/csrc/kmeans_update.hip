@@ -485,8 +485,8 @@ struct ChunkRuns {
 // 8 x 131072 x 1600 407 -> 399, 8 x 2985 x 37 15.8 -> 9.9.  One wavefront per cluster with
 // four accumulator sets (one to eight clusters per workgroup) is within 2 % on the large
 // shapes and 3 us slower on the small one; two wavefronts per cluster are slower everywhere.
-// Four clusters share the lines of the run table (a cluster uses 4 bytes of each: 420 MB through the
-// L2s for 13 MB of words at 8 x 131072 x 1600) and one's rows travel while the next one's members
+// Four clusters share the lines of the run table (a cluster uses 4 bytes of each: lines of 420 MB
+// for 13 MB of words at 8 x 131072 x 1600) and one's rows travel while the next one's members
 // are looked up; see update_clusters_per_workgroup for where that pays.
 constexpr int UPC_WAVES = 4;
 constexpr int UPC_STEPS = 8;                            // 16-row steps whose loads are in flight together

@@ -185,8 +185,8 @@ __device__ __forceinline__ float row_bcast(float v) {
 // Position i of a workgroup belongs to wavefront (i / 16) % NW.
 // One-dimensional grid: workgroup i runs on XCD i % 8 (round-robin dispatch), so the
 // n_split workgroups of a head-problem are given ids of one residue class and share
-// that XCD's L2 (sizes, offsets, scores or the centroid table).  Placement only affects
-// speed, never results.
+// that XCD's L2 (sizes, offsets, scores or the centroid table), except where launch_attn_t
+// spreads them over all XCDs.  Placement only affects speed, never results.
 // (Two wavefronts per SIMD is what the row stream's registers allow; the attribute keeps the
 // compiler from aiming higher and spilling.)
 // CACHED: the step over a home copy in host memory and the cluster cache (see cluster_cache.hip).  A
@@ -848,8 +848,8 @@ __global__ __launch_bounds__(D / 2) void k_attn_merge(const float* __restrict__ 
 // How a call is spread over the chip.  All forms of the step take the same rule: the split
 // boundaries fix the order of the fp32 sums, and they must give the same bits.
 //
-// All splits of a head-problem run on one XCD, ceil(HP / 8) head-problems share it, and the
-// registers allow two wavefronts per SIMD: 32 workgroups of eight wavefronts or 64 of four are
+// All splits of a head-problem run on one XCD (those that launch_attn_t spreads are counted the same),
+// ceil(HP / 8) head-problems share it, and the registers allow two wavefronts per SIMD: 32 workgroups of eight wavefronts or 64 of four are
 // resident on an XCD together.  One more and it runs its whole chain -- scoring, selection, rows
 // -- after the others are through, so a call takes as many splits as fit in ONE round:
 //  - eight wavefronts if they do: every phase is spread over the whole CU and fewer splits
@@ -876,9 +876,12 @@ __global__ __launch_bounds__(D / 2) void k_attn_merge(const float* __restrict__ 
 // Four wavefronts, one / two / three splits: HP = 264: 38.3 / 40.1 / 37.3 and 71.8 / 69.2 / 61.8,
 // 320: 41.5 / 42.6 / 41.7 and 77.5 / 76.0 / 73.5, 352: 43.4 / 45.9 / 46.1 and 82.3 / 82.5 / 87.5;
 // full attention over 2048 tokens at HP = 264: 57.9 / 54.8 / 48.8, 352: 65.2 / 68.1 / 69.4.
-// Full attention over 32864 tokens, eight / four: HP = 1: 21.8 / 24.9 (64 splits of eight, two rounds:
-// 28.1), 8: 27.0 / 27.0, 12: 42.4 / 39.7, 24: 80.7 / 78.7; 32: 104.5 / 113.2 and 40: 129.9 / 134.1 are
-// more than one round either way.
+// Full attention over 32864 tokens, eight / four: 8: 27.0 / 27.0, 12: 42.4 / 39.7, 24: 80.7 / 78.7;
+// 32: 104.5 / 113.2 and 40: 129.9 / 134.1 are more than one round either way.
+// Spread splits (HP < 8, long rows) would find 256 places for eight wavefronts, not 32 per head-problem,
+// but more of them have to be merged.  Full attention, this rule / 256 / HP splits: 1 x 8192 tokens
+// 9.2 / 10.8, 1 x 32864 16.8 / 20.8, 1 x 131072 37.2 / 37.6, 4 x 8192 10.8 / 14.2, 4 x 131072 56.2 /
+// 55.7, 7 x 32864 27.8 / 29.2, and ahead only at 3 x 50000 27.0 / 25.4 and 7 x 131072 97.3 / 92.5.
 struct AttnPlan {
   int waves;        // wavefronts per workgroup
   int max_splits;   // grows with the attended total: a workspace sized for more holds less
