@@ -762,7 +762,7 @@ int ck_cached_decode_step(const ck_shape* sh, const void* q, const void* K_home,
   //   8 x 1024 rows 105 / 92, 27 / 14     2 x 4096 110 / 112, 31 / 19    16 x 1024 176 / 174, 29 / 16
   //   4 x 2048      108 / 103, 28 / 15    4 x 4096 183 / 192, 31 / 19    64 x 256  158 / 163, 26 / 14
   //   8 x 2048      177 / 181, 29 / 16    1 x 16384 201 / 203, 47 / 38   256 x 64  120 / 127, 23 / 15
-  // So close to the line one launch loses a few us on an empty cache and is even from a quarter of the rows
+  // So close to the line one launch loses up to 9 % on an empty cache and is even from a quarter of the rows
   // held on (at 4 x 4096 from half).  Beyond it the link is all: 32 x 1024 252 / 261, 16 x 2048 269 / 286,
   // 32 x 1918 479 / 488, 128 x 700 635 / 645.
   if (dm.dtype == CK_BF16 && (int64_t)dm.HP * budget <= 16384)

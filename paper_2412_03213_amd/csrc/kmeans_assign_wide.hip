@@ -23,8 +23,8 @@ constexpr int WD_LDS_ROW = D + 8;                       // 272 B: rows shift 4 b
 // block before cut into slices between them; the loads and stores of the staging are such slices
 // too (issued between two blocks they left the matrix pipe idle: 104 000 cycles for the loop at
 // C = 2000 with one wavefront per SIMD, 89 000 in slices, 64 500 of matrix work).
-// Bound: the clock.  With both workgroups in their loops the matrix pipe is busy more than 80 % of
-// the time, and the chip lowers its clock to 1.6-1.7 GHz for it (2.2 GHz on constant keys).
+// Bound: the clock.  The matrix pipe is busy 80 % of the kernel's cycles (8 x 131072 x 1600, counters),
+// and the chip lowers its clock to 1.6-1.7 GHz for it (2.2 GHz on constant keys).
 // It takes the place of a kernel with eight wavefronts, a barrier every second tile and the
 // read-out behind the MFMAs, which ran at 2.05 GHz with the pipe 54 % busy.  Ten iterations, whole
 // call: 8 x 131072 x 1600 4048 us, now 3750; 4 x 100000 x 1250 1550 / 1445; 16 x 65536 x 800

@@ -642,15 +642,16 @@ static size_t chunk_runs_lds(int clusters, int n_chunks) {
 }
 
 // Four clusters to a workgroup where the run table weighs as much as the keys.  A cluster on its own
-// fetches a line of 128 bytes per chunk of 512 tokens and 256 bytes per member, so the table's share
-// grows with the clusters: it is three quarters of the rows at 768.  Below 2M words (lines of 256 MB in
-// all, the Infinity Cache) the lines come fast and the longer workgroups cost more than they spare, and
-// up to 128 chunks a table is scanned in two steps.  One / four, us per launch: 8 x 131072 x 1600
-// 56.8 / 50.9, 16 x 131072 x 819 118.3 / 113.2, 12 x 98304 x 1200 68.5 / 63.9, 6 x 196608 x 1012
-// 63.1 / 59.8, 5 x 262144 x 1016 77.0 / 69.3, but with few clusters 16 x 131072 x 400 103.9 / 107.9,
-// 9 x 262144 x 510 121.0 / 124.8, with few words 4 x 131072 x 1600 26.7 / 28.5, 8 x 131072 x 819
-// 48.9 / 49.8, 4 x 262144 x 1014 50.3 / 51.7, and with 128 chunks 24 x 65536 x 800 89.9 / 90.5 and ten
-// iterations of 16 x 65536 x 800 2202 / 2221.  With 144 and 160 chunks either is up to 3 % faster.
+// requests a line of 128 bytes per chunk of 512 tokens (6.28 M requests to the L2s at 8 x 131072 x 1600,
+// 3.97 M with four, the same bytes from HBM) and 256 bytes per member, so the table's share grows with
+// the clusters: it is three quarters of the rows' at 768.  Below 2M words, launches of about 50 us and
+// less, the longer workgroups cost more than they spare, and up to 128 chunks a table is scanned in
+// two steps.  One / four, us per launch: 8 x 131072 x 1600 56.8 / 50.9, 16 x 131072 x 819
+// 118.3 / 113.2, 12 x 98304 x 1200 68.5 / 63.9, 6 x 196608 x 1012 63.1 / 59.8, 5 x 262144 x 1016
+// 77.0 / 69.3, but with few clusters 16 x 131072 x 400 103.9 / 107.9, 9 x 262144 x 510 121.0 / 124.8,
+// with few words 4 x 131072 x 1600 26.7 / 28.5, 8 x 131072 x 819 48.9 / 49.8, 4 x 262144 x 1014
+// 50.3 / 51.7, and with 128 chunks 24 x 65536 x 800 89.9 / 90.5 and ten iterations of 16 x 65536 x 800
+// 2202 / 2221.  With 144 and 160 chunks either is up to 4 % faster.
 int update_clusters_per_workgroup(int n_chunks, int c_count, int hp) {
   return n_chunks > 128 && c_count >= 768 && (int64_t)n_chunks * c_count * hp >= 1 << 21 ? 4 : 1;
 }
