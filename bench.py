@@ -277,7 +277,8 @@ def cpu_baseline_other_configs(budget_s=12.0):
 def counter_legs(cfg, w, st, sh, q, cluster, decode):
     """A 1 GiB device copy (the calibration of the byte counters), then three launches of
     every kernel of the 32k layer (clustering, the assignment alone, the decode step, the
-    attention alone) and of the batch-8 layer (64 head-problems, B = 2048)."""
+    attention alone), of the batch-8 layer (64 head-problems, B = 2048) and of the 128k layer,
+    and three cached steps of the 32k layer on an empty cache."""
     import torch
     import paper_2412_03213_amd as ck
     from ck_synth import Config, MixtureWorkload, get_config, sample_init_indices
@@ -321,8 +322,33 @@ def counter_legs(cfg, w, st, sh, q, cluster, decode):
         st8.cluster(w8.K, init8, 0, cfg8.N, cfg8.C, cfg8.n_iter)
 
     legs(cfg8, w8, st8, sh8, q8, cluster8, lambda: ck.decode_step(st8, q8, w8.K, w8.V))
+    del w8, st8, init8
+    cfgL = get_config("long_context_128k")
+    wL = MixtureWorkload(cfgL, device=dev)
+    wL.token_center = None
+    initL = sample_init_indices(wL.K, cfgL.C, cfgL.seed).to(dev)
+    shL = ck.Shape(cfgL.S, cfgL.Hq, cfgL.Hkv, cfgL.N, cfgL.C)
+    stL = ck.ClusterState(shL, dev, budget=cfgL.B)
+    qL = wL.query()
+
+    def clusterL():
+        stL.n_clusters = 0
+        stL.cluster(wL.K, initL, 0, cfgL.N, cfgL.C, cfgL.n_iter)
+
+    legs(cfgL, wL, stL, shL, qL, clusterL, lambda: ck.decode_step(stL, qL, wL.K, wL.V))
+    home = []
+    for t in (w.K, w.V):
+        h = torch.empty(t.shape, dtype=t.dtype, pin_memory=True)
+        h.copy_(t)
+        home.append(h)
+    addr = [ck.ck_host_device_ptr(h) for h in home]
+    cache = ck.ClusterCache(sh, dev, cap_tokens=cfg.B)
+    for _ in range(3):
+        ck.ck_cache_reset(sh, cache)
+        ck.cached_decode_step(st, cache, q, *addr)
+    torch.cuda.synchronize()
     print(json.dumps({"counter_legs": "done", "workloads": [cfg.name, "batch-8 layer (64 "
-                      "head-problems, N=32768, C=400, B=2048)"]}))
+                      "head-problems, N=32768, C=400, B=2048)", cfgL.name, "cached step"]}))
 
 
 def graph_ms(fn, reps, per_graph=1):
