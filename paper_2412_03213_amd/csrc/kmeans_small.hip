@@ -7,10 +7,15 @@
 // Same arithmetic rules as the large path: bf16-rounded table rows compared in fp32,
 // ties to the lower id, fp32 sums in a fixed order, means of raw keys, an empty cluster
 // keeps its centroid.
+#include <type_traits>
+
 #include "ck_common.hpp"
 
 namespace ck {
 
+// Up to here the products have sixteen columns per wavefront (of 1024 threads) instead of 32: a branch
+// in the one kernel costs the large ranges registers (320 tokens 30.9 -> 31.8 us).
+constexpr int KM_SMALL_FEW_TOKENS = 256;
 
 struct SmallArgs {
   const bf16* K;
@@ -21,63 +26,97 @@ struct SmallArgs {
   int tok_count, C_cap, c_begin, c_count, max_iter, metric, converge;
 };
 
-// MAXC: compile-time bound of the cluster count; SM_THREADS: workgroup size.
+// By how much two similarities of a key may differ from what another order of their additions gives:
+// this factor, from the squared length of the key, times the length of the longest table row.  Every
+// partial sum is at most |k| |row|, and 128 additions, be they rounded or cut off, are off by 2^-23
+// of that each; the fixed order has a chain of twelve.  Lengths below 2^-60 count as 2^-60 (products
+// that the matrix cores take for zero), those of 2^50 and more as infinite (sums that overflow).
+__device__ __forceinline__ float key_bound(float n2) {
+  const float n = 1.001f * sqrtf(n2);
+  return n < 0x1p50f ? 0x1.1p-15f * fmaxf(n, 0x1p-60f) : INFINITY;
+}
+__device__ __forceinline__ float row_bound(float n) {
+  n *= 1.001f;
+  return n < 0x1p49f ? fmaxf(n, 0x1p-60f) : INFINITY;
+}
+
+// MAXC: compile-time bound of the cluster count; SM_THREADS: workgroup size; MAXTOK: bound of the range.
 //
-// Bound: a chain of max_iter dependent iterations on one CU per head-problem, each of them VALU
-// and cross-lane work on n_tok * C dot products.  Both halves of an iteration run on
-// v_mfma_f32_4x4x1_16b_f32 (16 independent 4 x 4 outer products, one fp32 multiply-add per
-// element and step, so the additions happen one by one in the order written here):
-//   dot products  block = eight channels of a key (one per step), rows = 4 clusters, columns = 4
-//                 keys: 8 steps replace 32 multiply-adds, and the sixteen partial sums of a
-//                 (key, cluster) are added by lane swaps that halve the registers on the way;
-//   update sums   block = four lanes of one key, rows = 4 clusters, A = 1 where the key's label
-//                 is the row's cluster: 8 steps replace 32 multiply-adds.
+// Bound: a chain of max_iter dependent iterations on one CU per head-problem, and in each the
+// instructions of sixteen wavefronts on four SIMDs.
+//   labels        v_mfma_f32_16x16x32_bf16, rows = the clusters (four, repeated, so that every lane has
+//                 all similarities of its key and the best of them needs no lane exchange), columns =
+//                 16 keys of the wavefront.  Where best and second are too close for the order of the
+//                 additions not to matter, the fixed order decides (exact_label; 1 key in 3000 of a
+//                 mixture), so the labels are those of the fixed order.
+//   update sums   v_mfma_f32_4x4x1_16b_f32, one fp32 addition per element and step, in the order
+//                 written here: block = four lanes of one key, rows = 4 clusters, A = 1 where the
+//                 key's label is the row's cluster; 8 steps replace 32 multiply-adds.
 // A wavefront keeps its keys in registers in both layouts for all iterations (no LDS pass over
 // the keys).  The wavefront of a cluster adds up that cluster's partial sums, keeps its mean in
-// registers and makes the next table row from it, so an iteration has two barriers.
-// 128 head-problems x 320 tokens x 4 clusters, 10 iterations: 85.3 -> 56.6 us, same bits; 53.0 since
-// a wavefront whose keys have all kept their labels leaves its sums of the iteration before standing
-// (a mixture of 128 centers: labels settle after 5 to 20 iterations, 9.7 on average).
-// MAXC = 2 is a form of its own: rows 2 and 3 of the products are idle there, and with the lane
-// exchanges of four clusters it was slower than the vector ALUs (352 tokens x 2 clusters: 55.6 us on
-// the vector ALUs, 62.8 as four clusters, 52.9 now; 100 tokens: 38.6, 33.1, 28.3).
-template <int MAXC, int SM_THREADS>
+// registers and makes the next table row from it, so an iteration has two barriers.  A wavefront whose
+// keys have all kept their labels leaves its sums of the iteration before standing.
+// 128 head-problems x 320 tokens x 4 clusters, 10 iterations: 53.7 us with the dot products too as
+// 4x4x1 steps (sixteen partial sums per key and cluster, added by lane swaps), 35.4 with the labels as
+// above, 32.7 with the operands of a round's sums made before its first product, 30.3 with all columns'
+// products issued together; same bits.  160 tokens 34.7 -> 20.1, 320 tokens x 8 clusters 90.9 -> 49.2,
+// x 2 45.9 -> 27.0.
+// MAXC = 2 is a form of its own: half the registers and lane exchanges of the sums.
+template <int MAXC, int SM_THREADS, int MAXTOK>
 __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) {
   constexpr int WAVES = SM_THREADS / WAVE, SETS = (MAXC + 3) / 4, ROWS = 4 * SETS;
   constexpr int KEYS = WAVES * 4;                       // keys per round, four per wavefront
-  constexpr int ROUNDS = (KM_SMALL_MAX_TOKENS + KEYS - 1) / KEYS;
-  static_assert((MAXC == 2 || MAXC % 4 == 0) && MAXC <= WAVES && KM_SMALL_MAX_TOKENS <= SM_THREADS, "mapping");
-  __shared__ __attribute__((aligned(16))) float table[ROWS][D];
+  constexpr int ROUNDS = (MAXTOK + KEYS - 1) / KEYS;
+  constexpr int TILES = (ROUNDS + 3) / 4;               // sixteen keys of a wavefront, four rounds
+  constexpr int WORDS = (ROUNDS + 7) / 8;               // of four bits per round
+  constexpr int TROW = D + 32;                          // table row in LDS: 320 B, rows shift 16 banks
+  static_assert((MAXC == 2 || MAXC % 4 == 0) && MAXC <= WAVES && MAXTOK <= SM_THREADS, "mapping");
+  __shared__ __attribute__((aligned(16))) bf16 table[ROWS][TROW];
   __shared__ __attribute__((aligned(16))) float part[WAVES][MAXC][D];
   __shared__ int cnt[WAVES][MAXC];
   __shared__ int wave_cnt[WAVES][MAXC];
-  __shared__ float bias[ROWS];
-  __shared__ int lab[KM_SMALL_MAX_TOKENS];
+  __shared__ __attribute__((aligned(16))) float bias[ROWS];
+  __shared__ float row_norm[ROWS];
+  __shared__ int lab[MAXTOK];
   __shared__ int s_changed[2];
 
   const int hp = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, row = lane >> 4, l4 = lane & 3;
   const int n_tok = a.tok_count, C = a.c_count;
   const bf16* Khp = a.K + (int64_t)hp * a.N_cap * D;
+  const uint4* R = reinterpret_cast<const uint4*>(Khp + a.tok_begin * D);
 
-  // ---- this wavefront's keys: of round r, keys 4 * wave + (0..3) ----
-  // dk: lane 4 b + x holds the eight channels of group bitreverse(b) of key x.  Lane bits 5, 4, 3, 2
-  // are then bits 0, 1, 2, 3 of the channel group, and the partial sums are added in the order
-  // of row16_sum.  uk: lanes 16 x + g hold channel group g of key x.
-  const int b = lane >> 2;
-  const int dgroup = ((b & 1) << 3) | ((b & 2) << 1) | ((b & 4) >> 1) | (b >> 3);
-  uint4 dk[ROUNDS], uk[ROUNDS];
+  // ---- this wavefront's keys: of round r, keys r * KEYS + 4 * wave + (0..3) ----
+  // dk: the columns of the products; column n of tile T is key n % 4 of round 4 T + n / 4, and lane
+  // 16 g + n holds channels 32 sl + 8 g .. + 8 of it.  uk: lanes 16 x + g hold channels 8 g .. + 8 of key x.
+  uint4 dk[TILES][4], uk[ROUNDS];
+  float thr[TILES];                                     // see exact_label
   {
-    const uint4* R = reinterpret_cast<const uint4*>(Khp + a.tok_begin * D);
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {                  // a key beyond the range re-reads the last one
-      const int td = r * KEYS + wave * 4 + l4, tu = r * KEYS + wave * 4 + row;
+      const int tu = r * KEYS + wave * 4 + row;
       uk[r] = R[(int64_t)(tu < n_tok ? tu : n_tok - 1) * 16 + l16];
-      dk[r] = R[(int64_t)(td < n_tok ? td : n_tok - 1) * 16 + dgroup];
+    }
+#pragma unroll
+    for (int T = 0; T < TILES; ++T) {
+      const int td = (4 * T + (l16 >> 2)) * KEYS + wave * 4 + l4;
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl) dk[T][sl] = R[(int64_t)(td < n_tok ? td : n_tok - 1) * 16 + 4 * sl + row];
     }
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r)                    // ... and adds nothing
       if (r * KEYS + wave * 4 + row >= n_tok) uk[r] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int T = 0; T < TILES; ++T) {
+      float n2 = 0.f;
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl) {
+        const uint32_t w[4] = {dk[T][sl].x, dk[T][sl].y, dk[T][sl].z, dk[T][sl].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) n2 = fmaf(lo_bf16(w[i]), lo_bf16(w[i]), fmaf(hi_bf16(w[i]), hi_bf16(w[i]), n2));
+      }
+      thr[T] = key_bound(xor32(xor16(n2, OpSum()), OpSum()));
+    }
   }
   // the mean of cluster `wave`: channels 2 * lane, 2 * lane + 1
   float m0 = 0.f, m1 = 0.f;
@@ -88,35 +127,71 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
     m0 = lo_bf16(w);
     m1 = hi_bf16(w);
   }
-  for (int e = C * D + tid; e < ROWS * D; e += SM_THREADS) table[e / D][e % D] = 0.f;
+  // rows without a cluster
+  for (int e = tid; e < (ROWS - C) * (TROW / 2); e += SM_THREADS) reinterpret_cast<uint32_t*>(table[C])[e] = 0;
+  if (tid >= C && tid < ROWS) bias[tid] = row_norm[tid] = 0.f;
 
-  // After the lane swaps row r of a register holds cluster 4 s + {0, 2, 1, 3}[r], or of two
-  // clusters {0, 0, 1, 1}[r]
-  const int rowc = MAXC == 2 ? row >> 1 : ((row & 1) << 1) | (row >> 1);
-  uint32_t labels[(ROUNDS + 7) / 8];                    // 4 bits per round: label of key `l4`
+  // The label of one token of the range in a fixed order of the additions: eight multiply-adds per
+  // group of eight channels, the sixteen groups as row16_sum adds them.  The labels are those of this
+  // order.  The matrix cores add the same exact products in another one; either is off by less than
+  // 128 * 2^-23 |k| |row|, and where the best similarity is not ahead of the second by twice that
+  // (thr, with the bound on the keys' side) the key is settled here.
+  auto exact_label = [&](int t) {
+    const uint4 k = R[(int64_t)t * 16 + l16];
+    const uint32_t kw[4] = {k.x, k.y, k.z, k.w};
+    float best = 0.f;
+    int bc = 0;
 #pragma unroll
-  for (int i = 0; i < (ROUNDS + 7) / 8; ++i) labels[i] = 0xFFFFFFFFu;
+    for (int s = 0; s < SETS; ++s) {
+      const uint4 x = *reinterpret_cast<const uint4*>(&table[4 * s + row][l16 * 8]);
+      const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
+      float d = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d = fmaf(lo_bf16(xw[i]), lo_bf16(kw[i]), d);
+        d = fmaf(hi_bf16(xw[i]), hi_bf16(kw[i]), d);
+      }
+      float v = row16_sum(d) + bias[4 * s + row];
+      // a NaN never wins over another cluster and is never beaten as cluster 0
+      v = v == v && 4 * s + row < C ? v : (4 * s + row == 0 ? INFINITY : -INFINITY);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {                     // the lower cluster where they are equal
+        const float vi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16 * i));
+        if ((s == 0 && i == 0) || vi > best) {
+          best = vi;
+          bc = 4 * s + i;
+        }
+      }
+    }
+    return bc;
+  };
+
+  int label[TILES];                                     // of column l16, in every row of lanes
+#pragma unroll
+  for (int T = 0; T < TILES; ++T) label[T] = -1;
 
   int n_done = 0;
   for (int it = 0; it < a.max_iter; ++it) {
     // ---- table row (and l2 bias) of cluster `wave` ----
     if (wave < C) {
-      float r0, r1;
+      uint32_t w;
       if (a.metric == CK_METRIC_COSINE) {
         // the fused product written out: the last bit of the norm must not depend on the
         // compiler's choice
         const float n2 = wave_sum(fmaf(m0, m0, m1 * m1));
         const float inv = n2 > 0.f ? 1.0f / sqrtf(n2) : 0.f;
-        r0 = bf16_bits_to_float(float_to_bf16_bits(m0 * inv));
-        r1 = bf16_bits_to_float(float_to_bf16_bits(m1 * inv));
+        w = (uint32_t)float_to_bf16_bits(m0 * inv) | ((uint32_t)float_to_bf16_bits(m1 * inv) << 16);
       } else {
-        r0 = bf16_bits_to_float(float_to_bf16_bits(m0));
-        r1 = bf16_bits_to_float(float_to_bf16_bits(m1));
+        w = (uint32_t)float_to_bf16_bits(m0) | ((uint32_t)float_to_bf16_bits(m1) << 16);
       }
-      *reinterpret_cast<float2*>(&table[wave][2 * lane]) = make_float2(r0, r1);
-      if (a.metric == CK_METRIC_L2) {
+      reinterpret_cast<uint32_t*>(table[wave])[lane] = w;
+      if (a.metric != CK_METRIC_COSINE) {
+        const float r0 = lo_bf16(w), r1 = hi_bf16(w);
         const float rn2 = wave_sum(fmaf(r0, r0, r1 * r1));
-        if (lane == 0) bias[wave] = -0.5f * rn2;
+        if (lane == 0) {
+          bias[wave] = a.metric == CK_METRIC_L2 ? -0.5f * rn2 : 0.f;
+          row_norm[wave] = sqrtf(rn2);
+        }
       } else if (lane == 0) {
         bias[wave] = 0.f;
       }
@@ -124,109 +199,134 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
     if (tid == 0) s_changed[it & 1] = 0;                // the other one may still be read
     __syncthreads();
 
-    float ta[SETS][8], bs[SETS];
+    // ---- labels: rows of the products are the clusters 4 s + (0..3), four times over, so that every
+    // lane ends with the similarities of key l16 to all of them ----
+    bool moved = false;
+    {
+      bf16x8 ta[SETS][4];
+      float4 bs[SETS];
 #pragma unroll
-    for (int s = 0; s < SETS; ++s) {
-      const float4* t = reinterpret_cast<const float4*>(&table[4 * s + l4][dgroup * 8]);
-      const float4 x = t[0], y = t[1];
-      ta[s][0] = x.x; ta[s][1] = x.y; ta[s][2] = x.z; ta[s][3] = x.w;
-      ta[s][4] = y.x; ta[s][5] = y.y; ta[s][6] = y.z; ta[s][7] = y.w;
-      // a row without a cluster is a NaN, which never wins
-      bs[s] = 4 * s + rowc < C ? bias[4 * s + rowc] : __builtin_nanf("");
-    }
-    uint32_t moved = 0;
+      for (int s = 0; s < SETS; ++s) {
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-      // two clusters: wavefronts without keys in a round sit it out (321 tokens 55.3 -> 51.4 us, but
-      // 320 tokens 49.0 -> 50.7, and 56.0 -> 57.6 with four clusters, where a round in full is the rule)
-      if (r * KEYS + (MAXC == 2 ? wave * 4 : 0) < n_tok) {   // wave-uniform
-        // unpacked here and not once before the iterations: there are no registers for that
-        asm volatile("" : "+v"(dk[r].x), "+v"(dk[r].y), "+v"(dk[r].z), "+v"(dk[r].w));
-        const uint32_t dw[4] = {dk[r].x, dk[r].y, dk[r].z, dk[r].w};
-        float best = 0.f;
-        int bc = 0;
+        for (int sl = 0; sl < 4; ++sl)
+          ta[s][sl] = *reinterpret_cast<const bf16x8*>(&table[4 * s + l4][32 * sl + 8 * row]);
+        bs[s] = *reinterpret_cast<const float4*>(&bias[4 * s]);
+      }
+      // length of the longest row (one, and a quarter more where the square of a mean was below the
+      // smallest normal number); rounding of the bias
+      float rn = 1.25f, slack = 0.f;
+      if (a.metric != CK_METRIC_COSINE) {
+        rn = row_norm[0];
+#pragma unroll
+        for (int c = 1; c < ROWS; ++c) rn = fmaxf(rn, row_norm[c]);
+        rn = row_bound(rn);
+        slack = 0x1p-20f * rn * rn;
+      }
+      floatx4 d[TILES][SETS];
+#pragma unroll
+      for (int s = 0; s < SETS; ++s)
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+          for (int T = 0; T < TILES; ++T)
+            d[T][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta[s][sl], __builtin_bit_cast(bf16x8, dk[T][sl]),
+                                                              sl ? d[T][s] : floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      int bc[TILES];
+      uint32_t open[TILES], any_open = 0;
+#pragma unroll
+      for (int T = 0; T < TILES; ++T) {
+        float best = 0.f, second = -INFINITY;
+        bc[T] = 0;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-          floatx4 d = {0.f, 0.f, 0.f, 0.f};             // [cluster 4 s + i] of key l4, channel group of b
+          const float b[4] = {bs[s].x, bs[s].y, bs[s].z, bs[s].w};
 #pragma unroll
-          for (int j = 0; j < 8; ++j)
-            d = __builtin_amdgcn_mfma_f32_4x4x1f32(ta[s][j], j & 1 ? hi_bf16(dw[j / 2]) : lo_bf16(dw[j / 2]), d, 0, 0, 0);
-          // sixteen channel groups: lane bits 5, 4 (two clusters share a register from there
-          // on), 3, 2
-          const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[0]), __float_as_uint(d[1]), false, false);
-          const float c01 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-          float c23 = c01;
-          if constexpr (MAXC > 2) {
-            const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2]), __float_as_uint(d[3]), false, false);
-            c23 = __uint_as_float(q[0]) + __uint_as_float(q[1]);
-          }
-          const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(c01), __float_as_uint(c23), false, false);
-          float v = __uint_as_float(w[0]) + __uint_as_float(w[1]);
-          v += dpp_f<DPP_ROR8>(v);
-          v += dpp_f<DPP_ROR4>(v);                      // lanes x and x ^ 8 are equal by now
-          v += bs[s];
-          // a NaN never wins over another cluster and is never beaten as cluster 0
-          v = v == v ? v : (4 * s + rowc == 0 ? INFINITY : -INFINITY);
-          // best of the four, the lower cluster where they are equal: rows hold 0, 2, 1, 3
-          const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-          const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
-          if constexpr (MAXC == 2) {
-            bc = x1 > x0 ? 1 : 0;
-          } else {
-            const float xv = x1 > x0 ? x1 : x0;
-            const unsigned xc = (row & 1) * 2 + (x1 > x0 ? 1 : 0);
-            const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(xv), __float_as_uint(xv), false, false);
-            const auto yc = __builtin_amdgcn_permlane16_swap(xc, xc, false, false);
-            const float y0 = __uint_as_float(y[0]), y1 = __uint_as_float(y[1]);
-            const float yv = y1 > y0 ? y1 : y0;
-            const int c = 4 * s + (int)(y1 > y0 ? yc[1] : yc[0]);
-            if (s == 0 || yv > best) {
-              best = yv;
-              bc = c;
+          for (int i = 0; i < (MAXC < 4 ? MAXC : 4); ++i) {
+            const int c = 4 * s + i;
+            const float v = c < C ? d[T][s][i] + b[i] : -INFINITY;
+            if (c == 0) {
+              best = v;
+            } else {                                    // a NaN leaves no distance
+              second = fmaxf(second, fminf(best, v));
+              bc[T] = v > best ? c : bc[T];
+              best = v > best ? v : best;
             }
           }
         }
+        const int t = (4 * T + (l16 >> 2)) * KEYS + wave * 4 + l4;
+        open[T] = (uint32_t)__ballot(t < n_tok && !(best - second > fmaf(thr[T], rn, slack))) & 0xFFFFu;
+        any_open |= open[T];
+      }
+      if (any_open) {                                   // wave-uniform
+#pragma unroll
+        for (int T = 0; T < TILES; ++T)
+          while (open[T]) {
+            const int n = __builtin_ctz(open[T]);
+            open[T] &= open[T] - 1;
+            const int c = exact_label((4 * T + (n >> 2)) * KEYS + wave * 4 + (n & 3));
+            bc[T] = l16 == n ? c : bc[T];
+          }
+      }
+#pragma unroll
+      for (int T = 0; T < TILES; ++T) {
         // a key that does not exist belongs to no cluster
-        if (r * KEYS + wave * 4 + l4 >= n_tok) bc = 15;
-        const uint32_t word = labels[r / 8], put = (word & ~(15u << (r % 8 * 4))) | ((uint32_t)bc << (r % 8 * 4));
-        moved |= word ^ put;
-        labels[r / 8] = put;
-        __builtin_amdgcn_sched_barrier(0);              // rounds one after another: registers
+        if ((4 * T + (l16 >> 2)) * KEYS + wave * 4 + l4 >= n_tok) bc[T] = 15;
+        moved |= bc[T] != label[T];
+        label[T] = bc[T];
       }
     }
     // ---- the sums over this wavefront's keys: where none of its labels has changed, those of the
     // iteration before stand in part and cnt ----
-    const bool any_moved = __ballot(moved != 0) != 0;
+    const bool any_moved = __ballot(moved) != 0;
     if (any_moved && lane == 0) s_changed[it & 1] = 1;
     if (any_moved || it == 0) {
       floatx4 acc[SETS][8];                               // [channel 8 l16 + j][cluster 4 s + i], key group `row`
-      int n[SETS];                                        // members of cluster 4 s + l4 in key group `row`
+      uint32_t mine[SETS][WORDS];                         // bit 4 r: key `row` of round r (+ 8 per word) is in cluster 4 s + l4
 #pragma unroll
       for (int s = 0; s < SETS; ++s) {
-        n[s] = 0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[s][j] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) mine[s][w] = 0;
+        int members_n[4];
+#pragma unroll
+        for (int i = 0; i < (MAXC < 4 ? MAXC : 4); ++i) {
+          uint32_t members[WORDS];
+          int n = 0;
+#pragma unroll
+          for (int w = 0; w < WORDS; ++w) {
+            members[w] = (uint32_t)__ballot(label[2 * w] == 4 * s + i) & 0xFFFFu;
+            if (2 * w + 1 < TILES) members[w] |= (uint32_t)__ballot(label[2 * w + 1 < TILES ? 2 * w + 1 : 0] == 4 * s + i) << 16;
+            n += __popc(members[w]);
+            mine[s][w] = l4 == i ? members[w] : mine[s][w];
+          }
+          members_n[i] = n;
+        }
+        if (lane == 0) {
+#pragma unroll
+          for (int i = 0; i < (MAXC < 4 ? MAXC : 4); ++i) cnt[wave][4 * s + i] = members_n[i];
+        }
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) mine[s][w] >>= row;
       }
 #pragma unroll
       for (int r = 0; r < ROUNDS; ++r) {
+        // two clusters: wavefronts without keys in a round sit it out (with four, a round in full is the rule)
         if (r * KEYS + (MAXC == 2 ? wave * 4 : 0) < n_tok) {   // wave-uniform
+          // unpacked here and not once before the iterations: there are no registers for that
           asm volatile("" : "+v"(uk[r].x), "+v"(uk[r].y), "+v"(uk[r].z), "+v"(uk[r].w));
-          const int bc = (int)(labels[r / 8] >> (r % 8 * 4)) & 15;
-          // label of key `row` into all lanes of that row: lane x of every quad has key x's
-          int ub = 0;
-          ub = __builtin_amdgcn_update_dpp(ub, bc, 0x00, 0x1, 0xf, false);
-          ub = __builtin_amdgcn_update_dpp(ub, bc, 0x55, 0x2, 0xf, false);
-          ub = __builtin_amdgcn_update_dpp(ub, bc, 0xAA, 0x4, 0xf, false);
-          ub = __builtin_amdgcn_update_dpp(ub, bc, 0xFF, 0x8, 0xf, false);
           const uint32_t uw[4] = {uk[r].x, uk[r].y, uk[r].z, uk[r].w};
+          float x[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) x[j] = j & 1 ? hi_bf16(uw[j / 2]) : lo_bf16(uw[j / 2]);
+          // all eight at once: one by one each product waits for its operand
+          asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
 #pragma unroll
           for (int s = 0; s < SETS; ++s) {
-            const bool mine = ub == 4 * s + l4;
-            const float on = mine ? 1.f : 0.f;
-            n[s] += mine ? 1 : 0;
+            const float on = (float)((mine[s][r / 8] >> (r % 8 * 4)) & 1u);
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-              acc[s][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(on, j & 1 ? hi_bf16(uw[j / 2]) : lo_bf16(uw[j / 2]), acc[s][j], 0, 0, 0);
+              acc[s][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(on, x[j], acc[s][j], 0, 0, 0);
           }
         }
       }
@@ -251,9 +351,6 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
           dst[0] = make_float4(o[0], o[1], o[2], o[3]);
           dst[1] = make_float4(o[4], o[5], o[6], o[7]);
         }
-        n[s] += __shfl_xor(n[s], 16, WAVE);
-        n[s] += __shfl_xor(n[s], 32, WAVE);
-        if (lane < 4 && 4 * s + lane < MAXC) cnt[wave][4 * s + lane] = n[s];
       }
     }
     __syncthreads();
@@ -267,13 +364,16 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
     // centroid ----
     if (wave < C) {
       float s0 = 0.f, s1 = 0.f;
-      int nn = 0;
+      int nn = l16 < WAVES ? cnt[l16 < WAVES ? l16 : 0][wave] : 0;
+      nn += dpp_i0<DPP_XOR1>(nn);
+      nn += dpp_i0<DPP_XOR2>(nn);
+      nn += dpp_i0<DPP_HALF_MIRROR>(nn);
+      nn += dpp_i0<DPP_MIRROR>(nn);
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) {
         const float2 v = *reinterpret_cast<const float2*>(&part[w][wave][2 * lane]);
         s0 += v.x;
         s1 += v.y;
-        nn += cnt[w][wave];
       }
       if (nn > 0) {
         const float inv = 1.0f / (float)nn;
@@ -289,11 +389,11 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
       break;
     }
   }
-  if (lane < 4) {
+  if (lane < 16) {
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-      const int t = r * KEYS + wave * 4 + lane;
-      if (t < n_tok) lab[t] = (int)(labels[r / 8] >> (r % 8 * 4)) & 15;
+    for (int T = 0; T < TILES; ++T) {
+      const int t = (4 * T + (lane >> 2)) * KEYS + wave * 4 + (lane & 3);
+      if (t < n_tok) lab[t] = label[T];
     }
   }
   __syncthreads();
@@ -363,12 +463,17 @@ hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin,
   a.max_iter = max_iter;
   a.metric = metric;
   a.converge = converge ? 1 : 0;
-  if (c_count <= 2)
-    hipLaunchKernelGGL((k_kmeans_small<2, 1024>), dim3(dm.HP), dim3(1024), 0, st, a);
-  else if (c_count <= 4)
-    hipLaunchKernelGGL((k_kmeans_small<4, 1024>), dim3(dm.HP), dim3(1024), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_kmeans_small<KM_SMALL_MAX_CLUSTERS, 512>), dim3(dm.HP), dim3(512), 0, st, a);
+  auto launch = [&](auto MT) {
+    constexpr int T = decltype(MT)::value;
+    if (c_count <= 2)
+      hipLaunchKernelGGL((k_kmeans_small<2, 1024, T>), dim3(dm.HP), dim3(1024), 0, st, a);
+    else if (c_count <= 4)
+      hipLaunchKernelGGL((k_kmeans_small<4, 1024, T>), dim3(dm.HP), dim3(1024), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_kmeans_small<KM_SMALL_MAX_CLUSTERS, 512, T>), dim3(dm.HP), dim3(512), 0, st, a);
+  };
+  if (tok_count <= KM_SMALL_FEW_TOKENS) launch(std::integral_constant<int, KM_SMALL_FEW_TOKENS>());
+  else launch(std::integral_constant<int, KM_SMALL_MAX_TOKENS>());
   return hipGetLastError();
 }
 

@@ -248,7 +248,7 @@ def test_one_cluster(n, max_iter, converge, ran):
 
 
 @pytest.mark.parametrize("C", [2, 3, 4, 5, 8])
-@pytest.mark.parametrize("n", [9, 64, 65, 127, 320, 321, 384])
+@pytest.mark.parametrize("n", [9, 64, 65, 127, 256, 257, 320, 321, 384])
 @pytest.mark.parametrize("metric", [O.COSINE, O.L2])
 def test_small_range_at_round_edges(C, n, metric):
     """The one-kernel form around its rounds of 32 and 64 keys, in each of its cluster bounds, one
@@ -264,3 +264,35 @@ def test_small_range_at_round_edges(C, n, metric):
             bad = (st.labels[s, h].cpu().numpy() != labels) & ~(tr.gap[-1] < NEAR_TIE)
             assert not bad.any()
             check_state(st, cfg, s, h, keys, labels)
+
+
+@pytest.mark.parametrize("C", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("n", [20, 255, 257, 384])
+def test_small_range_near_ties(C, n):
+    """Rows that differ by one bf16 step in one small channel: every key is a near-tie, and its label
+    is the one of the documented order of additions (eight multiply-adds per group of eight channels,
+    then the groups in pairs), evaluated here one rounding at a time."""
+    rng = np.random.default_rng(100 * C + n)
+    base = rng.standard_normal(128)
+    k = rng.standard_normal((n, 128))
+    for c in range(C):                                    # row c: one step up in channel 3 + 16 c
+        base[3 + 16 * c] = 2.0 ** -12
+    for c in range(C):
+        k[c] = base
+        k[c, 3 + 16 * c] += 2.0 ** -19
+    K = torch.from_numpy(k).to(torch.bfloat16)
+    st = ck.ClusterState(ck.Shape(1, 1, 1, n, C), DEV, budget=64)
+    init = torch.arange(C, dtype=torch.int32, device=DEV)[None, None]
+    st.cluster(K[None, None].to(DEV), init, 0, n, C, 1, flags=ck.CK_METRIC_IP)
+    rows = np64(K).reshape(n, 16, 8)
+    p = rows[:, None] * rows[None, :C]                    # [n, C, 16, 8], exact
+    d = np.zeros((n, C, 16), np.float32)
+    for j in range(8):
+        d = (p[..., j] + d.astype(np.float64)).astype(np.float32)   # fused: one rounding
+    while d.shape[-1] > 1:
+        d = d[..., 0::2] + d[..., 1::2]
+    want = d[..., 0].argmax(axis=1)
+    exact = p.sum(axis=(2, 3)).argmax(axis=1)
+    if n > 200:
+        assert (want != exact).mean() > 0.05              # the order of the additions is what decides
+    assert st.labels[0, 0].cpu().numpy().tolist() == want.tolist()
