@@ -255,12 +255,17 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
     e = ck::launch_fill_i32(ws.changed, (int64_t)max_iter * dm.HP, 0, st);
     if (e != hipSuccess) return hip_result(e, "counter fill launch");
   }
-  // the iterations need the sums of the clusters, not the sorted index: the update reads the
-  // chunk index of the assignment, and the metadata is built once, after the last iteration
-  const bool chunked = ck::update_chunks_fits(dm, tok_count);
+  // the iterations need the sums of the clusters, not the sorted index: the update reads the labels
+  // (short ranges, it then leaves the metadata too) or the chunk index of the assignment, from which
+  // the metadata is built once, after the last iteration ...
+  const bool by_labels = ck::update_labels_fits(dm, tok_count, c_count);
+  const bool chunked = !by_labels && ck::update_chunks_fits(dm, tok_count);
   // ... or, in ranges of more chunks than it can walk, only the counts for the counting sort
   ck::ChunkIndex chunks = ws.chunks;
   if (!chunked) chunks.list = nullptr;
+  if (by_labels) chunks.seg = nullptr;
+  // written by the launch that writes the metadata; in convergence mode by one of its own
+  int32_t* count_out = converge ? nullptr : iters_done;
   for (int it = 0; it < max_iter; ++it) {
     ck::KmCtl ctl;
     ctl.bias = bias;
@@ -275,7 +280,14 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
     e = ck::launch_assign(dm, Kb, tok_begin, tok_count, ws.mu_hat, c_begin, c_count, labels,
                           nullptr, chunks, ctl, st);
     if (e != hipSuccess) return hip_result(e, "assignment launch");
-    if (chunked) {
+    if (by_labels) {
+      // any iteration may turn out to be a head-problem's last in convergence mode
+      const bool last = converge || it == max_iter - 1;
+      e = ck::launch_update_labels(dm, Kb, labels, tok_begin, tok_count, c_begin, c_count,
+                                   (ck::bf16*)centroids, ws.mu_hat, sizes, metric, bias,
+                                   ws.bias_stride, gate, last ? offsets : nullptr, sorted_idx,
+                                   last ? count_out : nullptr, max_iter, st);
+    } else if (chunked) {
       e = ck::launch_update_chunks(dm, Kb, ws.chunks, tok_begin, tok_count, c_begin, c_count,
                                    (ck::bf16*)centroids, ws.mu_hat, sizes, metric, bias,
                                    ws.bias_stride, gate, st);
@@ -292,10 +304,10 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
     // the metadata of the last labels; a head-problem that stopped early has left its chunk
     // index as its last assignment wrote it
     e = ck::launch_emit_index(dm, ws.chunks, tok_begin, tok_count, c_begin, c_count, sizes,
-                              offsets, sorted_idx, st);
+                              offsets, sorted_idx, count_out, max_iter, st);
     if (e != hipSuccess) return hip_result(e, "metadata launch");
   }
-  if (iters_done) {
+  if (iters_done && (converge || !(by_labels || chunked))) {
     if (converge)
       e = ck::launch_iters_done(ws.changed, max_iter, dm.HP, iters_done, st);
     else

@@ -228,10 +228,20 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
                                 float* bias, int bias_stride, const int32_t* gate, hipStream_t st);
-// offsets and sorted_idx of the labels the chunk index holds (sizes: as the update wrote them)
+// offsets and sorted_idx of the labels the chunk index holds (sizes: as the update wrote them), and
+// n_iter into iters_done where that is given
 hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
                              int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
-                             int32_t* offsets, int32_t* sorted_idx, hipStream_t st);
+                             int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done, int n_iter,
+                             hipStream_t st);
+// the same update from the labels of a short range, and where offsets is given the metadata with it
+bool update_labels_fits(const Dims& dm, int64_t tok_count, int c_count);
+hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* labels,
+                                int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
+                                bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
+                                float* bias, int bias_stride, const int32_t* gate,
+                                int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done,
+                                int n_iter, hipStream_t st);
 hipError_t launch_select(const Dims& dm, const void* q, const void* centroids,
                          const int32_t* sizes, int n_clusters, int budget, uint32_t flags,
                          int32_t* sel_clusters, int32_t* n_sel_clusters, int32_t* n_sel_tokens,

@@ -54,22 +54,24 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
   const int n_chunks = (c_count + CHUNK_ROWS - 1) / CHUNK_ROWS;
   const int n_tiles = (c_count + 31) / 32;
   uint4 stage[SEGS];
+  // unconditional loads (rows beyond the table re-read its last row and are replaced by zeros when
+  // they are written to LDS): under a branch each waits for the one before
   auto fetch = [&](int ch) {
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int seg = tid + i * THREADS;
       const int r = ch * CHUNK_ROWS + (seg >> 4);
-      if (r < c_count)
-        stage[i] = *reinterpret_cast<const uint4*>(Mhp + (int64_t)r * D + (seg & 15) * 8);
-      else
-        stage[i] = make_uint4(0, 0, 0, 0);
+      stage[i] = *reinterpret_cast<const uint4*>(Mhp + (int64_t)(r < c_count ? r : c_count - 1) * D + (seg & 15) * 8);
     }
   };
-  auto stash = [&](int buf) {
+  auto stash = [&](int buf, int ch) {
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int seg = tid + i * THREADS;
-      *reinterpret_cast<uint4*>(&lds[buf][(seg >> 4) * LDS_ROW + (seg & 15) * 8]) = stage[i];
+      const bool real = ch * CHUNK_ROWS + (seg >> 4) < c_count;
+      uint4 v = stage[i];
+      v.x = real ? v.x : 0u; v.y = real ? v.y : 0u; v.z = real ? v.z : 0u; v.w = real ? v.w : 0u;
+      *reinterpret_cast<uint4*>(&lds[buf][(seg >> 4) * LDS_ROW + (seg & 15) * 8]) = v;
     }
   };
   // first centroid chunk ahead of the keys, so that it does not queue behind them
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
     bestp = up ? m : bestp;
   };
 
-  stash(0);
+  stash(0, 0);
   __syncthreads();
 
   for (int ch = 0; ch < n_chunks; ++ch) {
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
         reduce(t);
       }
     }
-    if (ch + 1 < n_chunks) stash((ch + 1) & 1);
+    if (ch + 1 < n_chunks) stash((ch + 1) & 1, ch + 1);
     __syncthreads();
   }
 

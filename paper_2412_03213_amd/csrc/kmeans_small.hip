@@ -47,7 +47,7 @@ __device__ __forceinline__ float row_bound(float n) {
 //   labels        v_mfma_f32_16x16x32_bf16, rows = the clusters (four, repeated, so that every lane has
 //                 all similarities of its key and the best of them needs no lane exchange), columns =
 //                 16 keys of the wavefront.  Where best and second are too close for the order of the
-//                 additions not to matter, the fixed order decides (exact_label; 1 key in 3000 of a
+//                 additions not to matter, the fixed order decides (exact_label; 1 key in 5000 of a
 //                 mixture), so the labels are those of the fixed order.
 //   update sums   v_mfma_f32_4x4x1_16b_f32, one fp32 addition per element and step, in the order
 //                 written here: block = four lanes of one key, rows = 4 clusters, A = 1 where the

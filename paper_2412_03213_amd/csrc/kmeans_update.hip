@@ -8,8 +8,9 @@
 // them in a fixed order (ascending token row).  No floating-point atomics, so the
 // centroids are bit-reproducible.  The cluster-contiguous index that the decode step
 // needs (sizes, prefix sum, sorted indices) is emitted once, from the chunk index of the
-// last assignment; the counting sort of given labels and the update from a sorted list
-// serve the calls that export the steps, and ranges of more chunks than the index holds.
+// last assignment.  Short ranges do without the index: their update looks through the labels, and
+// its last launch leaves the metadata.  The counting sort of given labels and the update from a
+// sorted list serve the calls that export the steps, and ranges of more chunks than the index holds.
 #include "chunk_sort.hpp"
 
 namespace ck {
@@ -584,6 +585,156 @@ __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chun
   }
 }
 
+// ------------------------------------------------------------------ from the labels
+// Short ranges: the workgroup of a cluster reads all labels of its range and keeps the tokens that
+// carry its own, in order.  That is one look-up in place of two (runs, then list), the assignment
+// need not order its chunks, and the labels below the cluster's own are the tokens in front of its
+// segment, so the launch can leave the metadata as well.  Additions in k_update's order.
+// Bound: launch, then labels and rows one after the other, and the instructions of looking through the
+// labels, which every cluster does: eight wavefronts share that (four: 3 % of the call).
+// Ten iterations at 8 x 2985 x 37: 108.5 us from the chunk index, with an index launch and a fill of the
+// iteration counts behind it, 94 from the labels.
+constexpr int UPL_WAVES = 8;                            // look at the labels; UPC_WAVES of them add the rows
+constexpr int UPL_ROUNDS = 16;                          // 64 labels each, per wavefront, at most
+
+template <int ROUNDS>
+__global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
+    const bf16* __restrict__ K, const int32_t* __restrict__ labels, int64_t N_cap, int64_t tok_begin,
+    int tok_count, int C_cap, int c_begin, int c_count, bf16* __restrict__ centroids,
+    bf16* __restrict__ mu_hat, int32_t* __restrict__ sizes, int metric, float* __restrict__ bias,
+    int bias_stride, const int32_t* __restrict__ gate, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter) {
+  __shared__ uint16_t member[UPL_WAVES * ROUNDS * WAVE];
+  __shared__ int found[UPL_WAVES], before[UPL_WAVES];
+  __shared__ __attribute__((aligned(16))) float part[UPC_WAVES][D];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int hp = blockIdx.y, c = blockIdx.x;
+  CK_FETCH_ARG(centroids);                              // used last, fetched with the others
+  CK_FETCH_ARG(metric);
+  CK_FETCH_ARG(offsets);
+  // a head-problem that has converged: labels, and with them everything below, are what they were
+  if (gate && gate[hp] == 0) return;
+  const int32_t* lab = labels + (int64_t)hp * N_cap + tok_begin;
+  const int first = wave * ROUNDS * WAVE + lane, mine = c_begin + c;
+  int l[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {                // unconditional: one round trip
+    const int t = first + r * WAVE;
+    l[r] = lab[t < tok_count ? t : tok_count - 1];
+  }
+  uint64_t here[ROUNDS];
+  int n_here = 0;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    here[r] = __ballot(first + r * WAVE < tok_count && l[r] == mine);
+    n_here += __popcll(here[r]);
+  }
+  if (offsets) {                                        // uniform
+    int n_before = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) n_before += __popcll(__ballot(first + r * WAVE < tok_count && l[r] < mine));
+    if (lane == 0) before[wave] = n_before;
+  }
+  if (lane == 0) found[wave] = n_here;
+  __syncthreads();
+  int base = 0, n = 0;
+#pragma unroll
+  for (int w = 0; w < UPL_WAVES; ++w) {
+    base += w < wave ? found[w] : 0;
+    n += found[w];
+  }
+  const uint64_t lt = ((uint64_t)1 << lane) - 1;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    if ((here[r] >> lane) & 1) member[base + __popcll(here[r] & lt)] = (uint16_t)(first + r * WAVE);
+    base += __popcll(here[r]);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    sizes[(int64_t)hp * C_cap + mine] = n;
+    if (iters_done && c == 0) iters_done[hp] = n_iter;
+  }
+  if (offsets) {
+    int32_t* off_g = offsets + (int64_t)hp * (C_cap + 1);
+    int seg0 = c_begin == 0 ? 0 : off_g[c_begin];
+#pragma unroll
+    for (int w = 0; w < UPL_WAVES; ++w) seg0 += before[w];
+    if (tid == 0) {
+      off_g[mine + 1] = seg0 + n;
+      if (mine == 0) off_g[0] = 0;
+    }
+    for (int j = tid; j < n; j += UPL_WAVES * 64) {
+      const int64_t pos = (int64_t)seg0 + j;
+      if (pos >= 0 && pos < N_cap) sorted_idx[(int64_t)hp * N_cap + pos] = (int32_t)(tok_begin + member[j]);
+    }
+  }
+  if (n == 0) return;                                   // empty cluster keeps its centroid
+
+  const bf16* Khp = K + ((int64_t)hp * N_cap + tok_begin) * D + l16 * 8;
+  float acc[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+  const int stream = wave * 4 + g4;
+  for (int j0 = stream; wave < UPC_WAVES && j0 - stream < n; j0 += 16 * UPC_STEPS) {
+    uint4 r[UPC_STEPS];
+#pragma unroll
+    for (int s = 0; s < UPC_STEPS; ++s) {
+      const int j = j0 + 16 * s;
+      r[s] = *reinterpret_cast<const uint4*>(Khp + (int64_t)member[j < n ? j : n - 1] * D);
+    }
+#pragma unroll
+    for (int s = 0; s < UPC_STEPS; ++s) {
+      const bool real = j0 + 16 * s < n;
+      const uint32_t x = real ? r[s].x : 0u, y = real ? r[s].y : 0u;
+      const uint32_t z = real ? r[s].z : 0u, q = real ? r[s].w : 0u;
+      acc[0] += lo_bf16(x); acc[1] += hi_bf16(x);
+      acc[2] += lo_bf16(y); acc[3] += hi_bf16(y);
+      acc[4] += lo_bf16(z); acc[5] += hi_bf16(z);
+      acc[6] += lo_bf16(q); acc[7] += hi_bf16(q);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float v = xor32(xor16(acc[j], OpSum()), OpSum());
+    if (wave < UPC_WAVES && lane < 16) part[wave][l16 * 8 + j] = v;
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  float m0 = part[0][2 * lane], m1 = part[0][2 * lane + 1];
+#pragma unroll
+  for (int w = 1; w < UPC_WAVES; ++w) {
+    m0 += part[w][2 * lane];
+    m1 += part[w][2 * lane + 1];
+  }
+  store_mean(m0, m1, n, hp, c, C_cap, c_begin, c_count, centroids, mu_hat, nullptr, metric, bias,
+             bias_stride);
+}
+
+// Where all workgroups are resident together (four per CU) and the labels read, over all clusters, are
+// few.  Ten iterations, chunk index / labels, us (head-problems x tokens x clusters): 8 x 1024 x 13
+// 96 / 82, 8 x 4096 x 51 112 / 98, 8 x 4096 x 128 126 / 117, 4 x 8192 x 102 125 / 118, 1 x 8192 x 102
+// 120 / 105, 60 x 1024 x 13 129 / 117, 20 x 4096 x 51 173 / 158; more labels: 8 x 8179 x 102 156 / 168,
+// 16 x 5000 x 62 171 / 184; more workgroups: 8 x 1024 x 256 166 / 172, 128 x 500 x 25 193 / 210, though
+// 128 x 1024 x 13 197 / 185.
+bool update_labels_fits(const Dims& dm, int64_t tok_count, int c_count) {
+  return tok_count <= UPL_WAVES * UPL_ROUNDS * WAVE && (int64_t)dm.HP * c_count <= 1024 &&
+         (int64_t)dm.HP * c_count * tok_count <= 1 << 22;
+}
+
+hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* labels,
+                                int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
+                                bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
+                                float* bias, int bias_stride, const int32_t* gate,
+                                int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done,
+                                int n_iter, hipStream_t st) {
+  const auto kernel = tok_count <= UPL_WAVES * 8 * WAVE ? k_update_labels<8> : k_update_labels<UPL_ROUNDS>;
+  hipLaunchKernelGGL(kernel, dim3(c_count, dm.HP), dim3(UPL_WAVES * 64), 0, st, K, labels,
+                     dm.N_cap, tok_begin, (int)tok_count, dm.C_cap, c_begin, c_count, centroids,
+                     mu_hat, sizes, metric, bias, bias_stride, gate, offsets, sorted_idx, iters_done,
+                     n_iter);
+  return hipGetLastError();
+}
+
 // Metadata of the final labels: offsets (prefix sum of the sizes the last update wrote) and
 // the label-sorted index, one wavefront per cluster.  One launch where the counting sort needs
 // two, and the index leaves in coalesced stores.
@@ -593,7 +744,7 @@ __global__ __launch_bounds__(EMIT_WAVES * 64) void k_emit_index(
     const uint32_t* __restrict__ seg, const uint16_t* __restrict__ list, int n_chunks,
     int chunk_tokens, int64_t N_cap, int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin,
     int c_count, const int32_t* __restrict__ sizes, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ sorted_idx) {
+    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter) {
   extern __shared__ uint32_t lds_u[];
   __shared__ int below[EMIT_WAVES], own[EMIT_WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -624,6 +775,7 @@ __global__ __launch_bounds__(EMIT_WAVES * 64) void k_emit_index(
   if (lane == 0) {
     off_g[c_begin + c + 1] = base + cr.n;
     if (c == 0 && c_begin == 0) off_g[0] = 0;
+    if (c == 0 && iters_done) iters_done[hp] = n_iter;
   }
   int32_t* out = sorted_idx + (int64_t)hp * N_cap;
   for (int j = lane; j < cr.n; j += WAVE) {
@@ -673,13 +825,14 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
 
 hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
                              int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
-                             int32_t* offsets, int32_t* sorted_idx, hipStream_t st) {
+                             int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done, int n_iter,
+                             hipStream_t st) {
   const int chunk_tokens = assign_tile_tokens(dm, tok_count);
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   hipLaunchKernelGGL(k_emit_index, dim3((c_count + EMIT_WAVES - 1) / EMIT_WAVES, dm.HP),
                      dim3(EMIT_WAVES * 64), chunk_runs_lds(EMIT_WAVES, n_chunks), st, chunks.seg, chunks.list,
                      n_chunks, chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin,
-                     c_count, sizes, offsets, sorted_idx);
+                     c_count, sizes, offsets, sorted_idx, iters_done, n_iter);
   return hipGetLastError();
 }
 

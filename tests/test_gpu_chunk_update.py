@@ -1,6 +1,6 @@
-"""The update that sums a cluster straight from the assignment's chunk index, and the metadata
-emitted from it, against the exported steps (assignment, counting sort, update from the sorted
-list) run one by one on the same tables: every output bit for bit (the sums run in the same
+"""The updates that sum a cluster straight from the assignment's chunk index or from its labels, and
+the metadata emitted with them, against the exported steps (assignment, counting sort, update from
+the sorted list) run one by one on the same tables: every output bit for bit (the sums run in the same
 order)."""
 import pytest
 import torch
@@ -12,9 +12,16 @@ DEV = "cuda:0"
 
 
 SHAPES = [
-    (1, 2, 385, 9, 0, 0),            # just beyond the one-kernel range; chunks of 128, last one short
-    (1, 1, 1000, 2, 16, 0),          # clusters of several hundred members: more than one pass of ids
-    (3, 1, 4099, 130, 3, 5),         # appended behind existing clusters, odd range
+    (1, 2, 385, 9, 0, 0),            # just beyond the one-kernel range; from the labels
+    (1, 1, 1000, 2, 16, 0),          # clusters of several hundred members: more than one pass of rows
+    (3, 1, 4099, 130, 3, 5),         # 4096 labels, appended behind existing clusters, odd range
+    (1, 1, 4097, 100, 0, 2),         # one label more: sixteen per lane
+    (1, 1, 8195, 512, 3, 0),         # as many labels, and read as often, as that form takes
+    (4, 4, 600, 64, 0, 0),           # as many workgroups
+    (16, 1, 600, 65, 5, 1),          # more: chunks of 128, last one short
+    (1, 1, 8193, 60, 0, 0),          # a label more: the same
+    (2, 1, 8192, 2, 0, 0),           # from the labels: members in many passes
+    (2, 8, 4050, 130, 3, 5),         # chunks of 128, appended behind existing clusters, odd range
     (2, 8, 4097, 513, 1, 0),         # table streamed in chunks; one token in the last chunk of 512
     (1, 8, 8200, 512, 0, 0),         # largest LDS-resident table
     (1, 1, 65535, 60, 0, 0),         # chunks of 128: exactly as many as the index holds
@@ -105,7 +112,8 @@ def test_empty_clusters_survive_the_iterations(S, Hkv, N, C, begin, c_begin):
 
 @pytest.mark.parametrize("S,Hkv,N,C", [(1, 8, 8200, 100),    # table in LDS, chunks of 512
                                        (1, 8, 8200, 520),    # table streamed in chunks
-                                       (2, 2, 1500, 40),     # chunks of 128
+                                       (2, 2, 1500, 40),     # from the labels
+                                       (1, 8, 4000, 130),    # chunks of 128
                                        (1, 2, 262700, 30)])  # counts only, sorted-list form
 def test_head_problems_stop_on_their_own(S, Hkv, N, C):
     """Run until convergence: a head-problem that has stopped keeps the chunk index, the sizes
