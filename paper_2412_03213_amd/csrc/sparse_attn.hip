@@ -882,6 +882,13 @@ __global__ __launch_bounds__(D / 2) void k_attn_merge(const float* __restrict__ 
 // but more of them have to be merged.  Full attention, this rule / 256 / HP splits: 1 x 8192 tokens
 // 9.2 / 10.8, 1 x 32864 16.8 / 20.8, 1 x 131072 37.2 / 37.6, 4 x 8192 10.8 / 14.2, 4 x 131072 56.2 /
 // 55.7, 7 x 32864 27.8 / 29.2, and ahead only at 3 x 50000 27.0 / 25.4 and 7 x 131072 97.3 / 92.5.
+// Two steps of eight wavefronts (129 to 256 positions) go to one workgroup, which writes the output
+// itself: a second step takes 0.9 us, publishing and merging two partials takes longer.  Two splits /
+// one, B = 256, 51 clusters: HP = 8 7.88 / 7.65, 32 8.0 / 7.75, 128 8.2 / 7.97; a list of 256 rows: HP = 8
+// 5.64 / 5.38, 128 6.12 / 5.73.  Below six head-problems it is two workgroups all the same: the cached
+// step takes the same rule, and one compute unit does not ask the host link for enough rows (four steps
+// of B = 256: HP = 2 58.3 / 63.9, 4 68.9 / 70.5, 6 81.6 / 79.9, 8 94.1 / 92.0, 64 449 / 424).
+// Four steps as two splits of two are slower than four of one (8.4 / 7.2).
 struct AttnPlan {
   int waves;        // wavefronts per workgroup
   int max_splits;   // grows with the attended total: a workspace sized for more holds less
@@ -914,6 +921,7 @@ static AttnPlan attn_plan(const Dims& dm, int64_t max_total) {
   // at least one full step of tokens per workgroup, no more positions than its row table holds
   const int64_t step = p.waves * ATT_TOKENS, by_work = (max_total + step - 1) / step;
   if (n > by_work) n = by_work;
+  if (p.waves == 8 && by_work == 2 && dm.HP >= 6) n = 1;
   if (n < need) n = need;
   p.max_splits = (int)n;
   // whole steps, and no split without a position: it would score and select for nothing

@@ -26,7 +26,8 @@ def clustered(cfg, dtype=torch.bfloat16):
 
 @pytest.mark.parametrize("home", ["pinned_host", "device"])
 @pytest.mark.parametrize("S,Hkv,G,N,C,B", [(2, 2, 4, 3000, 40, 512), (1, 2, 1, 2048 + 37, 50, 300),
-                                           (1, 1, 8, 700, 700, 64)])
+                                           (1, 1, 8, 700, 700, 64),
+                                           (2, 3, 2, 2500, 35, 250)])   # two steps, one workgroup
 def test_cached_steps_equal_uncached_and_count_misses(home, S, Hkv, G, N, C, B):
     cfg = Config("cache", 1, S, Hkv, Hkv * G, 128, N, 32, C, 10, B, 9)
     w, sh, st = clustered(cfg)

@@ -69,8 +69,8 @@ def test_single_launch_merge_equals_two_pass(S, Hq, Hkv, N, n_max, dtype):
         assert np.abs(got - want).max() <= tol * max(np.abs(want).max(), 1e-30)
 
 
-@pytest.mark.parametrize("S,Hkv", [(3, 1), (3, 8), (5, 8), (11, 8), (20, 8), (33, 8), (40, 8),
-                                   (65, 8)])
+@pytest.mark.parametrize("S,Hkv", [(3, 1), (5, 1), (6, 1), (3, 8), (5, 8), (11, 8), (20, 8), (33, 8),
+                                   (40, 8), (65, 8)])
 def test_splits_between_the_powers_of_two(S, Hkv):
     """Head-problem counts that do not divide the chip, attended totals around the steps of a
     workgroup and the 2048 positions it may own, one workspace for all of them (a larger total
@@ -83,7 +83,7 @@ def test_splits_between_the_powers_of_two(S, Hkv):
     ws2 = torch.empty_like(ws)
     a = torch.zeros(S, Hkv * G, 128, dtype=torch.bfloat16, device=DEV)
     b = torch.zeros_like(a)
-    for n in [700, 2100, 1, 384, 808, 809, 1300, 1832, 1833, 2100, 1024, 640, 128]:
+    for n in [700, 2100, 1, 384, 808, 40, 41, 809, 1300, 1832, 1833, 2100, 1024, 640, 128]:
         q = (2 * torch.randn(S, Hkv * G, 128, generator=g, device=DEV)).bfloat16()
         cnt = torch.full((S, Hkv), n, dtype=torch.int32, device=DEV)
         cnt[-1, 0] = n // 3
