@@ -172,11 +172,11 @@ int ck_build_metadata(const ck_shape* sh, const int32_t* labels, int64_t tok_beg
   CK_REQUIRE_PTR(sorted_idx);
   if (!workspace) return fail(CK_EWORKSPACE, "workspace is NULL");
   if (!aligned16(workspace)) return fail(CK_EMISALIGNED, "workspace is not 16-byte aligned");
-  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace);
+  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace, workspace_bytes);
   if (workspace_bytes < ws.bytes)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws.bytes);
   return hip_result(ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes,
-                                        offsets, sorted_idx, ws.chunks.seg, false, nullptr,
+                                        offsets, sorted_idx, ws.chunks, false, nullptr,
                                         (hipStream_t)stream),
                     "metadata launch");
 }
@@ -232,7 +232,7 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
   CK_OPTIONAL_PTR(iters_done);
   if (!workspace) return fail(CK_EWORKSPACE, "workspace is NULL");
   if (!aligned16(workspace)) return fail(CK_EMISALIGNED, "workspace is not 16-byte aligned");
-  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace);
+  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace, workspace_bytes);
   if (workspace_bytes < ws.bytes)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws.bytes);
 
@@ -259,7 +259,7 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
   // (short ranges, it then leaves the metadata too) or the chunk index of the assignment, from which
   // the metadata is built once, after the last iteration ...
   const bool by_labels = ck::update_labels_fits(dm, tok_count, c_count);
-  const bool chunked = !by_labels && ck::update_chunks_fits(dm, tok_count);
+  const bool chunked = !by_labels && ck::update_chunks_fits(ws.chunks.tokens, tok_count);
   // ... or, in ranges of more chunks than it can walk, only the counts for the counting sort
   ck::ChunkIndex chunks = ws.chunks;
   if (!chunked) chunks.list = nullptr;
@@ -293,7 +293,7 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
                                    ws.bias_stride, gate, st);
     } else {
       e = ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes, offsets,
-                              sorted_idx, ws.chunks.seg, true, gate, st);
+                              sorted_idx, ws.chunks, true, gate, st);
       if (e != hipSuccess) return hip_result(e, "metadata launch");
       e = ck::launch_update(dm, Kb, offsets, sorted_idx, c_begin, c_count, (ck::bf16*)centroids,
                             ws.mu_hat, nullptr, metric, bias, ws.bias_stride, gate, st);

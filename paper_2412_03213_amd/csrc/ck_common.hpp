@@ -148,6 +148,7 @@ struct Dims {
 };
 
 
+constexpr int CHUNK_RUNS_MAX = 512;         // chunks per head-problem the update walks (LDS: 2 words each)
 constexpr int KM_SMALL_MAX_TOKENS = 384;    // token ranges up to this size (and up to
 constexpr int KM_SMALL_MAX_CLUSTERS = 8;    // this many clusters) are clustered by one kernel
 constexpr int KM_MAX_ITER_CONVERGE = 256;   // iteration cap of the run-until-convergence mode
@@ -156,7 +157,8 @@ constexpr int KM_MAX_ITER_CONVERGE = 256;   // iteration cap of the run-until-co
 // tokens ordered by label (stable), and where each label's run stands in that list.
 struct ChunkIndex {
   uint32_t* seg = nullptr;    // [HP, n_chunks, seg_stride(c_count)] first list position | count << 16
-  uint16_t* list = nullptr;   // [HP, n_chunks, chunk_tokens] token offsets inside the chunk
+  uint16_t* list = nullptr;   // [HP, n_chunks, tokens] token offsets inside the chunk
+  int tokens = 0;             // of a chunk; 0 where nothing is left behind
 };
 
 struct ClusterWorkspace {
@@ -164,7 +166,7 @@ struct ClusterWorkspace {
   ChunkIndex chunks;
   float* bias;          // [HP, bias_stride] -|mu_c|^2 / 2 of the table rows (l2 metric)
   int bias_stride;      // c_count rounded up to whole 32-row tiles
-  int32_t* changed;     // [KM_MAX_ITER_CONVERGE + 1, HP] labels changed per iteration
+  int32_t* changed;     // [KM_MAX_ITER_CONVERGE + 1, HP] nonzero where an iteration changed labels
   size_t bytes;
 };
 
@@ -172,13 +174,14 @@ struct ClusterWorkspace {
 struct KmCtl {
   const float* bias = nullptr;     // l2 metric: added to <k, mu_c> before the argmax
   int bias_stride = 0;
-  const int32_t* skip = nullptr;   // [HP] changed-label counts of the previous iteration:
+  const int32_t* skip = nullptr;   // [HP] `changed` of the previous iteration:
                                    // 0 = that head-problem has converged, leave it alone
-  int32_t* changed = nullptr;      // [HP] receives the number of labels this launch changed
+  int32_t* changed = nullptr;      // [HP] left at 0 if this launch changes no label
   int first = 0;                   // no previous labels exist: count every token as changed
 };
-ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count,
-                                         void* base);
+// have: bytes there are, where that is known
+ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, void* base,
+                                         size_t have = SIZE_MAX);
 
 // metric: CK_METRIC_* of the table the assignment will read
 hipError_t launch_init_centroids(const Dims& dm, const bf16* K, const int32_t* init_idx,
@@ -193,8 +196,8 @@ hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin,
                                int32_t* iters_done, hipStream_t st);
 hipError_t launch_iters_done(const int32_t* changed, int max_iter, int HP, int32_t* iters_done,
                              hipStream_t st);
-int assign_tile_tokens(const Dims& dm, int64_t tok_count);
-// chunks (members nullable): index of every chunk of assign_tile_tokens() tokens by label;
+int assign_tile_tokens(const Dims& dm, int64_t tok_count, int c_count);
+// chunks (members nullable): index of every chunk of chunks.tokens tokens by label;
 // without list only the counts of seg
 hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,
                          const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
@@ -211,10 +214,10 @@ hipError_t launch_assign_wide(const Dims& dm, const bf16* K, int64_t tok_begin, 
                               const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
                               float* best_sim, const ChunkIndex& chunks, const KmCtl& ctl,
                               hipStream_t st);
-// have_seg: seg already holds the counts (written by launch_assign); overwritten either way
+// have_seg: chunks.seg already holds the counts (written by launch_assign); overwritten either way
 hipError_t launch_metadata(const Dims& dm, const int32_t* labels, int64_t tok_begin,
                            int64_t tok_count, int c_begin, int c_count, int32_t* sizes,
-                           int32_t* offsets, int32_t* sorted_idx, uint32_t* seg,
+                           int32_t* offsets, int32_t* sorted_idx, const ChunkIndex& chunks,
                            bool have_seg, const int32_t* gate, hipStream_t st);
 // gate (nullable, [HP]): head-problems whose entry is 0 are left untouched
 hipError_t launch_update(const Dims& dm, const bf16* K, const int32_t* offsets,
@@ -222,7 +225,7 @@ hipError_t launch_update(const Dims& dm, const bf16* K, const int32_t* offsets,
                          bf16* mu_hat, float* centroids_f32, int metric, float* bias,
                          int bias_stride, const int32_t* gate, hipStream_t st);
 // the same update straight from the chunk index of the assignment, no sorted list needed
-bool update_chunks_fits(const Dims& dm, int64_t tok_count);
+bool update_chunks_fits(int chunk_tokens, int64_t tok_count);
 int update_clusters_per_workgroup(int n_chunks, int c_count, int hp);
 hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,

@@ -54,6 +54,31 @@ struct KeyTile {
       }
     wave_lds_order();
   }
+  // the same through half of the room, sixteen keys at a time
+  __device__ __forceinline__ void to_operand_16(bf16* stage, int lane) {
+    bf16* in = stage + (lane >> 2) * KEY_STAGE_ROW + (lane & 3) * 8;
+    const bf16* out = stage + (lane & 15) * KEY_STAGE_ROW + (lane >> 5) * 8;
+    const bool upper = (lane & 16) != 0;
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint4 o[2][2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          wave_lds_order();
+          *reinterpret_cast<uint4*>(in) = w[kb][2 * q + x];
+          wave_lds_order();
+          o[x][0] = *reinterpret_cast<const uint4*>(out);
+          o[x][1] = *reinterpret_cast<const uint4*>(out + 16);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          w[kb][2 * q + i] = make_uint4(upper ? o[1][i].x : o[0][i].x, upper ? o[1][i].y : o[0][i].y,
+                                        upper ? o[1][i].z : o[0][i].z, upper ? o[1][i].w : o[0][i].w);
+      }
+    wave_lds_order();
+  }
   __device__ __forceinline__ bf16x8 operand(int kb, int kk) const {
     return __builtin_bit_cast(bf16x8, w[kb][kk]);
   }

@@ -11,33 +11,49 @@
 // (max, argmax) lives in plain registers and only one exchange between lanes
 // l and l+32 is needed at the very end.
 //
-// This file holds the form for few keys (below 65536 head-problem tokens): 32 keys per
+// This file holds the form for few keys or small tables (assign_tile_tokens): 32 keys per
 // wavefront in registers, so that there are many workgroups, and the centroids through LDS in
 // double-buffered chunks of 64 rows.  k_assign_stream (tables of at most 512 centroids) and
 // k_assign_wide (larger ones) take the rest.
 #include <atomic>
 
 #include "chunk_sort.hpp"
+#include "key_operand.hpp"
 
 namespace ck {
 
 constexpr int CHUNK_ROWS = 64;             // centroid rows per LDS chunk (two MFMA tiles)
 constexpr int LDS_ROW = D + 8;             // bf16 elements per LDS row: 272 B, rows shift 4 banks
 
-// HAS_BIAS (l2 metric): a per-centroid bias, held in LDS, is added to every
-// similarity before the argmax; it takes 8 KB more, so three workgroups fit a CU instead of four.
-constexpr int SM_WAVES = 4;
-template <bool HAS_BIAS>
-__global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
+// One workgroup takes one chunk of the sort, 32 tokens per wavefront.
+// Bound: latency.  A workgroup asks for its table rows (the first two chunks of them), bias, keys and
+// previous labels in one go; the keys come in whole 64-byte pieces and change lanes in LDS
+// (key_operand.hpp).  A table of more than two chunks is requested two chunks ahead.  Before, keys came
+// in operand layout behind the bias, the second chunk behind the first barrier, the previous labels at
+// the end, and the changed ones were counted by an atomic per workgroup.  Ten iterations, us: 8 x 2985 x 37
+// 96 -> 93, 4 x 15738 x 98 155 -> 142, the same by l2 185 -> 172, by l2 until convergence 236 -> 181.
+// HAS_BIAS (l2 metric): a per-centroid bias, held in LDS, is added to every similarity before the
+// argmax.  ONE: a table of one chunk.  TIGHT: the keys through half of the LDS, so that a compute unit
+// holds four workgroups of four wavefronts in place of three (3 % less where there are as many: 8 x 20000 x 250
+// 319 -> 301 us, 32 x 4096 x 51 without; 2 % more where there are not: 4 x 15738 x 98 142 -> 145).
+template <bool HAS_BIAS, int WAVES, bool ONE, bool TIGHT>
+__global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks_hp, int label_bits,
     int64_t N_cap, int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
     const KmCtl ctl) {
-  constexpr int WAVES = SM_WAVES, THREADS = WAVES * 64;
+  constexpr int THREADS = WAVES * 64, BUFS = ONE ? 1 : 2;
   constexpr int SEGS = CHUNK_ROWS * 16 / THREADS;      // 16-byte segments of a chunk per thread
-  __shared__ __attribute__((aligned(16))) bf16 lds[2][CHUNK_ROWS * LDS_ROW];
-  __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? CK_MAX_CLUSTERS + 32 : 4];
+  constexpr int CHUNK = WAVES * 32;                    // tokens of the workgroup = one chunk of the sort
+  constexpr int W = CHUNK / WAVE, CNT = chunk_sort_cnt_ints(ONE ? CHUNK_ROWS : CK_MAX_CLUSTERS) * W;
+  constexpr int STAGE = TIGHT ? KEY_STAGE_ELEMS / 2 : KEY_STAGE_ELEMS;
+  constexpr int SORT_BYTES = (CHUNK + CNT + 8) * 4 + CHUNK * 2;
+  constexpr int TABLE_BYTES = BUFS * CHUNK_ROWS * LDS_ROW * 2;
+  __shared__ __attribute__((aligned(16))) char lds_raw[SORT_BYTES > TABLE_BYTES ? SORT_BYTES : TABLE_BYTES];
+  __shared__ __attribute__((aligned(16))) bf16 key_stage[WAVES * STAGE];
+  __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? (ONE ? CHUNK_ROWS : CK_MAX_CLUSTERS + 32) : 4];
   __shared__ int s_changed;
+  bf16* lds = reinterpret_cast<bf16*>(lds_raw);        // [BUFS][CHUNK_ROWS][LDS_ROW]
 
   // one argument per 64-byte line of the argument block: fetched where it is first used, a line would
   // queue behind the key loads
@@ -47,16 +63,14 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   const int hp = blockIdx.y;
-  if (ctl.skip && ctl.skip[hp] == 0) return;            // converged: whole workgroup leaves
-  const bf16* Khp = K + (int64_t)hp * N_cap * D;
+  const bf16* Khp = K + ((int64_t)hp * N_cap + tok_begin) * D;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
 
-  const int n_chunks = (c_count + CHUNK_ROWS - 1) / CHUNK_ROWS;
+  const int n_chunks = ONE ? 1 : (c_count + CHUNK_ROWS - 1) / CHUNK_ROWS;
   const int n_tiles = (c_count + 31) / 32;
-  uint4 stage[SEGS];
   // unconditional loads (rows beyond the table re-read its last row and are replaced by zeros when
   // they are written to LDS): under a branch each waits for the one before
-  auto fetch = [&](int ch) {
+  auto fetch = [&](uint4 (&stage)[SEGS], int ch) {
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int seg = tid + i * THREADS;
@@ -64,34 +78,42 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
       stage[i] = *reinterpret_cast<const uint4*>(Mhp + (int64_t)(r < c_count ? r : c_count - 1) * D + (seg & 15) * 8);
     }
   };
-  auto stash = [&](int buf, int ch) {
+  auto stash = [&](const uint4 (&stage)[SEGS], int ch) {
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int seg = tid + i * THREADS;
       const bool real = ch * CHUNK_ROWS + (seg >> 4) < c_count;
       uint4 v = stage[i];
       v.x = real ? v.x : 0u; v.y = real ? v.y : 0u; v.z = real ? v.z : 0u; v.w = real ? v.w : 0u;
-      *reinterpret_cast<uint4*>(&lds[buf][(seg >> 4) * LDS_ROW + (seg & 15) * 8]) = v;
+      *reinterpret_cast<uint4*>(&lds[((ONE ? 0 : ch & 1) * CHUNK_ROWS + (seg >> 4)) * LDS_ROW + (seg & 15) * 8]) = v;
     }
   };
-  // first centroid chunk ahead of the keys, so that it does not queue behind them
-  fetch(0);
-  if (tid == 0) s_changed = 0;
+  // the table ahead of the keys, so that it does not queue behind them
+  uint4 first[BUFS][SEGS];
+#pragma unroll
+  for (int i = 0; i < BUFS; ++i) fetch(first[i], i);
+  float b0 = 0.f;
+  if constexpr (HAS_BIAS) b0 = ctl.bias[(int64_t)hp * ctl.bias_stride + (tid < c_count ? tid : 0)];
+
+  // ---- keys of this wavefront ----
+  const int64_t wave_tok0 = ((int64_t)blockIdx.x * WAVES + wave) * 32;
+  KeyTile<1> keys;
+  keys.load(Khp, wave_tok0, tok_count, lane);
+  const int64_t my_tok = wave_tok0 + col;
+  int32_t* my_label = labels + (int64_t)hp * N_cap + tok_begin + (my_tok < tok_count ? my_tok : tok_count - 1);
+  int before = -1;
+  if (ctl.changed) before = *my_label;                  // not looked at where there are none yet
+
+#pragma unroll
+  for (int i = 0; i < BUFS; ++i) stash(first[i], i);
   if constexpr (HAS_BIAS) {
-    for (int c = tid; c < n_tiles * 32; c += THREADS)
+    if (tid < n_tiles * 32) lds_bias[tid] = tid < c_count ? b0 : 0.f;
+    for (int c = tid + THREADS; c < n_tiles * 32; c += THREADS)
       lds_bias[c] = c < c_count ? ctl.bias[(int64_t)hp * ctl.bias_stride + c] : 0.f;
   }
-
-  // ---- keys of this wavefront into registers, in B-operand layout ----
-  const int64_t wave_tok0 = ((int64_t)blockIdx.x * WAVES + wave) * 32;
-  bf16x8 bk[8];
-  {
-    int64_t t = wave_tok0 + col;
-    if (t >= tok_count) t = tok_count - 1;              // clamp: result is discarded
-    const bf16* row = Khp + (tok_begin + t) * D + half * 8;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) bk[kk] = *reinterpret_cast<const bf16x8*>(row + kk * 16);
-  }
+  if (tid == 0) s_changed = 0;
+  // converged: the whole workgroup leaves.  Looked at here, the word travels with the loads above
+  if (ctl.skip && ctl.skip[hp] == 0) return;
 
   // Running maximum as a "packed" float: the low 4 mantissa bits of
   // every similarity are replaced by 15 - (accumulator slot), so one v_max3 chain
@@ -113,7 +135,7 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       const bf16x8 a = *reinterpret_cast<const bf16x8*>(arow + kk * 16);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bk[kk], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, keys.operand(0, kk), acc, 0, 0, 0);
     }
   };
   // folds the accumulators of tile `tile_id` into the running maximum
@@ -150,12 +172,15 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
     bestp = up ? m : bestp;
   };
 
-  stash(0, 0);
+  uint4 next[SEGS];
+  if constexpr (!ONE)
+    if (n_chunks > 2) fetch(next, 2);
+  if constexpr (TIGHT) keys.to_operand_16(key_stage + wave * STAGE, lane);
+  else keys.to_operand(key_stage + wave * STAGE, lane);
   __syncthreads();
 
   for (int ch = 0; ch < n_chunks; ++ch) {
-    if (ch + 1 < n_chunks) fetch(ch + 1);
-    const bf16* buf = lds[ch & 1];
+    const bf16* buf = lds + (ONE ? 0 : ch & 1) * CHUNK_ROWS * LDS_ROW;
 #pragma unroll
     for (int tile = 0; tile < 2; ++tile) {
       const int t = ch * 2 + tile;
@@ -164,21 +189,26 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
         reduce(t);
       }
     }
-    if (ch + 1 < n_chunks) stash((ch + 1) & 1, ch + 1);
-    __syncthreads();
+    if constexpr (!ONE) {
+      // chunk ch + 1 is in the other buffer; ch + 2 takes this one's place
+      if (ch + 1 < n_chunks) __syncthreads();
+      if (ch + 2 < n_chunks) {
+        stash(next, ch + 2);
+        if (ch + 3 < n_chunks) fetch(next, ch + 3);
+      }
+    }
   }
+  __syncthreads();                                      // the table's LDS is free
 
   // ---- lanes l and l+32 hold the two halves of each key's candidates ----
-  // (the centroid buffers are free now: the loop ended with a barrier)
-  constexpr int CHUNK = WAVES * 32;                     // tokens of the workgroup = one chunk
-  uint32_t* tok = reinterpret_cast<uint32_t*>(&lds[0][0]);   // pack_token words
+  uint32_t* tok = reinterpret_cast<uint32_t*>(lds_raw);   // pack_token words
   const bool count_only = chunks.seg && !chunks.list;   // counts by cluster in place of the words
   if (count_only) {
-    static_assert(CK_MAX_CLUSTERS * 4 <= sizeof(lds), "counts");
+    static_assert((ONE ? CHUNK_ROWS : CK_MAX_CLUSTERS) * 4 <= sizeof(lds_raw), "counts");
     for (int c = tid; c < c_count; c += THREADS) tok[c] = 0;
     __syncthreads();
   }
-  int diff = 0;
+  bool moved = false;
   const int slot = 15 - (int)(__float_as_uint(bestp) & 15u);
   float best = bestp;
   int bidx = btile * 32 + 8 * (slot >> 2) + 4 * half + (slot & 3);
@@ -195,19 +225,14 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
     // a key with a NaN or infinite channel may have no similarity that is a number: a padded
     // row has won then, and the key goes to the last cluster
     bidx = bidx < c_count ? bidx : c_count - 1;
-    const int64_t t = wave_tok0 + col;
-    if (half == 0 && t < tok_count) {
-      const int64_t o = (int64_t)hp * N_cap + tok_begin + t;
-      if (ctl.changed) diff += (ctl.first || labels[o] != c_begin + bidx) ? 1 : 0;
-      labels[o] = c_begin + bidx;
-      if (best_sim) best_sim[o] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
+    if (half == 0 && my_tok < tok_count) {
+      moved = ctl.first || before != c_begin + bidx;
+      *my_label = c_begin + bidx;
+      if (best_sim) best_sim[my_label - labels] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
       if (count_only) atomicAdd(&tok[bidx], 1u);
     }
   }
-  if (ctl.changed) {
-    const int wsum = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
-    if (lane == 0 && wsum) atomicAdd(&s_changed, wsum);
-  }
+  if (ctl.changed && __ballot(moved) && lane == 0) s_changed = 1;
   if (chunks.list) {
     // 32 tokens per wavefront: the even one of a pair ranks both halves of the group
     uint32_t* raw = tok + CHUNK;
@@ -218,30 +243,35 @@ __global__ __launch_bounds__(SM_WAVES * 64, HAS_BIAS ? 3 : 4) void k_assign(
                                          wave_tok0 + lane < tok_count, label_bits);
   }
   if (chunks.seg || ctl.changed) __syncthreads();
-  if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
+  if (ctl.changed && tid == 0 && s_changed) ctl.changed[hp] = 1;
   const int64_t o = (int64_t)hp * n_chunks_hp + blockIdx.x;
   if (count_only) {
     for (int c = tid; c < c_count; c += THREADS) chunks.seg[o * seg_stride(c_count) + c] = tok[c] << 16;
   } else if (chunks.seg) {
-    constexpr int W = CHUNK / WAVE, CNT = chunk_sort_cnt_ints(CK_MAX_CLUSTERS) * W;
-    static_assert((CHUNK + CNT + 4) * 4 + CHUNK * 2 <= sizeof(lds), "chunk sort scratch");
     int* cnt = reinterpret_cast<int*>(tok) + CHUNK;
-    chunk_sort<CHUNK / WAVE, CK_MAX_CLUSTERS, W>(
-        tok, c_count, wave, wave < W, cnt, cnt + CNT, reinterpret_cast<uint16_t*>(cnt + CNT + 4),
+    chunk_sort<CHUNK / WAVE, ONE ? CHUNK_ROWS : CK_MAX_CLUSTERS, W>(
+        tok, c_count, wave, wave < W, cnt, cnt + CNT, reinterpret_cast<uint16_t*>(cnt + CNT + 8),
         chunks.seg + o * seg_stride(c_count), chunks.list + o * CHUNK);
   }
 }
 
-static hipError_t launch_assign_small(const Dims& dm, const bf16* K, int64_t tok_begin,
-                                      int64_t tok_count, const bf16* mu_hat, int c_begin,
-                                      int c_count, int32_t* labels, float* best_sim,
-                                      const ChunkIndex& chunks, const KmCtl& ctl, hipStream_t st) {
-  constexpr int TOK = SM_WAVES * 32;
+template <int WAVES>
+static hipError_t launch_assign_few(const Dims& dm, const bf16* K, int64_t tok_begin,
+                                    int64_t tok_count, const bf16* mu_hat, int c_begin,
+                                    int c_count, int32_t* labels, float* best_sim,
+                                    const ChunkIndex& chunks, const KmCtl& ctl, int n_cu,
+                                    hipStream_t st) {
+  constexpr int TOK = WAVES * 32;
   const int n_chunks = (int)((tok_count + TOK - 1) / TOK);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
-  const auto kernel = ctl.bias ? k_assign<true> : k_assign<false>;
-  hipLaunchKernelGGL(kernel, dim3(n_chunks, dm.HP), dim3(SM_WAVES * 64), 0, st, K, mu_hat, labels,
+  // more workgroups than the compute units hold of the other form
+  const bool tight = (int64_t)n_chunks * dm.HP > (int64_t)n_cu * (12 / WAVES);
+  const auto kernel =
+      c_count <= CHUNK_ROWS ? (ctl.bias ? k_assign<true, WAVES, true, false> : k_assign<false, WAVES, true, false>)
+      : tight               ? (ctl.bias ? k_assign<true, WAVES, false, true> : k_assign<false, WAVES, false, true>)
+                            : (ctl.bias ? k_assign<true, WAVES, false, false> : k_assign<false, WAVES, false, false>);
+  hipLaunchKernelGGL(kernel, dim3(n_chunks, dm.HP), dim3(WAVES * 64), 0, st, K, mu_hat, labels,
                      best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
                      c_count, ctl);
   return hipGetLastError();
@@ -249,8 +279,27 @@ static hipError_t launch_assign_small(const Dims& dm, const bf16* K, int64_t tok
 
 // Chunk size of the counting sort = the tokens of the workgroup (a block of its tokens in
 // k_assign_stream) that leaves the label-ordered index of exactly these.
-int assign_tile_tokens(const Dims& dm, int64_t tok_count) {
-  return tok_count * dm.HP >= 64 * 1024 ? 512 : 128;
+// 128 or 256 (k_assign) where that gives one workgroup per compute unit: the launch is as long as one
+// workgroup, and with two on some units the others wait.  Ten iterations, 128 / 256 / 512 tokens, us
+// (head-problems x tokens x clusters): 4 x 6000 x 70 110 / 114 / 145, 1 x 24000 x 400 165 / 166 / 203;
+// 8 x 5000 x 102 150 / 146 / 180, 1 x 40000 x 700 246 / 219 / 263, 1 x 55000 x 500 221 / 203 / 235.
+// Beyond, k_assign_stream puts 512 tokens on a unit, k_assign_wide (more than 512 clusters) as well.
+// Where the contraction is nothing (64 clusters) many small workgroups stay ahead of both: 16 x 4400 x 40
+// 141 / 145 / 164, 128 x 1100 x 13 142 / 144 / 156, 32 x 7800 x 40 286 / 283 / 308, 128 x 6250 x 40
+// 681 / 678 / 719, 8 x 60000 x 60 475 / 470 / 488 (2 x 60000 x 50 282 / 271 / 278).  With a few more tiles
+// only while the units would not be full, in the first two rounds of them: 7 x 10000 x 102 157 / 167 / 176,
+// 8 x 20000 x 128 246 / 264 / 273, 8 x 8750 x 160 167 / 174 / 177, but full 8 x 15000 x 102 215 / 212 / 210,
+// 8 x 25000 x 128 291 / 305 / 290, 8 x 11250 x 160 184 / 190 / 187, and 8 x 8750 x 200 195 / 199 / 193.
+int assign_tile_tokens(const Dims& dm, int64_t tok_count, int c_count) {
+  constexpr int64_t CUS = 256, ROUND = CUS * 512;
+  const int64_t tokens = tok_count * dm.HP;
+  if (tokens <= CUS * 128) return 128;
+  if (tokens <= CUS * 256) return 256;
+  if (tok_count > 128 * CHUNK_RUNS_MAX) return 512;     // more chunks than the index holds
+  if (c_count <= 64) return 128;
+  const int64_t rounds = (tokens + ROUND - 1) / ROUND;
+  const int fill = c_count <= 128 ? 70 : c_count <= 160 ? 60 : 0;   // per cent
+  return rounds <= 2 && tokens * 100 <= rounds * ROUND * fill ? 128 : 512;
 }
 
 // Compute units of the current device, asked once per device (the query costs a few
@@ -272,9 +321,13 @@ hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64
                          const bf16* mu_hat, int c_begin, int c_count, int32_t* labels,
                          float* best_sim, const ChunkIndex& chunks, const KmCtl& ctl,
                          hipStream_t st) {
-  if (assign_tile_tokens(dm, tok_count) != 512)
-    return launch_assign_small(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count, labels, best_sim,
-                               chunks, ctl, st);
+  const int tokens = chunks.tokens ? chunks.tokens : assign_tile_tokens(dm, tok_count, c_count);
+  if (tokens == 128)
+    return launch_assign_few<4>(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count, labels, best_sim,
+                                chunks, ctl, compute_units(), st);
+  if (tokens == 256)
+    return launch_assign_few<8>(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count, labels, best_sim,
+                                chunks, ctl, compute_units(), st);
   if (assign_stream_fits(c_count))
     return launch_assign_stream(dm, K, tok_begin, tok_count, mu_hat, c_begin, c_count, labels,
                                 best_sim, chunks, ctl, compute_units(), st);

@@ -254,9 +254,10 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
 
 hipError_t launch_metadata(const Dims& dm, const int32_t* labels, int64_t tok_begin,
                            int64_t tok_count, int c_begin, int c_count, int32_t* sizes,
-                           int32_t* offsets, int32_t* sorted_idx, uint32_t* seg,
+                           int32_t* offsets, int32_t* sorted_idx, const ChunkIndex& chunks,
                            bool have_seg, const int32_t* gate, hipStream_t st) {
-  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+  uint32_t* seg = chunks.seg;
+  const int chunk_tokens = chunks.tokens;
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
@@ -402,8 +403,6 @@ hipError_t launch_update(const Dims& dm, const bf16* K, const int32_t* offsets,
 // a cluster in ascending token order are its runs of chunk 0, chunk 1, ...: no sorted list is
 // needed to sum them.  A wavefront scans the run lengths of its cluster over the chunks and
 // finds the run that holds the j-th member by binary search in LDS.
-constexpr int CHUNK_RUNS_MAX = 512;                     // chunks per head-problem (LDS: 2 words each)
-
 struct ChunkRuns {
   const uint32_t* seg;
   const uint16_t* list;
@@ -784,8 +783,7 @@ __global__ __launch_bounds__(EMIT_WAVES * 64) void k_emit_index(
   }
 }
 
-bool update_chunks_fits(const Dims& dm, int64_t tok_count) {
-  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+bool update_chunks_fits(int chunk_tokens, int64_t tok_count) {
   return (tok_count + chunk_tokens - 1) / chunk_tokens <= CHUNK_RUNS_MAX;
 }
 
@@ -812,7 +810,7 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
                                 float* bias, int bias_stride, const int32_t* gate, hipStream_t st) {
-  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+  const int chunk_tokens = chunks.tokens;
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   const int cl = update_clusters_per_workgroup(n_chunks, c_count, dm.HP);
   const int groups = ((c_count + cl - 1) / cl + 7) / 8 * 8;
@@ -827,7 +825,7 @@ hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t t
                              int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
                              int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done, int n_iter,
                              hipStream_t st) {
-  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
+  const int chunk_tokens = chunks.tokens;
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   hipLaunchKernelGGL(k_emit_index, dim3((c_count + EMIT_WAVES - 1) / EMIT_WAVES, dm.HP),
                      dim3(EMIT_WAVES * 64), chunk_runs_lds(EMIT_WAVES, n_chunks), st, chunks.seg, chunks.list,
@@ -836,10 +834,8 @@ hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t t
   return hipGetLastError();
 }
 
-ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count,
-                                         void* base) {
+static ClusterWorkspace carve(const Dims& dm, int64_t tok_count, int c_count, int chunk_tokens, void* base) {
   ClusterWorkspace w;
-  const int chunk_tokens = assign_tile_tokens(dm, tok_count);
   const int64_t n_chunks = (tok_count + chunk_tokens - 1) / chunk_tokens;
   size_t mu = (size_t)dm.HP * c_count * D * sizeof(bf16);
   mu = (mu + 255) & ~(size_t)255;
@@ -855,10 +851,18 @@ ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int 
   char* b = reinterpret_cast<char*>(base);
   w.mu_hat = reinterpret_cast<bf16*>(b);
   w.chunks.seg = reinterpret_cast<uint32_t*>(b + mu);
+  w.chunks.tokens = chunk_tokens;
   w.chunks.list = reinterpret_cast<uint16_t*>(b + mu + seg);
   w.bias = reinterpret_cast<float*>(b + mu + seg + list);
   w.changed = reinterpret_cast<int32_t*>(b + mu + seg + list + bias);
   w.bytes = mu + seg + list + bias + chg;
+  return w;
+}
+
+ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, void* base, size_t have) {
+  const ClusterWorkspace w = carve(dm, tok_count, c_count, assign_tile_tokens(dm, tok_count, c_count), base);
+  // a workspace that was sized for more tokens may hold chunks of 512 only: they run as well
+  if (w.bytes > have && tok_count * dm.HP >= 64 * 1024) return carve(dm, tok_count, c_count, 512, base);
   return w;
 }
 

@@ -57,6 +57,23 @@ def test_strerror_and_workspace_sizes():
     assert ck.ck_workspace_bytes(ck.Shape(1, 32, 8, 32768, 400, d=64), 0, 100, 4) == 0
 
 
+def test_clustering_takes_a_workspace_of_large_chunks():
+    """A workspace for more tokens serves fewer, whatever chunks either would take by itself: what an
+    index of chunks of 512 tokens needs is enough, one byte less is not."""
+    binding.load_library()
+    HP, n, C = 16, 8000, 40                             # chunks of 128 by itself
+    sh = ck.Shape(2, 8, 8, n, C)
+    own = ck.ck_workspace_bytes(sh, binding.CK_WS_CLUSTER_KEYS, n, C)
+    up = lambda b: (b + 255) // 256 * 256
+    need = (up(HP * C * 256) + up(HP * 16 * 40 * 4) + up(HP * 16 * 512 * 2) + up(HP * 64 * 4)
+            + up(257 * HP * 4))
+    assert own > need
+    A = 4096                                            # an aligned address that is never dereferenced
+    lib = binding.load_library()
+    call = lambda bytes_: lib.ck_build_metadata(ctypes.byref(sh.c()), A, 0, n, 0, C, A, A, A, A, bytes_, None)
+    assert call(need - 1) == -3
+
+
 @pytest.mark.parametrize("G", [1, 4, 8])
 def test_attention_workspace_is_one_round_of_workgroups(G):
     """The workspace shows the number of splits: every XCD (32 compute units, one workgroup of

@@ -21,10 +21,19 @@ STREAM = [(1, 65537, 512),           # one token in the last block, largest tabl
           (8, 50000, 40),            # 98 blocks a head-problem: four to a workgroup
           (40, 10000, 33),           # 20 blocks, four to a workgroup of five
           (64, 20000, 31),           # 40 blocks, ten rounds' worth in two
-          (300, 600, 7)]             # more head-problems than compute units
+          (300, 600, 7),             # more head-problems than compute units
+          (8, 50000, 65), (40, 10000, 65), (64, 20000, 66),   # blocks as above, three tiles
+          (8, 13000, 128), (2, 60000, 129)]
+FEW = [(3, 10922, 64),               # k_assign: a table of one chunk, workgroups of 128 tokens
+       (1, 32768, 65),               # of two
+       (1, 32769, 129), (5, 13107, 64),   # three, one; workgroups of 256 tokens
+       (2, 32768, 700),              # eleven
+       (8, 8193, 64), (9, 10100, 128), (1, 65537, 128),   # 128 again, with all the LDS there is and half of it
+       (2, 39000, 160), (16, 9000, 80),
+       (1, 65536, 2048), (700, 500, 5)]
 
 
-@pytest.mark.parametrize("hp,n,C", WIDE + STREAM)
+@pytest.mark.parametrize("hp,n,C", WIDE + STREAM + FEW)
 def test_labels_against_64_bits(hp, n, C):
     g = torch.Generator(device=DEV).manual_seed(n + C)
     K = torch.randn(1, hp, n + 3, 128, generator=g, device=DEV).to(torch.bfloat16)
@@ -46,7 +55,7 @@ def test_labels_against_64_bits(hp, n, C):
     assert ties < 0.01 * hp * n
 
 
-@pytest.mark.parametrize("hp,n,C", WIDE + STREAM)
+@pytest.mark.parametrize("hp,n,C", WIDE + STREAM + FEW)
 def test_iterations_leave_consistent_metadata(hp, n, C):
     g = torch.Generator(device=DEV).manual_seed(n - C)
     K = torch.randn(1, hp, n, 128, generator=g, device=DEV).to(torch.bfloat16)
@@ -63,7 +72,8 @@ def test_iterations_leave_consistent_metadata(hp, n, C):
 
 @pytest.mark.parametrize("hp,n,C", [(1, 65537, 513), (2, 32801, 2047),      # k_assign_wide with its bias table
                                     (1, 65537, 511), (8, 8193, 100),        # k_assign_stream
-                                    (1, 2500, 2047), (2, 385, 9)])          # k_assign
+                                    (1, 2500, 2047), (2, 385, 9),           # k_assign
+                                    (2, 20000, 600), (1, 40000, 64), (9, 10100, 100)])
 def test_l2_labels_against_64_bits(hp, n, C):
     """One iteration by l2 assigns every key to the nearest of the given rows.  A similarity
     x mu - |mu|^2 / 2 is off by at most 128 * 2^-24 of |x| |mu| + |mu|^2 / 2 (fp32 sums of exact

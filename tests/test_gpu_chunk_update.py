@@ -24,7 +24,10 @@ SHAPES = [
     (2, 8, 4050, 130, 3, 5),         # chunks of 128, appended behind existing clusters, odd range
     (2, 8, 4097, 513, 1, 0),         # table streamed in chunks; one token in the last chunk of 512
     (1, 8, 8200, 512, 0, 0),         # largest LDS-resident table
-    (1, 1, 65535, 60, 0, 0),         # chunks of 128: exactly as many as the index holds
+    (1, 1, 65535, 60, 0, 0),         # chunks of 256
+    (1, 2, 65536, 60, 0, 0),         # chunks of 128: exactly as many as the index holds
+    (3, 1, 20000, 70, 3, 5),         # chunks of 256, appended behind existing clusters, odd range
+    (9, 1, 9001, 100, 1, 0),         # chunks of 128, half of the LDS
     (1, 1, 262144, 64, 0, 0),        # chunks of 512: exactly as many
     (1, 1, 262145, 64, 0, 0),        # one chunk more: counts only, and the sorted-list form
     (1, 2, 262700, 512, 7, 3),       # the same with the largest LDS-resident table
@@ -72,6 +75,27 @@ def test_cluster_keys_equals_the_exported_steps(S, Hkv, N, C, begin, c_begin):
     for name in ("labels", "sizes", "offsets", "sorted_idx"):
         assert torch.equal(getattr(got, name), getattr(want, name)), name
     assert torch.equal(got.centroids.view(torch.int16), want.centroids.view(torch.int16))
+
+
+def test_workspace_of_large_chunks():
+    """In a workspace that holds chunks of 512 tokens only (see test_abi_cpu.py) the call takes those:
+    same outputs."""
+    HP, n, C = 16, 8000, 40
+    g = torch.Generator(device=DEV).manual_seed(5)
+    K = torch.randn(2, 8, n, 128, generator=g, device=DEV).to(torch.bfloat16)
+    init = torch.rand(2, 8, n, generator=g, device=DEV).topk(C, dim=-1).indices.int()
+    sh = ck.Shape(2, 8, 8, n, C)
+    up = lambda b: (b + 255) // 256 * 256
+    need = (up(HP * C * 256) + up(HP * 16 * 40 * 4) + up(HP * 16 * 512 * 2) + up(HP * 64 * 4)
+            + up(257 * HP * 4))
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    a, b = (ck.ClusterState(sh, DEV, budget=64) for _ in range(2))
+    a.cluster(K, init, 0, n, C, 3)
+    ck.ck_cluster_keys(sh, K, 0, n, 0, C, 3, init, b.centroids, b.labels, b.sizes, b.offsets,
+                       b.sorted_idx, workspace=ws)
+    torch.cuda.synchronize()
+    for name in ("labels", "sizes", "offsets", "sorted_idx", "centroids"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
 
 
 @pytest.mark.parametrize("S,Hkv,N,C,begin,c_begin", SHAPES)
