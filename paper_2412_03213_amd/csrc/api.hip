@@ -247,14 +247,11 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
   float* bias = metric == CK_METRIC_L2 ? ws.bias : nullptr;
   hipError_t e = ck::launch_init_centroids(dm, Kb, init_idx, c_begin, c_count,
                                            (ck::bf16*)centroids, ws.mu_hat, metric, bias,
-                                           ws.bias_stride, st);
+                                           // one row per iteration, all zero: a head-problem that
+                                           // stops leaves its later rows at zero, which is what
+                                           // keeps it stopped
+                                           ws.bias_stride, converge ? ws.changed : nullptr, max_iter, st);
   if (e != hipSuccess) return hip_result(e, "init launch");
-  if (converge) {
-    // one row of changed-label counters per iteration, all zero: a head-problem that
-    // stops leaves its later rows at zero, which is what keeps it stopped
-    e = ck::launch_fill_i32(ws.changed, (int64_t)max_iter * dm.HP, 0, st);
-    if (e != hipSuccess) return hip_result(e, "counter fill launch");
-  }
   // the iterations need the sums of the clusters, not the sorted index: the update reads the labels
   // (short ranges, it then leaves the metadata too) or the chunk index of the assignment, from which
   // the metadata is built once, after the last iteration ...
@@ -264,8 +261,10 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
   ck::ChunkIndex chunks = ws.chunks;
   if (!chunked) chunks.list = nullptr;
   if (by_labels) chunks.seg = nullptr;
-  // written by the launch that writes the metadata; in convergence mode by one of its own
-  int32_t* count_out = converge ? nullptr : iters_done;
+  // the counts are written by the launch that writes the metadata, unless a head-problem may have left
+  // before it (convergence from the labels) or there are two such launches
+  const bool count_apart = !chunked && (converge || !by_labels);
+  int32_t* count_out = count_apart ? nullptr : iters_done;
   for (int it = 0; it < max_iter; ++it) {
     ck::KmCtl ctl;
     ctl.bias = bias;
@@ -304,10 +303,11 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
     // the metadata of the last labels; a head-problem that stopped early has left its chunk
     // index as its last assignment wrote it
     e = ck::launch_emit_index(dm, ws.chunks, tok_begin, tok_count, c_begin, c_count, sizes,
-                              offsets, sorted_idx, count_out, max_iter, st);
+                              offsets, sorted_idx, count_out, max_iter,
+                              converge ? ws.changed : nullptr, st);
     if (e != hipSuccess) return hip_result(e, "metadata launch");
   }
-  if (iters_done && (converge || !(by_labels || chunked))) {
+  if (iters_done && count_apart) {
     if (converge)
       e = ck::launch_iters_done(ws.changed, max_iter, dm.HP, iters_done, st);
     else

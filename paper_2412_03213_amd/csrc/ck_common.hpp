@@ -183,10 +183,12 @@ struct KmCtl {
 ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, void* base,
                                          size_t have = SIZE_MAX);
 
-// metric: CK_METRIC_* of the table the assignment will read
+// metric: CK_METRIC_* of the table the assignment will read; n_changed rows of `changed` (nullable) are
+// cleared
 hipError_t launch_init_centroids(const Dims& dm, const bf16* K, const int32_t* init_idx,
                                  int c_begin, int c_count, bf16* centroids, bf16* mu_hat,
-                                 int metric, float* bias, int bias_stride, hipStream_t st);
+                                 int metric, float* bias, int bias_stride, int32_t* changed,
+                                 int n_changed, hipStream_t st);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 bool kmeans_small_fits(int64_t tok_count, int c_count);
 hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,
@@ -232,11 +234,11 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
                                 float* bias, int bias_stride, const int32_t* gate, hipStream_t st);
 // offsets and sorted_idx of the labels the chunk index holds (sizes: as the update wrote them), and
-// n_iter into iters_done where that is given
+// into iters_done, where that is given, n_iter or what the rows of `changed` say
 hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
                              int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
                              int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done, int n_iter,
-                             hipStream_t st);
+                             const int32_t* changed, hipStream_t st);
 // the same update from the labels of a short range, and where offsets is given the metadata with it
 bool update_labels_fits(const Dims& dm, int64_t tok_count, int c_count);
 hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* labels,

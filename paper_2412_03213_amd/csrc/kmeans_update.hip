@@ -18,12 +18,15 @@ namespace ck {
 // ------------------------------------------------------------------ init
 // centroid c of head-problem hp := key row init_idx[hp][c]; also the row of the table the
 // assignment reads: its unit-length copy (cosine) or the row itself (l2, inner product),
-// and for l2 the bias -|row|^2 / 2.
+// and for l2 the bias -|row|^2 / 2.  In run-until-convergence mode n_changed rows of `changed` are
+// cleared here (a launch of its own for that took 2 us).
 __global__ __launch_bounds__(64) void k_init_centroids(
     const bf16* __restrict__ K, const int32_t* __restrict__ init_idx, int64_t N_cap, int C_cap,
     int c_begin, int c_count, bf16* __restrict__ centroids, bf16* __restrict__ mu_hat, int metric,
-    float* __restrict__ bias, int bias_stride) {
+    float* __restrict__ bias, int bias_stride, int32_t* __restrict__ changed, int n_changed) {
   const int c = blockIdx.x, hp = blockIdx.y, lane = threadIdx.x;
+  if (changed && c == 0)
+    for (int t = lane; t < n_changed; t += WAVE) changed[(int64_t)t * gridDim.y + hp] = 0;
   int64_t row = init_idx[(int64_t)hp * c_count + c];
   row = row < 0 ? 0 : (row >= N_cap ? N_cap - 1 : row);
   const uint32_t w = reinterpret_cast<const uint32_t*>(K + ((int64_t)hp * N_cap + row) * D)[lane];
@@ -49,33 +52,36 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {
 }
 
 // iterations a head-problem ran: up to and including the first assignment that changed
-// no label, or all of them
-__global__ void k_iters_done(const int32_t* __restrict__ changed, int max_iter, int HP,
-                             int32_t* __restrict__ iters_done) {
-  const int hp = blockIdx.x * blockDim.x + threadIdx.x;
-  if (hp >= HP) return;
-  int n = max_iter;
-  for (int t = 1; t < max_iter; ++t)
-    if (changed[(int64_t)t * HP + hp] == 0) {
-      n = t + 1;
-      break;
-    }
-  iters_done[hp] = n;
+// no label, or all of them; by one wavefront
+__device__ __forceinline__ int iterations_run(const int32_t* __restrict__ changed, int max_iter, int HP, int hp) {
+  const int lane = threadIdx.x & 63;
+  for (int t0 = 1; t0 < max_iter; t0 += WAVE) {
+    const int t = t0 + lane;
+    const uint64_t still = __ballot(t < max_iter && changed[(int64_t)min(t, max_iter - 1) * HP + hp] == 0);
+    if (still) return t0 + __builtin_ctzll(still) + 1;
+  }
+  return max_iter;
+}
+
+__global__ __launch_bounds__(64) void k_iters_done(const int32_t* __restrict__ changed, int max_iter,
+                                                   int32_t* __restrict__ iters_done) {
+  const int n = iterations_run(changed, max_iter, gridDim.x, blockIdx.x);
+  if (threadIdx.x == 0) iters_done[blockIdx.x] = n;
 }
 
 hipError_t launch_iters_done(const int32_t* changed, int max_iter, int HP, int32_t* iters_done,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_iters_done, dim3((HP + 63) / 64), dim3(64), 0, st, changed, max_iter, HP,
-                     iters_done);
+  hipLaunchKernelGGL(k_iters_done, dim3(HP), dim3(64), 0, st, changed, max_iter, iters_done);
   return hipGetLastError();
 }
 
 hipError_t launch_init_centroids(const Dims& dm, const bf16* K, const int32_t* init_idx,
                                  int c_begin, int c_count, bf16* centroids, bf16* mu_hat,
-                                 int metric, float* bias, int bias_stride, hipStream_t st) {
+                                 int metric, float* bias, int bias_stride, int32_t* changed,
+                                 int n_changed, hipStream_t st) {
   hipLaunchKernelGGL(k_init_centroids, dim3(c_count, dm.HP), dim3(64), 0, st, K, init_idx,
                      dm.N_cap, dm.C_cap, c_begin, c_count, centroids, mu_hat, metric, bias,
-                     bias_stride);
+                     bias_stride, changed, n_changed);
   return hipGetLastError();
 }
 
@@ -506,13 +512,13 @@ __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chun
   // on XCD i % 8)
   const int hp = blockIdx.y, c0 = (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8) * CL;
   if (c0 >= c_count) return;
-  if (gate && gate[hp] == 0) return;
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
   ChunkRuns cr[CL];
 #pragma unroll
   for (int cl = 0; cl < CL; ++cl) cr[cl] = {seg, list, n_chunks, chunk_tokens, tok_count};
   cr[0].template load<CL, UPC_WAVES * 64>(lds_u, hp, c0, c_count);
+  if (gate && gate[hp] == 0) return;                    // here the word has travelled with the table
 #pragma unroll
   for (int cl = 0; cl < CL; ++cl) {
     cr[cl].scan(lds_u, hp, cl);
@@ -611,8 +617,6 @@ __global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
   CK_FETCH_ARG(offsets);
-  // a head-problem that has converged: labels, and with them everything below, are what they were
-  if (gate && gate[hp] == 0) return;
   const int32_t* lab = labels + (int64_t)hp * N_cap + tok_begin;
   const int first = wave * ROUNDS * WAVE + lane, mine = c_begin + c;
   int l[ROUNDS];
@@ -636,6 +640,8 @@ __global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
   }
   if (lane == 0) found[wave] = n_here;
   __syncthreads();
+  // a head-problem that has converged: labels, and with them everything below, are what they were
+  if (gate && gate[hp] == 0) return;
   int base = 0, n = 0;
 #pragma unroll
   for (int w = 0; w < UPL_WAVES; ++w) {
@@ -736,14 +742,18 @@ hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* la
 
 // Metadata of the final labels: offsets (prefix sum of the sizes the last update wrote) and
 // the label-sorted index, one wavefront per cluster.  One launch where the counting sort needs
-// two, and the index leaves in coalesced stores.
+// two, and the index leaves in coalesced stores: the segments of a workgroup's clusters follow each
+// other, so its threads share them whatever their sizes (a wavefront for each cluster took 11.2 us at
+// 4 x 24553 x 306 by inner product, where a few clusters hold most keys, now 5.0; 31.6 -> 12.8 at
+// 16 x 50000 x 600).
 constexpr int EMIT_WAVES = 8;                           // clusters per workgroup
 
 __global__ __launch_bounds__(EMIT_WAVES * 64) void k_emit_index(
     const uint32_t* __restrict__ seg, const uint16_t* __restrict__ list, int n_chunks,
     int chunk_tokens, int64_t N_cap, int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin,
     int c_count, const int32_t* __restrict__ sizes, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter) {
+    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter,
+    const int32_t* __restrict__ changed) {
   extern __shared__ uint32_t lds_u[];
   __shared__ int below[EMIT_WAVES], own[EMIT_WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -767,19 +777,38 @@ __global__ __launch_bounds__(EMIT_WAVES * 64) void k_emit_index(
     own[wave] = cr.n;
   }
   __syncthreads();
-  if (c >= c_count) return;
-  int base = base0;
+  int base = base0, total = 0, n_of[EMIT_WAVES];        // base: of the first cluster
+  int end = cr.n;                                       // of this wavefront's, relative to it
 #pragma unroll
-  for (int w = 0; w < EMIT_WAVES; ++w) base += below[w] + (w < wave ? own[w] : 0);
-  if (lane == 0) {
-    off_g[c_begin + c + 1] = base + cr.n;
-    if (c == 0 && c_begin == 0) off_g[0] = 0;
-    if (c == 0 && iters_done) iters_done[hp] = n_iter;
+  for (int w = 0; w < EMIT_WAVES; ++w) {
+    base += below[w];
+    n_of[w] = own[w];                                   // zero behind the last cluster
+    total += n_of[w];
+    end += w < wave ? n_of[w] : 0;
   }
+  if (c < c_count && lane == 0) {
+    off_g[c_begin + c + 1] = base + end;
+    if (c == 0 && c_begin == 0) off_g[0] = 0;
+  }
+  if (iters_done && c == 0) {
+    const int n = changed ? iterations_run(changed, n_iter, gridDim.y, hp) : n_iter;
+    if (lane == 0) iters_done[hp] = n;
+  }
+  const int cpad = (n_chunks + 63) & ~63;
   int32_t* out = sorted_idx + (int64_t)hp * N_cap;
-  for (int j = lane; j < cr.n; j += WAVE) {
+  for (int j = tid; j < total; j += EMIT_WAVES * 64) {
+    int k = j, w = 0;                                   // member k of cluster c0 + w
+#pragma unroll
+    for (int i = 0; i + 1 < EMIT_WAVES; ++i)
+      if (w == i && k >= n_of[i]) {
+        k -= n_of[i];
+        w = i + 1;
+      }
+    cr.runs = lds_u + (size_t)w * 2 * cpad;
+    cr.upto = reinterpret_cast<const int*>(cr.runs + cpad);
+    cr.n = k + 1;
     const int64_t pos = (int64_t)base + j;
-    if (pos >= 0 && pos < N_cap) out[pos] = (int32_t)(tok_begin + cr.member(j));
+    if (pos >= 0 && pos < N_cap) out[pos] = (int32_t)(tok_begin + cr.member(k));
   }
 }
 
@@ -824,13 +853,13 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
 hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
                              int64_t tok_count, int c_begin, int c_count, const int32_t* sizes,
                              int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done, int n_iter,
-                             hipStream_t st) {
+                             const int32_t* changed, hipStream_t st) {
   const int chunk_tokens = chunks.tokens;
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   hipLaunchKernelGGL(k_emit_index, dim3((c_count + EMIT_WAVES - 1) / EMIT_WAVES, dm.HP),
                      dim3(EMIT_WAVES * 64), chunk_runs_lds(EMIT_WAVES, n_chunks), st, chunks.seg, chunks.list,
                      n_chunks, chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin,
-                     c_count, sizes, offsets, sorted_idx, iters_done, n_iter);
+                     c_count, sizes, offsets, sorted_idx, iters_done, n_iter, changed);
   return hipGetLastError();
 }
 
