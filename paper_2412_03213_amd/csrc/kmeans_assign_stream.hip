@@ -45,7 +45,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     const KmCtl ctl) {
   constexpr int NKB = ST_NKB, THREADS = ST_WAVES * 64;
   __shared__ __attribute__((aligned(16))) bf16 table[ST_MAX_TILES * 32 * LDS_ROW];
-  __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? ST_MAX_TILES * 32 : 4];
+  __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? (ST_MAX_TILES + 1) * 32 : 4];
   __shared__ uint32_t tok[ST_MAX_BLOCKS * ST_CHUNK];     // pack_token words of this workgroup's tokens, or
                                                          // [chunk][cluster] counts (clusters <= ST_CHUNK)
   __shared__ int s_changed, s_next_task;
@@ -55,29 +55,30 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   CK_FETCH_ARG(labels);
   CK_FETCH_ARG(tok_count);
   CK_FETCH_ARG(ctl.first);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int hp = blockIdx.y;
-  if (ctl.skip && ctl.skip[hp] == 0) return;            // converged: whole workgroup leaves
   const bf16* Khp = K + (int64_t)hp * N_cap * D;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
+  int32_t* lab = labels + (int64_t)hp * N_cap + tok_begin;
   const int n_tiles = (c_count + 31) / 32;
   const int64_t wg_tok0 = (int64_t)blockIdx.x * blocks * ST_CHUNK;
 
   // keys of task b (64 consecutive tokens of this workgroup's range), in B-operand layout
+  const char* Kwg = reinterpret_cast<const char*>(Khp + (tok_begin + wg_tok0) * D);
+  const int wg_count = (int)min(tok_count - wg_tok0, (int64_t)ST_MAX_BLOCKS * ST_CHUNK);
   auto load_keys = [&](int b, bf16x8 (&bk)[NKB][8]) {
-    const bf16* rows[NKB];
+    uint32_t row[NKB];
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
-      int64_t t = wg_tok0 + (int64_t)b * (NKB * 32) + kb * 32 + col;
-      if (t >= tok_count) t = tok_count - 1;            // clamp: result is discarded
-      rows[kb] = Khp + (tok_begin + t) * D + half * 8;
+      const int t = min(b * (NKB * 32) + kb * 32 + col, wg_count - 1);   // clamp: result is discarded
+      row[kb] = (uint32_t)t * (D * 2) + half * 16;
     }
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk)
-        bk[kb][kk] = *reinterpret_cast<const bf16x8*>(rows[kb] + kk * 16);
+        bk[kb][kk] = *reinterpret_cast<const bf16x8*>(Kwg + row[kb] + kk * 32);
   };
   bf16x8 ka[NKB][8], kb2[NKB][8];
 
@@ -106,6 +107,8 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
         *reinterpret_cast<uint4*>(&table[(seg >> 4) * LDS_ROW + (seg & 15) * 8]) = v;
     }
   }
+  // converged: the whole workgroup leaves.  Looked at here, the word travels with the table
+  if (ctl.skip && ctl.skip[hp] == 0) return;
   // EARLY: a small table is staged before the key requests pile up.  Otherwise they come behind
   // the barrier: a compute unit has about 32 KB of loads in flight, and a wavefront whose request
   // does not fit stands still, in front of the barrier with all others (8 x 32768 x 400: barrier
@@ -126,7 +129,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   if constexpr (!EARLY) load_keys(wave, ka);
 
   const int n_tasks = blocks * ST_WAVES;
-  int diff = 0;
+  bool moved = false;
   const bf16* arow0 = table + col * LDS_ROW + half * 8; // this lane's A fragments of tile 0
 
   // One task, 64 keys against every centroid tile, then its labels.
@@ -145,6 +148,20 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) a[kk] = *reinterpret_cast<const bf16x8*>(arow0 + kk * 16);
 
+    // l2: what is added to accumulators 4 j .. 4 j + 3 of a tile, read once for both key blocks (two
+    // words for every slice of a read-out, each waited for where it was added: 37.8 us a launch at
+    // 8 x 32768 x 400, now 33.8, 45.6 -> 41.2 at 32 x 17623 x 220).  The registers for it come from
+    // key addresses of 32 bits behind one base: with ten of them spilled it was half the gain.
+    float bias[HAS_BIAS ? 16 : 1];
+    auto load_bias = [&](int tile_id, int j) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(&lds_bias[tile_id * 32 + 8 * j + 4 * half]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias[HAS_BIAS ? 4 * j + e : 0] = v[e];
+    };
+    if constexpr (HAS_BIAS) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) load_bias(0, j);
+    }
     // Slice r (0..7) of the read-out of one accumulator: two of its 16 similarities
     // join the packed running maximum; the last slice settles tile and value.
     // accumulator i of a lane is centroid row 8*(i/4) + 4*half + i%4 of the tile
@@ -153,8 +170,10 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
       float v0 = acc[kb][2 * r], v1 = acc[kb][2 * r + 1];
       const int row = tile_id * 32 + 8 * (r >> 1) + 4 * half + 2 * (r & 1);
       if constexpr (HAS_BIAS) {
-        v0 += lds_bias[row];
-        v1 += lds_bias[row + 1];
+        v0 += bias[2 * r];
+        v1 += bias[2 * r + 1];
+        // behind the second key block of this tile: those of the next one, four accumulators at a time
+        if (kb == NKB - 1 && (r & 1)) load_bias(tile_id + 1, r >> 1);
       }
       if (last_tile) {                                  // zero-padded rows lose (finite: no NaN)
         v0 = row >= c_count ? -3.0e38f : v0;
@@ -198,6 +217,9 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     using No = std::false_type;
     const int last = n_tiles - 1;
     step(T0(), No(), 0, false, nullptr);                // tile 0, key block 0: nothing to read out yet
+    // label of token `lane` before, in front of the next keys: behind them it would wait for them
+    int before = 0;
+    if (ctl.changed) before = lab[min((uint32_t)wave_tok0 + lane, (uint32_t)tok_count - 1)];
     // not before the matrix work has begun: the wavefront stands still until its requests fit
     if (nxt < n_tasks) load_keys(nxt, nk);
     for (int tile = 0; tile < last; ++tile) {
@@ -228,12 +250,13 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
       bidx = bidx < c_count ? bidx : c_count - 1;
       if (half == kb) lane_label = bidx;
       const int64_t t = wave_tok0 + kb * 32 + col;
-      if (half == 0 && t < tok_count) {
-        const int64_t o = (int64_t)hp * N_cap + tok_begin + t;
-        if (ctl.changed) diff += (ctl.first || labels[o] != c_begin + bidx) ? 1 : 0;
-        labels[o] = c_begin + bidx;
-        if (best_sim) best_sim[o] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
-      }
+      if (best_sim && half == 0 && t < tok_count)
+        best_sim[(int64_t)hp * N_cap + tok_begin + t] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
+    }
+    const uint32_t t = (uint32_t)wave_tok0 + lane;      // a range has less than 2^31 tokens
+    if (t < (uint32_t)tok_count) {
+      moved |= ctl.first || before != c_begin + lane_label;
+      lab[t] = c_begin + lane_label;
     }
     // the ranking inside the group runs here, under the other wavefront's matrix work
     if (chunks.list)
@@ -266,12 +289,9 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     cur = nxt;
   }
 
-  if (ctl.changed) {
-    const int wsum = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
-    if (lane == 0 && wsum) atomicAdd(&s_changed, wsum);
-  }
+  if (ctl.changed && __ballot(moved) && lane == 0) s_changed = 1;
   if (chunks.seg || ctl.changed) __syncthreads();
-  if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
+  if (ctl.changed && tid == 0 && s_changed) ctl.changed[hp] = 1;
   if (chunks.seg && !chunks.list) {
     for (int e = tid; e < blocks * c_count; e += THREADS) {
       const int64_t ch = (int64_t)blockIdx.x * blocks + e / c_count;

@@ -39,7 +39,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     const KmCtl ctl) {
   constexpr int NKB = WD_NKB, THREADS = WD_WAVES * 64, PER = 32 * 16 / THREADS;
   __shared__ __attribute__((aligned(16))) bf16 ring[WD_SLOTS * 32 * WD_LDS_ROW];
-  __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? CK_MAX_CLUSTERS + 32 : 4];
+  __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? CK_MAX_CLUSTERS + 64 : 4];
   __shared__ __attribute__((aligned(16))) bf16 key_stage[WD_WAVES * KEY_STAGE_ELEMS];
   __shared__ int s_changed;
 
@@ -102,6 +102,19 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) a[kk] = *reinterpret_cast<const bf16x8*>(arow + kk * 16);
 
+  // l2: what is added to accumulators 4 j .. 4 j + 3 of a tile, read once for all key blocks (two words
+  // for every slice of a read-out, each waited for where it was added: 147 us a launch at
+  // 16 x 50000 x 600, now 121, and 392 -> 347 at 8 x 131072 x 1600; without a bias 111 and 317)
+  float bias[HAS_BIAS ? 16 : 1];
+  auto load_bias = [&](int tile_id, int j) {
+    const floatx4 b = *reinterpret_cast<const floatx4*>(&lds_bias[tile_id * 32 + 8 * j + 4 * half]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias[HAS_BIAS ? 4 * j + e : 0] = b[e];
+  };
+  if constexpr (HAS_BIAS) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) load_bias(0, j);
+  }
   // Slice r (0..7) of the read-out of key block kb: two of its 16 similarities join the packed
   // running maximum; the last slice settles tile and value.
   // accumulator i of a lane is centroid row 8*(i/4) + 4*half + i%4 of the tile
@@ -110,8 +123,10 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     float v0 = acc[kb & 1][2 * r], v1 = acc[kb & 1][2 * r + 1];
     const int row = tile_id * 32 + 8 * (r >> 1) + 4 * half + 2 * (r & 1);
     if constexpr (HAS_BIAS) {
-      v0 += lds_bias[row];
-      v1 += lds_bias[row + 1];
+      v0 += bias[2 * r];
+      v1 += bias[2 * r + 1];
+      // behind the last key block of this tile: those of the next one, four accumulators at a time
+      if (kb == NKB - 1 && (r & 1)) load_bias(tile_id + 1, r >> 1);
     }
     if (last_tile) {                                    // zero-padded rows lose (finite: no NaN)
       v0 = row >= c_count ? -3.0e38f : v0;
@@ -198,7 +213,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     __syncthreads();
   }
   int lane_label[NKB / 2];                              // labels of tokens 64 i + lane of this wavefront
-  int diff = 0;
+  bool moved = false;
 #pragma unroll
   for (int kb = 0; kb < NKB; ++kb) {
     const int slot = 15 - (int)(__float_as_uint(bestp[kb]) & 15u);
@@ -220,16 +235,13 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     const int64_t t = wave_tok0 + kb * 32 + col;
     if (half == 0 && t < tok_count) {
       const int64_t o = (int64_t)hp * N_cap + tok_begin + t;
-      if (ctl.changed) diff += (ctl.first || labels[o] != c_begin + bidx) ? 1 : 0;
+      if (ctl.changed) moved |= ctl.first || labels[o] != c_begin + bidx;
       labels[o] = c_begin + bidx;
       if (best_sim) best_sim[o] = __uint_as_float(__float_as_uint(best) & 0xFFFFFFF0u);
       if (count_only) atomicAdd(&tok[bidx], 1u);
     }
   }
-  if (ctl.changed) {
-    const int wsum = __builtin_amdgcn_readlane(wave_inclusive_scan(diff), WAVE - 1);
-    if (lane == 0 && wsum) atomicAdd(&s_changed, wsum);
-  }
+  if (ctl.changed && __ballot(moved) && lane == 0) s_changed = 1;
   if (chunks.list) {
 #pragma unroll
     for (int i = 0; i < NKB / 2; ++i)
@@ -237,7 +249,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
           pack_token(lane_label[i], wave_tok0 + i * WAVE + lane < tok_count, label_bits);
   }
   if (chunks.seg || ctl.changed) __syncthreads();
-  if (ctl.changed && tid == 0 && s_changed) atomicAdd(&ctl.changed[hp], s_changed);
+  if (ctl.changed && tid == 0 && s_changed) ctl.changed[hp] = 1;
   const int64_t o = (int64_t)hp * n_chunks + blockIdx.x;
   if (count_only) {
     for (int c = tid; c < c_count; c += THREADS) chunks.seg[o * seg_stride(c_count) + c] = tok[c] << 16;
