@@ -41,7 +41,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks_hp, int label_bits,
     int64_t N_cap, int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
-    const KmCtl ctl) {
+    const KmCtl ctl, const TileMap map) {
   constexpr int THREADS = WAVES * 64, BUFS = ONE ? 1 : 2;
   constexpr int SEGS = CHUNK_ROWS * 16 / THREADS;      // 16-byte segments of a chunk per thread
   constexpr int CHUNK = WAVES * 32;                    // tokens of the workgroup = one chunk of the sort
@@ -62,7 +62,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
   CK_FETCH_ARG(ctl.first);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
-  const int hp = blockIdx.y;
+  int wg, hp;
+  if (!map.mine<true>(wg, hp)) return;
   const bf16* Khp = K + ((int64_t)hp * N_cap + tok_begin) * D;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
 
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
   if constexpr (HAS_BIAS) b0 = ctl.bias[(int64_t)hp * ctl.bias_stride + (tid < c_count ? tid : 0)];
 
   // ---- keys of this wavefront ----
-  const int64_t wave_tok0 = ((int64_t)blockIdx.x * WAVES + wave) * 32;
+  const int64_t wave_tok0 = ((int64_t)wg * WAVES + wave) * 32;
   KeyTile<1> keys;
   keys.load(Khp, wave_tok0, tok_count, lane);
   const int64_t my_tok = wave_tok0 + col;
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
   }
   if (chunks.seg || ctl.changed) __syncthreads();
   if (ctl.changed && tid == 0 && s_changed) ctl.changed[hp] = 1;
-  const int64_t o = (int64_t)hp * n_chunks_hp + blockIdx.x;
+  const int64_t o = (int64_t)hp * n_chunks_hp + wg;
   if (count_only) {
     for (int c = tid; c < c_count; c += THREADS) chunks.seg[o * seg_stride(c_count) + c] = tok[c] << 16;
   } else if (chunks.seg) {
@@ -271,9 +272,10 @@ static hipError_t launch_assign_few(const Dims& dm, const bf16* K, int64_t tok_b
       c_count <= CHUNK_ROWS ? (ctl.bias ? k_assign<true, WAVES, true, false> : k_assign<false, WAVES, true, false>)
       : tight               ? (ctl.bias ? k_assign<true, WAVES, false, true> : k_assign<false, WAVES, false, true>)
                             : (ctl.bias ? k_assign<true, WAVES, false, false> : k_assign<false, WAVES, false, false>);
-  hipLaunchKernelGGL(kernel, dim3(n_chunks, dm.HP), dim3(WAVES * 64), 0, st, K, mu_hat, labels,
+  const TileMap map(n_chunks, dm.HP);
+  hipLaunchKernelGGL(kernel, map.grid(), dim3(WAVES * 64), 0, st, K, mu_hat, labels,
                      best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
-                     c_count, ctl);
+                     c_count, ctl, map);
   return hipGetLastError();
 }
 

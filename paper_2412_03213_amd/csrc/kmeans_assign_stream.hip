@@ -42,7 +42,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks, int label_bits,
     int64_t N_cap, int64_t tok_begin, int64_t tok_count, int c_begin, int c_count, int blocks,
-    const KmCtl ctl) {
+    const KmCtl ctl, const TileMap map) {
   constexpr int NKB = ST_NKB, THREADS = ST_WAVES * 64;
   __shared__ __attribute__((aligned(16))) bf16 table[ST_MAX_TILES * 32 * LDS_ROW];
   __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? (ST_MAX_TILES + 1) * 32 : 4];
@@ -57,12 +57,13 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   CK_FETCH_ARG(ctl.first);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
-  const int hp = blockIdx.y;
+  int wg, hp;
+  if (!map.mine<true>(wg, hp)) return;
   const bf16* Khp = K + (int64_t)hp * N_cap * D;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
   int32_t* lab = labels + (int64_t)hp * N_cap + tok_begin;
   const int n_tiles = (c_count + 31) / 32;
-  const int64_t wg_tok0 = (int64_t)blockIdx.x * blocks * ST_CHUNK;
+  const int64_t wg_tok0 = (int64_t)wg * blocks * ST_CHUNK;
 
   // keys of task b (64 consecutive tokens of this workgroup's range), in B-operand layout
   const char* Kwg = reinterpret_cast<const char*>(Khp + (tok_begin + wg_tok0) * D);
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   if (ctl.changed && tid == 0 && s_changed) ctl.changed[hp] = 1;
   if (chunks.seg && !chunks.list) {
     for (int e = tid; e < blocks * c_count; e += THREADS) {
-      const int64_t ch = (int64_t)blockIdx.x * blocks + e / c_count;
+      const int64_t ch = (int64_t)wg * blocks + e / c_count;
       if (ch < n_chunks)
         chunks.seg[((int64_t)hp * n_chunks + ch) * seg_stride(c_count) + e % c_count] = tok[e] << 16;
     }
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
       constexpr int SCRATCH = (CNT + 8) * 4 + ST_CHUNK * 2;
       static_assert(ST_WAVES / W * SCRATCH <= sizeof(table), "chunk sort scratch");
       const int k = wave / W;
-      const int64_t ch = (int64_t)blockIdx.x * blocks + k, o = (int64_t)hp * n_chunks + ch;
+      const int64_t ch = (int64_t)wg * blocks + k, o = (int64_t)hp * n_chunks + ch;
       int* cnt = reinterpret_cast<int*>(reinterpret_cast<char*>(table) + k * SCRATCH);
       chunk_sort<ST_CHUNK / WAVE, ST_MAX_TILES * 32, W>(
           tok + k * ST_CHUNK, c_count, wave % W, k < blocks && ch < n_chunks, cnt, cnt + CNT,
@@ -342,15 +343,15 @@ hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin
       blocks = b;
     }
   }
-  const dim3 grid((unsigned)((chunks_hp + blocks - 1) / blocks), dm.HP);
+  const TileMap map((chunks_hp + blocks - 1) / blocks, dm.HP);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
   const auto kernel = c_count <= ST_EARLY_TILES * 32
                           ? (ctl.bias ? k_assign_stream<true, true> : k_assign_stream<false, true>)
                           : (ctl.bias ? k_assign_stream<true, false> : k_assign_stream<false, false>);
-  hipLaunchKernelGGL(kernel, grid, dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels, best_sim, chunks,
+  hipLaunchKernelGGL(kernel, map.grid(), dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels, best_sim, chunks,
                      (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count, c_begin, c_count,
-                     (int)blocks, ctl);
+                     (int)blocks, ctl, map);
   return hipGetLastError();
 }
 

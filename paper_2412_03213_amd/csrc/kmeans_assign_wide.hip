@@ -36,7 +36,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks, int label_bits,
     int64_t N_cap, int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
-    const KmCtl ctl) {
+    const KmCtl ctl, const TileMap map) {
   constexpr int NKB = WD_NKB, THREADS = WD_WAVES * 64, PER = 32 * 16 / THREADS;
   __shared__ __attribute__((aligned(16))) bf16 ring[WD_SLOTS * 32 * WD_LDS_ROW];
   __shared__ __attribute__((aligned(16))) float lds_bias[HAS_BIAS ? CK_MAX_CLUSTERS + 64 : 4];
@@ -50,7 +50,8 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
   CK_FETCH_ARG(ctl.first);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
-  const int hp = blockIdx.y;
+  int wg, hp;
+  if (!map.mine<true>(wg, hp)) return;
   if (ctl.skip && ctl.skip[hp] == 0) return;            // converged: whole workgroup leaves
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
   const int n_tiles = (c_count + 31) / 32;
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     *reinterpret_cast<uint4*>(&ring[(slot * 32 + srow + i * (THREADS / 16)) * WD_LDS_ROW + sseg * 8]) = v;
   };
 
-  const int64_t wave_tok0 = ((int64_t)blockIdx.x * WD_WAVES + wave) * (NKB * 32);
+  const int64_t wave_tok0 = ((int64_t)wg * WD_WAVES + wave) * (NKB * 32);
   {
     uint4 first[WD_AHEAD][PER];
 #pragma unroll
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
   }
   if (chunks.seg || ctl.changed) __syncthreads();
   if (ctl.changed && tid == 0 && s_changed) ctl.changed[hp] = 1;
-  const int64_t o = (int64_t)hp * n_chunks + blockIdx.x;
+  const int64_t o = (int64_t)hp * n_chunks + wg;
   if (count_only) {
     for (int c = tid; c < c_count; c += THREADS) chunks.seg[o * seg_stride(c_count) + c] = tok[c] << 16;
   } else if (chunks.seg) {
@@ -270,15 +271,15 @@ hipError_t launch_assign_wide(const Dims& dm, const bf16* K, int64_t tok_begin, 
   const int n_chunks = (int)((tok_count + WD_CHUNK - 1) / WD_CHUNK);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
-  const dim3 grid(n_chunks, dm.HP);
+  const TileMap map(n_chunks, dm.HP);
   if (ctl.bias)
-    hipLaunchKernelGGL(k_assign_wide<true>, grid, dim3(WD_WAVES * 64), 0, st, K, mu_hat, labels,
+    hipLaunchKernelGGL(k_assign_wide<true>, map.grid(), dim3(WD_WAVES * 64), 0, st, K, mu_hat, labels,
                        best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
-                       c_count, ctl);
+                       c_count, ctl, map);
   else
-    hipLaunchKernelGGL(k_assign_wide<false>, grid, dim3(WD_WAVES * 64), 0, st, K, mu_hat, labels,
+    hipLaunchKernelGGL(k_assign_wide<false>, map.grid(), dim3(WD_WAVES * 64), 0, st, K, mu_hat, labels,
                        best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
-                       c_count, ctl);
+                       c_count, ctl, map);
   return hipGetLastError();
 }
 

@@ -503,15 +503,15 @@ __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chun
     const uint16_t* __restrict__ list, int n_chunks, int chunk_tokens, int64_t N_cap,
     int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin, int c_count,
     bf16* __restrict__ centroids, bf16* __restrict__ mu_hat, int32_t* __restrict__ sizes,
-    int metric, float* __restrict__ bias, int bias_stride, const int32_t* __restrict__ gate) {
+    int metric, float* __restrict__ bias, int bias_stride, const int32_t* __restrict__ gate,
+    const TileMap map) {
   constexpr int SPAN = 256;                             // members whose ids a workgroup holds at once
   extern __shared__ uint32_t lds_u[];
   __shared__ __attribute__((aligned(16))) float part[CL][UPC_WAVES][D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
-  // neighbouring clusters, whose run words share cache lines, go to one XCD (workgroup i runs
-  // on XCD i % 8)
-  const int hp = blockIdx.y, c0 = (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8) * CL;
-  if (c0 >= c_count) return;
+  int wg, hp;                                           // neighbouring clusters, whose run words share
+  if (!map.mine<false>(wg, hp)) return;                        // cache lines, are on one XCD
+  const int c0 = wg * CL;
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
   ChunkRuns cr[CL];
@@ -608,12 +608,13 @@ __global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
     int tok_count, int C_cap, int c_begin, int c_count, bf16* __restrict__ centroids,
     bf16* __restrict__ mu_hat, int32_t* __restrict__ sizes, int metric, float* __restrict__ bias,
     int bias_stride, const int32_t* __restrict__ gate, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter) {
+    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter, const TileMap map) {
   __shared__ uint16_t member[UPL_WAVES * ROUNDS * WAVE];
   __shared__ int found[UPL_WAVES], before[UPL_WAVES];
   __shared__ __attribute__((aligned(16))) float part[UPC_WAVES][D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
-  const int hp = blockIdx.y, c = blockIdx.x;
+  int c, hp;
+  if (!map.mine<false>(c, hp)) return;
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
   CK_FETCH_ARG(offsets);
@@ -733,10 +734,11 @@ hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* la
                                 int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done,
                                 int n_iter, hipStream_t st) {
   const auto kernel = tok_count <= UPL_WAVES * 8 * WAVE ? k_update_labels<8> : k_update_labels<UPL_ROUNDS>;
-  hipLaunchKernelGGL(kernel, dim3(c_count, dm.HP), dim3(UPL_WAVES * 64), 0, st, K, labels,
+  const TileMap map(c_count, dm.HP);
+  hipLaunchKernelGGL(kernel, map.grid(), dim3(UPL_WAVES * 64), 0, st, K, labels,
                      dm.N_cap, tok_begin, (int)tok_count, dm.C_cap, c_begin, c_count, centroids,
                      mu_hat, sizes, metric, bias, bias_stride, gate, offsets, sorted_idx, iters_done,
-                     n_iter);
+                     n_iter, map);
   return hipGetLastError();
 }
 
@@ -842,11 +844,11 @@ hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex&
   const int chunk_tokens = chunks.tokens;
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   const int cl = update_clusters_per_workgroup(n_chunks, c_count, dm.HP);
-  const int groups = ((c_count + cl - 1) / cl + 7) / 8 * 8;
-  hipLaunchKernelGGL(cl == 4 ? k_update_chunks<4> : k_update_chunks<1>, dim3(groups, dm.HP), dim3(UPC_WAVES * 64),
+  const TileMap map((c_count + cl - 1) / cl, dm.HP);
+  hipLaunchKernelGGL(cl == 4 ? k_update_chunks<4> : k_update_chunks<1>, map.grid(), dim3(UPC_WAVES * 64),
                      chunk_runs_lds(cl, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
                      chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin, c_count,
-                     centroids, mu_hat, sizes, metric, bias, bias_stride, gate);
+                     centroids, mu_hat, sizes, metric, bias, bias_stride, gate, map);
   return hipGetLastError();
 }
 

@@ -77,6 +77,23 @@ def test_cluster_keys_equals_the_exported_steps(S, Hkv, N, C, begin, c_begin):
     assert torch.equal(got.centroids.view(torch.int16), want.centroids.view(torch.int16))
 
 
+@pytest.mark.parametrize("hp,tiles", [(1, 1), (1, 7), (3, 5), (7, 13), (9, 1), (8, 8), (37, 11), (300, 3)])
+def test_every_tile_has_its_workgroup(hp, tiles):
+    """Head-problems times tiles that eight XCDs share evenly or not, one tile of 128 tokens each: every
+    label of the assignment is written, none outside."""
+    n = tiles * 128 - 5
+    g = torch.Generator(device=DEV).manual_seed(hp * 100 + tiles)
+    K = torch.randn(1, hp, n + 4, 128, generator=g, device=DEV).to(torch.bfloat16)
+    hat = K[:, :, 2:12].contiguous()                    # every key is compared with the first ten
+    labels = torch.full((1, hp, n + 4), -1, dtype=torch.int32, device=DEV)
+    ck.ck_kmeans_assign(ck.Shape(1, hp, hp, n + 4, 10), K, 2, n, hat, 0, 10, labels)
+    torch.cuda.synchronize()
+    assert (labels[:, :, :2] == -1).all() and (labels[:, :, n + 2:] == -1).all()
+    sim = (K[0, :, 2:n + 2].double() @ hat[0].double().transpose(1, 2).contiguous()).topk(2, dim=-1)
+    clear = sim.values[..., 0] - sim.values[..., 1] > 1e-2
+    assert torch.equal(labels[0, :, 2:n + 2][clear], sim.indices[..., 0][clear].int())
+
+
 def test_workspace_of_large_chunks():
     """In a workspace that holds chunks of 512 tokens only (see test_abi_cpu.py) the call takes those:
     same outputs."""
