@@ -172,7 +172,8 @@ int ck_build_metadata(const ck_shape* sh, const int32_t* labels, int64_t tok_beg
   CK_REQUIRE_PTR(sorted_idx);
   if (!workspace) return fail(CK_EWORKSPACE, "workspace is NULL");
   if (!aligned16(workspace)) return fail(CK_EMISALIGNED, "workspace is not 16-byte aligned");
-  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace, workspace_bytes);
+  // no assignment behind it: the counting sort is quickest over large chunks
+  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace, 0);
   if (workspace_bytes < ws.bytes)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws.bytes);
   return hip_result(ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes,
