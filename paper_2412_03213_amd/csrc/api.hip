@@ -103,7 +103,7 @@ size_t ck_workspace_bytes(const ck_shape* sh, int which, int64_t n, int32_t c) {
   if (check_shape(sh, &dm, false) != CK_OK) return 0;
   if (which == CK_WS_CLUSTER_KEYS) {
     if (n < 1 || c < 1 || c > CK_MAX_CLUSTERS) return 0;
-    return ck::carve_cluster_workspace(dm, n, c, nullptr).bytes;
+    return ck::cluster_workspace_bytes(dm, n, c);
   }
   if (which == CK_WS_SPARSE_ATTN) {
     if (n < 0) return 0;
@@ -172,8 +172,8 @@ int ck_build_metadata(const ck_shape* sh, const int32_t* labels, int64_t tok_beg
   CK_REQUIRE_PTR(sorted_idx);
   if (!workspace) return fail(CK_EWORKSPACE, "workspace is NULL");
   if (!aligned16(workspace)) return fail(CK_EMISALIGNED, "workspace is not 16-byte aligned");
-  // no assignment behind it: the counting sort is quickest over large chunks
-  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace, 0);
+  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(
+      dm, tok_count, c_count, ck::sort_tile_tokens(dm, tok_count), workspace, workspace_bytes);
   if (workspace_bytes < ws.bytes)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws.bytes);
   return hip_result(ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes,
@@ -233,7 +233,8 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
   CK_OPTIONAL_PTR(iters_done);
   if (!workspace) return fail(CK_EWORKSPACE, "workspace is NULL");
   if (!aligned16(workspace)) return fail(CK_EMISALIGNED, "workspace is not 16-byte aligned");
-  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(dm, tok_count, c_count, workspace, workspace_bytes);
+  const ck::ClusterWorkspace ws = ck::carve_cluster_workspace(
+      dm, tok_count, c_count, ck::assign_tile_tokens(dm, tok_count, c_count), workspace, workspace_bytes);
   if (workspace_bytes < ws.bytes)
     return fail(CK_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws.bytes);
 

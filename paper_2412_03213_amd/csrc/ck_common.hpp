@@ -211,9 +211,11 @@ struct KmCtl {
   int32_t* changed = nullptr;      // [HP] left at 0 if this launch changes no label
   int first = 0;                   // no previous labels exist: count every token as changed
 };
-// have: bytes there are, where that is known
-ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, void* base,
-                                         size_t have = SIZE_MAX);
+// chunk_tokens: the chunk size that the caller prefers; have: bytes there are
+ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, int chunk_tokens,
+                                         void* base, size_t have);
+// enough for the chunk sizes that clustering and the counting sort of given labels prefer
+size_t cluster_workspace_bytes(const Dims& dm, int64_t tok_count, int c_count);
 
 // metric: CK_METRIC_* of the table the assignment will read; n_changed rows of `changed` (nullable) are
 // cleared
@@ -231,6 +233,7 @@ hipError_t launch_kmeans_small(const Dims& dm, const bf16* K, int64_t tok_begin,
 hipError_t launch_iters_done(const int32_t* changed, int max_iter, int HP, int32_t* iters_done,
                              hipStream_t st);
 int assign_tile_tokens(const Dims& dm, int64_t tok_count, int c_count);
+int sort_tile_tokens(const Dims& dm, int64_t tok_count);
 // chunks (members nullable): index of every chunk of chunks.tokens tokens by label;
 // without list only the counts of seg
 hipError_t launch_assign(const Dims& dm, const bf16* K, int64_t tok_begin, int64_t tok_count,

@@ -890,8 +890,24 @@ static ClusterWorkspace carve(const Dims& dm, int64_t tok_count, int c_count, in
   return w;
 }
 
-ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, void* base, size_t have) {
-  const ClusterWorkspace w = carve(dm, tok_count, c_count, assign_tile_tokens(dm, tok_count, c_count), base);
+// Chunk size of the counting sort with no assignment in front of it.  Not the one that the assignment
+// prefers for small tables: the scan goes through all chunks of a head-problem, and four times as many
+// are only longer.
+int sort_tile_tokens(const Dims& dm, int64_t tok_count) {
+  return tok_count * dm.HP >= 64 * 1024 ? 512 : 128;
+}
+
+// Neither chunk size is the larger one for all shapes: 512 tokens save run words, but a range ends in a
+// chunk that is filled up (128 head-problems of 600 tokens, 7 clusters: 647680 bytes, 561664 with 128).
+size_t cluster_workspace_bytes(const Dims& dm, int64_t tok_count, int c_count) {
+  const size_t a = carve(dm, tok_count, c_count, assign_tile_tokens(dm, tok_count, c_count), nullptr).bytes;
+  const size_t s = carve(dm, tok_count, c_count, sort_tile_tokens(dm, tok_count), nullptr).bytes;
+  return a > s ? a : s;
+}
+
+ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, int chunk_tokens,
+                                         void* base, size_t have) {
+  const ClusterWorkspace w = carve(dm, tok_count, c_count, chunk_tokens, base);
   // a workspace that was sized for more tokens may hold chunks of 512 only: they run as well
   if (w.bytes > have && tok_count * dm.HP >= 64 * 1024) return carve(dm, tok_count, c_count, 512, base);
   return w;

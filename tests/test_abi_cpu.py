@@ -74,6 +74,34 @@ def test_clustering_takes_a_workspace_of_large_chunks():
     assert call(need - 1) == -3
 
 
+# Head-problem tokens on both sides of 32768, 65536 and a full round of the chip, rows from one chunk of 128
+# tokens to hundreds, C around 64, 128 and 160: every choice of chunk size, and ranges that fill large chunks badly.
+WS_SHAPES = [(hp, n, C)
+             for hp in (1, 3, 8, 16, 64, 128, 700, 1000)
+             for T in (20000, 32768, 32769, 40000, 65535, 65536, 70000, 80000, 131072, 200000)
+             for n in (max(1, T // hp), T // hp + 1)
+             for C in (4, 7, 13, 40, 64, 65, 100, 128, 129, 160, 161, 400, 700) if C <= n]
+WS_SHAPES += [(128, 600, 7), (128, 1100, 13), (64, 1025, 12), (700, 100, 4), (1, 300000, 50), (8, 131072, 1600)]
+
+
+def clustering_needs(hp, n, C):
+    """Bytes that ck_build_metadata and ck_cluster_keys ask for, from what they say to a workspace of one
+    byte.  The addresses are aligned and never dereferenced."""
+    lib, sh = binding.load_library(), ck.Shape(1, hp, hp, n, C).c()
+    out = []
+    for rc in (lib.ck_build_metadata(ctypes.byref(sh), A, 0, n, 0, C, A, A, A, A, 1, None),
+               lib.ck_cluster_keys(ctypes.byref(sh), A, 0, n, 0, C, 1, A, A, A, A, A, A, A, 1, None)):
+        assert rc == -3
+        out.append(int(re.search(r"(\d+) needed", lib.ck_last_error_detail().decode()).group(1)))
+    return out
+
+
+def test_prescribed_workspace_is_enough():
+    for hp, n, C in WS_SHAPES:
+        have = ck.ck_workspace_bytes(ck.Shape(1, hp, hp, n, C), binding.CK_WS_CLUSTER_KEYS, n, C)
+        assert max(clustering_needs(hp, n, C)) <= have, (hp, n, C)
+
+
 @pytest.mark.parametrize("G", [1, 4, 8])
 def test_attention_workspace_is_one_round_of_workgroups(G):
     """The workspace shows the number of splits: every XCD (32 compute units, one workgroup of

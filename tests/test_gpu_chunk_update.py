@@ -24,6 +24,7 @@ SHAPES = [
     (2, 8, 4050, 130, 3, 5),         # chunks of 128, appended behind existing clusters, odd range
     (2, 8, 4097, 513, 1, 0),         # table streamed in chunks; one token in the last chunk of 512
     (1, 8, 8200, 512, 0, 0),         # largest LDS-resident table
+    (128, 1, 600, 7, 0, 0),          # chunks of 128; the exported sort's of 512 need the larger workspace
     (1, 1, 65535, 60, 0, 0),         # chunks of 256
     (1, 2, 65536, 60, 0, 0),         # chunks of 128: exactly as many as the index holds
     (3, 1, 20000, 70, 3, 5),         # chunks of 256, appended behind existing clusters, odd range
