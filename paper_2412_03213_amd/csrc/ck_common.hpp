@@ -211,7 +211,8 @@ struct KmCtl {
   int32_t* changed = nullptr;      // [HP] left at 0 if this launch changes no label
   int first = 0;                   // no previous labels exist: count every token as changed
 };
-// chunk_tokens: the chunk size that the caller prefers; have: bytes there are
+// chunk_tokens: the chunk size that the caller prefers; have: bytes there are.  Where that size does not
+// fit it is another one, the one that needs least where none does
 ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, int chunk_tokens,
                                          void* base, size_t have);
 // enough for the chunk sizes that clustering and the counting sort of given labels prefer

@@ -907,10 +907,14 @@ size_t cluster_workspace_bytes(const Dims& dm, int64_t tok_count, int c_count) {
 
 ClusterWorkspace carve_cluster_workspace(const Dims& dm, int64_t tok_count, int c_count, int chunk_tokens,
                                          void* base, size_t have) {
-  const ClusterWorkspace w = carve(dm, tok_count, c_count, chunk_tokens, base);
-  // a workspace that was sized for more tokens may hold chunks of 512 only: they run as well
-  if (w.bytes > have && tok_count * dm.HP >= 64 * 1024) return carve(dm, tok_count, c_count, 512, base);
-  return w;
+  ClusterWorkspace best = carve(dm, tok_count, c_count, chunk_tokens, base);
+  // a workspace that was sized for more tokens holds one of the sizes, and every one of them runs
+  for (const int other : {512, 256, 128}) {
+    if (best.bytes <= have) break;
+    const ClusterWorkspace w = carve(dm, tok_count, c_count, other, base);
+    if (w.bytes < best.bytes) best = w;
+  }
+  return best;
 }
 
 }  // namespace ck

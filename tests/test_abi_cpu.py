@@ -102,6 +102,21 @@ def test_prescribed_workspace_is_enough():
         assert max(clustering_needs(hp, n, C)) <= have, (hp, n, C)
 
 
+@pytest.mark.parametrize("hp", [1, 8, 128, 700, 1000])
+def test_workspace_for_more_serves_less(hp):
+    """Fewer tokens, fewer clusters or both, across every change of the chunk size."""
+    rows = sorted({max(4, T // hp + d) for T in (20000, 32768, 34000, 65536, 70000, 131072) for d in (-1, 0, 1, 13)})
+    counts = [4, 40, 64, 65, 128, 160, 161, 400]
+    size = {(n, C): ck.ck_workspace_bytes(ck.Shape(1, hp, hp, n, C), binding.CK_WS_CLUSTER_KEYS, n, C)
+            for n in rows for C in counts}
+    for n in rows:
+        for C in counts:
+            if C <= n:
+                need = max(clustering_needs(hp, n, C))
+                short = [k for k, b in size.items() if k[0] >= n and k[1] >= C and b < need]
+                assert not short, (n, C, short)
+
+
 @pytest.mark.parametrize("G", [1, 4, 8])
 def test_attention_workspace_is_one_round_of_workgroups(G):
     """The workspace shows the number of splits: every XCD (32 compute units, one workgroup of

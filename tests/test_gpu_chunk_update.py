@@ -116,6 +116,36 @@ def test_workspace_of_large_chunks():
         assert torch.equal(getattr(a, name), getattr(b, name)), name
 
 
+@pytest.mark.parametrize("hp,n,C,tokens", [(8, 4096, 400, 512), (300, 250, 100, 256), (1000, 125, 100, 128),
+                                           (4, 8192, 513, 512), (128, 1100, 13, 128)])
+def test_smallest_workspace(hp, n, C, tokens):
+    """What the chunk size that needs least asks for is enough, whatever would be preferred: same outputs,
+    also of the exported sort."""
+    g = torch.Generator(device=DEV).manual_seed(hp)
+    K = torch.randn(1, hp, n, 128, generator=g, device=DEV).to(torch.bfloat16)
+    init = torch.rand(1, hp, n, generator=g, device=DEV).topk(C, dim=-1).indices.int()
+    sh = ck.Shape(1, hp, hp, n, C)
+    up = lambda b: (b + 255) // 256 * 256
+    chunks, stride = -(-n // tokens), -(-C // 4) * 4
+    need = (up(hp * C * 256) + up(hp * chunks * stride * 4) + up(hp * chunks * tokens * 2)
+            + up(hp * -(-C // 32) * 128) + up(257 * hp * 4))
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    a, b = (ck.ClusterState(sh, DEV, budget=64) for _ in range(2))
+    with pytest.raises(ck.ClusterKVError, match="workspace"):
+        ck.ck_build_metadata(sh, a.labels, 0, n, 0, C, a.sizes, a.offsets, a.sorted_idx, workspace=ws[:-1])
+    a.cluster(K, init, 0, n, C, 3)
+    ck.ck_cluster_keys(sh, K, 0, n, 0, C, 3, init, b.centroids, b.labels, b.sizes, b.offsets,
+                       b.sorted_idx, workspace=ws)
+    torch.cuda.synchronize()
+    names = ("labels", "sizes", "offsets", "sorted_idx", "centroids")
+    assert all(torch.equal(getattr(a, x), getattr(b, x)) for x in names)
+    for x in names[1:4]:
+        getattr(b, x).fill_(-1)
+    ck.ck_build_metadata(sh, a.labels, 0, n, 0, C, b.sizes, b.offsets, b.sorted_idx, workspace=ws)
+    torch.cuda.synchronize()
+    assert all(torch.equal(getattr(a, x), getattr(b, x)) for x in names)
+
+
 @pytest.mark.parametrize("S,Hkv,N,C,begin,c_begin", SHAPES)
 def test_empty_clusters_survive_the_iterations(S, Hkv, N, C, begin, c_begin):
     """The same by inner product, whose table is the stored centroids themselves: long rows draw
