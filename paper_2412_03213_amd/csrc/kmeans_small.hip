@@ -29,8 +29,12 @@ struct SmallArgs {
 // By how much two similarities of a key may differ from what another order of their additions gives:
 // this factor, from the squared length of the key, times the length of the longest table row.  Every
 // partial sum is at most |k| |row|, and 128 additions, be they rounded or cut off, are off by 2^-23
-// of that each; the fixed order has a chain of twelve.  Lengths below 2^-60 count as 2^-60 (products
-// that the matrix cores take for zero), those of 2^50 and more as infinite (sums that overflow).
+// of that each; the fixed order has a chain of twelve.  Lengths of 2^50 and more count as infinite (sums
+// that overflow).  Lengths below 2^-60 count as 2^-60, and KM_SMALL_SLACK is added whatever the lengths:
+// nothing is assumed of what the matrix cores make of a channel, a product or a sum below the smallest
+// normal number.  Taken for zero, a channel loses 2^-126 times the other side's length, each of 128 products
+// and as many sums 2^-126, in either similarity 2^-118 in all.
+constexpr float KM_SMALL_SLACK = 0x1p-116f;
 __device__ __forceinline__ float key_bound(float n2) {
   const float n = 1.001f * sqrtf(n2);
   return n < 0x1p50f ? 0x1.1p-15f * fmaxf(n, 0x1p-60f) : INFINITY;
@@ -213,14 +217,14 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
         bs[s] = *reinterpret_cast<const float4*>(&bias[4 * s]);
       }
       // length of the longest row (one, and a quarter more where the square of a mean was below the
-      // smallest normal number); rounding of the bias
-      float rn = 1.25f, slack = 0.f;
+      // smallest normal number); rounding of the bias, and see KM_SMALL_SLACK
+      float rn = 1.25f, slack = KM_SMALL_SLACK;
       if (a.metric != CK_METRIC_COSINE) {
         rn = row_norm[0];
 #pragma unroll
         for (int c = 1; c < ROWS; ++c) rn = fmaxf(rn, row_norm[c]);
         rn = row_bound(rn);
-        slack = 0x1p-20f * rn * rn;
+        slack = fmaf(0x1p-20f * rn, rn, KM_SMALL_SLACK);
       }
       floatx4 d[TILES][SETS];
 #pragma unroll

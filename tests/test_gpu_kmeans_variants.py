@@ -266,6 +266,19 @@ def test_small_range_at_round_edges(C, n, metric):
             check_state(st, cfg, s, h, keys, labels)
 
 
+def fixed_order_labels(keys, C):
+    """Labels by inner product with the first C keys in the documented order of additions: eight
+    multiply-adds per group of eight channels, then the groups in pairs, one rounding at a time."""
+    rows = keys.reshape(-1, 16, 8)
+    p = rows[:, None] * rows[None, :C]                    # [n, C, 16, 8], exact
+    d = np.zeros(p.shape[:3], np.float32)
+    for j in range(8):
+        d = (p[..., j] + d.astype(np.float64)).astype(np.float32)   # fused: one rounding
+    while d.shape[-1] > 1:
+        d = d[..., 0::2] + d[..., 1::2]
+    return d[..., 0].argmax(axis=1)
+
+
 @pytest.mark.parametrize("C", [2, 3, 4, 5, 8])
 @pytest.mark.parametrize("n", [20, 255, 257, 384])
 def test_small_range_near_ties(C, n):
@@ -284,15 +297,23 @@ def test_small_range_near_ties(C, n):
     st = ck.ClusterState(ck.Shape(1, 1, 1, n, C), DEV, budget=64)
     init = torch.arange(C, dtype=torch.int32, device=DEV)[None, None]
     st.cluster(K[None, None].to(DEV), init, 0, n, C, 1, flags=ck.CK_METRIC_IP)
-    rows = np64(K).reshape(n, 16, 8)
-    p = rows[:, None] * rows[None, :C]                    # [n, C, 16, 8], exact
-    d = np.zeros((n, C, 16), np.float32)
-    for j in range(8):
-        d = (p[..., j] + d.astype(np.float64)).astype(np.float32)   # fused: one rounding
-    while d.shape[-1] > 1:
-        d = d[..., 0::2] + d[..., 1::2]
-    want = d[..., 0].argmax(axis=1)
-    exact = p.sum(axis=(2, 3)).argmax(axis=1)
+    want = fixed_order_labels(np64(K), C)
+    exact = (np64(K) @ np64(K)[:C].T).argmax(axis=1)
     if n > 200:
         assert (want != exact).mean() > 0.05              # the order of the additions is what decides
     assert st.labels[0, 0].cpu().numpy().tolist() == want.tolist()
+
+
+@pytest.mark.parametrize("C", [2, 4, 8])
+@pytest.mark.parametrize("n,shift", [(160, 62), (320, 64), (320, 66), (384, 70), (256, 73)])
+def test_small_range_subnormal_products(n, shift, C):
+    """Keys whose products with the initial rows are below the smallest normal number, in part (2^-62 a
+    channel) or all of them: the labels are those of the documented order of additions all the same."""
+    hp = 4
+    rng = np.random.default_rng(10 * n + shift)
+    K = torch.from_numpy(rng.standard_normal((hp, n, 128)) * 2.0 ** -shift).to(torch.bfloat16)
+    st = ck.ClusterState(ck.Shape(1, hp, hp, n, C), DEV, budget=64)
+    init = torch.arange(C, dtype=torch.int32, device=DEV).expand(1, hp, C).contiguous()
+    st.cluster(K[None].to(DEV), init, 0, n, C, 1, flags=ck.CK_METRIC_IP)
+    for h in range(hp):
+        assert st.labels[0, h].cpu().tolist() == fixed_order_labels(np64(K[h]), C).tolist(), h
