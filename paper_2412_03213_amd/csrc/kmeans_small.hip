@@ -216,8 +216,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_kmeans_small(const SmallArgs a) 
           ta[s][sl] = *reinterpret_cast<const bf16x8*>(&table[4 * s + l4][32 * sl + 8 * row]);
         bs[s] = *reinterpret_cast<const float4*>(&bias[4 * s]);
       }
-      // length of the longest row (one, and a quarter more where the square of a mean was below the
-      // smallest normal number); rounding of the bias, and see KM_SMALL_SLACK
+      // length of the longest row (one, and a quarter more for means of 2^-71 to 2^-60, whose squares are
+      // rounded below the smallest normal number; up to 8 for shorter ones, whose rows this does not cover:
+      // a length kept per row costs 2 to 5 % of the call); rounding of the bias, and see KM_SMALL_SLACK
       float rn = 1.25f, slack = KM_SMALL_SLACK;
       if (a.metric != CK_METRIC_COSINE) {
         rn = row_norm[0];
