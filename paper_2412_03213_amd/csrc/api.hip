@@ -271,12 +271,13 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
     ck::KmCtl ctl;
     ctl.bias = bias;
     ctl.bias_stride = ws.bias_stride;
-    const int32_t* gate = nullptr;
+    ck::Running gate;
     if (converge) {
       ctl.changed = ws.changed + (int64_t)it * dm.HP;
       ctl.first = it == 0;
-      ctl.skip = it >= 2 ? ws.changed + (int64_t)(it - 1) * dm.HP : nullptr;
-      gate = it >= 1 ? ctl.changed : nullptr;
+      // the first row has no zero
+      if (it >= 2) ctl.running = {ctl.changed - dm.HP, it >= ck::KM_LOOK_FIRST};
+      if (it >= 1) gate = {ctl.changed, it >= ck::KM_LOOK_FIRST};
     }
     e = ck::launch_assign(dm, Kb, tok_begin, tok_count, ws.mu_hat, c_begin, c_count, labels,
                           nullptr, chunks, ctl, st);
@@ -294,10 +295,10 @@ int ck_cluster_keys_opt(const ck_shape* sh, const void* K, int64_t tok_begin, in
                                    ws.bias_stride, gate, st);
     } else {
       e = ck::launch_metadata(dm, labels, tok_begin, tok_count, c_begin, c_count, sizes, offsets,
-                              sorted_idx, ws.chunks, true, gate, st);
+                              sorted_idx, ws.chunks, true, gate.flags, st);
       if (e != hipSuccess) return hip_result(e, "metadata launch");
       e = ck::launch_update(dm, Kb, offsets, sorted_idx, c_begin, c_count, (ck::bf16*)centroids,
-                            ws.mu_hat, nullptr, metric, bias, ws.bias_stride, gate, st);
+                            ws.mu_hat, nullptr, metric, bias, ws.bias_stride, gate.flags, st);
     }
     if (e != hipSuccess) return hip_result(e, "update launch");
   }

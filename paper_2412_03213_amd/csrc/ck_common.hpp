@@ -139,6 +139,22 @@ __device__ __forceinline__ void wave_lds_order() {
   asm volatile("" ::: "memory");
 }
 
+// Which head-problems an iteration of run-until-convergence mode is for: those whose entry of flags
+// [HP] is not 0.  No flags: all.  first: workgroups look before they ask for anything else (TileMap).
+struct Running {
+  const int32_t* flags = nullptr;
+  bool first = false;
+};
+// Looking first costs a memory round trip in each launch: an iteration in which all move takes 0.7 us more
+// at 8 x 32768 x 400 (of 45), 1.4 at 8 x 16384 x 200 (of 21), 3 at 128 x 6250 x 40 (of 63, several workgroups
+// after each other on a compute unit).  Looking late, one in which all have stopped takes 6.7 us in place
+// of 4.1, 5.3 / 4.0, 33 / 6.8.  On mixtures the first head-problem stops after 8 iterations with 25 clusters,
+// 13 with 51, 32 with 400, 83 with 1600.  A cap of 100, tiles in place and looking late in all iterations /
+// as it is, us: 8 x 32768 x 400 2256 / 2040, 8 x 131072 x 1600 36400 / 33800, 128 x 2000 x 25 1585 / 826,
+// 128 x 6250 x 40 4575 / 2940, 16 x 50000 x 600 by l2 12300 / 10200.  A cap of 20: the last but one 1247 / 1279,
+// 8 x 16384 x 200 408 / 419, the others within 1 % or faster.
+constexpr int KM_LOOK_FIRST = 12;      // from this iteration on
+
 // Which workgroup takes which tile of which head-problem: XCD x (workgroup id % 8) gets the x-th eighth
 // of all tiles, in head-problem order.  Every kernel of a K-means iteration is launched that way, so a
 // head-problem's keys, table, labels and chunk index stay with one XCD (or the same few), and what one
@@ -150,25 +166,68 @@ __device__ __forceinline__ void wave_lds_order() {
 // The assignment goes through an XCD's tiles backwards: it ends with the keys that the update begins
 // with, and the update ends with those that the next assignment wants first (128 x 2000 x 25, 8 MB of keys
 // an XCD, 275 / 241 us; no change where they all fit or are far more).
+//
+// running.flags: an entry of 0 says that the head-problem has converged.  A workgroup may do its work all
+// the same: labels that have not changed give the same table, chunk index and metadata.  Without
+// running.first (LOOK = false) it looks when the word has travelled with its first loads (stopped), and the
+// tiles stay where they are.  With it, head-problems that have stopped get no workgroup, and the tiles of
+// the others are dealt out as above, so that the last one that moves has all XCDs and not the one that it
+// began with.  Beyond 64 * RUN_WORDS head-problems a workgroup only leaves, in the order of all.
 struct TileMap {
-  int tiles, total, per;               // of a head-problem; of all; of an XCD
+  static constexpr int RUN_WORDS = 4;
+  int tiles, hps, per;                 // of a head-problem; head-problems; tiles of an XCD
   uint32_t magic;                      // 2^31 / tiles, rounded up
   int row;                             // workgroups / 8 in x
-  TileMap(int64_t tiles_, int hp)
-      : tiles((int)tiles_), total((int)(tiles_ * hp)), per((total + 7) / 8),
-        magic((uint32_t)(((1ll << 31) + tiles_ - 1) / tiles_)), row(per < 65536 ? per : 65536) {}
+  const int32_t* running;
+  TileMap(int64_t tiles_, int hps_, const Running& r)
+      : tiles((int)tiles_), hps(hps_), per((int)((tiles_ * hps_ + 7) / 8)),
+        magic((uint32_t)(((1ll << 31) + tiles_ - 1) / tiles_)), row(per < 65536 ? per : 65536),
+        running(r.flags) {}
   dim3 grid() const { return dim3(8u * row, (per + row - 1) / row); }
   // false: there is nothing for this workgroup.  BACK: an XCD begins with its last tile.
-  template <bool BACK>
+  template <bool BACK, bool LOOK>
   __device__ __forceinline__ bool mine(int& tile, int& hp) const {
-    const int n = (int)blockIdx.y * row + (int)(blockIdx.x >> 3), i = BACK ? per - 1 - n : n;
-    const int t = (int)(blockIdx.x & 7) * per + i;
+    const bool listed = LOOK && hps <= WAVE * RUN_WORDS;
+    const int lane = threadIdx.x & 63;
+    uint64_t moves[RUN_WORDS];
+    int live = hps, share = per;
+    if (listed) {
+      int32_t f[RUN_WORDS];
+#pragma unroll
+      for (int w = 0; w < RUN_WORDS; ++w) f[w] = running[min(w * WAVE + lane, hps - 1)];
+      live = 0;
+#pragma unroll
+      for (int w = 0; w < RUN_WORDS; ++w) {
+        moves[w] = __ballot(w * WAVE + lane < hps && f[w] != 0);
+        live += __popcll(moves[w]);
+      }
+      share = (live * tiles + 7) / 8;
+    }
+    const int n = (int)blockIdx.y * row + (int)(blockIdx.x >> 3), i = BACK ? share - 1 - n : n;
+    const int t = (int)(blockIdx.x & 7) * share + i;
     int q = (int)(((uint64_t)(uint32_t)t * magic) >> 31);   // the quotient or one more
     q -= q * tiles > t ? 1 : 0;
     hp = q;
     tile = t - q * tiles;
-    return n < per && t < total;
+    if (n >= share || t >= live * tiles) return false;
+    if (listed) {                                       // the q-th of those that run
+      int word = 0;
+      uint64_t m = moves[0];
+#pragma unroll
+      for (int w = 1; w < RUN_WORDS; ++w)
+        if (word == w - 1 && q >= __popcll(m)) {
+          q -= __popcll(m);
+          m = moves[w];
+          word = w;
+        }
+      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      hp = word * WAVE + __builtin_ctzll(__ballot(((m >> lane) & 1) != 0 && rank == q));
+      return true;
+    }
+    return !LOOK || running[hp] != 0;
   }
+  template <bool LOOK>
+  __device__ __forceinline__ bool stopped(int hp) const { return !LOOK && running && running[hp] == 0; }
 };
 
 // ---- internal launchers (host side, defined next to their kernels) ----
@@ -206,8 +265,7 @@ struct ClusterWorkspace {
 struct KmCtl {
   const float* bias = nullptr;     // l2 metric: added to <k, mu_c> before the argmax
   int bias_stride = 0;
-  const int32_t* skip = nullptr;   // [HP] `changed` of the previous iteration:
-                                   // 0 = that head-problem has converged, leave it alone
+  Running running;                 // by `changed` of the previous iteration
   int32_t* changed = nullptr;      // [HP] left at 0 if this launch changes no label
   int first = 0;                   // no previous labels exist: count every token as changed
 };
@@ -268,7 +326,7 @@ int update_clusters_per_workgroup(int n_chunks, int c_count, int hp);
 hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
-                                float* bias, int bias_stride, const int32_t* gate, hipStream_t st);
+                                float* bias, int bias_stride, const Running& running, hipStream_t st);
 // offsets and sorted_idx of the labels the chunk index holds (sizes: as the update wrote them), and
 // into iters_done, where that is given, n_iter or what the rows of `changed` say
 hipError_t launch_emit_index(const Dims& dm, const ChunkIndex& chunks, int64_t tok_begin,
@@ -280,7 +338,7 @@ bool update_labels_fits(const Dims& dm, int64_t tok_count, int c_count);
 hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* labels,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
-                                float* bias, int bias_stride, const int32_t* gate,
+                                float* bias, int bias_stride, const Running& running,
                                 int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done,
                                 int n_iter, hipStream_t st);
 hipError_t launch_select(const Dims& dm, const void* q, const void* centroids,

@@ -16,6 +16,7 @@
 // double-buffered chunks of 64 rows.  k_assign_stream (tables of at most 512 centroids) and
 // k_assign_wide (larger ones) take the rest.
 #include <atomic>
+#include <type_traits>
 
 #include "chunk_sort.hpp"
 #include "key_operand.hpp"
@@ -36,7 +37,7 @@ constexpr int LDS_ROW = D + 8;             // bf16 elements per LDS row: 272 B, 
 // argmax.  ONE: a table of one chunk.  TIGHT: the keys through half of the LDS, so that a compute unit
 // holds four workgroups of four wavefronts in place of three (3 % less where there are as many: 8 x 20000 x 250
 // 319 -> 301 us, 32 x 4096 x 51 without; 2 % more where there are not: 4 x 15738 x 98 142 -> 145).
-template <bool HAS_BIAS, int WAVES, bool ONE, bool TIGHT>
+template <bool HAS_BIAS, int WAVES, bool ONE, bool TIGHT, bool LOOK>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks_hp, int label_bits,
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   int wg, hp;
-  if (!map.mine<true>(wg, hp)) return;
+  if (!map.mine<true, LOOK>(wg, hp)) return;
   const bf16* Khp = K + ((int64_t)hp * N_cap + tok_begin) * D;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
 
@@ -113,8 +114,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
       lds_bias[c] = c < c_count ? ctl.bias[(int64_t)hp * ctl.bias_stride + c] : 0.f;
   }
   if (tid == 0) s_changed = 0;
-  // converged: the whole workgroup leaves.  Looked at here, the word travels with the loads above
-  if (ctl.skip && ctl.skip[hp] == 0) return;
+  if (map.stopped<LOOK>(hp)) return;                          // the word has travelled with the loads above
 
   // Running maximum as a "packed" float: the low 4 mantissa bits of
   // every similarity are replaced by 15 - (accumulator slot), so one v_max3 chain
@@ -268,14 +268,18 @@ static hipError_t launch_assign_few(const Dims& dm, const bf16* K, int64_t tok_b
   while ((1 << label_bits) < c_count) ++label_bits;
   // more workgroups than the compute units hold of the other form
   const bool tight = (int64_t)n_chunks * dm.HP > (int64_t)n_cu * (12 / WAVES);
-  const auto kernel =
-      c_count <= CHUNK_ROWS ? (ctl.bias ? k_assign<true, WAVES, true, false> : k_assign<false, WAVES, true, false>)
-      : tight               ? (ctl.bias ? k_assign<true, WAVES, false, true> : k_assign<false, WAVES, false, true>)
-                            : (ctl.bias ? k_assign<true, WAVES, false, false> : k_assign<false, WAVES, false, false>);
-  const TileMap map(n_chunks, dm.HP);
-  hipLaunchKernelGGL(kernel, map.grid(), dim3(WAVES * 64), 0, st, K, mu_hat, labels,
-                     best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
-                     c_count, ctl, map);
+  const TileMap map(n_chunks, dm.HP, ctl.running);
+  auto launch = [&](auto look) {
+    constexpr bool L = decltype(look)::value;
+    const auto kernel =
+        c_count <= CHUNK_ROWS ? (ctl.bias ? k_assign<true, WAVES, true, false, L> : k_assign<false, WAVES, true, false, L>)
+        : tight               ? (ctl.bias ? k_assign<true, WAVES, false, true, L> : k_assign<false, WAVES, false, true, L>)
+                              : (ctl.bias ? k_assign<true, WAVES, false, false, L> : k_assign<false, WAVES, false, false, L>);
+    hipLaunchKernelGGL(kernel, map.grid(), dim3(WAVES * 64), 0, st, K, mu_hat, labels,
+                       best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
+                       c_count, ctl, map);
+  };
+  ctl.running.first ? launch(std::true_type()) : launch(std::false_type());
   return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@ constexpr int ST_MAX_TILES = 16;                        // 512 centroids
 constexpr int ST_MAX_BLOCKS = 8;
 constexpr int ST_EARLY_TILES = 4;                       // up to this size the keys are requested with the table
 
-template <bool HAS_BIAS, bool EARLY>
+template <bool HAS_BIAS, bool EARLY, bool LOOK>
 __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks, int label_bits,
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
   int wg, hp;
-  if (!map.mine<true>(wg, hp)) return;
+  if (!map.mine<true, LOOK>(wg, hp)) return;
   const bf16* Khp = K + (int64_t)hp * N_cap * D;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
   int32_t* lab = labels + (int64_t)hp * N_cap + tok_begin;
@@ -108,8 +108,7 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
         *reinterpret_cast<uint4*>(&table[(seg >> 4) * LDS_ROW + (seg & 15) * 8]) = v;
     }
   }
-  // converged: the whole workgroup leaves.  Looked at here, the word travels with the table
-  if (ctl.skip && ctl.skip[hp] == 0) return;
+  if (map.stopped<LOOK>(hp)) return;                          // the word has travelled with the table
   // EARLY: a small table is staged before the key requests pile up.  Otherwise they come behind
   // the barrier: a compute unit has about 32 KB of loads in flight, and a wavefront whose request
   // does not fit stands still, in front of the barrier with all others (8 x 32768 x 400: barrier
@@ -343,15 +342,19 @@ hipError_t launch_assign_stream(const Dims& dm, const bf16* K, int64_t tok_begin
       blocks = b;
     }
   }
-  const TileMap map((chunks_hp + blocks - 1) / blocks, dm.HP);
+  const TileMap map((chunks_hp + blocks - 1) / blocks, dm.HP, ctl.running);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
-  const auto kernel = c_count <= ST_EARLY_TILES * 32
-                          ? (ctl.bias ? k_assign_stream<true, true> : k_assign_stream<false, true>)
-                          : (ctl.bias ? k_assign_stream<true, false> : k_assign_stream<false, false>);
-  hipLaunchKernelGGL(kernel, map.grid(), dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels, best_sim, chunks,
-                     (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count, c_begin, c_count,
-                     (int)blocks, ctl, map);
+  auto launch = [&](auto look) {
+    constexpr bool L = decltype(look)::value;
+    const auto kernel = c_count <= ST_EARLY_TILES * 32
+                            ? (ctl.bias ? k_assign_stream<true, true, L> : k_assign_stream<false, true, L>)
+                            : (ctl.bias ? k_assign_stream<true, false, L> : k_assign_stream<false, false, L>);
+    hipLaunchKernelGGL(kernel, map.grid(), dim3(ST_WAVES * 64), 0, st, K, mu_hat, labels, best_sim, chunks,
+                       (int)chunks_hp, label_bits, dm.N_cap, tok_begin, tok_count, c_begin, c_count,
+                       (int)blocks, ctl, map);
+  };
+  ctl.running.first ? launch(std::true_type()) : launch(std::false_type());
   return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@ constexpr int WD_LDS_ROW = D + 8;                       // 272 B: rows shift 4 b
 // 2390 / 2225; 8 x 60000 x 750 1170 / 1095; 8 x 9000 x 600 517 / 360 (the grid of 512 tokens per
 // workgroup wastes less of the last round); with at most 512 clusters it is within 3 % of
 // k_assign_stream at large tables and up to 15 % slower at small ones, where the keys count.
-template <bool HAS_BIAS>
+template <bool HAS_BIAS, bool LOOK>
 __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
     float* __restrict__ best_sim, const ChunkIndex chunks, int n_chunks, int label_bits,
@@ -51,8 +51,7 @@ __global__ __launch_bounds__(WD_WAVES * 64, 2) void k_assign_wide(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, half = lane >> 5;
   int wg, hp;
-  if (!map.mine<true>(wg, hp)) return;
-  if (ctl.skip && ctl.skip[hp] == 0) return;            // converged: whole workgroup leaves
+  if (!map.mine<true, LOOK>(wg, hp) || map.stopped<LOOK>(hp)) return;
   const bf16* Mhp = mu_hat + (int64_t)hp * c_count * D;
   const int n_tiles = (c_count + 31) / 32;
 
@@ -271,15 +270,14 @@ hipError_t launch_assign_wide(const Dims& dm, const bf16* K, int64_t tok_begin, 
   const int n_chunks = (int)((tok_count + WD_CHUNK - 1) / WD_CHUNK);
   int label_bits = 0;
   while ((1 << label_bits) < c_count) ++label_bits;
-  const TileMap map(n_chunks, dm.HP);
-  if (ctl.bias)
-    hipLaunchKernelGGL(k_assign_wide<true>, map.grid(), dim3(WD_WAVES * 64), 0, st, K, mu_hat, labels,
-                       best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
-                       c_count, ctl, map);
-  else
-    hipLaunchKernelGGL(k_assign_wide<false>, map.grid(), dim3(WD_WAVES * 64), 0, st, K, mu_hat, labels,
-                       best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin, tok_count, c_begin,
-                       c_count, ctl, map);
+  const TileMap map(n_chunks, dm.HP, ctl.running);
+  auto launch = [&](auto look) {
+    constexpr bool L = decltype(look)::value;
+    hipLaunchKernelGGL((ctl.bias ? k_assign_wide<true, L> : k_assign_wide<false, L>), map.grid(), dim3(WD_WAVES * 64),
+                       0, st, K, mu_hat, labels, best_sim, chunks, n_chunks, label_bits, dm.N_cap, tok_begin,
+                       tok_count, c_begin, c_count, ctl, map);
+  };
+  ctl.running.first ? launch(std::true_type()) : launch(std::false_type());
   return hipGetLastError();
 }
 

@@ -11,6 +11,8 @@
 // last assignment.  Short ranges do without the index: their update looks through the labels, and
 // its last launch leaves the metadata.  The counting sort of given labels and the update from a
 // sorted list serve the calls that export the steps, and ranges of more chunks than the index holds.
+#include <type_traits>
+
 #include "chunk_sort.hpp"
 
 namespace ck {
@@ -497,20 +499,19 @@ struct ChunkRuns {
 constexpr int UPC_WAVES = 4;
 constexpr int UPC_STEPS = 8;                            // 16-row steps whose loads are in flight together
 
-template <int CL>
+template <int CL, bool LOOK>
 __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chunks(
     const bf16* __restrict__ K, const uint32_t* __restrict__ seg,
     const uint16_t* __restrict__ list, int n_chunks, int chunk_tokens, int64_t N_cap,
     int64_t tok_begin, int64_t tok_count, int C_cap, int c_begin, int c_count,
     bf16* __restrict__ centroids, bf16* __restrict__ mu_hat, int32_t* __restrict__ sizes,
-    int metric, float* __restrict__ bias, int bias_stride, const int32_t* __restrict__ gate,
-    const TileMap map) {
+    int metric, float* __restrict__ bias, int bias_stride, const TileMap map) {
   constexpr int SPAN = 256;                             // members whose ids a workgroup holds at once
   extern __shared__ uint32_t lds_u[];
   __shared__ __attribute__((aligned(16))) float part[CL][UPC_WAVES][D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
   int wg, hp;                                           // neighbouring clusters, whose run words share
-  if (!map.mine<false>(wg, hp)) return;                        // cache lines, are on one XCD
+  if (!map.mine<false, LOOK>(wg, hp)) return;           // cache lines, are on one XCD
   const int c0 = wg * CL;
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chun
 #pragma unroll
   for (int cl = 0; cl < CL; ++cl) cr[cl] = {seg, list, n_chunks, chunk_tokens, tok_count};
   cr[0].template load<CL, UPC_WAVES * 64>(lds_u, hp, c0, c_count);
-  if (gate && gate[hp] == 0) return;                    // here the word has travelled with the table
+  if (map.stopped<LOOK>(hp)) return;                          // here the word has travelled with the table
 #pragma unroll
   for (int cl = 0; cl < CL; ++cl) {
     cr[cl].scan(lds_u, hp, cl);
@@ -602,19 +603,19 @@ __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chun
 constexpr int UPL_WAVES = 8;                            // look at the labels; UPC_WAVES of them add the rows
 constexpr int UPL_ROUNDS = 16;                          // 64 labels each, per wavefront, at most
 
-template <int ROUNDS>
+template <int ROUNDS, bool LOOK>
 __global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
     const bf16* __restrict__ K, const int32_t* __restrict__ labels, int64_t N_cap, int64_t tok_begin,
     int tok_count, int C_cap, int c_begin, int c_count, bf16* __restrict__ centroids,
     bf16* __restrict__ mu_hat, int32_t* __restrict__ sizes, int metric, float* __restrict__ bias,
-    int bias_stride, const int32_t* __restrict__ gate, int32_t* __restrict__ offsets,
+    int bias_stride, int32_t* __restrict__ offsets,
     int32_t* __restrict__ sorted_idx, int32_t* __restrict__ iters_done, int n_iter, const TileMap map) {
   __shared__ uint16_t member[UPL_WAVES * ROUNDS * WAVE];
   __shared__ int found[UPL_WAVES], before[UPL_WAVES];
   __shared__ __attribute__((aligned(16))) float part[UPC_WAVES][D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
   int c, hp;
-  if (!map.mine<false>(c, hp)) return;
+  if (!map.mine<false, LOOK>(c, hp)) return;
   CK_FETCH_ARG(centroids);                              // used last, fetched with the others
   CK_FETCH_ARG(metric);
   CK_FETCH_ARG(offsets);
@@ -641,8 +642,7 @@ __global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
   }
   if (lane == 0) found[wave] = n_here;
   __syncthreads();
-  // a head-problem that has converged: labels, and with them everything below, are what they were
-  if (gate && gate[hp] == 0) return;
+  if (map.stopped<LOOK>(hp)) return;
   int base = 0, n = 0;
 #pragma unroll
   for (int w = 0; w < UPL_WAVES; ++w) {
@@ -730,15 +730,19 @@ bool update_labels_fits(const Dims& dm, int64_t tok_count, int c_count) {
 hipError_t launch_update_labels(const Dims& dm, const bf16* K, const int32_t* labels,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
-                                float* bias, int bias_stride, const int32_t* gate,
+                                float* bias, int bias_stride, const Running& running,
                                 int32_t* offsets, int32_t* sorted_idx, int32_t* iters_done,
                                 int n_iter, hipStream_t st) {
-  const auto kernel = tok_count <= UPL_WAVES * 8 * WAVE ? k_update_labels<8> : k_update_labels<UPL_ROUNDS>;
-  const TileMap map(c_count, dm.HP);
-  hipLaunchKernelGGL(kernel, map.grid(), dim3(UPL_WAVES * 64), 0, st, K, labels,
-                     dm.N_cap, tok_begin, (int)tok_count, dm.C_cap, c_begin, c_count, centroids,
-                     mu_hat, sizes, metric, bias, bias_stride, gate, offsets, sorted_idx, iters_done,
-                     n_iter, map);
+  const TileMap map(c_count, dm.HP, running);
+  auto launch = [&](auto look) {
+    constexpr bool L = decltype(look)::value;
+    const auto kernel = tok_count <= UPL_WAVES * 8 * WAVE ? k_update_labels<8, L> : k_update_labels<UPL_ROUNDS, L>;
+    hipLaunchKernelGGL(kernel, map.grid(), dim3(UPL_WAVES * 64), 0, st, K, labels,
+                       dm.N_cap, tok_begin, (int)tok_count, dm.C_cap, c_begin, c_count, centroids,
+                       mu_hat, sizes, metric, bias, bias_stride, offsets, sorted_idx, iters_done,
+                       n_iter, map);
+  };
+  running.first ? launch(std::true_type()) : launch(std::false_type());
   return hipGetLastError();
 }
 
@@ -840,15 +844,19 @@ int update_clusters_per_workgroup(int n_chunks, int c_count, int hp) {
 hipError_t launch_update_chunks(const Dims& dm, const bf16* K, const ChunkIndex& chunks,
                                 int64_t tok_begin, int64_t tok_count, int c_begin, int c_count,
                                 bf16* centroids, bf16* mu_hat, int32_t* sizes, int metric,
-                                float* bias, int bias_stride, const int32_t* gate, hipStream_t st) {
+                                float* bias, int bias_stride, const Running& running, hipStream_t st) {
   const int chunk_tokens = chunks.tokens;
   const int n_chunks = (int)((tok_count + chunk_tokens - 1) / chunk_tokens);
   const int cl = update_clusters_per_workgroup(n_chunks, c_count, dm.HP);
-  const TileMap map((c_count + cl - 1) / cl, dm.HP);
-  hipLaunchKernelGGL(cl == 4 ? k_update_chunks<4> : k_update_chunks<1>, map.grid(), dim3(UPC_WAVES * 64),
-                     chunk_runs_lds(cl, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
-                     chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin, c_count,
-                     centroids, mu_hat, sizes, metric, bias, bias_stride, gate, map);
+  const TileMap map((c_count + cl - 1) / cl, dm.HP, running);
+  auto launch = [&](auto look) {
+    constexpr bool L = decltype(look)::value;
+    hipLaunchKernelGGL((cl == 4 ? k_update_chunks<4, L> : k_update_chunks<1, L>), map.grid(), dim3(UPC_WAVES * 64),
+                       chunk_runs_lds(cl, n_chunks), st, K, chunks.seg, chunks.list, n_chunks,
+                       chunk_tokens, dm.N_cap, tok_begin, tok_count, dm.C_cap, c_begin, c_count,
+                       centroids, mu_hat, sizes, metric, bias, bias_stride, map);
+  };
+  running.first ? launch(std::true_type()) : launch(std::false_type());
   return hipGetLastError();
 }
 

@@ -216,3 +216,46 @@ def test_head_problems_stop_on_their_own(S, Hkv, N, C):
                     continue
                 for name in ("labels", "sizes", "offsets", "sorted_idx", "centroids"):
                     assert torch.equal(getattr(st, name)[s, h], getattr(ref, name)[s, h]), (h, name)
+
+
+# (head-problems, tokens, clusters)
+STOPPING = [(9, 9500, 30),           # k_assign, chunks of 256; from the chunk index
+            (70, 1500, 13),          # k_assign, chunks of 128; two words of head-problems
+            (8, 30000, 100),         # table in LDS, keys requested with it
+            (8, 33000, 400),         # and behind it
+            (3, 50000, 600),         # table streamed
+            (130, 500, 9),           # three words
+            (260, 600, 9),           # more head-problems than are listed
+            (40, 800, 10),           # from the labels
+            (2, 262700, 30)]         # counts only, sorted-list form
+
+
+@pytest.mark.parametrize("metric", [ck.CK_METRIC_COSINE, ck.CK_METRIC_L2])
+@pytest.mark.parametrize("hp,n,C", STOPPING)
+def test_head_problems_stop_early_and_late(hp, n, C, metric):
+    """Head-problems that stop in the second iteration, between the others and after all of them: while
+    workgroups look late whether theirs has stopped, and when only those that run are dealt out."""
+    max_iter = 40
+    g = torch.Generator(device=DEV).manual_seed(hp * n + C)
+    K = torch.empty(1, hp, n, 128, dtype=torch.bfloat16, device=DEV)
+    for h in range(hp):
+        far = torch.randn(C, 128, generator=g, device=DEV) * 4
+        k = torch.randn(n, 128, generator=g, device=DEV)
+        # every third head settles at once, the others the later the wider the clusters are
+        pick = torch.arange(n, device=DEV) % C
+        K[0, h] = k if h % 3 == 2 else far[pick] + (0.02 if h % 3 == 0 else 3.5) * k
+    init = torch.rand(1, hp, n, generator=g, device=DEV).topk(C, dim=-1).indices.int()
+    init[:, 0::3] = torch.arange(C, device=DEV).int()    # one row of every center
+    sh = ck.Shape(1, hp, hp, n, C)
+    st, ref = (ck.ClusterState(sh, DEV, budget=64) for _ in range(2))
+    iters = torch.zeros(1, hp, dtype=torch.int32, device=DEV)
+    st.cluster(K, init, 0, n, C, max_iter, metric | ck.CK_KM_UNTIL_CONVERGED, iters)
+    ran = iters[0].cpu()
+    assert (ran[0::3] == 2).all() and ran.max() > 12 and (ran <= max_iter).all()   # 12: KM_LOOK_FIRST
+    for n_iter in sorted(set(ran.tolist())):
+        ref.n_clusters = 0
+        ref.cluster(K, init, 0, n, C, n_iter, metric)
+        those = (ran == n_iter).nonzero()[:, 0].to(DEV)
+        for name in ("labels", "sizes", "offsets", "sorted_idx"):
+            assert torch.equal(getattr(st, name)[0, those], getattr(ref, name)[0, those]), (n_iter, name)
+        assert torch.equal(st.centroids.view(torch.int16)[0, those], ref.centroids.view(torch.int16)[0, those])
