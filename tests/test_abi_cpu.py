@@ -408,3 +408,15 @@ def test_form_of_the_chunk_update():
     for S, Hkv, N, C, begin, _ in FOUR:
         assert (N - begin) * S * Hkv >= 65536           # chunks of 512 tokens
         assert rule((N - begin + 511) // 512, C, S * Hkv) == 4 and C % 4
+
+
+def test_forms_of_the_assignment():
+    """The shapes of the GPU tests run the kernels that they are listed under."""
+    from tests import forms
+    from tests.test_gpu_assign_forms import FORMS, L2_FORMS
+    from tests.test_gpu_chunk_update import STOPPING
+    for lists in (FORMS, L2_FORMS):
+        for form, shapes in lists.items():
+            assert [forms.assignment(*shape) for shape in shapes] == [form] * len(shapes)
+    for shape, kernels in STOPPING.items():
+        assert (forms.assignment(*shape), forms.update(*shape)) == kernels, shape

@@ -9,31 +9,45 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 NEAR_TIE = 1e-4                      # cosine gap below which either of two labels may stand
 
-# (head-problems, tokens, clusters)
-WIDE = [(1, 65537, 513),             # one row in the last tile, one token in the last workgroup
-        (2, 32800, 544),             # whole tiles, ragged last workgroup
-        (1, 66000, 575),             # 18 tiles: the ring of six three times round
-        (3, 21900, 609),             # 20 tiles, one row in the last
-        (1, 65536, 2048)]            # most clusters
-STREAM = [(1, 65537, 512),           # one token in the last block, largest table
-          (2, 40960, 129),           # keys requested behind the staging of the table
-          (8, 8193, 128),            # with it
-          (8, 50000, 40),            # 98 blocks a head-problem: four to a workgroup
-          (40, 10000, 33),           # 20 blocks, four to a workgroup of five
-          (64, 20000, 31),           # 40 blocks, ten rounds' worth in two
-          (300, 600, 7),             # more head-problems than compute units
-          (8, 50000, 65), (40, 10000, 65), (64, 20000, 66),   # blocks as above, three tiles
-          (8, 13000, 128), (2, 60000, 129)]
-FEW = [(3, 10922, 64),               # k_assign: a table of one chunk, workgroups of 128 tokens
-       (1, 32768, 65),               # of two
-       (1, 32769, 129), (5, 13107, 64),   # three, one; workgroups of 256 tokens
-       (2, 32768, 700),              # eleven
-       (8, 8193, 64), (9, 10100, 128), (1, 65537, 128),   # 128 again, with all the LDS there is and half of it
-       (2, 39000, 160), (16, 9000, 80),
-       (1, 65536, 2048), (700, 500, 5)]
+# (head-problems, tokens, clusters) by the form that takes them (see forms.py; held to it by test_abi_cpu.py)
+FORMS = {
+    "wide": [(1, 65537, 513),            # one row in the last tile, one token in the last workgroup
+             (2, 32800, 544),            # whole tiles, ragged last workgroup
+             (1, 66000, 575),            # 18 tiles: the ring of six three times round
+             (3, 21900, 609),            # 20 tiles, one row in the last
+             (2, 33000, 2048)],          # most clusters
+    "stream": [(1, 65537, 512),          # one token in the last block, largest table
+               (2, 40960, 129), (2, 60000, 129)],
+    "stream early": [(1, 65537, 128), (8, 13000, 128), (8, 12000, 128),
+                     (8, 50000, 65),     # 98 blocks a head-problem: four to a workgroup
+                     (40, 10000, 65),    # 20 blocks, four to a workgroup of five
+                     (64, 20000, 66),    # 40 blocks, ten rounds' worth in two
+                     (300, 700, 65)],    # more head-problems than compute units
+    "few 128 one": [(3, 10922, 64), (8, 8193, 64), (700, 500, 5), (8, 50000, 40), (40, 10000, 33),
+                    (64, 20000, 31), (300, 600, 7)],
+    "few 128": [(1, 32768, 65), (8, 8193, 128), (9, 10100, 128), (2, 39000, 160)],
+    "few 128 tight": [(16, 9000, 80)],
+    "few 256 one": [(5, 13107, 64)],
+    "few 256": [(1, 32769, 129),
+                (2, 32768, 700),         # a table of eleven chunks
+                (1, 65536, 2048)],
+    "few 256 tight": [(33, 1900, 100)],
+}
+ALL = [shape for shapes in FORMS.values() for shape in shapes]
+L2_FORMS = {
+    "wide": [(1, 65537, 513), (2, 32801, 2047)],
+    "stream": [(1, 65537, 511)],
+    "stream early": [(8, 13000, 100), (8, 50000, 65)],
+    "few 128 one": [(2, 385, 9)],
+    "few 128": [(1, 2500, 2047), (8, 8193, 100), (9, 10100, 100)],
+    "few 128 tight": [(16, 9000, 80)],
+    "few 256 one": [(1, 40000, 64)],
+    "few 256": [(2, 20000, 600)],
+    "few 256 tight": [(33, 1900, 100)],
+}
 
 
-@pytest.mark.parametrize("hp,n,C", WIDE + STREAM + FEW)
+@pytest.mark.parametrize("hp,n,C", ALL)
 def test_labels_against_64_bits(hp, n, C):
     g = torch.Generator(device=DEV).manual_seed(n + C)
     K = torch.randn(1, hp, n + 3, 128, generator=g, device=DEV).to(torch.bfloat16)
@@ -55,7 +69,7 @@ def test_labels_against_64_bits(hp, n, C):
     assert ties < 0.01 * hp * n
 
 
-@pytest.mark.parametrize("hp,n,C", WIDE + STREAM + FEW)
+@pytest.mark.parametrize("hp,n,C", ALL)
 def test_iterations_leave_consistent_metadata(hp, n, C):
     g = torch.Generator(device=DEV).manual_seed(n - C)
     K = torch.randn(1, hp, n, 128, generator=g, device=DEV).to(torch.bfloat16)
@@ -70,10 +84,7 @@ def test_iterations_leave_consistent_metadata(hp, n, C):
     assert torch.equal(st.sorted_idx[0].long(), lab.sort(dim=1, stable=True).indices)
 
 
-@pytest.mark.parametrize("hp,n,C", [(1, 65537, 513), (2, 32801, 2047),      # k_assign_wide with its bias table
-                                    (1, 65537, 511), (8, 8193, 100),        # k_assign_stream
-                                    (1, 2500, 2047), (2, 385, 9),           # k_assign
-                                    (2, 20000, 600), (1, 40000, 64), (9, 10100, 100)])
+@pytest.mark.parametrize("hp,n,C", [shape for shapes in L2_FORMS.values() for shape in shapes])
 def test_l2_labels_against_64_bits(hp, n, C):
     """One iteration by l2 assigns every key to the nearest of the given rows.  A similarity
     x mu - |mu|^2 / 2 is off by at most 128 * 2^-24 of |x| |mu| + |mu|^2 / 2 (fp32 sums of exact

@@ -21,14 +21,19 @@ SHAPES = [
     (16, 1, 600, 65, 5, 1),          # more: chunks of 128, last one short
     (1, 1, 8193, 60, 0, 0),          # a label more: the same
     (2, 1, 8192, 2, 0, 0),           # from the labels: members in many passes
-    (2, 8, 4050, 130, 3, 5),         # chunks of 128, appended behind existing clusters, odd range
-    (2, 8, 4097, 513, 1, 0),         # table streamed in chunks; one token in the last chunk of 512
+    (1, 8, 4050, 130, 3, 5),         # chunks of 128, appended behind existing clusters, odd range
+    (2, 8, 4050, 130, 3, 5),         # of 256
+    (2, 8, 4097, 513, 1, 0),         # exactly sixteen of them
+    (2, 8, 4098, 513, 1, 0),         # table streamed in chunks; one token in the last chunk of 512
     (1, 8, 8200, 512, 0, 0),         # largest LDS-resident table
-    (128, 1, 600, 7, 0, 0),          # chunks of 128; the exported sort's of 512 need the larger workspace
+    (128, 1, 600, 7, 0, 0),          # from the labels; the exported sort's chunks of 512 need the larger workspace
     (1, 1, 65535, 60, 0, 0),         # chunks of 256
     (1, 2, 65536, 60, 0, 0),         # chunks of 128: exactly as many as the index holds
     (3, 1, 20000, 70, 3, 5),         # chunks of 256, appended behind existing clusters, odd range
-    (9, 1, 9001, 100, 1, 0),         # chunks of 128, half of the LDS
+    (9, 1, 9001, 100, 1, 0),         # chunks of 128, two table chunks
+    (16, 1, 9001, 80, 1, 0),         # the same with the keys through half of the LDS
+    (33, 1, 1900, 100, 0, 0),        # and chunks of 256
+    (1100, 1, 520, 512, 0, 0),       # more workgroups of the update than a grid has in x
     (1, 1, 262144, 64, 0, 0),        # chunks of 512: exactly as many
     (1, 1, 262145, 64, 0, 0),        # one chunk more: counts only, and the sorted-list form
     (1, 2, 262700, 512, 7, 3),       # the same with the largest LDS-resident table
@@ -182,7 +187,7 @@ def test_empty_clusters_survive_the_iterations(S, Hkv, N, C, begin, c_begin):
         assert empty > 0
 
 
-@pytest.mark.parametrize("S,Hkv,N,C", [(1, 8, 8200, 100),    # table in LDS, chunks of 512
+@pytest.mark.parametrize("S,Hkv,N,C", [(1, 8, 8200, 100),    # chunks of 128, two table chunks
                                        (1, 8, 8200, 520),    # table streamed in chunks
                                        (2, 2, 1500, 40),     # from the labels
                                        (1, 8, 4000, 130),    # chunks of 128
@@ -218,16 +223,19 @@ def test_head_problems_stop_on_their_own(S, Hkv, N, C):
                     assert torch.equal(getattr(st, name)[s, h], getattr(ref, name)[s, h]), (h, name)
 
 
-# (head-problems, tokens, clusters)
-STOPPING = [(9, 9500, 30),           # k_assign, chunks of 256; from the chunk index
-            (70, 1500, 13),          # k_assign, chunks of 128; two words of head-problems
-            (8, 30000, 100),         # table in LDS, keys requested with it
-            (8, 33000, 400),         # and behind it
-            (3, 50000, 600),         # table streamed
-            (130, 500, 9),           # three words
-            (260, 600, 9),           # more head-problems than are listed
-            (40, 800, 10),           # from the labels
-            (2, 262700, 30)]         # counts only, sorted-list form
+# (head-problems, tokens, clusters): the forms of assignment and update (see forms.py; held to them by
+# test_abi_cpu.py)
+STOPPING = {(7, 9000, 30): ("few 256 one", "chunks"),
+            (16, 9000, 80): ("few 128 tight", "chunks"),
+            (70, 1500, 16): ("few 128 one", "chunks"),       # two words of head-problems
+            (5, 13107, 100): ("few 256 tight", "chunks"),
+            (8, 30000, 100): ("stream early", "chunks"),
+            (8, 33000, 400): ("stream", "chunks"),
+            (3, 50000, 600): ("wide", "chunks"),
+            (130, 500, 9): ("few 256 one", "chunks"),        # three words
+            (260, 600, 9): ("few 128 one", "chunks"),        # more head-problems than are listed
+            (40, 800, 10): ("few 128 one", "labels"),
+            (2, 262700, 30): ("stream early", "sorted")}
 
 
 @pytest.mark.parametrize("metric", [ck.CK_METRIC_COSINE, ck.CK_METRIC_L2])

@@ -204,9 +204,8 @@ def test_assignment_many_head_problems_all_keys_teacher_forced():
 @pytest.mark.parametrize("C", [600, 1100])
 def test_assignment_chunk_streaming_kernel_all_keys_teacher_forced(C):
     """Tables of more than 512 centroids take the kernel that streams the table through
-    LDS in chunks: with 16 head-problems of 32768 tokens (more 1024-token tiles than
-    compute units) C = 600 runs its four-wavefront form, C = 1100 the eight-wavefront one.
-    Every key of two head-problems against the oracle, given unit centroids made from
+    LDS in chunks: 16 head-problems of 32768 tokens, four rounds of workgroups, over 19 and
+    over 35 tiles of the table.  Every key of two head-problems against the oracle, given unit centroids made from
     sampled key rows."""
     S, Hkv, N = 2, 8, 32768
     cfg = Config("assign_chunks", 1, S, Hkv, Hkv, 128, N, 1024, C, 1, 256, seed=400 + C)
@@ -234,11 +233,12 @@ def test_assignment_chunk_streaming_kernel_all_keys_teacher_forced(C):
     print(f"assignment, C={C}, 16 head-problems: near-tie keys {flagged}/{len(picks) * N}")
 
 
-@pytest.mark.parametrize("S,Hkv,C", [(1, 2, 200), (2, 8, 200), (1, 2, 600), (2, 8, 600)])
+@pytest.mark.parametrize("S,Hkv,C", [(1, 2, 200), (1, 3, 200), (2, 8, 200), (1, 2, 600), (1, 3, 600), (2, 8, 600)])
 def test_l2_assignment_large_tiles_all_keys(S, Hkv, C):
     """The l2 metric (bias -|mu|^2/2 added in the assignment read-out) at 32768 tokens per
     head-problem: C = 200 takes the streaming kernel (table in LDS), C = 600 the wide one
-    (tiles through a ring in LDS), with 128 workgroups and with 1024.  One iteration from the
+    (tiles through a ring in LDS), with 192 workgroups and with 1024; two head-problems are few
+    keys for either and take k_assign.  One iteration from the
     given initial rows is a teacher-forced assignment: the labels must be the oracle's nearest
     stored centroid off near-ties."""
     N = 32768
