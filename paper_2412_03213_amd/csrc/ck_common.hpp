@@ -46,8 +46,6 @@ __device__ __forceinline__ int dpp_i0(int v) {      // lanes without a source re
 constexpr int DPP_XOR1 = 0xB1;          // quad_perm:[1,0,3,2]
 constexpr int DPP_XOR2 = 0x4E;          // quad_perm:[2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <-> 7 - i inside each 8
-constexpr int DPP_ROR4 = 0x124;         // rotation by 4 inside each row of 16
-constexpr int DPP_ROR8 = 0x128;         // by 8: lane i <-> i ^ 8
 constexpr int DPP_MIRROR = 0x140;       // lane i <-> 15 - i inside each row of 16
 
 struct OpSum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
@@ -156,8 +154,9 @@ struct Running {
 constexpr int KM_LOOK_FIRST = 12;      // from this iteration on
 
 // Which workgroup takes which tile of which head-problem: XCD x (workgroup id % 8) gets the x-th eighth
-// of all tiles, in head-problem order.  Every kernel of a K-means iteration is launched that way, so a
-// head-problem's keys, table, labels and chunk index stay with one XCD (or the same few), and what one
+// of all tiles, in head-problem order.  The assignment and the updates from the chunk index and from the
+// labels are launched that way (not the counting sort and the update from its list, which ranges of more than
+// CHUNK_RUNS_MAX chunks take), so a head-problem's keys, table, labels and chunk index stay with one XCD (or the same few), and what one
 // kernel leaves in that XCD's L2 of 4 MB is there for the next: the assignment's keys for the update,
 // the update's table for the assignment.  Ten iterations, tiles dealt out one by one / by eighths, us
 // (head-problems x tokens x clusters): 8 x 2985 x 37 93 / 91, 4 x 15738 x 98 142 / 132, 16 x 5306 x 66

@@ -35,8 +35,11 @@ constexpr int LDS_ROW = D + 8;             // bf16 elements per LDS row: 272 B, 
 // 96 -> 93, 4 x 15738 x 98 155 -> 142, the same by l2 185 -> 172, by l2 until convergence 236 -> 181.
 // HAS_BIAS (l2 metric): a per-centroid bias, held in LDS, is added to every similarity before the
 // argmax.  ONE: a table of one chunk.  TIGHT: the keys through half of the LDS, so that a compute unit
-// holds four workgroups of four wavefronts in place of three (3 % less where there are as many: 8 x 20000 x 250
-// 319 -> 301 us, 32 x 4096 x 51 without; 2 % more where there are not: 4 x 15738 x 98 142 -> 145).
+// holds four workgroups of four wavefronts in place of three.  Where there are as many workgroups, ten
+// iterations without / with it: 8 x 20000 x 128 221 / 207 us, 8 x 18000 x 160 228 / 219, 20 x 7000 x 100 217 /
+// 208, 60 x 2500 x 100 300 / 293, but 8 x 20000 x 128 by l2 253 / 254, 250 x 700 x 80 598 / 604, and with eight
+// wavefronts, where ragged ranges alone make more workgroups than compute units, 33 x 1900 x 100 190 / 197.
+// Where there are not as many it costs: 4 x 15738 x 98 142 / 145.
 template <bool HAS_BIAS, int WAVES, bool ONE, bool TIGHT, bool LOOK>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_assign(
     const bf16* __restrict__ K, const bf16* __restrict__ mu_hat, int32_t* __restrict__ labels,
@@ -287,15 +290,17 @@ static hipError_t launch_assign_few(const Dims& dm, const bf16* K, int64_t tok_b
 // k_assign_stream) that leaves the label-ordered index of exactly these.
 // 128 or 256 (k_assign) where that gives one workgroup per compute unit: the launch is as long as one
 // workgroup, and with two on some units the others wait.  Ten iterations, 128 / 256 / 512 tokens, us
-// (head-problems x tokens x clusters): 4 x 6000 x 70 110 / 114 / 145, 1 x 24000 x 400 165 / 166 / 203;
-// 8 x 5000 x 102 150 / 146 / 180, 1 x 40000 x 700 246 / 219 / 263, 1 x 55000 x 500 221 / 203 / 235.
+// (head-problems x tokens x clusters): 4 x 6000 x 70 112 / 117 / 147, 1 x 24000 x 400 166 / 169 / 205;
+// 8 x 5000 x 102 144 / 142 / 172, 1 x 40000 x 700 247 / 222 / 265, 1 x 55000 x 500 223 / 200 / 236.
 // Beyond, k_assign_stream puts 512 tokens on a unit, k_assign_wide (more than 512 clusters) as well.
 // Where the contraction is nothing (64 clusters) many small workgroups stay ahead of both: 16 x 4400 x 40
-// 141 / 145 / 164, 128 x 1100 x 13 142 / 144 / 156, 32 x 7800 x 40 286 / 283 / 308, 128 x 6250 x 40
-// 681 / 678 / 719, 8 x 60000 x 60 475 / 470 / 488 (2 x 60000 x 50 282 / 271 / 278).  With a few more tiles
-// only while the units would not be full, in the first two rounds of them: 7 x 10000 x 102 157 / 167 / 176,
-// 8 x 20000 x 128 246 / 264 / 273, 8 x 8750 x 160 167 / 174 / 177, but full 8 x 15000 x 102 215 / 212 / 210,
-// 8 x 25000 x 128 291 / 305 / 290, 8 x 11250 x 160 184 / 190 / 187, and 8 x 8750 x 200 195 / 199 / 193.
+// 130 / 132 / 155, 128 x 1100 x 13 151 / 155 / 212, 32 x 7800 x 40 239 / 233 / 273, 128 x 6250 x 40
+// 607 / 611 / 699, 8 x 60000 x 60 432 / 427 / 468 (2 x 60000 x 50 280 / 270 / 276).  With a few more tiles
+// only while the units would not be full, in the first two rounds of them: 7 x 10000 x 102 148 / 156 / 167,
+// 8 x 20000 x 128 209 / 216 / 247, 8 x 8750 x 160 153 / 160 / 167.  These lines (70 and 60 per cent, 160
+// clusters) are where 512 was ahead while tiles were dealt out one by one.  By eighths it is no longer: beyond
+// them 8 x 15000 x 102 172 / 165 / 175, 8 x 25000 x 128 255 / 262 / 268, 8 x 32000 x 66 302 / 299 / 310,
+// 8 x 11250 x 160 155 / 160 / 169, 8 x 8750 x 200 181 / 187 / 186, 4 x 32768 x 100 202 / 197 / 201.
 int assign_tile_tokens(const Dims& dm, int64_t tok_count, int c_count) {
   constexpr int64_t CUS = 256, ROUND = CUS * 512;
   const int64_t tokens = tok_count * dm.HP;

@@ -112,8 +112,8 @@ __global__ __launch_bounds__(ST_WAVES * 64, 2) void k_assign_stream(
   // EARLY: a small table is staged before the key requests pile up.  Otherwise they come behind
   // the barrier: a compute unit has about 32 KB of loads in flight, and a wavefront whose request
   // does not fit stands still, in front of the barrier with all others (8 x 32768 x 400: barrier
-  // passed after 6.0 us, now 3.1).  Ten iterations, early / behind: 128 x 2048 x 25 320 / 333 us,
-  // 64 x 8179 x 102 530 / 536, 8 x 16384 x 200 238 / 225, 8 x 32768 x 400 475 / 455.
+  // passed after 6.0 us, now 3.1).  Ten iterations, early / behind: 64 x 8179 x 102 517 / 522 us, 128 x 4000 x 100
+  // 600 / 606, 64 x 8179 x 128 532 / 537, x 160 576 / 577, 8 x 16384 x 200 198 / 195, 8 x 32768 x 400 434 / 430.
   if constexpr (EARLY) load_keys(wave, ka);
   if constexpr (HAS_BIAS) {
     for (int c = tid; c < n_tiles * 32; c += THREADS)

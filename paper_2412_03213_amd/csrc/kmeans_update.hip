@@ -598,8 +598,8 @@ __global__ __launch_bounds__(UPC_WAVES * 64, CL == 1 ? 7 : 6) void k_update_chun
 // segment, so the launch can leave the metadata as well.  Additions in k_update's order.
 // Bound: launch, then labels and rows one after the other, and the instructions of looking through the
 // labels, which every cluster does: eight wavefronts share that (four: 3 % of the call).
-// Ten iterations at 8 x 2985 x 37: 108.5 us from the chunk index, with an index launch and a fill of the
-// iteration counts behind it, 94 from the labels.
+// Ten iterations at 8 x 2985 x 37: 100 us from the chunk index, with an index launch behind it, 92 from the
+// labels.
 constexpr int UPL_WAVES = 8;                            // look at the labels; UPC_WAVES of them add the rows
 constexpr int UPL_ROUNDS = 16;                          // 64 labels each, per wavefront, at most
 
@@ -718,10 +718,10 @@ __global__ __launch_bounds__(UPL_WAVES * 64) void k_update_labels(
 
 // Where all workgroups are resident together (four per CU) and the labels read, over all clusters, are
 // few.  Ten iterations, chunk index / labels, us (head-problems x tokens x clusters): 8 x 1024 x 13
-// 96 / 82, 8 x 4096 x 51 112 / 98, 8 x 4096 x 128 126 / 117, 4 x 8192 x 102 125 / 118, 1 x 8192 x 102
-// 120 / 105, 60 x 1024 x 13 129 / 117, 20 x 4096 x 51 173 / 158; more labels: 8 x 8179 x 102 156 / 168,
-// 16 x 5000 x 62 171 / 184; more workgroups: 8 x 1024 x 256 166 / 172, 128 x 500 x 25 193 / 210, though
-// 128 x 1024 x 13 197 / 185.
+// 95 / 84, 8 x 4096 x 51 101 / 92, 8 x 4096 x 128 113 / 112, 4 x 8192 x 102 118 / 113, 1 x 8192 x 102
+// 114 / 105, 60 x 1024 x 13 113 / 110, 20 x 4096 x 51 127 / 125; more labels: 8 x 8179 x 102 129 / 151,
+// 16 x 5000 x 62 125 / 146; more workgroups: 8 x 1024 x 256 154 / 164, 128 x 500 x 25 155 / 187,
+// 128 x 1024 x 13 143 / 153.
 bool update_labels_fits(const Dims& dm, int64_t tok_count, int c_count) {
   return tok_count <= UPL_WAVES * UPL_ROUNDS * WAVE && (int64_t)dm.HP * c_count <= 1024 &&
          (int64_t)dm.HP * c_count * tok_count <= 1 << 22;
@@ -836,7 +836,9 @@ static size_t chunk_runs_lds(int clusters, int n_chunks) {
 // 77.0 / 69.3, but with few clusters 16 x 131072 x 400 103.9 / 107.9, 9 x 262144 x 510 121.0 / 124.8,
 // with few words 4 x 131072 x 1600 26.7 / 28.5, 8 x 131072 x 819 48.9 / 49.8, 4 x 262144 x 1014
 // 50.3 / 51.7, and with 128 chunks 24 x 65536 x 800 89.9 / 90.5 and ten iterations of 16 x 65536 x 800
-// 2202 / 2221.  With 144 and 160 chunks either is up to 4 % faster.
+// 2202 / 2221.  With 144 and 160 chunks either is up to 4 % faster.  With tiles by XCD, ten iterations:
+// 8 x 131072 x 1600 3655 / 3626, 16 x 131072 x 819 4449 / 4420, 12 x 98304 x 1200 3331 / 3309, 4 x 131072 x 1600
+// 1891 / 1908, 8 x 131072 x 819 2216 / 2226, 16 x 65536 x 800 2137 / 2152.
 int update_clusters_per_workgroup(int n_chunks, int c_count, int hp) {
   return n_chunks > 128 && c_count >= 768 && (int64_t)n_chunks * c_count * hp >= 1 << 21 ? 4 : 1;
 }
