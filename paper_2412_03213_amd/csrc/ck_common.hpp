@@ -156,9 +156,9 @@ constexpr int KM_LOOK_FIRST = 12;      // from this iteration on
 // Which workgroup takes which tile of which head-problem: XCD x (workgroup id % 8) gets the x-th eighth
 // of all tiles, in head-problem order.  The assignment and the updates from the chunk index and from the
 // labels are launched that way (not the counting sort and the update from its list, which ranges of more than
-// CHUNK_RUNS_MAX chunks take), so a head-problem's keys, table, labels and chunk index stay with one XCD (or the same few), and what one
-// kernel leaves in that XCD's L2 of 4 MB is there for the next: the assignment's keys for the update,
-// the update's table for the assignment.  Ten iterations, tiles dealt out one by one / by eighths, us
+// CHUNK_RUNS_MAX chunks take), so a head-problem's keys, table, labels and chunk index stay with one XCD (or
+// the same few), and what one kernel leaves in that XCD's L2 of 4 MB is there for the next: the assignment's
+// keys for the update, the update's table for the assignment.  Ten iterations, tiles dealt out one by one / by eighths, us
 // (head-problems x tokens x clusters): 8 x 2985 x 37 93 / 91, 4 x 15738 x 98 142 / 132, 16 x 5306 x 66
 // 165 / 138, 8 x 14100 x 176 214 / 181, 32 x 4096 x 51 193 / 152, 128 x 1100 x 13 210 / 152; with more keys
 // than the L2s hold 8 x 32768 x 400 466 / 450, 64 x 8179 x 102 546 / 529, 1 x 131072 x 500 the same.

@@ -302,6 +302,7 @@ static hipError_t launch_assign_few(const Dims& dm, const bf16* K, int64_t tok_b
 // them 8 x 15000 x 102 172 / 165 / 175, 8 x 25000 x 128 255 / 262 / 268, 8 x 32000 x 66 302 / 299 / 310,
 // 8 x 11250 x 160 155 / 160 / 169, 8 x 8750 x 200 181 / 187 / 186, 4 x 32768 x 100 202 / 197 / 201.
 int assign_tile_tokens(const Dims& dm, int64_t tok_count, int c_count) {
+  // a constant and not the current device's: the size of a workspace follows from this
   constexpr int64_t CUS = 256, ROUND = CUS * 512;
   const int64_t tokens = tok_count * dm.HP;
   if (tokens <= CUS * 128) return 128;
